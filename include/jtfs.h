@@ -420,11 +420,11 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * workgroups of twice the LDS), else 4096. */
 #define JTFS_TUNE_LDS_BATCH8K 1024
 /* ... and the t-columns per workgroup of the forward contraction (its t-chunk):
- * 1024 or 2048 where one of these bits is set (1024 if both), else 4096.  Shorter
- * chunks give more workgroups to small batches and more partial V slots to sum;
- * the workspace size follows the choice (query it again after setting it).
- * Changing it rewrites two small device tables of the plan: not while work of
- * the plan is in flight. */
+ * 1024 or 2048 where one of these bits is set (1024 if both), else 4096 in FP32
+ * mode and, in the split modes, a length of 256 to 4096 columns that the plan
+ * takes from its shapes (so that one signal fills the GPU).  Shorter chunks give
+ * more workgroups to small batches and more partial V slots to sum; the
+ * workspace size follows the bits (query it again after setting them). */
 #define JTFS_TUNE_TCHUNK_1K   2048
 #define JTFS_TUNE_TCHUNK_2K   4096
 typedef struct {

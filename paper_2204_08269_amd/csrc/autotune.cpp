@@ -53,11 +53,8 @@ void set_rows(jtfs_plan* P, int mask) {
     P->tune.batch8k = (mask & JTFS_TUNE_LDS_BATCH8K) != 0;
     const int chunk = (mask & JTFS_TUNE_TCHUNK_1K) ? 1024 : (mask & JTFS_TUNE_TCHUNK_2K) ? 2048 : kChunkT;
     if (chunk != P->tune.chunk) {
-        // the partial-V slot tables of the shapes and their device copies
-        P->tune.chunk = chunk;
+        P->tune.chunk = chunk;           // the plan holds the device tables of every length
         set_chunks(&P->s, chunk);
-        (void)hipMemcpy(P->d_vchoff, P->s.vchoff.data(), sizeof(int64_t) * P->s.n_alpha, hipMemcpyHostToDevice);
-        (void)hipMemcpy(P->d_nch, P->s.nch.data(), sizeof(int) * P->s.n_alpha, hipMemcpyHostToDevice);
     }
 }
 

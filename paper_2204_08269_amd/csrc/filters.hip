@@ -259,6 +259,72 @@ int build_family(DevAlloc& A, const Family& f, float** vals, int** band, int64_t
     return JTFS_OK;
 }
 
+// The tables by which one launch covers every temporal rate: the rates, the
+// 128-column tiles, and the forward contraction's t-chunks for each chunk length
+// (one allocation and one copy for all of them), and the split contraction's own
+// chunk length.  That length is the longest that gives each CU about three
+// workgroups for one signal, kept to 256 columns or more (a workgroup pays for its
+// resident W tile and the sum of its waves' V) and to what the workspace holds; it
+// follows the plan alone, so that a signal's sums do not depend on its batch.
+// One launch for all rates with this length, against one launch per rate with 4096
+// columns: one signal of 2^11, 2^16 and 2^18 samples 166, 1337 and 4645 us before,
+// 86, 444 and 2469 us after; 16 x 2^16 fwd+bwd 9.97 and 9.86 ms; 32 x 2^18 (4096
+// columns either way) 132.9 and 132.5 ms.
+int build_unit_tables(DevAlloc& A, jtfs_plan* P) {
+    const Shapes& s = P->s;
+    constexpr int nset = kChunkLogs[1] - kChunkLogs[0] + 1;
+    std::vector<FreqRate> rates(s.n_alpha);
+    std::vector<FreqUnit> tiles;
+    for (int a = 0; a < s.n_alpha; ++a) {
+        const float sphi = P->sphi.empty() ? 1.f : P->sphi[a];
+        rates[a] = FreqRate{s.yoff[a], s.phioff[a], (int64_t)2 * s.Mp * (s.yoff[a] / s.Kp), s.Tp[a], sphi,
+                            1.f / (P->sw * sphi), 0};
+        for (int t = 0; t < s.Tp[a]; t += kTileTh) tiles.push_back(FreqUnit{a, t, kTileTh, 0});
+    }
+    std::vector<int64_t> vch[nset];
+    std::vector<int> nch[nset];
+    std::vector<FreqUnit> units[nset];
+    size_t bytes = sizeof(FreqRate) * rates.size() + sizeof(FreqUnit) * tiles.size();
+    for (int q = 0; q < nset; ++q) {
+        const int len = 1 << (kChunkLogs[0] + q);
+        int slot = 0;
+        for (int a = 0; a < s.n_alpha; ++a) {
+            const int c = std::min(s.Tp[a], len);
+            vch[q].push_back(slot);
+            nch[q].push_back(s.Tp[a] / c);
+            for (int t = 0; t < s.Tp[a]; t += c) units[q].push_back(FreqUnit{a, t, c, slot++});
+        }
+        std::stable_sort(units[q].begin(), units[q].end(),
+                         [](const FreqUnit& x, const FreqUnit& y) { return x.ncols > y.ncols; });
+        bytes += sizeof(FreqUnit) * units[q].size() + (sizeof(int64_t) + 8) * s.n_alpha;
+    }
+    std::vector<char> host(bytes);
+    char* dev = A.get<char>(bytes);
+    if (A.failed) { set_error("device allocation failed"); return JTFS_ENOMEM; }
+    size_t o = 0;
+    auto put = [&](const void* src, size_t n) {      // every table is a multiple of 8 bytes
+        std::memcpy(host.data() + o, src, n);
+        char* d = dev + o;
+        o += (n + 7) / 8 * 8;
+        return (void*)d;
+    };
+    P->d_rates = (FreqRate*)put(rates.data(), sizeof(FreqRate) * rates.size());
+    P->d_tiles = (FreqUnit*)put(tiles.data(), sizeof(FreqUnit) * tiles.size());
+    for (int q = 0; q < nset; ++q) {
+        ChunkSet& c = P->cset[q];
+        c.sumch = (int64_t)units[q].size();
+        c.d_units = (FreqUnit*)put(units[q].data(), sizeof(FreqUnit) * units[q].size());
+        c.d_vchoff = (int64_t*)put(vch[q].data(), sizeof(int64_t) * s.n_alpha);
+        c.d_nch = (int*)put(nch[q].data(), sizeof(int) * s.n_alpha);
+    }
+    HIPCHK(hipMemcpy(dev, host.data(), o, hipMemcpyHostToDevice));
+    const int64_t per = s.sumTp / kTileTh * (s.Mp / kTileL) / (3 * 256);   // 128-column tiles of a third of a CU's share
+    int q = 0;
+    while (q + 1 < nset && (((int64_t)2 << (kChunkLogs[0] + q)) / kTileTh <= per || !fits_slots(s, P->cset[q].sumch))) ++q;
+    P->auto_chunk = q;
+    return JTFS_OK;
+}
+
 }  // namespace
 
 namespace jtfs {
@@ -382,8 +448,6 @@ extern "C" int jtfs_plan_create_ex(jtfs_plan** out, const jtfs_params* p) {
         P->d_yoff = upload(A, s.yoff);
         P->d_Tp = upload(A, s.Tp);
         P->d_Ta = upload(A, s.Ta);
-        P->d_vchoff = upload(A, s.vchoff);
-        P->d_nch = upload(A, s.nch);
         P->d_pfoff = upload(A, s.pfoff);
         P->d_Lb = upload(A, s.Lb);
         P->d_rowoff = upload(A, s.rowoff);
@@ -391,6 +455,7 @@ extern "C" int jtfs_plan_create_ex(jtfs_plan** out, const jtfs_params* p) {
     }
     if (hipDeviceSynchronize() != hipSuccess) { set_error("plan construction failed on the device"); return fail(JTFS_EHIP); }
     if ((st = build_split_tables(P, A.ptrs)) != JTFS_OK) return fail(st);
+    if ((st = build_unit_tables(A, P)) != JTFS_OK) return fail(st);
     // the plan keeps every allocation; stash the list for destroy
     auto* keep = new (std::nothrow) std::vector<void*>(A.ptrs);
     if (!keep) return fail(JTFS_ENOMEM);

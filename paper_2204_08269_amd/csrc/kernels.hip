@@ -521,6 +521,22 @@ __global__ void __launch_bounds__(256) k_freq_fwd(const float2* __restrict__ Y, 
     }
 }
 
+// Sum of n partial-V slots, `stride` floats apart, in slot order; eight loads are
+// in flight at a time (one at a time, each slot cost the latency of a load).
+__device__ __forceinline__ float sum_slots(const float* __restrict__ v, int64_t stride, int n) {
+    float acc = 0.f;
+    int s = 0;
+    for (; s + 8 <= n; s += 8) {
+        float q[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) q[j] = v[(s + j) * stride];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc += q[j];
+    }
+    for (; s < n; ++s) acc += v[s * stride];
+    return acc;
+}
+
 // Frequency lowpass (eq. (3)): S2[b][alpha][beta][theta][m][tau] =
 // sum_l PF_beta[m][l] V[theta][rowoff + l][tau], V summed over the partial slots
 // of the contraction's t-chunks.  grid (n_beta, 2 n_alpha, B), every temporal rate
@@ -562,9 +578,9 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
                     float v = 0.f;
                     if (l < lc && tb + tt < NT) {
                         const int row = ro + l0 + l, lt = row / kTileL, lr = row % kTileL;
-                        for (int sl = 0; sl < nslots; ++sl)
-                            v += Vb[(((int64_t)(slot0 + sl) * nlt + lt) * 2 + th) * NTp * kTileL +
-                                    (int64_t)(tb + tt) * kTileL + lr];
+                        const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL +
+                                          (int64_t)(tb + tt) * kTileL + lr;
+                        v = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
                     }
                     Vs[l][tt] = v;
                 }
@@ -607,9 +623,8 @@ __global__ void __launch_bounds__(256) k_v_out(const float* __restrict__ Vp, int
     for (int e = threadIdx.x; e < Lb * NT; e += blockDim.x) {
         const int tau = e / Lb, l = e - tau * Lb;
         const int row = ro + l, lt = row / kTileL, lr = row % kTileL;
-        float acc = 0.f;
-        for (int sl = 0; sl < nslots; ++sl)
-            acc += Vb[(((int64_t)(slot0 + sl) * nlt + lt) * 2 + th) * NTp * kTileL + (int64_t)tau * kTileL + lr];
+        const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL + (int64_t)tau * kTileL + lr;
+        const float acc = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
         o[(int64_t)l * NT + tau] = mulog_out(acc, mu2, inv);
     }
 }
@@ -1241,7 +1256,7 @@ static bool split_backward(const jtfs_plan* P) {
 static Workspace plan_layout(const jtfs_plan* P, int64_t B) {
     const bool split = P->contraction != JTFS_CONTRACTION_FP32;          // SPLIT_F16 or SPLIT_F16_PHASE
     const bool phase = P->contraction == JTFS_CONTRACTION_SPLIT_F16_PHASE && !P->s.tscat;
-    return layout(P->s, B, split, !(split && split_backward(P)), phase);
+    return layout(P->s, B, split, !(split && split_backward(P)), phase, split ? split_chunks(P).sumch : 2 * P->s.sumch);
 }
 
 // forward_only: a forward needs the leading part of the layout only
@@ -1344,14 +1359,14 @@ int forward_impl(const jtfs_plan* P, const float* x, int64_t B, float* s1, float
     }
     const bool split = P->contraction != JTFS_CONTRACTION_FP32 && !s.tscat;
     unsigned* phase = P->contraction == JTFS_CONTRACTION_SPLIT_F16_PHASE && !s.tscat ? (unsigned*)(base + w.phase) : nullptr;
-    for (int a = 0; a < s.n_alpha && split; ++a) {
+    if (split) {
         unsigned short* Yh = (unsigned short*)(base + w.Yh);
         float* ysc = (float*)(base + w.yscale);
         JTFS_TIMED(JTFS_STAGE_OPERAND_SPLIT, st,
-                   rc = launch_ysplit(P, a, Y2, (const float*)(base + w.rowmax), Yh, ysc, B, st));
+                   rc = launch_ysplit(P, Y2, (const float*)(base + w.rowmax), Yh, ysc, B, st));
         if (rc != JTFS_OK) { set_error("operand split kernel failed"); return rc; }
         JTFS_TIMED(JTFS_STAGE_FREQ_FWD, st,
-                   rc = launch_freq_fwd_split(P, a, Yh, ysc, Vp, w.vp_bstride, phase, w.ph_bstride, B, st));
+                   rc = launch_freq_fwd_split(P, Yh, ysc, Vp, w.vp_bstride, phase, w.ph_bstride, B, st));
         if (rc != JTFS_OK) { if (rc == JTFS_EHIP) set_error("split contraction launch failed"); return rc; }
     }
     for (int a = 0; a < s.n_alpha && !split && !s.tscat; ++a) {
@@ -1375,15 +1390,16 @@ int forward_impl(const jtfs_plan* P, const float* x, int64_t B, float* s1, float
         // every temporal rate in one launch; the FP32 contraction writes two partial
         // slots per t-chunk (both halves of its row tile), the split one one
         const int mult = split ? 1 : 2;
+        const ChunkSet& cs = split ? split_chunks(P) : fp32_chunks(P);
         const dim3 grid((unsigned)s.n_beta, (unsigned)(2 * s.n_alpha), (unsigned)B);
         if (s.avg_fr) {
             auto k = s.NT <= 16 ? k_s2_out<16> : k_s2_out<32>;
-            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k, grid, dim3(256), 0, st, Vp, w.vp_bstride, P->d_vchoff,
-                               P->d_nch, mult, nlt, s.NTp, s.NT, P->PFt, P->d_pfoff, P->d_Lb, P->d_rowoff, s.NL, s.NLo, s.n_alpha, s2,
+            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k, grid, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
+                               cs.d_nch, mult, nlt, s.NTp, s.NT, P->PFt, P->d_pfoff, P->d_Lb, P->d_rowoff, s.NL, s.NLo, s.n_alpha, s2,
                                ml.mu2, ml.eps));
         } else {
-            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k_v_out, grid, dim3(256), 0, st, Vp, w.vp_bstride, P->d_vchoff,
-                               P->d_nch, mult, nlt, s.NTp, s.NT, P->d_Lb, P->d_rowoff, s.Mh, s.n_alpha, s2,
+            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k_v_out, grid, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
+                               cs.d_nch, mult, nlt, s.NTp, s.NT, P->d_Lb, P->d_rowoff, s.Mh, s.n_alpha, s2,
                                ml.mu2, ml.eps));
         }
         LAUNCHCHK("frequency lowpass");
@@ -1480,16 +1496,14 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
     unsigned short* Yh = (unsigned short*)(base + w.Yh);
     float* ysc = (float*)(base + w.yscale);
     if (split && !reuse) {
-        for (int a = 0; a < s.n_alpha; ++a) {
-            JTFS_TIMED(JTFS_STAGE_OPERAND_SPLIT, st,
-                       rc = launch_ysplit(P, a, Y2, (const float*)(base + w.rowmax), Yh, ysc, B, st));
-            if (rc != JTFS_OK) { set_error("operand split kernel failed"); return rc; }
-            if (regen_phase) {
-                JTFS_TIMED(JTFS_STAGE_FREQ_FWD, st,
-                           rc = launch_freq_fwd_split(P, a, Yh, ysc, (float*)(base + w.Vp), w.vp_bstride,
-                                                      (unsigned*)(base + w.phase), w.ph_bstride, B, st));
-                if (rc != JTFS_OK) { if (rc == JTFS_EHIP) set_error("split contraction launch failed"); return rc; }
-            }
+        JTFS_TIMED(JTFS_STAGE_OPERAND_SPLIT, st,
+                   rc = launch_ysplit(P, Y2, (const float*)(base + w.rowmax), Yh, ysc, B, st));
+        if (rc != JTFS_OK) { set_error("operand split kernel failed"); return rc; }
+        if (regen_phase) {
+            JTFS_TIMED(JTFS_STAGE_FREQ_FWD, st,
+                       rc = launch_freq_fwd_split(P, Yh, ysc, (float*)(base + w.Vp), w.vp_bstride,
+                                                  (unsigned*)(base + w.phase), w.ph_bstride, B, st));
+            if (rc != JTFS_OK) { if (rc == JTFS_EHIP) set_error("split contraction launch failed"); return rc; }
         }
     }
     if (from_phase) {

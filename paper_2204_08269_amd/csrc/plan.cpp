@@ -192,7 +192,16 @@ int check_supported(const Shapes& s) {
     return JTFS_OK;
 }
 
-Workspace layout(const Shapes& s, int64_t B, bool with_split, bool with_pq, bool with_phase) {
+// floats of one partial-V slot: (l-tile, spin, tau, l)
+static int64_t vslot_floats(const Shapes& s) { return (int64_t)(s.Mp / kTileL) * 2 * s.NTp * kTileL; }
+
+bool fits_slots(const Shapes& s, int64_t vslots) {
+    const int64_t region = (int64_t)sizeof(double2) * s.N + (int64_t)sizeof(float2) * s.n1 * (s.NX / 2 + 1) +
+                           (int64_t)sizeof(float) * s.sumch * 2 * vslot_floats(s);
+    return (int64_t)sizeof(float) * vslots * vslot_floats(s) <= region;
+}
+
+Workspace layout(const Shapes& s, int64_t B, bool with_split, bool with_pq, bool with_phase, int64_t vslots) {
     Workspace w;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t r = o; o += (bytes + 255) / 256 * 256; return r; };
@@ -203,13 +212,17 @@ Workspace layout(const Shapes& s, int64_t B, bool with_split, bool with_pq, bool
     w.tmp64 = take(sizeof(double2) * B * (s.N / 2));     // input transform in FP64
     w.z64 = take(sizeof(double2) * B * (s.N / 2));
     w.Xh = take(sizeof(float2) * B * s.n1 * w.Xh_pitch);
+    // partial V: per signal, per (alpha, t-chunk, t-half) slot, per l-tile, spin, tau,
+    // l.  Nothing reads the three arrays above once the second order is done, so it
+    // starts at the first of them; the region ends with the 2 sumch slots that the
+    // FP32 contraction takes
+    w.vp_bstride = vslots * vslot_floats(s);
+    w.Vp = w.tmp64;
+    (void)take(sizeof(float) * B * s.sumch * 2 * vslot_floats(s));
     w.Y2 = take(sizeof(float2) * B * s.Kp * s.sumTp);
     w.Yh = take(with_split ? sizeof(float2) * B * s.Kp * s.sumTp : 0);   // 4 halves per complex value
     w.rowmax = take(sizeof(float) * B * s.n_alpha * s.Kp);
     w.yscale = take(sizeof(float) * B * s.n_alpha);
-    // partial V: per signal, per (alpha, t-chunk, t-half) slot, per l-tile, spin, tau, l
-    w.vp_bstride = s.sumch * 2 * (s.Mp / kTileL) * 2 * (int64_t)s.NTp * kTileL;
-    w.Vp = take(sizeof(float) * B * w.vp_bstride);
     w.ph_bstride = (int64_t)2 * s.sumTp * s.Mp;
     w.phase = take(with_phase ? sizeof(uint32_t) * B * w.ph_bstride : 0);
     w.fwd_total = o;                 // the forward touches nothing beyond this point
@@ -248,7 +261,7 @@ int jtfs_query(const jtfs_params* p, jtfs_info* out) {
     out->s2_per_signal = s.tscat    ? (int64_t)s.n_alpha * s.n1 * s.NT
                          : s.avg_fr ? (int64_t)s.n_alpha * s.n_beta * 2 * s.NLo * s.NT
                                     : (int64_t)s.n_alpha * 2 * s.Mh * s.NT;
-    const jtfs::Workspace w = jtfs::layout(s, 1, true, true, false);
+    const jtfs::Workspace w = jtfs::layout(s, 1, true, true, false, 2 * s.sumch);
     out->ws_fwd = (int64_t)w.fwd_total;
     out->ws_bwd = (int64_t)w.total;
     return st;

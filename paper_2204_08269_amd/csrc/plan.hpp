@@ -90,8 +90,12 @@ struct Workspace {
 };
 // with_split: the split-FP16 operand copy of Y2; with_pq: the FP32 backward's P/Q';
 // with_phase: the stored unit phase of the contraction output, per signal and rate
-// [spin][Mp / 32][4][Tp][8] elements of two snorm16.
-Workspace layout(const Shapes& s, int64_t B, bool with_split, bool with_pq, bool with_phase);
+// [spin][Mp / 32][4][Tp][8] elements of two snorm16.  vslots: partial-V slots per
+// signal.  The partial V lies over the input transform's FP64 scratch and X_hat,
+// which are dead when the contraction writes it; fits_slots tells whether that
+// region (with the 2 sumch slots of the FP32 contraction at its end) holds vslots.
+Workspace layout(const Shapes& s, int64_t B, bool with_split, bool with_pq, bool with_phase, int64_t vslots);
+bool fits_slots(const Shapes& s, int64_t vslots);
 
 }  // namespace jtfs
 
@@ -107,8 +111,30 @@ struct Tuning {
     // register-resident rows: radix-8 passes instead of radix-16 ones, per stage
     bool r8_scalogram = false, r8_second = false, r8_rowfft = false, r8_first_adj = false;
     bool batch8k = false;        // in-LDS row transforms: 8192 points per workgroup (else 4096)
-    int chunk = kChunkT;         // t-columns per workgroup of the forward contraction (1024, 2048 or 4096)
+    // t-columns per workgroup of the forward contraction: 1024 or 2048 as set, or
+    // kChunkT: 4096 in FP32, auto_chunk of the plan in the split modes
+    int chunk = kChunkT;
 };
+// A temporal rate as the split contraction's kernels read it (device table, one per alpha).
+struct FreqRate {
+    int64_t yoff, phioff, phase_off;   // its Y2 block, Phi block and stored-phase block
+    int Tp;                            // padded columns
+    float sphi;                        // scale of its split Phi
+    float unscale_wphi;                // 1 / (sw sphi)
+    int pad;
+};
+// Columns t0 .. t0 + ncols - 1 of one rate; slot: its partial V (forward chunks only).
+struct FreqUnit {
+    int alpha, t0, ncols, slot;
+};
+// The t-chunks of the forward contraction for one chunk length, built with the plan.
+struct ChunkSet {
+    int64_t sumch = 0;                 // chunks, i.e. partial-V slots, per signal
+    int64_t* d_vchoff = nullptr;       // per alpha: first slot
+    int* d_nch = nullptr;              // per alpha: slots
+    FreqUnit* d_units = nullptr;       // [sumch], longest first
+};
+constexpr int kChunkLogs[2] = {8, 12}; // chunk lengths 2^8 .. 2^12
 // points per workgroup of the in-LDS second-order and gY2 row transforms
 inline int lds_batch_log(const Tuning& t) { return t.batch8k ? 13 : 12; }
 // rows of 2^logn points take the register-resident kernels above 2^14 always, at
@@ -141,8 +167,10 @@ struct jtfs_plan {
     int64_t* d_yoff = nullptr;     // per alpha: offset of its Y2 block
     int* d_Tp = nullptr;           // per alpha: padded length
     int* d_Ta = nullptr;           // per alpha: length NX / 2^k2
-    int64_t* d_vchoff = nullptr;   // per alpha: first partial-V slot
-    int* d_nch = nullptr;          // per alpha: partial-V slots (t-chunks)
+    jtfs::ChunkSet cset[5];        // t-chunks of 2^8 .. 2^12 columns
+    int auto_chunk = 4;            // index of the split contraction's own choice
+    jtfs::FreqRate* d_rates = nullptr;   // [n_alpha]
+    jtfs::FreqUnit* d_tiles = nullptr;   // [sumTp / 128]: the 128-column tiles in Y2 order
     int64_t* d_pfoff = nullptr;    // per beta: offset of its frequency-lowpass matrix
     int* d_Lb = nullptr;           // per beta: L / 2^kfr
     int* d_rowoff = nullptr;       // per beta: first row of the contraction
@@ -164,3 +192,14 @@ struct jtfs_plan {
     std::vector<float> sphi;
     void* owned = nullptr;         // list of device allocations released by destroy
 };
+
+namespace jtfs {
+// the chunk set of the plan's tuning: as set, else 4096 columns (FP32 contraction)
+// or the plan's own choice (split contraction)
+inline const ChunkSet& fp32_chunks(const jtfs_plan* P) {
+    return P->cset[P->tune.chunk == 1024 ? 2 : P->tune.chunk == 2048 ? 3 : 4];
+}
+inline const ChunkSet& split_chunks(const jtfs_plan* P) {
+    return P->tune.chunk == kChunkT ? P->cset[P->auto_chunk] : fp32_chunks(P);
+}
+}  // namespace jtfs

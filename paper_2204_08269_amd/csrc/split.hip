@@ -143,14 +143,20 @@ __global__ void k_phtsplit(const float* __restrict__ Phi, int Tp, int NTp, float
 // lo, im hi, im lo): each lane of the contraction reads 8 consecutive lambda_1 of
 // one t as 16 bytes, and the 32 lanes of a column block read 512 contiguous bytes.
 // sy = 2^(13-e) from the block maximum (row maxima written by the second-order
-// kernel).  grid (Tp/64, B, Z), 256 threads: block z takes the 32-row chunks
-// z, z + Z, ... (Z > 1 where Tp/64 x B alone would leave the GPU idle).
-__global__ void __launch_bounds__(256) k_ysplit(const float2* __restrict__ Y, int64_t y_bstride, int Tp, int Kp,
-                                                const float* __restrict__ rowmax, int alpha, int n_alpha,
+// kernel).  Every temporal rate in one launch: grid (sum Tp / 64, B, Z), 256
+// threads; block x is half of tile x / 2 of the plan's 128-column tiles, block z
+// takes the 32-row chunks z, z + Z, ... (Z > 1 where the grid alone would leave
+// the GPU idle).
+__global__ void __launch_bounds__(256) k_ysplit(const float2* __restrict__ Y, int64_t y_bstride, int Kp,
+                                                const FreqRate* __restrict__ rates, const FreqUnit* __restrict__ tiles,
+                                                const float* __restrict__ rowmax, int n_alpha,
                                                 unsigned short* __restrict__ Yh, float* __restrict__ yscale) {
     __shared__ float2 tile[32][65];
     __shared__ float red[256];
-    const int t0 = blockIdx.x * 64;
+    const FreqUnit tl = tiles[blockIdx.x >> 1];
+    const int alpha = tl.alpha, t0 = tl.t0 + 64 * (int)(blockIdx.x & 1);
+    const int Tp = rates[alpha].Tp;
+    const int64_t yoff = rates[alpha].yoff;
     const int64_t b = blockIdx.y;
     const float* rm = rowmax + (b * n_alpha + alpha) * Kp;
     float m = 0.f;
@@ -162,9 +168,9 @@ __global__ void __launch_bounds__(256) k_ysplit(const float2* __restrict__ Y, in
         __syncthreads();
     }
     const float sy = pow2_scale(red[0]);
-    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) yscale[b * n_alpha + alpha] = sy;
-    const float2* Yb = Y + b * y_bstride;
-    _Float16* Ho = (_Float16*)Yh + b * y_bstride * 4;
+    if (t0 == 0 && blockIdx.z == 0 && threadIdx.x == 0) yscale[b * n_alpha + alpha] = sy;
+    const float2* Yb = Y + b * y_bstride + yoff;
+    _Float16* Ho = (_Float16*)Yh + (b * y_bstride + yoff) * 4;
     for (int k0 = 32 * (int)blockIdx.z; k0 < Kp; k0 += 32 * (int)gridDim.z) {
         const int nk = min(32, Kp - k0);
         __syncthreads();
@@ -249,13 +255,17 @@ constexpr int kPhaseTrp = 64 * (16 * NK * 8 + 16) + 8 * 32 * 36 * 4 <= kMaxDynLd
 // The modulus enters the second product split with a per-column power-of-two
 // scale, removed from that tile's contribution before accumulation.
 // Workgroups are mapped so that the row tiles sharing a t-chunk run on one XCD.
+// One launch covers the t-chunks of every temporal rate and signal (nU units,
+// longest chunks first): the short rates' few workgroups, which alone leave most
+// of the GPU idle for a launch each, run beside and behind the long ones.
 template <int NTB, int NK>
-__global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __restrict__ Yh, int64_t yh_bstride, int Tp,
-                                                    int chunk, int nch, int nU, int nlt,
+__global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __restrict__ Yh, int64_t yh_bstride,
+                                                    const FreqRate* __restrict__ rates,
+                                                    const FreqUnit* __restrict__ units, int nB, int u0, int nU, int nlt,
                                                     const unsigned short* __restrict__ Wsp,
-                                                    const unsigned short* __restrict__ Phsp, float unscale_wphi,
-                                                    const float* __restrict__ yscale, int alpha, int n_alpha,
-                                                    float* __restrict__ Vp, int64_t vp_bstride, int slot0,
+                                                    const unsigned short* __restrict__ Phall,
+                                                    const float* __restrict__ yscale, int n_alpha,
+                                                    float* __restrict__ Vp, int64_t vp_bstride,
                                                     unsigned* __restrict__ phase, int64_t ph_bstride, float sw) {
     constexpr int NTp = 32 * NTB;
     constexpr int Kp = 16 * NK;            // K = NK k-steps of 16 (compile time: the K loop is unrolled)
@@ -264,11 +274,14 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
     unsigned char* lw_ = lds;
 
     const int g = blockIdx.x;
-    const int u = ((g >> 3) / nlt) * 8 + (g & 7);
+    const int u = u0 + ((g >> 3) / nlt) * 8 + (g & 7);
     const int lt = (g >> 3) % nlt;
     if (u >= nU) return;
-    const int64_t b = u / nch;
-    const int ch = u % nch;
+    const int64_t b = u % nB;
+    const FreqUnit un = units[u / nB];
+    const FreqRate rate = rates[un.alpha];
+    const int alpha = un.alpha, Tp = rate.Tp;
+    const unsigned short* __restrict__ Phsp = Phall + rate.phioff * 2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, i32 = lane & 31;
     const int wl = wave & 1, wt = wave >> 1;
@@ -283,7 +296,8 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
             *(uint4*)(lw_ + r * WS + c * 16) = src[e];
         }
     }
-    const unsigned short* Yb = Yh + b * yh_bstride;
+    const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
+    if (phase) phase += rate.phase_off;
     // floor of |z|^2 in the scaled units of z (kEpsMod2 (sw sy)^2, kept a normal number)
     float eps2s = 0.f;
     if (phase) {
@@ -302,7 +316,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
     // before the current tile's epilogue.  W fragments come from the resident
     // LDS rows.  The Phi fragments of a tile are requested before its Y loads,
     // so that waiting for them never waits for Y.
-    const int tbeg = ch * chunk, tend = (ch + 1) * chunk;
+    const int tbeg = un.t0, tend = un.t0 + un.ncols;
     auto ycol_at = [&](int t0) {
         return launder_v((const uint4*)Yb + (((int64_t)((t0 >> 5) + wt) * nkb + h) * 128 + i32));
     };
@@ -459,7 +473,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
         if constexpr (!early) next_tile();
     }
     // sum the four t-quarter waves of each row half through LDS, unscale, store
-    const float unscale = unscale_wphi / yscale[b * n_alpha + alpha];
+    const float unscale = rate.unscale_wphi / yscale[b * n_alpha + alpha];
     float* red = (float*)lds;                        // [wave][spin][64 lanes][16]
 #pragma unroll
     for (int n = 0; n < NTB; ++n) {
@@ -480,7 +494,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
 #pragma unroll
                     for (int q = 0; q < 4; ++q) acc += red[(((wl + 2 * q) * 2 + spin) * 64 + lane) * 16 + r];
                     const int tau = n * 32 + crow(r, h);
-                    o[((((int64_t)(slot0 + ch) * nlt + lt) * 2 + spin) * NTp + tau) * kTileL + wl * 32 + i32] =
+                    o[((((int64_t)un.slot * nlt + lt) * 2 + spin) * NTp + tau) * kTileL + wl * 32 + i32] =
                         acc * unscale;
                 }
             }
@@ -569,12 +583,13 @@ constexpr size_t fwdq_lds(int Kp, int NTQ, bool with_phase) {
 // accumulation.  NTQ blocks of 16 frames (N/T <= 32).  Workgroups are mapped as in
 // k_freq_fwd_h.
 template <int NK, int NTQ>
-__global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __restrict__ Yh, int64_t yh_bstride, int Tp,
-                                                    int chunk, int nch, int nU, int nlt,
+__global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __restrict__ Yh, int64_t yh_bstride,
+                                                    const FreqRate* __restrict__ rates,
+                                                    const FreqUnit* __restrict__ units, int nB, int u0, int nU, int nlt,
                                                     const unsigned short* __restrict__ Wq,
-                                                    const unsigned short* __restrict__ Phq, float unscale_wphi,
-                                                    const float* __restrict__ yscale, int alpha, int n_alpha,
-                                                    float* __restrict__ Vp, int64_t vp_bstride, int slot0,
+                                                    const unsigned short* __restrict__ Phall,
+                                                    const float* __restrict__ yscale, int n_alpha,
+                                                    float* __restrict__ Vp, int64_t vp_bstride,
                                                     unsigned* __restrict__ phase, int64_t ph_bstride, float sw) {
     constexpr int NTp = 32;                  // tau slots of the partial-V layout
     constexpr int Kp = 16 * NK;
@@ -584,11 +599,14 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     extern __shared__ __align__(16) unsigned char lds[];
 
     const int g = blockIdx.x;
-    const int u = ((g >> 3) / nlt) * 8 + (g & 7);
+    const int u = u0 + ((g >> 3) / nlt) * 8 + (g & 7);
     const int lt = (g >> 3) % nlt;
     if (u >= nU) return;
-    const int64_t b = u / nch;
-    const int ch = u % nch;
+    const int64_t b = u % nB;
+    const FreqUnit un = units[u / nB];
+    const FreqRate rate = rates[un.alpha];
+    const int alpha = un.alpha, Tp = rate.Tp;
+    const unsigned short* __restrict__ Phq = Phall + rate.phioff * 2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j16 = lane & 15, g4 = lane >> 4;
     constexpr int nkb = Kp / 8;
@@ -600,7 +618,8 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
 #pragma unroll
         for (int e = 0; e < 2 * NS; ++e) dst[e * 512 + tid] = src[e * 512 + tid];
     }
-    const unsigned short* Yb = Yh + b * yh_bstride;
+    const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
+    if (phase) phase += rate.phase_off;
     float eps2s;                             // the floor of |z|^2 in the scaled units of Z
     {
         const double wy = (double)sw * (double)yscale[b * n_alpha + alpha];
@@ -620,7 +639,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
         for (int p = 0; p < 4; ++p) w[p] = wfr[((ks * 4 + lb) * 4 + p) * 64];
     };
     // this lane's Y fragments: column t, k-group 4 ks + g4, plane p (uint4 units)
-    const int tbeg = ch * chunk, tend = (ch + 1) * chunk;
+    const int tbeg = un.t0, tend = un.t0 + un.ncols;
     auto ycol_at = [&](int t0) {
         // the column offset formed from the thread index here, not kept live across
         // the tile loop (at 256 registers the compiler spilled it, and its reload
@@ -762,7 +781,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
         }
     }
     // sum the eight waves' partial V through LDS, unscale, store
-    const float unscale = unscale_wphi / yscale[b * n_alpha + alpha];
+    const float unscale = rate.unscale_wphi / yscale[b * n_alpha + alpha];
     float* red = (float*)lds;                // [wave][n][lb][spin][64 lanes][4]
     __syncthreads();
 #pragma unroll
@@ -775,7 +794,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
                     make_float4(vacc[n][lb][spin][0], vacc[n][lb][spin][1], vacc[n][lb][spin][2],
                                 vacc[n][lb][spin][3]);
     __syncthreads();
-    float* o = Vp + b * vp_bstride + ((int64_t)(slot0 + ch) * nlt + lt) * 2 * NTp * kTileL;
+    float* o = Vp + b * vp_bstride + ((int64_t)un.slot * nlt + lt) * 2 * NTp * kTileL;
     for (int e = tid; e < NTQ * 4 * 2 * 64 * 4; e += 512) {
         // e = (((n * 4 + lb) * 2 + spin) * 64 + ln) * 4 + r: element tau = 16 n + 4 (ln / 16) + r,
         // l = 16 lb + ln % 16
@@ -1903,6 +1922,8 @@ int build_split_tables(jtfs_plan* P, std::vector<void*>& owned) {
 
 // largest K (in k-steps of 16) whose resident W tile fits the dynamic LDS limit
 constexpr int kMaxFwdNK = (kMaxDynLds / 64 - 16) / 8 / 16;
+// workgroups of 512 threads in one launch of the forward contraction (a grid holds 2^32 threads)
+constexpr int kMaxFwdGroups = 1 << 22;
 
 template <int NTB, int NK = 1>
 static int fwd_attributes() {
@@ -1965,52 +1986,53 @@ static void launch_fwd_nk(int nk, dim3 grid, size_t lds, hipStream_t st, Args...
     }
 }
 
-int launch_ysplit(const jtfs_plan* P, int a, const float2* Y2, const float* rowmax, unsigned short* Yh, float* yscale,
+int launch_ysplit(const jtfs_plan* P, const float2* Y2, const float* rowmax, unsigned short* Yh, float* yscale,
                   int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int64_t yb = (int64_t)s.Kp * s.sumTp;
     // chunks of 32 rows spread over grid z until there are about 2048 workgroups
-    const int64_t base = (int64_t)(s.Tp[a] / 64) * B;
+    const int64_t base = s.sumTp / 64 * B;
     const int nchunk = (s.Kp + 31) / 32;
     const int z = (int)std::max<int64_t>(1, std::min<int64_t>(nchunk, (2048 + base - 1) / base));
-    hipLaunchKernelGGL(k_ysplit, dim3(s.Tp[a] / 64, (unsigned)B, (unsigned)z), dim3(256), 0, st, Y2 + s.yoff[a], yb,
-                       s.Tp[a], s.Kp, rowmax, a, s.n_alpha, Yh + s.yoff[a] * 4, yscale);
+    hipLaunchKernelGGL(k_ysplit, dim3((unsigned)(s.sumTp / 64), (unsigned)B, (unsigned)z), dim3(256), 0, st, Y2, yb, s.Kp,
+                       P->d_rates, P->d_tiles, rowmax, s.n_alpha, Yh, yscale);
     return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
 }
 
-int launch_freq_fwd_split(const jtfs_plan* P, int a, const unsigned short* Yh, const float* yscale, float* Vp,
+int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const float* yscale, float* Vp,
                           int64_t vp_bstride, unsigned* phase, int64_t ph_bstride, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int nlt = s.Mp / kTileL;
-    const int nU = (int)(B * s.nch[a]);
-    const unsigned grid = (unsigned)(((nU + 7) / 8) * 8 * nlt);
+    const ChunkSet& cs = split_chunks(P);
+    const int nU = (int)(B * cs.sumch), nB = (int)B;
+    // one launch, unless its workgroups pass the limit of a grid (2^32 threads)
+    const int per = kMaxFwdGroups / nlt / 8 * 8;
     const int64_t yhb = (int64_t)s.Kp * s.sumTp * 4;
-    const float unscale = 1.f / (P->sw * P->sphi[a]);
     const size_t lds = split_fwd_lds(s, phase != nullptr);
     if (lds > (size_t)kMaxDynLds) { set_error("K beyond the split contraction's LDS tile"); return JTFS_ENOTSUP; }
-    const unsigned short* Ya = Yh + s.yoff[a] * 4;
-    const unsigned short* Ph = P->Phsp + s.phioff[a] * 2;
-    const int slot0 = (int)s.vchoff[a];
     const int nk = s.Kp / 16;
     if (nk < 1 || nk > kMaxFwdNK) { set_error("K beyond the split contraction's LDS tile"); return JTFS_ENOTSUP; }
-    // this rate's block of the stored phase (2 Mp Tp elements) after the rates before it
-    unsigned* pha = phase ? phase + (int64_t)2 * s.Mp * (s.yoff[a] / s.Kp) : nullptr;
-    if (P->tune.fwd16 && fwdq_supported(P, phase != nullptr)) {
-        const int ntq = (s.NT + 15) / 16;
-        const size_t ldsq = fwdq_lds(s.Kp, ntq, phase != nullptr);
-        const unsigned short* Pq = P->Phq + s.phioff[a] * 2;
-        if (ntq == 1)
-            launch_fwdq_nk<1>(nk, dim3(grid), ldsq, st, Ya, yhb, s.Tp[a], s.chunk[a], s.nch[a], nU, nlt, (const unsigned short*)P->Wq, Pq, unscale, yscale, a, s.n_alpha, Vp, vp_bstride, slot0, pha, ph_bstride, P->sw);
+    const FreqRate* rt = P->d_rates;
+    const FreqUnit* un = cs.d_units;
+    const bool tile16 = P->tune.fwd16 && fwdq_supported(P, phase != nullptr);
+    const int ntq = (s.NT + 15) / 16;
+    const size_t ldsq = fwdq_lds(s.Kp, ntq, phase != nullptr);
+    const unsigned short *Wq = P->Wq, *Pq = P->Phq, *Wsp = P->Wsp, *Ph = P->Phsp;
+    if (!tile16 && s.NTp > 64) { set_error("unsupported N/T"); return JTFS_ENOTSUP; }
+    for (int u0 = 0; u0 < nU; u0 += per) {
+        const int n = std::min(per, nU - u0), end = u0 + n;
+        const dim3 grid((unsigned)((n + 7) / 8 * 8 * nlt));
+        if (tile16 && ntq == 1)
+            launch_fwdq_nk<1>(nk, grid, ldsq, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wq, Pq, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
+        else if (tile16)
+            launch_fwdq_nk<2>(nk, grid, ldsq, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wq, Pq, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
+        else if (s.NTp == 32)
+            launch_fwd_nk<1>(nk, grid, lds, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wsp, Ph, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
         else
-            launch_fwdq_nk<2>(nk, dim3(grid), ldsq, st, Ya, yhb, s.Tp[a], s.chunk[a], s.nch[a], nU, nlt, (const unsigned short*)P->Wq, Pq, unscale, yscale, a, s.n_alpha, Vp, vp_bstride, slot0, pha, ph_bstride, P->sw);
-        return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
+            launch_fwd_nk<2>(nk, grid, lds, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wsp, Ph, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
+        if (hipGetLastError() != hipSuccess) return JTFS_EHIP;
     }
-    switch (s.NTp / 32) {
-        case 1: launch_fwd_nk<1>(nk, dim3(grid), lds, st, Ya, yhb, s.Tp[a], s.chunk[a], s.nch[a], nU, nlt, (const unsigned short*)P->Wsp, Ph, unscale, yscale, a, s.n_alpha, Vp, vp_bstride, slot0, pha, ph_bstride, P->sw); break;
-        case 2: launch_fwd_nk<2>(nk, dim3(grid), lds, st, Ya, yhb, s.Tp[a], s.chunk[a], s.nch[a], nU, nlt, (const unsigned short*)P->Wsp, Ph, unscale, yscale, a, s.n_alpha, Vp, vp_bstride, slot0, pha, ph_bstride, P->sw); break;
-        default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
-    }
-    return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
+    return JTFS_OK;
 }
 
 template <int NTB>

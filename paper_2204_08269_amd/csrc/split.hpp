@@ -10,13 +10,14 @@ namespace jtfs {
 bool split_supported(const Shapes& s);
 int build_split_tables(jtfs_plan* P, std::vector<void*>& owned);
 int split_attributes();
-int launch_ysplit(const jtfs_plan* P, int a, const float2* Y2, const float* rowmax, unsigned short* Yh, float* yscale,
+// every temporal rate in one launch
+int launch_ysplit(const jtfs_plan* P, const float2* Y2, const float* rowmax, unsigned short* Yh, float* yscale,
                   int64_t B, hipStream_t st);
 int launch_freq_bwd_split(const jtfs_plan* P, int a, const unsigned short* Yh, const float* yscale, const float* gV,
                           const float* gvmax, float2* gY2, int64_t B, hipStream_t st);
-// phase: NULL, or the stored-phase buffer of the workspace (ph_bstride packed snorm16
-// pairs per signal)
-int launch_freq_fwd_split(const jtfs_plan* P, int a, const unsigned short* Yh, const float* yscale, float* Vp,
+// every temporal rate in one launch; phase: NULL, or the stored-phase buffer of the
+// workspace (ph_bstride packed snorm16 pairs per signal)
+int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const float* yscale, float* Vp,
                           int64_t vp_bstride, unsigned* phase, int64_t ph_bstride, int64_t B, hipStream_t st);
 // backward contraction from the phase the forward stored (no recomputation of Z)
 int launch_freq_bwd_phase(const jtfs_plan* P, int a, const unsigned* phase, int64_t ph_bstride, const uint4* Gs,

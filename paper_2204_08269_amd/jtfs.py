@@ -192,7 +192,8 @@ class JTFS:
         register-resident; contraction tiles; stages whose register-resident
         transforms use radix-8 passes (else radix 16); points per workgroup of
         the in-LDS row transforms (4096 or 8192); t-columns per workgroup of the
-        forward contraction (1024, 2048 or 4096; the workspace size follows)."""
+        forward contraction (1024, 2048, or 4096 for the plan's own choice of up to
+        4096; the workspace size follows)."""
         mode = _lib.CONTRACTIONS[contraction]
         if lds_batch not in (4096, 8192):
             raise ValueError("lds_batch must be 4096 or 8192")

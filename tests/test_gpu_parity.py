@@ -985,3 +985,24 @@ def test_autotune_cache_reuses_the_choice(tmp_path, monkeypatch):
     # another batch size is another key
     third = op.autotune(3, torch.from_numpy(synth.batch(1, B=3)).cuda(), reps=1)
     assert not third["from_cache"]
+
+
+@pytest.mark.parametrize("p", [P1, dict(N=2 ** 14, J=10, Q=(12, 1), J_fr=3, Q_fr=1, T=2 ** 8, F=4),
+                               dict(N=2 ** 15, J=11, Q=(16, 1), J_fr=4, Q_fr=2, T=2 ** 11, F=8)],
+                         ids=lambda p: f"N{p['N']}_T{p['T']}")
+def test_forward_chunk_lengths_agree(p):
+    """The plan's own t-chunks (rates shorter, equal and longer than a chunk, 64 frames among them) against the
+    set lengths: the same FP32 terms summed in another order, at most 2^7 slots of 8 waves (2^10 roundings of
+    2^-24, so 1e-4 of the largest value at the very worst and about 2e-6 in norm); and a batch gives each signal's
+    bits."""
+    x = synth.batch(5, B=3, N=p["N"])
+    op = gpu_op(p, "split16")
+    a1, a2 = run_forward(op, x)
+    for tile in (32, 16) if p["N"] // p["T"] <= 32 else (32,):
+        for chunk in (1024, 2048, 4096):
+            op.set_tuning("split16", ALL_ROWS, fwd_tile=tile, t_chunk=chunk)
+            b1, b2 = run_forward(op, x)
+            assert np.array_equal(a1, b1)
+            assert rel_l2(b2, a2) <= 2e-6
+        c1, c2 = run_forward(op, x[1:2])
+        assert np.array_equal(c1[0], b1[1]) and np.array_equal(c2[0], b2[1])
