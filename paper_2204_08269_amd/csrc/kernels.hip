@@ -1510,17 +1510,19 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
         JTFS_TIMED(JTFS_STAGE_OPERAND_SPLIT, st, rc = launch_gv_split(P, gV, (uint4*)(base + w.gvs), B, st));
         if (rc != JTFS_OK) { if (rc == JTFS_EHIP) set_error("gV split launch failed"); return rc; }
     }
-    for (int a = 0; a < s.n_alpha && split; ++a) {
+    if (split) {
+        // every temporal rate in one launch (from the phase, one or two, each timed on its own)
         if (from_phase) {
-            // (one or two launches, each timed on its own)
-            rc = launch_freq_bwd_phase(P, a, (const unsigned*)(base + w.phase), w.ph_bstride,
+            rc = launch_freq_bwd_phase(P, (const unsigned*)(base + w.phase), w.ph_bstride,
                                        (const uint4*)(base + w.gvs), w.gvs_bstride, (const float*)(base + w.gvmax),
                                        gY2, B, st);
         } else {
             JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st,
-                       rc = launch_freq_bwd_split(P, a, Yh, ysc, gV, (const float*)(base + w.gvmax), gY2, B, st));
+                       rc = launch_freq_bwd_split(P, Yh, ysc, gV, (const float*)(base + w.gvmax), gY2, B, st));
         }
         if (rc != JTFS_OK) { if (rc == JTFS_EHIP) set_error("split backward contraction launch failed"); return rc; }
+    }
+    for (int a = 0; a < s.n_alpha && split; ++a) {
         rc = gy2_row_fft(P, a, gY2, yb, B, st);
         if (rc != JTFS_OK) return rc;
     }

@@ -1050,15 +1050,20 @@ __device__ __forceinline__ void bwd_chunk(int c, int nC, int Mp, int wave, int l
     __syncthreads();
 }
 
+// One launch covers every rate's tiles (the short rates, one or two workgroups per
+// signal each, had a launch of a full chunk loop's length to themselves): one
+// signal of 2^11 samples fwd+bwd 431 -> 200 us with the forward's single launch,
+// 3 x 2^15 2475 -> 1005 us, 16 x 2^16 (stored phase) 9.91 -> 9.42 ms.
 template <int NTB, int NI, int NK>
 __global__ void __launch_bounds__(256) k_freq_bwd_h(const unsigned short* __restrict__ Yh, int64_t yh_bstride,
-                                                    int Tp, int nTt, int nU,
+                                                    const FreqRate* __restrict__ rates,
+                                                    const FreqUnit* __restrict__ tiles, int nT, int nU,
                                                     const unsigned short* __restrict__ Wsp,
                                                     const unsigned short* __restrict__ WTsp, int Mp,
-                                                    const unsigned short* __restrict__ PhTsp, float sphi,
-                                                    const float* __restrict__ gV, int64_t gv_bstride,
+                                                    const unsigned short* __restrict__ PhTsp,
+                                                    const float* __restrict__ gV,
                                                     const float* __restrict__ gvmax, int n_beta,
-                                                    const float* __restrict__ yscale, int alpha, int n_alpha,
+                                                    const float* __restrict__ yscale, int n_alpha,
                                                     float sw, float2* __restrict__ gY, int64_t gy_bstride) {
     constexpr int NTp = 32 * NTB;
     constexpr int Kp = 16 * NK, nkb = 2 * NK;
@@ -1067,8 +1072,11 @@ __global__ void __launch_bounds__(256) k_freq_bwd_h(const unsigned short* __rest
     __shared__ uint4 Ls_T1[NI * 512];
     const int u = blockIdx.x;
     if (u >= nU) return;                            // whole block
-    const int64_t b = u / nTt;
-    const int t0 = (u % nTt) * kTileTh;
+    const int64_t b = u / nT;
+    const FreqUnit un = tiles[u % nT];
+    const FreqRate rate = rates[un.alpha];
+    const int alpha = un.alpha, t0 = un.t0, Tp = rate.Tp;
+    const float sphi = rate.sphi;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, i32 = lane & 31;
     const int tw0 = t0 + wave * 32;                 // this wave's columns
@@ -1087,10 +1095,10 @@ __global__ void __launch_bounds__(256) k_freq_bwd_h(const unsigned short* __rest
 #pragma unroll
     for (int q = 0; q < NI; ++q) { gyr[q] = z16(); gyi[q] = z16(); }
 
-    const unsigned short* Yb = Yh + b * yh_bstride;
+    const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
     const uint4* ycol = (const uint4*)Yb + (((int64_t)(tw0 >> 5) * nkb + h) * 128 + i32);   // B operand: column t
-    const float* gvb = gV + b * gv_bstride;
-    const uint4* phrow = (const uint4*)(PhTsp + ((int64_t)(tw0 + i32) * (NTp / 8) + h) * 16);
+    const float* gvb = gV + (b * n_alpha + alpha) * 2 * Mp * NTp;
+    const uint4* phrow = (const uint4*)(PhTsp + rate.phioff * 2 + ((int64_t)(tw0 + i32) * (NTp / 8) + h) * 16);
     const uint4* Wsrc = (const uint4*)Wsp;
     const uint4* Tsrc = (const uint4*)WTsp;
 
@@ -1119,7 +1127,7 @@ __global__ void __launch_bounds__(256) k_freq_bwd_h(const unsigned short* __rest
     }
     // ---- store gY rows i < Kp, columns tw0.. (FP32 complex)
     const float inv = 1.f / (sw * spq);
-    float2* o = gY + b * gy_bstride;
+    float2* o = gY + b * gy_bstride + rate.yoff;
 #pragma unroll
     for (int q = 0; q < NI; ++q)
 #pragma unroll
@@ -1428,12 +1436,13 @@ __device__ __forceinline__ void bwd_phase_chunk(int c, int nC, int wave, int lan
 // budget holds at most 8 at 32 frames; larger K runs as several launches over
 // disjoint i-ranges, each repeating the modulus adjoint).
 template <int NTB, int NI>
-__global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__ phase, int64_t ph_bstride, int Tp,
-                                                    int nTt, int nU, const unsigned short* __restrict__ WTsp,
-                                                    int q_base, int nit,
+__global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__ phase, int64_t ph_bstride,
+                                                    const FreqRate* __restrict__ rates,
+                                                    const FreqUnit* __restrict__ tiles, int nT, int nU,
+                                                    const unsigned short* __restrict__ WTsp, int q_base, int nit,
                                                     int Mp, int Kp, const unsigned short* __restrict__ PhTsp,
-                                                    float sphi, const uint4* __restrict__ Gs, int64_t gs_bstride,
-                                                    const float* __restrict__ gvmax, int n_beta, int alpha,
+                                                    const uint4* __restrict__ Gs, int64_t gs_bstride,
+                                                    const float* __restrict__ gvmax, int n_beta,
                                                     int n_alpha, float sw, float2* __restrict__ gY,
                                                     int64_t gy_bstride) {
     constexpr int NTp = 32 * NTB;
@@ -1442,8 +1451,11 @@ __global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__
     __shared__ uint4 Ls_G[gvs_chunk<NTB>()];
     const int u = blockIdx.x;
     if (u >= nU) return;                            // whole block
-    const int64_t b = u / nTt;
-    const int t0 = (u % nTt) * kTileTh;
+    const int64_t b = u / nT;
+    const FreqUnit un = tiles[u % nT];
+    const FreqRate rate = rates[un.alpha];
+    const int alpha = un.alpha, t0 = un.t0, Tp = rate.Tp;
+    const float sphi = rate.sphi;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, i32 = lane & 31;
     const int tw0 = t0 + wave * 32;                 // this wave's columns
@@ -1458,13 +1470,13 @@ __global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__
 #pragma unroll
     for (int q = 0; q < NI; ++q) { gyr[q] = z16(); gyi[q] = z16(); }
 
-    const uint4* phrow = (const uint4*)(PhTsp + ((int64_t)(tw0 + i32) * (NTp / 8) + h) * 16);
+    const uint4* phrow = (const uint4*)(PhTsp + rate.phioff * 2 + ((int64_t)(tw0 + i32) * (NTp / 8) + h) * 16);
     const uint4* Tsrc = (const uint4*)WTsp + (int64_t)q_base * 512;
     const int64_t cstride = (int64_t)nit * 512;
-    const uint4* Gb = Gs + b * gs_bstride;
+    const uint4* Gb = Gs + b * gs_bstride + (int64_t)alpha * (Mp / 32) * gvs_chunk<NTB>();
     // this lane's column of the stored phase, rows 4h.. of each 8-row group
     // (blocks [spin][Mp / 32], each four row groups of Tp x 8 elements)
-    const unsigned* pbase = phase + b * ph_bstride + (int64_t)(tw0 + i32) * 8 + 4 * h;
+    const unsigned* pbase = phase + b * ph_bstride + rate.phase_off + (int64_t)(tw0 + i32) * 8 + 4 * h;
     const int64_t spin_stride = (int64_t)Tp * Mp, c_stride = (int64_t)Tp * 32;
 
     uint4 phv[NTB * 2][2];
@@ -1495,7 +1507,7 @@ __global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__
                                  c_stride, c0, cstride, Ls_T1, Ls_T0, gyr, gyi, gu, pv, ph, pl);
     }
     const float inv = 1.f / (sw * spq);
-    float2* o = gY + b * gy_bstride;
+    float2* o = gY + b * gy_bstride + rate.yoff;
 #pragma unroll
     for (int q = 0; q < NI; ++q)
 #pragma unroll
@@ -1707,21 +1719,26 @@ __device__ __forceinline__ void bwdq_half(const uint4* Lh, const uint4* Lg, int 
 // next barrier (a wait for a register load while a copy is in flight is a wait
 // for everything).  The last chunks request their own operands again.
 template <int NI>
-__global__ void __launch_bounds__(256) k_freq_bwd_q(const unsigned* __restrict__ phase, int64_t ph_bstride, int Tp,
-                                                    int nTt, int nU, const unsigned short* __restrict__ WTq, int Mp,
-                                                    int Kp, const unsigned short* __restrict__ PhTsp, float sphi,
+__global__ void __launch_bounds__(256) k_freq_bwd_q(const unsigned* __restrict__ phase, int64_t ph_bstride,
+                                                    const FreqRate* __restrict__ rates,
+                                                    const FreqUnit* __restrict__ tiles, int nT, int nU,
+                                                    const unsigned short* __restrict__ WTq, int Mp,
+                                                    int Kp, const unsigned short* __restrict__ PhTsp,
                                                     const uint4* __restrict__ Gs, int64_t gs_bstride,
-                                                    const float* __restrict__ gvmax, int n_beta, int alpha,
+                                                    const float* __restrict__ gvmax, int n_beta,
                                                     int n_alpha, float sw, float2* __restrict__ gY,
                                                     int64_t gy_bstride) {
     constexpr int NTp = 32, NQ = 2 * NI;
     __shared__ uint4 Ls_X[NI * 256];
     __shared__ uint4 Ls_Y[NI * 256];
     __shared__ uint4 Ls_G[512];
-    const int u = blockIdx.x;
+    const int u = blockIdx.x;                         // half of a 128-column tile
     if (u >= nU) return;                              // whole block
-    const int64_t b = u / nTt;
-    const int t0 = (u % nTt) * 64;
+    const int64_t b = (u >> 1) / nT;
+    const FreqUnit un = tiles[(u >> 1) % nT];
+    const FreqRate rate = rates[un.alpha];
+    const int alpha = un.alpha, t0 = un.t0 + 64 * (u & 1), Tp = rate.Tp;
+    const float sphi = rate.sphi;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j16 = lane & 15, g4 = lane >> 4;
@@ -1738,13 +1755,13 @@ __global__ void __launch_bounds__(256) k_freq_bwd_q(const unsigned* __restrict__
     for (int q = 0; q < NQ; ++q) { gyr[q] = z4(); gyi[q] = z4(); }
 
     // Phi of the lane's column, tau 8 g4 .. 8 g4 + 7: hi and lo planes
-    const uint4* phrow = (const uint4*)(PhTsp + ((int64_t)t * (NTp / 8) + g4) * 16);
+    const uint4* phrow = (const uint4*)(PhTsp + rate.phioff * 2 + ((int64_t)t * (NTp / 8) + g4) * 16);
     const half8 fh = as_h8(phrow[0]), fl = as_h8(phrow[1]);
-    const uint4* Gb = Gs + b * gs_bstride;
+    const uint4* Gb = Gs + b * gs_bstride + (int64_t)alpha * (Mp / 32) * gvs_chunk<1>();
     const uint4* Wt = (const uint4*)WTq;
     // the lane's phase rows: 4 (g4 % 2) .. of row group g4 / 2 (rows 4 g4 ..) and of
     // group 2 + g4 / 2 (rows 16 + 4 g4 ..)
-    const unsigned* pbase = phase + b * ph_bstride + (int64_t)t * 8 + 4 * (g4 & 1);
+    const unsigned* pbase = phase + b * ph_bstride + rate.phase_off + (int64_t)t * 8 + 4 * (g4 & 1);
     const int64_t spin_stride = (int64_t)Tp * Mp, c_stride = (int64_t)Tp * 32, g_stride = (int64_t)Tp * 8;
     const int one = 1 < nC ? 1 : 0;
 
@@ -1801,7 +1818,7 @@ __global__ void __launch_bounds__(256) k_freq_bwd_q(const unsigned* __restrict__
         snext = sfree;
     }
     const float inv = 1.f / (sw * spq);
-    float2* o = gY + b * gy_bstride;
+    float2* o = gY + b * gy_bstride + rate.yoff;
 #pragma unroll
     for (int it = 0; it < NQ; ++it)
 #pragma unroll
@@ -2036,22 +2053,21 @@ int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const fl
 }
 
 template <int NTB>
-static void launch_bwd_ni(int NI, int NK, dim3 grid, hipStream_t st, const unsigned short* Ya, int64_t yhb, int Tp,
-                          int nTt, int nU, const jtfs_plan* P, const unsigned short* PhT, float sphi,
-                          const float* gVa, int64_t gvb, const float* gvmax, const float* yscale, int a, float2* gYa,
-                          int64_t gyb) {
+static void launch_bwd_ni(int NI, int NK, dim3 grid, hipStream_t st, const unsigned short* Yh, const float* yscale,
+                          const float* gV, const float* gvmax, float2* gY, int nT, const jtfs_plan* P) {
     const Shapes& s = P->s;
+    const int64_t yb = (int64_t)s.Kp * s.sumTp;
     // NK = Kp / 16 k-steps is 2 NI - 1 or 2 NI (Kp is a multiple of 16, KpT = 32 NI)
-#define JTFS_BWD_CASE(ni)                                                                                      \
-    case ni:                                                                                                   \
-        if (NK == 2 * ni)                                                                                      \
-            hipLaunchKernelGGL((k_freq_bwd_h<NTB, ni, 2 * ni>), grid, dim3(256), 0, st, Ya, yhb, Tp, nTt, nU, \
-                               P->Wsp, P->WTsp, s.Mp, PhT, sphi, gVa, gvb, gvmax, s.n_beta, yscale, a,         \
-                               s.n_alpha, P->sw, gYa, gyb);                                                    \
-        else                                                                                                   \
-            hipLaunchKernelGGL((k_freq_bwd_h<NTB, ni, 2 * ni - 1>), grid, dim3(256), 0, st, Ya, yhb, Tp, nTt, \
-                               nU, P->Wsp, P->WTsp, s.Mp, PhT, sphi, gVa, gvb, gvmax, s.n_beta, yscale, a,     \
-                               s.n_alpha, P->sw, gYa, gyb);                                                    \
+#define JTFS_BWD_CASE(ni)                                                                                         \
+    case ni:                                                                                                      \
+        if (NK == 2 * ni)                                                                                         \
+            hipLaunchKernelGGL((k_freq_bwd_h<NTB, ni, 2 * ni>), grid, dim3(256), 0, st, Yh, yb * 4, P->d_rates,   \
+                               P->d_tiles, nT, (int)grid.x, P->Wsp, P->WTsp, s.Mp, P->PhTsp, gV, gvmax, s.n_beta, \
+                               yscale, s.n_alpha, P->sw, gY, yb);                                                 \
+        else                                                                                                      \
+            hipLaunchKernelGGL((k_freq_bwd_h<NTB, ni, 2 * ni - 1>), grid, dim3(256), 0, st, Yh, yb * 4,           \
+                               P->d_rates, P->d_tiles, nT, (int)grid.x, P->Wsp, P->WTsp, s.Mp, P->PhTsp, gV,      \
+                               gvmax, s.n_beta, yscale, s.n_alpha, P->sw, gY, yb);                                \
         break;
     // LDS 24 NI KB and one wave per SIMD without scratch: NI <= 6 at N/T <= 32, NI <= 5 at N/T = 64
     if constexpr (NTB == 1) {
@@ -2069,23 +2085,16 @@ static void launch_bwd_ni(int NI, int NK, dim3 grid, hipStream_t st, const unsig
 #undef JTFS_BWD_CASE
 }
 
-int launch_freq_bwd_split(const jtfs_plan* P, int a, const unsigned short* Yh, const float* yscale, const float* gV,
+int launch_freq_bwd_split(const jtfs_plan* P, const unsigned short* Yh, const float* yscale, const float* gV,
                           const float* gvmax, float2* gY2, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int NI = P->KpT / 32;
     if (!P->split_bwd_ok) { set_error("split backward not available for these shapes"); return JTFS_ENOTSUP; }
-    const int nTt = s.Tp[a] / kTileTh;
-    const int nU = (int)(B * nTt);
-    const int64_t yhb = (int64_t)s.Kp * s.sumTp * 4;
-    const int64_t yb = (int64_t)s.Kp * s.sumTp;
-    const unsigned short* Ya = Yh + s.yoff[a] * 4;
-    const unsigned short* PhT = P->PhTsp + s.phioff[a] * 2;
-    const float* gVa = gV + (int64_t)a * 2 * s.Mp * s.NTp;
-    const int64_t gvb = (int64_t)s.n_alpha * 2 * s.Mp * s.NTp;
-    float2* gYa = gY2 + s.yoff[a];
+    const int nT = (int)(s.sumTp / kTileTh);
+    const dim3 grid((unsigned)(B * nT));
     switch (s.NTp / 32) {
-        case 1: launch_bwd_ni<1>(NI, s.Kp / 16, dim3(nU), st, Ya, yhb, s.Tp[a], nTt, nU, P, PhT, P->sphi[a], gVa, gvb, gvmax, yscale, a, gYa, yb); break;
-        case 2: launch_bwd_ni<2>(NI, s.Kp / 16, dim3(nU), st, Ya, yhb, s.Tp[a], nTt, nU, P, PhT, P->sphi[a], gVa, gvb, gvmax, yscale, a, gYa, yb); break;
+        case 1: launch_bwd_ni<1>(NI, s.Kp / 16, grid, st, Yh, yscale, gV, gvmax, gY2, nT, P); break;
+        case 2: launch_bwd_ni<2>(NI, s.Kp / 16, grid, st, Yh, yscale, gV, gvmax, gY2, nT, P); break;
         default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
     }
     return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
@@ -2096,15 +2105,15 @@ int launch_freq_bwd_split(const jtfs_plan* P, int a, const unsigned short* Yh, c
 int bwdp_max_ni(int NTp) { return NTp == 32 ? 8 : NTp == 64 ? 5 : 0; }
 
 template <int NTB>
-static void launch_bwdp_ni(int NI, int q_base, int nit, dim3 grid, hipStream_t st, const unsigned* pha, int64_t phb,
-                           int Tp, int nTt, int nU, const jtfs_plan* P, const unsigned short* PhT, float sphi,
-                           const uint4* Gsa, int64_t gsb, const float* gvmax, int a, float2* gYa, int64_t gyb) {
+static void launch_bwdp_ni(int NI, int q_base, int nit, dim3 grid, hipStream_t st, const unsigned* phase, int64_t phb,
+                           int nT, const jtfs_plan* P, const uint4* Gs, int64_t gsb, const float* gvmax, float2* gY) {
     const Shapes& s = P->s;
-#define JTFS_BWDP_CASE(ni)                                                                                    \
-    case ni:                                                                                                  \
-        hipLaunchKernelGGL((k_freq_bwd_p<NTB, ni>), grid, dim3(256), 0, st, pha, phb, Tp, nTt, nU, P->WTsp, \
-                           q_base, nit, s.Mp, s.Kp, PhT, sphi, Gsa, gsb, gvmax, s.n_beta, a, s.n_alpha, P->sw, \
-                           gYa, gyb);                                                                         \
+    const int64_t yb = (int64_t)s.Kp * s.sumTp;
+#define JTFS_BWDP_CASE(ni)                                                                                       \
+    case ni:                                                                                                     \
+        hipLaunchKernelGGL((k_freq_bwd_p<NTB, ni>), grid, dim3(256), 0, st, phase, phb, P->d_rates, P->d_tiles, \
+                           nT, (int)grid.x, P->WTsp, q_base, nit, s.Mp, s.Kp, P->PhTsp, Gs, gsb, gvmax,          \
+                           s.n_beta, s.n_alpha, P->sw, gY, yb);                                                  \
         break;
     if constexpr (NTB == 1) {
         switch (NI) {
@@ -2139,34 +2148,28 @@ bool bwdq_supported(const jtfs_plan* P) {
 }
 
 template <int NI = 1>
-static void launch_bwdq_ni(int ni, unsigned nU, hipStream_t st, const unsigned* pha, int64_t phb, int Tp, int nTt,
-                           const jtfs_plan* P, const unsigned short* PhT, float sphi, const uint4* Gsa, int64_t gsb,
-                           const float* gvmax, int a, float2* gYa, int64_t gyb) {
+static void launch_bwdq_ni(int ni, unsigned nU, hipStream_t st, const unsigned* phase, int64_t phb, int nT,
+                           const jtfs_plan* P, const uint4* Gs, int64_t gsb, const float* gvmax, float2* gY) {
     if constexpr (NI <= 9) {
         if (ni != NI) {
-            launch_bwdq_ni<NI + 1>(ni, nU, st, pha, phb, Tp, nTt, P, PhT, sphi, Gsa, gsb, gvmax, a, gYa, gyb);
+            launch_bwdq_ni<NI + 1>(ni, nU, st, phase, phb, nT, P, Gs, gsb, gvmax, gY);
             return;
         }
         const Shapes& s = P->s;
-        hipLaunchKernelGGL((k_freq_bwd_q<NI>), dim3(nU), dim3(256), 0, st, pha, phb, Tp, nTt, (int)nU, P->WTq, s.Mp,
-                           s.Kp, PhT, sphi, Gsa, gsb, gvmax, s.n_beta, a, s.n_alpha, P->sw, gYa, gyb);
+        hipLaunchKernelGGL((k_freq_bwd_q<NI>), dim3(nU), dim3(256), 0, st, phase, phb, P->d_rates, P->d_tiles, nT,
+                           (int)nU, P->WTq, s.Mp, s.Kp, P->PhTsp, Gs, gsb, gvmax, s.n_beta, s.n_alpha, P->sw, gY,
+                           (int64_t)s.Kp * s.sumTp);
     }
 }
 
-int launch_freq_bwd_phase(const jtfs_plan* P, int a, const unsigned* phase, int64_t ph_bstride, const uint4* Gs,
+int launch_freq_bwd_phase(const jtfs_plan* P, const unsigned* phase, int64_t ph_bstride, const uint4* Gs,
                           int64_t gs_bstride, const float* gvmax, float2* gY2, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int NI = P->KpT / 32;
+    const int nT = (int)(s.sumTp / kTileTh);
     if (P->tune.bwd16 && bwdq_supported(P)) {
-        const int nTt = s.Tp[a] / 64;
-        const unsigned nU = (unsigned)(B * nTt);
-        const int64_t yb = (int64_t)s.Kp * s.sumTp;
-        const unsigned* pha = phase + (int64_t)2 * s.Mp * (s.yoff[a] / s.Kp);
-        const unsigned short* PhT = P->PhTsp + s.phioff[a] * 2;
-        const uint4* Gsa = Gs + (int64_t)a * (s.Mp / 32) * (512 * (s.NTp / 32) + 16);
         JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st,
-                   launch_bwdq_ni(NI, nU, st, pha, ph_bstride, s.Tp[a], nTt, P, PhT, P->sphi[a], Gsa, gs_bstride, gvmax,
-                                  a, gY2 + s.yoff[a], yb));
+                   launch_bwdq_ni(NI, (unsigned)(B * nT * 2), st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2));
         return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
     }
     if (!P->split_bwdp_ok) { set_error("stored-phase backward not available for these shapes"); return JTFS_ENOTSUP; }
@@ -2175,19 +2178,12 @@ int launch_freq_bwd_phase(const jtfs_plan* P, int a, const unsigned* phase, int6
     const int nmax = bwdp_max_ni(s.NTp);
     const int ng = NI <= nmax ? 1 : 2;
     const int nia = (NI + ng - 1) / ng;
-    const int nTt = s.Tp[a] / kTileTh;
-    const int nU = (int)(B * nTt);
-    const int64_t yb = (int64_t)s.Kp * s.sumTp;
-    const unsigned* pha = phase + (int64_t)2 * s.Mp * (s.yoff[a] / s.Kp);
-    const unsigned short* PhT = P->PhTsp + s.phioff[a] * 2;
-    // this rate's chunks of the split gV
-    const uint4* Gsa = Gs + (int64_t)a * (s.Mp / 32) * (512 * (s.NTp / 32) + 16);
-    float2* gYa = gY2 + s.yoff[a];
+    const dim3 grid((unsigned)(B * nT));
     for (int g = 0, q0 = 0; g < ng; ++g) {
         const int ni = g == 0 ? nia : NI - nia;
         switch (s.NTp / 32) {
-            case 1: JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st, launch_bwdp_ni<1>(ni, q0, NI, dim3(nU), st, pha, ph_bstride, s.Tp[a], nTt, nU, P, PhT, P->sphi[a], Gsa, gs_bstride, gvmax, a, gYa, yb)); break;
-            case 2: JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st, launch_bwdp_ni<2>(ni, q0, NI, dim3(nU), st, pha, ph_bstride, s.Tp[a], nTt, nU, P, PhT, P->sphi[a], Gsa, gs_bstride, gvmax, a, gYa, yb)); break;
+            case 1: JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st, launch_bwdp_ni<1>(ni, q0, NI, grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2)); break;
+            case 2: JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st, launch_bwdp_ni<2>(ni, q0, NI, grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2)); break;
             default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
         }
         q0 += ni;

@@ -13,14 +13,14 @@ int split_attributes();
 // every temporal rate in one launch
 int launch_ysplit(const jtfs_plan* P, const float2* Y2, const float* rowmax, unsigned short* Yh, float* yscale,
                   int64_t B, hipStream_t st);
-int launch_freq_bwd_split(const jtfs_plan* P, int a, const unsigned short* Yh, const float* yscale, const float* gV,
+int launch_freq_bwd_split(const jtfs_plan* P, const unsigned short* Yh, const float* yscale, const float* gV,
                           const float* gvmax, float2* gY2, int64_t B, hipStream_t st);
 // every temporal rate in one launch; phase: NULL, or the stored-phase buffer of the
 // workspace (ph_bstride packed snorm16 pairs per signal)
 int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const float* yscale, float* Vp,
                           int64_t vp_bstride, unsigned* phase, int64_t ph_bstride, int64_t B, hipStream_t st);
 // backward contraction from the phase the forward stored (no recomputation of Z)
-int launch_freq_bwd_phase(const jtfs_plan* P, int a, const unsigned* phase, int64_t ph_bstride, const uint4* Gs,
+int launch_freq_bwd_phase(const jtfs_plan* P, const unsigned* phase, int64_t ph_bstride, const uint4* Gs,
                           int64_t gs_bstride, const float* gvmax, float2* gY2, int64_t B, hipStream_t st);
 // gV of every rate split into the FP16 planes and row scales the stored-phase
 // backward reads (Gs: gs_bstride 16-byte units per signal)
