@@ -359,17 +359,45 @@ __global__ void __launch_bounds__(256) k_s0_bwd(const float* __restrict__ gs0, i
     gx[b * N + n] += acc;
 }
 
+// The temporal rates whose rows are transformed in LDS, as one launch covers them:
+// blocks blk0[q] .. blk0[q + 1] - 1 of the grid take rate q, `rows` rows each.  A
+// launch per rate left most of the GPU idle for several microseconds each, in the
+// second order and again in the row FFTs of its adjoint: one signal of 2^11 samples
+// (6 such rates) forward 86 -> 58 us, fwd+bwd 200 -> 162 us; 2^18 (14) forward 2469
+// -> 2360 us.
+struct ShortRate {
+    int64_t yoff, psoff;             // its Y2 block and its spectrum in psi2
+    int lo, hi, logTa, Tp, rows, alpha;
+};
+constexpr int kMaxShort = 32;        // rates per launch (1.7 KB of kernel arguments)
+struct ShortRates {
+    int n;
+    int blk0[kMaxShort];
+    ShortRate r[kMaxShort];
+};
+// the rate of this block: the last one that starts at or before it
+__device__ __forceinline__ int short_rate(const ShortRates& sr) {
+    int q = 0;
+    for (int k = 1; k < sr.n; ++k) q += (int)blockIdx.x >= sr.blk0[k] ? 1 : 0;
+    return q;
+}
+
 // Second order: Y2[b][alpha][lambda][t] = (X_lambda (*) psi_alpha)[t 2^k2] for t < Ta,
 // zero for Ta <= t < Tp and for lambda >= n1 (the K padding of the contraction).
 __global__ void __launch_bounds__(1024) k_second_order(const float2* __restrict__ Xh, int64_t Xh_pitch, int n1,
-                                                      const float* __restrict__ ps, int lo, int hi, int logTa, int Tp,
-                                                      int rows, int Kp, float2* __restrict__ Y, int64_t y_bstride,
+                                                      const float* __restrict__ psi2, const ShortRates sr,
+                                                      int Kp, float2* __restrict__ Y, int64_t y_bstride,
                                                       float invNX, const float2* __restrict__ tw, int tw_log,
-                                                      float* __restrict__ rowmax, int alpha, int n_alpha) {
+                                                      float* __restrict__ rowmax, int n_alpha) {
     extern __shared__ float2 s[];
     __shared__ unsigned int rmx[64];
     const int64_t b = blockIdx.y;
-    const int r0 = blockIdx.x * rows;
+    const int q_ = short_rate(sr);
+    const ShortRate rt = sr.r[q_];
+    const int rows = rt.rows, lo = rt.lo, hi = rt.hi, logTa = rt.logTa, Tp = rt.Tp, alpha = rt.alpha;
+    const float* __restrict__ ps = psi2 + rt.psoff;
+    Y += rt.yoff;
+    const int r0 = ((int)blockIdx.x - sr.blk0[q_]) * rows;
     const int Ta = 1 << logTa, rs = lpad_len(Ta);    // row stride in LDS
     const int nr = min(rows, Kp - r0);
     if (r0 >= n1) {
@@ -436,6 +464,36 @@ __global__ void __launch_bounds__(1024) k_second_order(const float2* __restrict_
     }
     __syncthreads();
     if ((int)threadIdx.x < nr) rowmax[(b * n_alpha + alpha) * Kp + r0 + threadIdx.x] = __uint_as_float(rmx[threadIdx.x]);
+}
+
+// Forward FFT of the gY2 rows lambda < n1 of the rates in sr, in place: `rows` rows
+// of 2^logTa points per block.
+__global__ void __launch_bounds__(1024) k_rowfft_short(float2* __restrict__ Y, int64_t y_bstride, int n1,
+                                                      const ShortRates sr, const float2* __restrict__ tw,
+                                                      int tw_log) {
+    extern __shared__ float2 s[];
+    const int q_ = short_rate(sr);
+    const ShortRate rt = sr.r[q_];
+    const int logTa = rt.logTa, Ta = 1 << logTa, rs = lpad_len(Ta) + 1;   // odd stride: rows in distinct banks
+    const int r0 = ((int)blockIdx.x - sr.blk0[q_]) * rt.rows;
+    const int tot = min(rt.rows, n1 - r0) << logTa;
+    float2* row = Y + blockIdx.y * y_bstride + rt.yoff + (int64_t)r0 * rt.Tp;
+    // all of a thread's loads (at most 16) before any LDS store
+    float2 v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int e = threadIdx.x + q * blockDim.x;
+        if (e < tot) v[q] = row[(int64_t)(e >> logTa) * rt.Tp + (e & (Ta - 1))];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int e = threadIdx.x + q * blockDim.x;
+        if (e < tot) s[(e >> logTa) * rs + lpad(e & (Ta - 1))] = v[q];
+    }
+    __syncthreads();
+    lds_fft<16>(s, logTa, tot >> logTa, rs, tw, tw_log, false);
+    for (int e = threadIdx.x; e < tot; e += blockDim.x)
+        row[(int64_t)(e >> logTa) * rt.Tp + (e & (Ta - 1))] = s[(e >> logTa) * rs + lpad(e & (Ta - 1))];
 }
 
 // ---------------------------------------------------------------------------
@@ -1153,7 +1211,7 @@ int setup_kernel_attributes() {
     const void* ks[] = {(const void*)k_fft_cols_t<float2, float2>, (const void*)k_fft_cols_t<float2, double2>,
                         (const void*)k_fft_cols_t<double2, double2>, (const void*)k_scalogram, (const void*)k_s1,
                         (const void*)k_s2_bwd, (const void*)k_s2_bwd_avg<16>, (const void*)k_s2_bwd_avg<32>,
-                        (const void*)k_second_order, (const void*)k_scal_bwd_a, (const void*)k_scal_bwd_b};
+                        (const void*)k_second_order, (const void*)k_rowfft_short, (const void*)k_scal_bwd_a, (const void*)k_scal_bwd_b};
     for (const void* k : ks) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) {
@@ -1285,6 +1343,37 @@ extern "C" int jtfs_forward_workspace_size(const jtfs_plan* P, int64_t B, size_t
 
 namespace {
 
+// whether rows of 2^logn points take the register-resident transform (2^11 to 2^13 with the choice of 2^14)
+bool reg_row(int logn, bool knob) {
+    return use_reg_rows(logn, knob) || (logn >= kRegMinLogRows - 3 && logn < kRegMinLogRows && knob);
+}
+
+// The next launch over `nrows` rows of each rate from *a on that is transformed in
+// LDS (false where none is left).  Rows per workgroup: what fills its LDS (4096 or
+// 8192 points), at most max_rows, and fewer where the launch would hold under about
+// 1024 workgroups.
+bool short_rates(const jtfs_plan* P, bool knob, int* a, int nrows, int max_rows, int64_t B, ShortRates* sr,
+                 unsigned* blocks, size_t* lds) {
+    const Shapes& s = P->s;
+    sr->n = 0;
+    for (; *a < s.n_alpha_psi && sr->n < kMaxShort; ++*a)
+        if (!reg_row(s.logNX - s.k2[*a], knob)) sr->r[sr->n++].alpha = *a;
+    if (!sr->n) return false;
+    const int fill = (int)std::min<int64_t>(1 << 20, std::max<int64_t>(1, ((int64_t)nrows * sr->n * B + 1023) / 1024));
+    unsigned blk = 0;
+    *lds = 0;
+    for (int q = 0; q < sr->n; ++q) {
+        const int al = sr->r[q].alpha, logTa = s.logNX - s.k2[al];
+        const int rows = std::min({max_rows, std::max(1, (1 << lds_batch_log(P->tune)) >> logTa), fill});
+        sr->blk0[q] = (int)blk;
+        sr->r[q] = ShortRate{s.yoff[al], s.f2.off[al], s.f2.lo[al], s.f2.hi[al], logTa, s.Tp[al], rows, al};
+        blk += (unsigned)((nrows + rows - 1) / rows);
+        *lds = std::max(*lds, sizeof(float2) * rows * (lpad_len(s.Ta[al]) + 1));
+    }
+    *blocks = blk;
+    return true;
+}
+
 // x -> x_hat -> X_hat -> S1, Y2
 int forward_front(const jtfs_plan* P, const float* x, int64_t B, float* s1, char* base, const Workspace& w,
                   const MuLogArg& ml, hipStream_t st) {
@@ -1314,25 +1403,18 @@ int forward_front(const jtfs_plan* P, const float* x, int64_t B, float* s1, char
         LAUNCHCHK("first-order lowpass");
     }
     for (int a = 0; a < s.n_alpha_psi; ++a) {
-        const int logTa = s.logNX - s.k2[a];
-        // rows of 2^11 to 2^13 points take the register-resident transform with the same choice as 2^14
-        if (use_reg_rows(logTa, P->tune.reg_second) ||
-            (logTa >= kRegMinLogRows - 3 && logTa < kRegMinLogRows && P->tune.reg_second)) {
-            JTFS_TIMED(JTFS_STAGE_SECOND_ORDER, st,
-                       launch_second_order_r(P, a, Xh, w.Xh_pitch, Y2, (float*)(base + w.rowmax), B, st));
-            LAUNCHCHK("second order");
-            continue;
-        }
-        // <= 64 rows (row-maximum slots), and fewer where the grid would hold under ~1024 workgroups
-        const int fill = (int)std::max<int64_t>(1, ((int64_t)s.Kp * B + 1023) / 1024);
-        const int rows = std::min({64, std::max(1, (1 << lds_batch_log(P->tune)) >> logTa), fill});
-        const size_t lds = sizeof(float2) * rows * lpad_len(s.Ta[a]);
-        const Family& f2 = s.f2;
-        // packed second-order spectrum of alpha: the plan's device table at its offset
-        JTFS_TIMED(JTFS_STAGE_SECOND_ORDER, st, hipLaunchKernelGGL(k_second_order, dim3((unsigned)((s.Kp + rows - 1) / rows), (unsigned)B), dim3(1024), lds, st,
-                           Xh, w.Xh_pitch, s.n1, P->psi2 + f2.off[a], f2.lo[a], f2.hi[a], logTa, s.Tp[a], rows, s.Kp,
-                           Y2 + s.yoff[a], (int64_t)s.Kp * s.sumTp, 1.0f / (float)s.NX, P->tw, P->tw_log,
-                           (float*)(base + w.rowmax), a, s.n_alpha));
+        if (!reg_row(s.logNX - s.k2[a], P->tune.reg_second)) continue;
+        JTFS_TIMED(JTFS_STAGE_SECOND_ORDER, st,
+                   launch_second_order_r(P, a, Xh, w.Xh_pitch, Y2, (float*)(base + w.rowmax), B, st));
+        LAUNCHCHK("second order");
+    }
+    ShortRates sr;
+    size_t lds = 0;
+    unsigned blocks = 0;
+    for (int a = 0; short_rates(P, P->tune.reg_second, &a, s.Kp, 64, B, &sr, &blocks, &lds);) {
+        JTFS_TIMED(JTFS_STAGE_SECOND_ORDER, st, hipLaunchKernelGGL(k_second_order, dim3(blocks, (unsigned)B), dim3(1024), lds, st,
+                           Xh, w.Xh_pitch, s.n1, P->psi2, sr, s.Kp, Y2, (int64_t)s.Kp * s.sumTp, 1.0f / (float)s.NX,
+                           P->tw, P->tw_log, (float*)(base + w.rowmax), s.n_alpha));
         LAUNCHCHK("second order");
     }
     return JTFS_OK;
@@ -1414,29 +1496,29 @@ extern "C" int jtfs_forward(const jtfs_plan* P, const float* x, int64_t B, float
     return forward_impl(P, x, B, s1, s2, ws, ws_bytes, MuLogArg{}, st);
 }
 
-// forward FFT of every gY2 row of alpha (length T_alpha, rows lambda < n1), in place
-static int gy2_row_fft(const jtfs_plan* P, int a, float2* gY2, int64_t yb, int64_t B, hipStream_t st) {
+namespace {
+
+// forward FFT of every gY2 row lambda < n1 (length T_alpha), in place; phi_T's rows go
+// back through the S1 adjoint untransformed
+int gy2_row_ffts(const jtfs_plan* P, float2* gY2, int64_t yb, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
-    if (a >= s.n_alpha_psi) return JTFS_OK;      // phi_T's rows go back through the S1 adjoint untransformed
-    const int logTa = s.logNX - s.k2[a];
-    const int lb = lds_batch_log(P->tune);
-    const int logC = logTa >= lb ? 0 : lb - logTa;
-    const size_t lds = (size_t)(1 << logC) * (lpad_len(s.Ta[a]) + 1) * sizeof(float2);
-    // rows of 2^11 to 2^13 points take the register-resident transform with the same choice as 2^14
-    if (use_reg_rows(logTa, P->tune.reg_rowfft) ||
-        (logTa >= kRegMinLogRows - 3 && logTa < kRegMinLogRows && P->tune.reg_rowfft)) {
+    for (int a = 0; a < s.n_alpha_psi; ++a) {
+        const int logTa = s.logNX - s.k2[a];
+        if (!reg_row(logTa, P->tune.reg_rowfft)) continue;
         JTFS_TIMED(JTFS_STAGE_SECOND_ADJ_FFT, st,
                    launch_rowfft_r(P, gY2 + s.yoff[a], yb, (int64_t)s.Tp[a], s.n1, logTa, B, st));
-    } else {
-        JTFS_TIMED(JTFS_STAGE_SECOND_ADJ_FFT, st, hipLaunchKernelGGL((k_fft_cols), dim3((unsigned)((s.n1 + (1 << logC) - 1) >> logC), (unsigned)B), dim3(1024), lds,
-                       st, gY2 + s.yoff[a], gY2 + s.yoff[a], logTa, s.n1, logC, yb, (int64_t)s.Tp[a], (int64_t)1,
-                       yb, (int64_t)s.Tp[a], (int64_t)1, 0, P->tw, P->tw_log, 0, 1.0f));
+        LAUNCHCHK("second-order adjoint FFT");
     }
-    LAUNCHCHK("second-order adjoint FFT");
+    ShortRates sr;
+    size_t lds = 0;
+    unsigned blocks = 0;
+    for (int a = 0; short_rates(P, P->tune.reg_rowfft, &a, s.n1, s.n1, B, &sr, &blocks, &lds);) {
+        JTFS_TIMED(JTFS_STAGE_SECOND_ADJ_FFT, st, hipLaunchKernelGGL(k_rowfft_short, dim3(blocks, (unsigned)B), dim3(1024), lds, st,
+                           gY2, yb, s.n1, sr, P->tw, P->tw_log));
+        LAUNCHCHK("second-order adjoint FFT");
+    }
     return JTFS_OK;
 }
-
-namespace {
 
 int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const float* gs2, float* gx, int64_t B,
                   void* ws, size_t ws_bytes, uint32_t flags, const MuLogArg& ml, hipStream_t st) {
@@ -1467,8 +1549,6 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
                            yb, s.Tp[a], s.Ta[a], P->Phi + s.phioff[a], s.NTp, s.NT, a, s.n_alpha, gs2,
                            gY2 + s.yoff[a], ml));
         LAUNCHCHK("time-scattering adjoint");
-        rc = gy2_row_fft(P, a, gY2, yb, B, st);
-        if (rc != JTFS_OK) return rc;
     }
     if (!s.tscat) {
         // every temporal rate in one launch
@@ -1522,10 +1602,6 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
         }
         if (rc != JTFS_OK) { if (rc == JTFS_EHIP) set_error("split backward contraction launch failed"); return rc; }
     }
-    for (int a = 0; a < s.n_alpha && split; ++a) {
-        rc = gy2_row_fft(P, a, gY2, yb, B, st);
-        if (rc != JTFS_OK) return rc;
-    }
     for (int a = 0; a < s.n_alpha && !split && !s.tscat; ++a) {
         dim3 grid(nlt, s.Tp[a] / kTileT, (unsigned)B);
         const float2* Ya = Y2 + s.yoff[a];
@@ -1545,9 +1621,9 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
         JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_WH, st, hipLaunchKernelGGL(k_bwd_gy, dim3((s.Kp + 63) / 64, s.Tp[a] / kTileT, (unsigned)B), dim3(256), 0, st, PQ,
                            s.Tp[a], P->Wl, s.Mp, s.Kp, gY2 + s.yoff[a], yb));
         LAUNCHCHK("contraction adjoint (W^H)");
-        rc = gy2_row_fft(P, a, gY2, yb, B, st);
-        if (rc != JTFS_OK) return rc;
     }
+    rc = gy2_row_ffts(P, gY2, yb, B, st);
+    if (rc != JTFS_OK) return rc;
     const int logNT = s.logN - s.logT;
     const size_t lds_a = sizeof(float2) * (lpad_len(s.NX / 2) + 1 + lpad_len(s.NT));   // g1 at lpad(H) + 1
     const float2* gYphi = s.complete ? gY2 + s.yoff[s.n_alpha_psi] : nullptr;

@@ -1006,3 +1006,18 @@ def test_forward_chunk_lengths_agree(p):
             assert rel_l2(b2, a2) <= 2e-6
         c1, c2 = run_forward(op, x[1:2])
         assert np.array_equal(c1[0], b1[1]) and np.array_equal(c2[0], b2[1])
+
+
+def test_more_short_rates_than_one_launch_holds():
+    """71 temporal rates, all transformed in LDS: their second order and row FFTs take three launches (32 rates each)."""
+    p = dict(N=2048, J=9, Q=(4, 10), J_fr=2, Q_fr=1, T=64, F=2)
+    P = oracle_plan(p)
+    assert P.n_alpha > 32
+    x = synth.batch(1, B=2, N=p["N"])
+    gs1, gs2 = synth.cotangents((2,) + P.s1_shape(), (2,) + P.s2_shape())
+    op = gpu_op(p, "split16")
+    s1, s2 = run_forward(op, x)
+    gx = op.vjp(torch.from_numpy(x).cuda(), torch.from_numpy(gs1).cuda(), torch.from_numpy(gs2).cuda()).cpu().numpy()
+    for b in range(2):
+        check_paths(s1[b], s2[b], *O.jtfs(x[b].astype(np.float64), P))
+        assert rel_l2(gx[b], O.jtfs_vjp(x[b].astype(np.float64), gs1[b], gs2[b], P)) <= TOL_VJP
