@@ -228,11 +228,8 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     const int all_rows = JTFS_REG_SCALOGRAM | JTFS_REG_SECOND_ORDER | JTFS_REG_ROW_FFT | JTFS_REG_FIRST_ADJ;
     // second run: rows in LDS and the 16 x 16 contraction tiles, where any of these choices exists
     const bool tile16 = P->split_ok && !s.tscat && fwdq_supported(P, false);
-    const bool btile16 = P->split_ok && P->split_bwdp_ok && !s.tscat && bwdq_supported(P);
     std::vector<int> row_opts{all_rows};
-    if (has14 || tile16 || btile16)
-        row_opts.push_back((has14 ? 0 : all_rows) | (tile16 ? JTFS_TUNE_FWD_TILE16 : 0) |
-                           (btile16 ? JTFS_TUNE_BWD_TILE16 : 0));
+    if (has14 || tile16) row_opts.push_back((has14 ? 0 : all_rows) | (tile16 ? JTFS_TUNE_FWD_TILE16 : 0));
     // buffers: the largest workspace over the modes (at the shortest t-chunk, whose
     // partial V is largest); the coefficients double as cotangents
     size_t wsb = 0;
@@ -289,23 +286,19 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
         return tile16 && row_opts.size() == 2 && modes[mi] != JTFS_CONTRACTION_FP32 &&
                fwdq_supported(P, modes[mi] == JTFS_CONTRACTION_SPLIT_F16_PHASE);
     };
-    auto btile_ok = [&](size_t mi) {
-        return btile16 && row_opts.size() == 2 && modes[mi] == JTFS_CONTRACTION_SPLIT_F16_PHASE;
-    };
     size_t best_m = 0;
     double best_c = 1e300;
     for (size_t mi = 0; mi < modes.size(); ++mi) {
         double c = tile_ok(mi) ? std::min(fwd_ms(mi, 0), fwd_ms(mi, 1)) : fwd_ms(mi, 0);
-        c += btile_ok(mi) ? std::min(bwd_ms(mi, 0), bwd_ms(mi, 1)) : bwd_ms(mi, 0);
+        c += bwd_ms(mi, 0);
         for (int k : cstages) c += stage[mi][0][k];
         if (c < best_c) { best_c = c; best_m = mi; }
     }
     const bool use16 = tile_ok(best_m) && fwd_ms(best_m, 1) < fwd_ms(best_m, 0);
-    const bool buse16 = btile_ok(best_m) && bwd_ms(best_m, 1) < bwd_ms(best_m, 0);
     out->fwd_ms[0] = fwd_ms(best_m, 0);
     out->fwd_ms[1] = tile_ok(best_m) ? fwd_ms(best_m, 1) : 0.0;
     out->bwd_ms[0] = bwd_ms(best_m, 0);
-    out->bwd_ms[1] = btile_ok(best_m) ? bwd_ms(best_m, 1) : 0.0;
+    out->bwd_ms[1] = 0.0;                  // one kernel per mode
     // rows of 2^14 points: per stage, the faster of the two runs of the chosen mode
     int rows = all_rows;
     if (has14) {
@@ -321,7 +314,6 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
         }
     }
     if (use16) rows |= JTFS_TUNE_FWD_TILE16;
-    if (buse16) rows |= JTFS_TUNE_BWD_TILE16;
     P->contraction = modes[best_m];
     set_rows(P, rows);
     auto fail = [&](int rc) {

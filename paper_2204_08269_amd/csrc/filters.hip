@@ -79,16 +79,16 @@ __global__ void k_fb_psi_fr(const double* __restrict__ xi, const double* __restr
     out[(int64_t)beta * L + j] = make_double2(re * cnorm[0] / L, im * cnorm[0] / L);
 }
 
-// W[row=(beta,l)][i] = psi_{beta,-1}[(l 2^kfr - i) mod L] for i < n1, 0 for padding,
-// stored k-major (Wt[i][row]) and row-major (Wl[row][i]).
+// W[slot of (beta,l)][i] = psi_{beta,-1}[(l 2^kfr - i) mod L] for i < n1, 0 for padding,
+// stored k-major (Wt[i][slot]) and row-major (Wl[slot][i]).
 __global__ void k_fb_W(const double2* __restrict__ psi, const int* __restrict__ row_beta, const int* __restrict__ row_l,
-                       const int* __restrict__ kfr, int Mh, int Mp, int n1, int Kp, int L,
+                       const int* __restrict__ kfr, int Mp, int n1, int Kp, int L,
                        float2* __restrict__ Wt, float2* __restrict__ Wl) {
     const int row = blockIdx.y;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= Kp) return;
     float2 w = make_float2(0.f, 0.f);
-    if (row < Mh && i < n1) {
+    if (row_beta[row] >= 0 && i < n1) {
         const int beta = row_beta[row], l = row_l[row];
         const int j = (((l << kfr[beta]) - i) % L + L) % L;
         const double2 v = psi[(int64_t)beta * L + j];
@@ -376,12 +376,15 @@ extern "C" int jtfs_plan_create_ex(jtfs_plan** out, const jtfs_params* p) {
         double* dsg = upload(A, s.ffr.sigma);
         double* dc = upload(A, std::vector<double>{P->cfr});
         double2* psi = A.get<double2>((size_t)s.n_beta * s.L);
-        std::vector<int> rb(s.Mh), rl(s.Mh);
-        for (int b = 0; b < s.n_beta; ++b)
-            for (int l = 0; l < s.Lb[b]; ++l) { rb[s.rowoff[b] + l] = b; rl[s.rowoff[b] + l] = l; }
-        int* drb = upload(A, rb);
-        int* drl = upload(A, rl);
-        int* dkfr = upload(A, s.kfr);
+        std::vector<int> pad;
+        for (int r = 0; r < s.Mp; ++r)
+            if (s.slot_beta[r] < 0) pad.push_back(r);
+        P->psi_fr = psi;
+        P->d_slot_beta = upload(A, s.slot_beta);
+        P->d_slot_l = upload(A, s.slot_l);
+        P->d_rowpos = upload(A, s.rowpos);
+        P->d_pad = upload(A, pad);
+        P->d_kfr = upload(A, s.kfr);
         P->Wt = A.get<float2>((size_t)s.Kp * s.Mp);
         P->Wl = A.get<float2>((size_t)s.Mp * s.Kp);
         if (A.failed) { set_error("device allocation failed"); return fail(JTFS_ENOMEM); }
@@ -389,7 +392,7 @@ extern "C" int jtfs_plan_create_ex(jtfs_plan** out, const jtfs_params* p) {
         if (s.complete)
             hipLaunchKernelGGL(k_fb_phi_fr, dim3((s.L + 127) / 128), dim3(128), 0, 0, psi + (size_t)s.n_beta_psi * s.L,
                                s.L, kSigma0 / (double)s.F);
-        hipLaunchKernelGGL(k_fb_W, dim3((s.Kp + 63) / 64, s.Mp), dim3(64), 0, 0, psi, drb, drl, dkfr, s.Mh, s.Mp, s.n1,
+        hipLaunchKernelGGL(k_fb_W, dim3((s.Kp + 63) / 64, s.Mp), dim3(64), 0, 0, psi, P->d_slot_beta, P->d_slot_l, P->d_kfr, s.Mp, s.n1,
                            s.Kp, s.L, P->Wt, P->Wl);
         if (hipGetLastError() != hipSuccess) { set_error("frequential wavelet kernels failed"); return fail(JTFS_EHIP); }
     }
@@ -532,7 +535,7 @@ extern "C" int jtfs_plan_table(const jtfs_plan* P, int which, void* host_dst, si
         HIPCHK(hipMemcpy(Wl.data(), P->Wl, sizeof(float2) * Wl.size(), hipMemcpyDeviceToHost));
         float2* dst = (float2*)host_dst;
         for (int r = 0; r < s.Mh; ++r)
-            for (int i = 0; i < s.n1; ++i) dst[(int64_t)r * s.n1 + i] = Wl[(int64_t)r * s.Kp + i];
+            for (int i = 0; i < s.n1; ++i) dst[(int64_t)r * s.n1 + i] = Wl[(int64_t)s.rowpos[r] * s.Kp + i];
         return JTFS_OK;
     }
     set_error("unknown table");

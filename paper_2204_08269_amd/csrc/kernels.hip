@@ -608,7 +608,8 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
                                                 const int64_t* __restrict__ vchoff, const int* __restrict__ nch,
                                                 int slot_mult, int nlt, int NTp, int NT, const float* __restrict__ PFt,
                                                 const int64_t* __restrict__ pfoff, const int* __restrict__ Lbv,
-                                                const int* __restrict__ rowoffv, int NL, int NLo, int n_alpha,
+                                                const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
+                                                int NL, int NLo, int n_alpha,
                                                 float* __restrict__ S2, const float* __restrict__ mu2, float eps) {
     // NLo <= NL output rows (the unpadded lambda axis keeps the first NLo)
     constexpr int LC = 64, MB = 32, NG = 256 / TT, RR = MB / NG;
@@ -635,7 +636,7 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
                     const int tt = e / LC, l = e - tt * LC;
                     float v = 0.f;
                     if (l < lc && tb + tt < NT) {
-                        const int row = ro + l0 + l, lt = row / kTileL, lr = row % kTileL;
+                        const int row = rowpos[ro + l0 + l], lt = row / kTileL, lr = row % kTileL;
                         const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL +
                                           (int64_t)(tb + tt) * kTileL + lr;
                         v = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
@@ -668,7 +669,8 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
 __global__ void __launch_bounds__(256) k_v_out(const float* __restrict__ Vp, int64_t vp_bstride,
                                                const int64_t* __restrict__ vchoff, const int* __restrict__ nch,
                                                int slot_mult, int nlt, int NTp, int NT, const int* __restrict__ Lbv,
-                                               const int* __restrict__ rowoffv, int Mh, int n_alpha,
+                                               const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
+                                               int Mh, int n_alpha,
                                                float* __restrict__ S2, const float* __restrict__ mu2, float eps) {
     // grid (n_beta, 2 n_alpha, B): every temporal rate in one launch
     const int beta = blockIdx.x, th = blockIdx.y & 1, alpha = blockIdx.y >> 1;
@@ -680,7 +682,7 @@ __global__ void __launch_bounds__(256) k_v_out(const float* __restrict__ Vp, int
     const float inv = mulog_inv(mu2, (alpha * (int)gridDim.x + beta) * 2 + th, eps);
     for (int e = threadIdx.x; e < Lb * NT; e += blockDim.x) {
         const int tau = e / Lb, l = e - tau * Lb;
-        const int row = ro + l, lt = row / kTileL, lr = row % kTileL;
+        const int row = rowpos[ro + l], lt = row / kTileL, lr = row % kTileL;
         const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL + (int64_t)tau * kTileL + lr;
         const float acc = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
         o[(int64_t)l * NT + tau] = mulog_out(acc, mu2, inv);
@@ -788,7 +790,8 @@ __device__ __forceinline__ float group_sum(float a, int width) {
 // row before one LDS atomic per row segment.
 __global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, const float* __restrict__ PFall,
                                                 const int64_t* __restrict__ pfoff, const int* __restrict__ Lbv,
-                                                const int* __restrict__ rowoffv, int n_beta, int NL, int NLo, int NT, int NTp,
+                                                const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
+                                                const int* __restrict__ pad, int n_beta, int NL, int NLo, int NT, int NTp,
                                                 int Mh, int Mp, int n_alpha, int avg, int stage_pf,
                                                 float* __restrict__ gV, float* __restrict__ gvmax, MuLogArg ml) {
     extern __shared__ float sm[];      // rowsum [Lb] | gS2 tile [NL][NT] | (stage_pf) PF [NL][Lb]
@@ -797,7 +800,7 @@ __global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, c
     const int64_t b = blockIdx.z;
     float* g = gV + (((b * n_alpha + alpha) * 2 + th) * (int64_t)Mp) * NTp;
     if (beta == n_beta) {
-        for (int e = threadIdx.x; e < (Mp - Mh) * NTp; e += blockDim.x) g[(int64_t)Mh * NTp + e] = 0.f;
+        for (int e = threadIdx.x; e < (Mp - Mh) * NTp; e += blockDim.x) g[(int64_t)pad[e / NTp] * NTp + e % NTp] = 0.f;
         return;
     }
     const int Lb = Lbv[beta], ro = rowoffv[beta];
@@ -832,7 +835,7 @@ __global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, c
                 acc = mulog_cot(src[(int64_t)l * NT + tau], ml.mu2, em, osrc ? osrc[(int64_t)l * NT + tau] : 0.f);
             }
         }
-        if (valid) g[(int64_t)(ro + l) * NTp + tau] = acc;
+        if (valid) g[(int64_t)rowpos[ro + l] * NTp + tau] = acc;
         float a = fabsf(acc);
         a = group_sum(a, width);
         if (valid && (tau & (width - 1)) == 0) atomicAdd(&rowsum[l], a);
@@ -857,7 +860,8 @@ __global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, c
 template <int TT>
 __global__ void __launch_bounds__(256) k_s2_bwd_avg(const float* __restrict__ gS2, const float* __restrict__ PFall,
                                                     const int64_t* __restrict__ pfoff, const int* __restrict__ Lbv,
-                                                    const int* __restrict__ rowoffv, int n_beta, int NLo, int NT,
+                                                    const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
+                                                    const int* __restrict__ pad, int n_beta, int NLo, int NT,
                                                     int NTp, int Mh, int Mp, int n_alpha, float* __restrict__ gV,
                                                     float* __restrict__ gvmax, MuLogArg ml) {
     extern __shared__ __align__(16) float st[];      // gS2 tile [NLo][NT]
@@ -866,7 +870,7 @@ __global__ void __launch_bounds__(256) k_s2_bwd_avg(const float* __restrict__ gS
     const int64_t b = blockIdx.z;
     float* g = gV + (((b * n_alpha + alpha) * 2 + th) * (int64_t)Mp) * NTp;
     if (beta == n_beta) {
-        for (int e = threadIdx.x; e < (Mp - Mh) * NTp; e += blockDim.x) g[(int64_t)Mh * NTp + e] = 0.f;
+        for (int e = threadIdx.x; e < (Mp - Mh) * NTp; e += blockDim.x) g[(int64_t)pad[e / NTp] * NTp + e % NTp] = 0.f;
         return;
     }
     const int Lb = Lbv[beta], ro = rowoffv[beta];
@@ -880,7 +884,7 @@ __global__ void __launch_bounds__(256) k_s2_bwd_avg(const float* __restrict__ gS
     __syncthreads();
     float mx = 0.f;
     for (int l = threadIdx.x; l < Lb; l += blockDim.x) {
-        float* grow = g + (int64_t)(ro + l) * NTp;
+        float* grow = g + (int64_t)rowpos[ro + l] * NTp;
         float rs = 0.f;
         for (int t0 = 0; t0 < NTp; t0 += TT) {
             float acc[TT];
@@ -1477,11 +1481,11 @@ int forward_impl(const jtfs_plan* P, const float* x, int64_t B, float* s1, float
         if (s.avg_fr) {
             auto k = s.NT <= 16 ? k_s2_out<16> : k_s2_out<32>;
             JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k, grid, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
-                               cs.d_nch, mult, nlt, s.NTp, s.NT, P->PFt, P->d_pfoff, P->d_Lb, P->d_rowoff, s.NL, s.NLo, s.n_alpha, s2,
+                               cs.d_nch, mult, nlt, s.NTp, s.NT, P->PFt, P->d_pfoff, P->d_Lb, P->d_rowoff, P->d_rowpos, s.NL, s.NLo, s.n_alpha, s2,
                                ml.mu2, ml.eps));
         } else {
             JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k_v_out, grid, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
-                               cs.d_nch, mult, nlt, s.NTp, s.NT, P->d_Lb, P->d_rowoff, s.Mh, s.n_alpha, s2,
+                               cs.d_nch, mult, nlt, s.NTp, s.NT, P->d_Lb, P->d_rowoff, P->d_rowpos, s.Mh, s.n_alpha, s2,
                                ml.mu2, ml.eps));
         }
         LAUNCHCHK("frequency lowpass");
@@ -1556,11 +1560,11 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
         if (s.avg_fr) {
             auto k = s.NTp % 32 == 0 && s.NT >= 32 ? k_s2_bwd_avg<32> : k_s2_bwd_avg<16>;
             JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k, grid, dim3(256), sizeof(float) * s.NLo * s.NT, st, gs2,
-                               P->PF, P->d_pfoff, P->d_Lb, P->d_rowoff, s.n_beta, s.NLo, s.NT, s.NTp, s.Mh, s.Mp,
+                               P->PF, P->d_pfoff, P->d_Lb, P->d_rowoff, P->d_rowpos, P->d_pad, s.n_beta, s.NLo, s.NT, s.NTp, s.Mh, s.Mp,
                                s.n_alpha, gV, (float*)(base + w.gvmax), ml));
         } else {
             JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k_s2_bwd, grid, dim3(256), s2_bwd_lds(s), st, gs2, P->PF, P->d_pfoff, P->d_Lb,
-                               P->d_rowoff, s.n_beta, s.NL, s.NLo, s.NT, s.NTp, s.Mh, s.Mp, s.n_alpha, (int)s.avg_fr,
+                               P->d_rowoff, P->d_rowpos, P->d_pad, s.n_beta, s.NL, s.NLo, s.NT, s.NTp, s.Mh, s.Mp, s.n_alpha, (int)s.avg_fr,
                                s2_bwd_stage(s), gV, (float*)(base + w.gvmax), ml));
         }
         LAUNCHCHK("frequency lowpass adjoint");

@@ -74,6 +74,58 @@ static void family_supports(Family* f) {
     f->total = off;
 }
 
+// row of scale b that mirrors row l (l itself at a fixed point), -1 if none does
+static int mirror_row(const Shapes& s, int b, int l) {
+    const int d = 1 << s.kfr[b];
+    if (s.fold.c2 % d) return -1;
+    return ((s.fold.c2 / d - l) % s.Lb[b] + s.Lb[b]) % s.Lb[b];
+}
+
+// Slots of the contraction's rows: the mirrored pairs of every scale first, then the
+// rows without a mirror image two by two.  The mirror keeps every scale's grid whose
+// step divides c2; the step it is rounded to stays at 16 bins (c2 <= n1 + 14), and
+// the few rows of coarser scales off that grid count as unpaired.
+static void lay_out_rows(Shapes* s) {
+    int kmax = 0;
+    for (int b = 0; b < s->n_beta; ++b) kmax = std::max(kmax, s->kfr[b]);
+    FoldPlan& f = s->fold;
+    f.c2 = (int)rup(s->n1 - 1, 1 << std::min(kmax, 4));
+    f.NS = (f.c2 / 2 + 16) / 16;
+    f.shortD = f.NS > 1 && f.c2 % 2 == 0 && f.c2 / 2 <= 16 * (f.NS - 1);
+    f.nD = s->Mp / kTileL;
+    s->rowpos.assign(s->Mh, 0);
+    s->slot_beta.assign(s->Mp, -1);
+    s->slot_l.assign(s->Mp, 0);
+    int q = 0;                                        // pairs placed
+    auto place = [&](int pos, int b, int l) {
+        s->rowpos[s->rowoff[b] + l] = pos;
+        s->slot_beta[pos] = b;
+        s->slot_l[pos] = l;
+    };
+    auto pos_of = [&](int pair, int second) { return 64 * (pair / 32) + 32 * second + pair % 32; };
+    for (int b = 0; b < s->n_beta; ++b)
+        for (int l = 0; l < s->Lb[b]; ++l) {
+            const int m = mirror_row(*s, b, l);
+            if (m <= l) continue;
+            place(pos_of(q, 0), b, l);
+            place(pos_of(q, 1), b, m);
+            ++q;
+        }
+    const int pairs = q;
+    int second = 0;
+    for (int b = 0; b < s->n_beta; ++b)
+        for (int l = 0; l < s->Lb[b]; ++l) {
+            const int m = mirror_row(*s, b, l);
+            if (m >= 0 && m != l) continue;
+            place(pos_of(q, second), b, l);
+            if (second) ++q;
+            second ^= 1;
+        }
+    const int used = q + second;                      // pairs and unpaired twos
+    f.t0 = pairs / 32;
+    f.nI = f.nD + (used > pairs ? (used - 1) / 32 - f.t0 + 1 : 0);
+}
+
 int solve_shapes(const jtfs_params& p, Shapes* s) {
     *s = Shapes{};
     s->p = p;
@@ -163,6 +215,7 @@ int solve_shapes(const jtfs_params& p, Shapes* s) {
     }
     s->Mh = ro;
     s->Mp = (int)rup(ro, kTileL);
+    lay_out_rows(s);
     // phi_T support on the NX grid (frequency m/N cycles/sample)
     {
         const double sg = kSigma0 / (double)p.T;

@@ -43,6 +43,19 @@ struct Family {
     int n() const { return (int)xi.size(); }
 };
 
+// The fold of the log-frequency axis by which the stored-phase backward halves its
+// products: columns i and c2 - i, rows l and c2 - l (mod L).  The rows of the
+// contraction are laid out for it in 64-row tiles, slot 32 + p of a tile the mirror
+// image of slot p; rows without one share the last tiles, in any order.
+struct FoldPlan {
+    int c2 = 0;          // mirror: lambda -> c2 - lambda
+    int nD = 0, nI = 0;  // 64-row tiles; passes, with a second one over each tile that holds unpaired rows
+    int t0 = 0;          // first such tile
+    int NS = 0;          // 16-column tiles of columns 0 .. c2 / 2 (the sums)
+    int shortD = 0;      // 1: the differences, zero at i = c2 / 2, take one tile less
+};
+constexpr int kMaxFoldNS = 10;
+
 struct Shapes {
     jtfs_params p{};
     int logN = 0, logT = 0, logF = 0;
@@ -60,6 +73,9 @@ struct Shapes {
     std::vector<int64_t> yoff, phioff, vchoff; // per alpha offsets
     int64_t sumTp = 0, sumch = 0, sumT = 0;
     std::vector<int> kfr, Lb, rowoff;          // per beta
+    std::vector<int> rowpos;                   // [Mh]: slot (row of W, V, gV) of row rowoff[beta] + l
+    std::vector<int> slot_beta, slot_l;        // [Mp]: the scale and row of a slot; -1 for padding
+    FoldPlan fold;
     std::vector<int64_t> pfoff;
     int Mphi = 0;                    // phi_T support on the NX grid (bins 0..Mphi)
     Family f1, f2, ffr;
@@ -107,7 +123,7 @@ struct Tuning {
     bool reg_rowfft = true;      // FFT of the gY2 rows of 2^14 points
     bool reg_first_adj = true;   // first-order adjoint rows of 2^14 points
     bool fwd16 = false;          // forward contraction in 16 x 16 tiles (else 32 x 32)
-    bool bwd16 = false;          // stored-phase backward in 16 x 16 tiles (else 32 x 32)
+    bool bwd16 = false;          // (accepted and reported back: the stored-phase backward has one kernel)
     // register-resident rows: radix-8 passes instead of radix-16 ones, per stage
     bool r8_scalogram = false, r8_second = false, r8_rowfft = false, r8_first_adj = false;
     bool batch8k = false;        // in-LDS row transforms: 8192 points per workgroup (else 4096)
@@ -187,7 +203,9 @@ struct jtfs_plan {
     unsigned short* WTsp = nullptr;  // [Mp/32][KpT/32][16][32][8]: W^T * sw, chunks in LDS order
     unsigned short* PhTsp = nullptr; // per alpha [Tp][NTp/8][2][8]: Phi * sphi[alpha], tau contiguous
     unsigned short* Phq = nullptr;   // per alpha [Tp/16][NTp/16][64][2][4]: Phi * sphi[alpha] (N/T <= 32)
-    unsigned short* WTq = nullptr;   // [Mp/32][KpT/16][4][64][8]: W^T * sw in the 16 x 16 backward's k order
+    unsigned short* Wf = nullptr;    // [nI][tiles][4][64][8]: folded coefficients * sw / 2 of the stored-phase backward
+    double2* psi_fr = nullptr;       // [n_beta][L]: the frequential wavelets along lambda, FP64
+    int *d_rowpos = nullptr, *d_slot_beta = nullptr, *d_slot_l = nullptr, *d_pad = nullptr, *d_kfr = nullptr;
     unsigned short* Wq = nullptr;    // [Mp/64][ceil(Kp/32)][4][4][64][8]: W * sw in the 16 x 16 forward's read order
     std::vector<float> sphi;
     void* owned = nullptr;         // list of device allocations released by destroy

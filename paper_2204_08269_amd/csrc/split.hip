@@ -1189,71 +1189,6 @@ __global__ void k_gvsplit(const float* __restrict__ gV, int Mp, int64_t nrows, u
     ((float*)(blk + 512 * NTB))[spin * 32 + i] = ldexpf(1.f, -se);
 }
 
-// Chunk c of the split gV into LDS (all 256 threads; lane order = source order).
-template <int NTB>
-__device__ __forceinline__ void stage_g(uint4* Ls, const uint4* Gb, int c, int tid) {
-    const uint4* src = Gb + (int64_t)c * gvs_chunk<NTB>();
-    uint4* dst = Ls + 64 * (tid >> 6);
-#pragma unroll
-    for (int k = 0; k < 2 * NTB; ++k) dma16(src + 256 * k, (uint32_t)tid * 16u, dst + 256 * k);
-    if (tid < 16) dma16(src + 512 * NTB, (uint32_t)tid * 16u, Ls + 512 * NTB);
-}
-
-// Stored unit phase of rows crow(r, h), r = 8 s .. 8 s + 7 (g = 2 s, 2 s + 1), of one
-// 32-row block, this lane's column t, both spins: one 16-byte load (four rows) per
-// (spin, g); a wave's load is one contiguous 1 KB run.  pcol points at element 4 h
-// of the lane's column in row group 0 of the block of spin 0; row groups are
-// g_stride elements apart.
-__device__ __forceinline__ void load_phase_half(uint4 (&pv)[2][4], int s, gptr<uint4> pcol, int64_t spin_stride,
-                                                int64_t g_stride) {
-#pragma unroll
-    for (int spin = 0; spin < 2; ++spin)
-#pragma unroll
-        for (int gg = 0; gg < 2; ++gg) {
-            const int g = 2 * s + gg;
-            gptr<u32x4> p = (gptr<u32x4>)(pcol + (spin * spin_stride + g * g_stride) / 4);   // element offsets, % 4 = 0
-            pv[spin][g] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(p));   // read once
-        }
-}
-
-// the two snorm16 of row crow(r, h) as integers in [-32767, 32767] (real, imaginary)
-__device__ __forceinline__ float2 phase_at(const uint4 (&pv)[2][4], int spin, int r) {
-    const uint4 q = pv[spin][r >> 2];
-    const unsigned w = (r & 3) == 0 ? q.x : (r & 3) == 1 ? q.y : (r & 3) == 2 ? q.z : q.w;
-    return make_float2((float)(int)(short)(w & 0xffffu), (float)((int)w >> 16));
-}
-
-// gU = gV Phi^T of one chunk for both spins (A operand from the split gV in LDS, Phi
-// pre-split in registers); each row then scaled by its 2^-se times c0 (the scale of
-// P and Q' over the snorm16 unit of the phase).
-template <int NTB>
-__device__ __forceinline__ void gu_chunk(const uint4* Lg, const uint4 (&phv)[NTB * 2][2], int h, int i32, float c0,
-                                         floatx16 (&gu)[2]) {
-    const float4* rs = (const float4*)(Lg + 512 * NTB);
-#pragma unroll
-    for (int spin = 0; spin < 2; ++spin) {
-        floatx16 acc = z16();
-#pragma unroll
-        for (int kb = 0; kb < NTB * 2; ++kb) {
-            const half8 ah = as_h8(Lg[(((spin * 2 * NTB + kb) * 2 + 0) * 2 + h) * 32 + i32]);
-            const half8 al = as_h8(Lg[(((spin * 2 * NTB + kb) * 2 + 1) * 2 + h) * 32 + i32]);
-            const half8 bh = as_h8(phv[kb][0]), bl = as_h8(phv[kb][1]);
-            acc = mfma16(ah, bh, acc);
-            acc = mfma16(ah, bl, acc);
-            acc = mfma16(al, bh, acc);
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float4 q = rs[spin * 8 + 2 * g + h];        // rows 8 g + 4 h .. + 3
-            acc[4 * g + 0] *= q.x * c0;
-            acc[4 * g + 1] *= q.y * c0;
-            acc[4 * g + 2] *= q.z * c0;
-            acc[4 * g + 3] *= q.w * c0;
-        }
-        gu[spin] = acc;
-    }
-}
-
 // hi / lo FP16 split (as split_h) of two values, each packed as a pair: hp = (hi0,
 // hi1) by one packed conversion, lp = (lo0, lo1) by two mixed-precision FMAs that
 // form v - hi exactly in FP32 and round it once, writing the low and high halves.
@@ -1265,80 +1200,6 @@ __device__ __forceinline__ void split2(float v0, float v1, unsigned& hp, unsigne
         "v_fma_mixhi_f16 %0, %2, 1.0, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
         : "=&v"(lp)
         : "v"(v0), "v"(v1), "v"(hp));
-}
-
-// Modulus adjoint of row pairs 8 s + 2 p0 .. 8 s + 2 p1 - 1 from the scaled gU and
-// the stored phase: P and Q', split into FP16 hi / lo (lanes r - 8 s of ph[s],
-// pl[s]).
-__device__ __forceinline__ void modadj_pairs(int s, int p0, int p1, const floatx16 (&gu)[2], const uint4 (&pv)[2][4],
-                                             half8 (&ph)[2][4], half8 (&pl)[2][4]) {
-#pragma unroll
-    for (int pr = 0; pr < 4; ++pr) {
-        if (pr < p0 || pr >= p1) continue;
-        float vals[2][4];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int r = 8 * s + 2 * pr + e;
-            const float2 u = phase_at(pv, 0, r), d = phase_at(pv, 1, r);
-            const float su = gu[0][r], sd = gu[1][r];
-            vals[e][0] = su * u.x + sd * d.x;
-            vals[e][1] = su * u.y + sd * d.y;
-            vals[e][2] = su * u.y - sd * d.y;
-            vals[e][3] = sd * d.x - su * u.x;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            unsigned hp, lp;
-            split2(vals[0][q], vals[1][q], hp, lp);
-            uint4 hv = __builtin_bit_cast(uint4, ph[s][q]), lv = __builtin_bit_cast(uint4, pl[s][q]);
-            if (pr == 0) { hv.x = hp; lv.x = lp; }
-            else if (pr == 1) { hv.y = hp; lv.y = lp; }
-            else if (pr == 2) { hv.z = hp; lv.z = lp; }
-            else { hv.w = hp; lv.w = lp; }
-            ph[s][q] = __builtin_bit_cast(half8, hv);
-            pl[s][q] = __builtin_bit_cast(half8, lv);
-        }
-    }
-}
-__device__ __forceinline__ void modadj_half(int s, const floatx16 (&gu)[2], const uint4 (&pv)[2][4],
-                                            half8 (&ph)[2][4], half8 (&pl)[2][4]) {
-    modadj_pairs(s, 0, 4, gu, pv, ph, pl);
-}
-
-// W^T fragments (hi, lo of Wr and Wi) of i-blocks q0 and q0 + 1 (clamped to q0 past
-// NI) for the rows of half sp of the staged chunk.
-struct WtFrag {
-    half8 wr[2][2], wi[2][2];             // [block][hi, lo]
-};
-template <int NI>
-__device__ __forceinline__ void load_wt(WtFrag& f, const uint4* Tcur, int sp, int q0, int h, int i32) {
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-        const int q = q0 + d < NI ? q0 + d : q0;
-        const uint4* lt = Tcur + (q * 16 + (sp * 2 + h) * 4) * 32 + i32;
-        f.wr[d][0] = as_h8(lt[0]); f.wr[d][1] = as_h8(lt[32]);
-        f.wi[d][0] = as_h8(lt[64]); f.wi[d][1] = as_h8(lt[96]);
-    }
-}
-
-// gY[q0], gY[q0 + 1] += Wr^T P + Wi^T Q' over the rows of half sp: the two i-blocks
-// alternate, so that four accumulations are in flight.
-template <int NI>
-__device__ __forceinline__ void mma_group(const WtFrag& f, int sp, int q0, const half8 (&ph)[2][4],
-                                          const half8 (&pl)[2][4], floatx16 (&gyr)[NI], floatx16 (&gyi)[NI]) {
-#pragma unroll
-    for (int term = 0; term < 6; ++term) {
-        const int wsel = term < 3 ? 0 : 1, whl = (term % 3) == 2 ? 1 : 0, phl = (term % 3) == 1 ? 1 : 0;
-#pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            if (q0 + d >= NI) continue;
-            const half8 a = wsel ? f.wi[d][whl] : f.wr[d][whl];
-            const half8 br = phl ? pl[sp][wsel * 2] : ph[sp][wsel * 2];
-            const half8 bi = phl ? pl[sp][wsel * 2 + 1] : ph[sp][wsel * 2 + 1];
-            gyr[q0 + d] = mfma16(a, br, gyr[q0 + d]);
-            gyi[q0 + d] = mfma16(a, bi, gyi[q0 + d]);
-        }
-    }
 }
 
 // Scheduling hint for a half: NM groups of one MFMA followed by NV VALU
@@ -1353,479 +1214,374 @@ __device__ __forceinline__ void interleave_mfma_valu() {
     }
 }
 
-// Values a half produces for the next half are pinned before its barrier (an empty
-// asm that reads and writes them), so that the compiler cannot sink their
-// arithmetic past the barrier into the next half, where it would not overlap with
-// matrix work.
-__device__ __forceinline__ void pin_pq(half8 (&ph)[2][4], half8 (&pl)[2][4], int s) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(ph[s][q]), "+v"(pl[s][q]));
-}
-__device__ __forceinline__ void pin_gu(floatx16 (&gu)[2]) {
-    asm volatile("" : "+v"(gu[0]), "+v"(gu[1]));
-}
+// ------------------- backward from the stored phase, folded along lambda
 
-// One 32-row chunk c in two halves.  On entry: P/Q' of rows 0-15 in ph/pl[0], gU of
-// the chunk (scaled) in gu, the phase of rows 16-31 in pv[.][2..3], W^T of the chunk
-// in Tcur.  First half: the W^T product over rows 0-15 while the modulus adjoint of
-// rows 16-31 runs; the next chunk's W^T, split gV and phase of rows 0-15 are
-// requested at its start.  Second half: the product over rows 16-31 while gU of the
-// next chunk and the modulus adjoint of its rows 0-15 run; the phase of its rows
-// 16-31 is requested at its start.  Each half ends with a full wait and a barrier,
-// so every request has a half chunk of matrix work to land.  Within a half, each
-// pair of i-blocks is one scheduling region: the W^T fragments of the next pair are
-// read from LDS at its top (they land while its products run) and a share of the
-// rows' modulus adjoint is interleaved with its products.
-template <int NTB, int NI>
-__device__ __forceinline__ void bwd_phase_chunk(int c, int nC, int wave, int lane, int tid, int h, int i32,
-                                                const uint4 (&phv)[NTB * 2][2], const uint4* Tsrc, const uint4* Gb,
-                                                uint4* Ls_G, const unsigned* pbase, int64_t spin_stride,
-                                                int64_t c_stride, float c0, int64_t cstride, const uint4* Tcur,
-                                                uint4* Tnext,
-                                                floatx16 (&gyr)[NI], floatx16 (&gyi)[NI], floatx16 (&gu)[2],
-                                                uint4 (&pv)[2][4], half8 (&ph)[2][4], half8 (&pl)[2][4]) {
-    constexpr int NG = (NI + 1) / 2;             // pairs of i-blocks
-    const int cn = c + 1 < nC ? c + 1 : c;       // the last chunk reloads itself
-    WtFrag f[2];
-    // ---- first half
-    stage_t<NI>(Tnext, Tsrc, cn, cstride, wave, lane);
-    stage_g<NTB>(Ls_G, Gb, cn, tid);
-    load_phase_half(pv, 0, launder_v((const uint4*)(pbase + cn * c_stride)), spin_stride, c_stride / 4);
-    load_wt<NI>(f[0], Tcur, 0, 0, h, i32);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g + 1 < NG) load_wt<NI>(f[(g + 1) & 1], Tcur, 0, 2 * (g + 1), h, i32);
-        __builtin_amdgcn_sched_barrier(0);
-        mma_group<NI>(f[g & 1], 0, 2 * g, ph, pl, gyr, gyi);
-        modadj_pairs(1, g * 4 / NG, (g + 1) * 4 / NG, gu, pv, ph, pl);
-        interleave_mfma_valu<24, 4>();
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    pin_pq(ph, pl, 1);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    // ---- second half
-    load_phase_half(pv, 1, launder_v((const uint4*)(pbase + cn * c_stride)), spin_stride, c_stride / 4);
-    load_wt<NI>(f[0], Tcur, 1, 0, h, i32);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g + 1 < NG) load_wt<NI>(f[(g + 1) & 1], Tcur, 1, 2 * (g + 1), h, i32);
-        __builtin_amdgcn_sched_barrier(0);
-        mma_group<NI>(f[g & 1], 1, 2 * g, ph, pl, gyr, gyi);
-        if (g == 0) {
-            gu_chunk<NTB>(Ls_G, phv, h, i32, c0, gu);
-            if (NG == 1) modadj_pairs(0, 0, 4, gu, pv, ph, pl);
-            interleave_mfma_valu<24 + 6 * NTB, 2>();
-        } else {
-            modadj_pairs(0, (g - 1) * 4 / (NG - 1), g * 4 / (NG - 1), gu, pv, ph, pl);
-            interleave_mfma_valu<24, 5>();
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    pin_pq(ph, pl, 0);
-    pin_gu(gu);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-}
-
-// Backward contraction from the stored phase: one signal, 128 columns t (four
-// waves of 32), all rows l in 32-row chunks; gY accumulated in registers for the
-// NI i-blocks q_base .. q_base + NI - 1 of the nit blocks of W^T (the register
-// budget holds at most 8 at 32 frames; larger K runs as several launches over
-// disjoint i-ranges, each repeating the modulus adjoint).
-template <int NTB, int NI>
-__global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__ phase, int64_t ph_bstride,
-                                                    const FreqRate* __restrict__ rates,
-                                                    const FreqUnit* __restrict__ tiles, int nT, int nU,
-                                                    const unsigned short* __restrict__ WTsp, int q_base, int nit,
-                                                    int Mp, int Kp, const unsigned short* __restrict__ PhTsp,
-                                                    const uint4* __restrict__ Gs, int64_t gs_bstride,
-                                                    const float* __restrict__ gvmax, int n_beta,
-                                                    int n_alpha, float sw, float2* __restrict__ gY,
-                                                    int64_t gy_bstride) {
-    constexpr int NTp = 32 * NTB;
-    __shared__ uint4 Ls_T0[NI * 512];
-    __shared__ uint4 Ls_T1[NI * 512];
-    __shared__ uint4 Ls_G[gvs_chunk<NTB>()];
-    const int u = blockIdx.x;
-    if (u >= nU) return;                            // whole block
-    const int64_t b = u / nT;
-    const FreqUnit un = tiles[u % nT];
-    const FreqRate rate = rates[un.alpha];
-    const int alpha = un.alpha, t0 = un.t0, Tp = rate.Tp;
-    const float sphi = rate.sphi;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = lane >> 5, i32 = lane & 31;
-    const int tw0 = t0 + wave * 32;                 // this wave's columns
-    const int nC = Mp / 32;
-
-    float G = 0.f;
-    for (int q = 0; q < 2 * n_beta; ++q) G = fmaxf(G, gvmax[(b * n_alpha + alpha) * 2 * n_beta + q]);
-    const float spq = pow2_scale(2.f * G * 16384.f / sphi);
-    const float c0 = spq / sphi * kSnormInv;
-
-    floatx16 gyr[NI], gyi[NI];
-#pragma unroll
-    for (int q = 0; q < NI; ++q) { gyr[q] = z16(); gyi[q] = z16(); }
-
-    const uint4* phrow = (const uint4*)(PhTsp + rate.phioff * 2 + ((int64_t)(tw0 + i32) * (NTp / 8) + h) * 16);
-    const uint4* Tsrc = (const uint4*)WTsp + (int64_t)q_base * 512;
-    const int64_t cstride = (int64_t)nit * 512;
-    const uint4* Gb = Gs + b * gs_bstride + (int64_t)alpha * (Mp / 32) * gvs_chunk<NTB>();
-    // this lane's column of the stored phase, rows 4h.. of each 8-row group
-    // (blocks [spin][Mp / 32], each four row groups of Tp x 8 elements)
-    const unsigned* pbase = phase + b * ph_bstride + rate.phase_off + (int64_t)(tw0 + i32) * 8 + 4 * h;
-    const int64_t spin_stride = (int64_t)Tp * Mp, c_stride = (int64_t)Tp * 32;
-
-    uint4 phv[NTB * 2][2];
-#pragma unroll
-    for (int kb = 0; kb < NTB * 2; ++kb) {
-        phv[kb][0] = phrow[4 * kb];
-        phv[kb][1] = phrow[4 * kb + 1];
-    }
-    uint4 pv[2][4];
-    floatx16 gu[2];
-    half8 ph[2][4], pl[2][4];
-    // chunk 0: operands, gU and the P/Q' of its rows 0-15
-    stage_t<NI>(Ls_T0, Tsrc, 0, cstride, wave, lane);
-    stage_g<NTB>(Ls_G, Gb, 0, tid);
-    load_phase_half(pv, 0, (gptr<uint4>)pbase, spin_stride, c_stride / 4);
-    load_phase_half(pv, 1, (gptr<uint4>)pbase, spin_stride, c_stride / 4);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    gu_chunk<NTB>(Ls_G, phv, h, i32, c0, gu);
-    modadj_half(0, gu, pv, ph, pl);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    // nC is even (Mp is a multiple of 64): the W^T buffers alternate at compile time
-    for (int c = 0; c < nC; c += 2) {
-        bwd_phase_chunk<NTB, NI>(c, nC, wave, lane, tid, h, i32, phv, Tsrc, Gb, Ls_G, pbase, spin_stride, c_stride,
-                                 c0, cstride, Ls_T0, Ls_T1, gyr, gyi, gu, pv, ph, pl);
-        bwd_phase_chunk<NTB, NI>(c + 1, nC, wave, lane, tid, h, i32, phv, Tsrc, Gb, Ls_G, pbase, spin_stride,
-                                 c_stride, c0, cstride, Ls_T1, Ls_T0, gyr, gyi, gu, pv, ph, pl);
-    }
-    const float inv = 1.f / (sw * spq);
-    float2* o = gY + b * gy_bstride + rate.yoff;
-#pragma unroll
-    for (int q = 0; q < NI; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = (q_base + q) * 32 + crow(r, h);
-            if (i < Kp) o[(int64_t)i * Tp + tw0 + i32] = make_float2(gyr[q][r] * inv, gyi[q][r] * inv);
-        }
-}
-
-
-// ------------------------------ backward from the stored phase, 16 x 16 tiles
-
-// Row of the 32-row chunk that k-slot j (0..7) of lane group g holds in the
-// W^H product of k_freq_bwd_q: 4 g + j, then 16 + 4 g + j - 4 -- the rows whose
-// gU a lane holds after the 16 x 16 lowpass-adjoint products of the chunk's two
-// 16-row halves, and whose stored phase it loads.
+// The product gY[i] = sum_l Wr[l][i] P[l] + Wi[l][i] Q'[l] over rows l in 16 x 16 tiles,
+// with half the matrix operations.  The frequential wavelets have real spectra, so
+// that w[-n] = conj w[n]: reflecting both axes about c2 / 2 (l -> c2 - l, i -> c2 - i)
+// leaves Wr as it is and negates Wi.  For a pair of mirrored rows l, l' and of
+// mirrored columns i, i' the sums S = gY[i] + gY[i'] and D = gY[i] - gY[i'] need
+// one product each where gY[i] and gY[i'] needed four,
+//   S += (Wr[l][i] + Wr[l][i']) (P[l] + P[l']) + (Wi[l][i] + Wi[l][i']) (Q[l] - Q[l'])
+//   D += (Wr[l][i] - Wr[l][i']) (P[l] - P[l']) + (Wi[l][i] - Wi[l][i']) (Q[l] + Q[l']),
+// for the columns i <= c2 / 2 alone.  The plan lays the rows out so that the two
+// 32-row chunks of a 64-row tile mirror each other.  Rows without a mirror image
+// (the fixed points, at most two per scale) share the last tiles two by two: with
+// the means and half-differences of their coefficients the formulas above give
+// the terms even in the exchange of the two, and one more pass over such a tile
+// with the second row's sign reversed gives the odd ones.
+// k-slot j of lane group g holds pair qrow(g, j) of the tile in the S tables and pair
+// qrow(g, j ^ 4) in the D tables: a lane forms the operands of four of its eight
+// pairs (the wave's half of the rows) and takes the other four from the wave of
+// the other tables, which come second in either.
 __device__ __forceinline__ int qrow(int g, int j) { return j < 4 ? 4 * g + j : 12 + 4 * g + j; }
 
-// WTq[c][it][p][lane][j] = split(W[l][i] * sw), p = re hi, re lo, im hi, im lo, for
-// i = 16 it + lane % 16 and l = 32 c + qrow(lane / 16, j): the A operand of the
-// 16 x 16 x 32 W^H product, a chunk (KpT x 32) contiguous.  Rows i >= Kp are zero.
-__global__ void k_wtqsplit(const float2* __restrict__ Wl, int Mp, int Kp, int KpT, float sw,
-                           unsigned short* __restrict__ WTq) {
+// Wf[it][tile][p][lane][j], p = re hi, re lo, im hi, im lo of the coefficients above
+// times sf: pass it's tiles in the order in which the kernel stages them (H1 S tiles,
+// H1 D tiles, the remaining S tiles, the remaining D tiles).
+__global__ void k_wfold(const double2* __restrict__ psi, int L, const int* __restrict__ slot_beta,
+                        const int* __restrict__ slot_l, const int* __restrict__ kfr, FoldPlan f, float sf,
+                        unsigned short* __restrict__ Wf) {
+    const int ntile = 2 * f.NS - f.shortD, H1 = (f.NS + 1) / 2, H2 = f.NS - H1;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)KpT * Mp) return;
-    const int j = (int)(e & 7);
-    const int lane = (int)((e >> 3) & 63);
+    if (e >= (int64_t)f.nI * ntile * 512) return;
+    const int j = (int)(e & 7), lane = (int)((e >> 3) & 63);
     const int64_t r = e >> 9;
-    const int nq = KpT / 16;
-    const int it = (int)(r % nq);
-    const int c = (int)(r / nq);
-    const int i = 16 * it + (lane & 15);
-    const int l = 32 * c + qrow(lane >> 4, j);
-    const float2 w = i < Kp ? Wl[(int64_t)l * Kp + i] : make_float2(0.f, 0.f);
-    _Float16 a, bb, cc, d;
-    split_h(w.x * sw, a, bb);
-    split_h(w.y * sw, cc, d);
-    _Float16* o = (_Float16*)WTq + ((((int64_t)c * nq + it) * 4) * 64 + lane) * 8 + j;
-    o[0] = a; o[512] = bb; o[1024] = cc; o[1536] = d;      // planes 64 lanes x 8 halves apart
+    const int tq = (int)(r % ntile), it = (int)(r / ntile);
+    const int role = tq < H1 ? 0 : tq < 2 * H1 ? 1 : tq < 2 * H1 + H2 ? 0 : 1;
+    const int k = tq < H1 ? tq : tq < 2 * H1 ? tq - H1 : tq < 2 * H1 + H2 ? tq - H1 : tq - H1 - H2;
+    const int i = 16 * k + (lane & 15);
+    const bool odd = it >= f.nD;
+    const int t = odd ? f.t0 + it - f.nD : it;
+    const int p = qrow(lane >> 4, role ? j ^ 4 : j);
+    double cr[2] = {0.0, 0.0}, ci[2] = {0.0, 0.0};   // of the slot's two rows
+    for (int q = 0; q < 2; ++q) {
+        const int slot = 64 * t + 32 * q + p, beta = slot_beta[slot];
+        if (beta < 0 || i > f.c2 / 2) continue;
+        const double2* h = psi + (int64_t)beta * L;
+        const int l = slot_l[slot] << kfr[beta];
+        const double2 a = h[((l - i) % L + L) % L], b = h[((l - f.c2 + i) % L + L) % L];
+        cr[q] = role ? a.x - b.x : a.x + b.x;
+        ci[q] = role ? a.y - b.y : a.y + b.y;
+    }
+    // S: P[l] + P[l'] and Q[l] - Q[l']; D: P[l] - P[l'] and Q[l] + Q[l']; the odd pass the other way round
+    const double s = (role != 0) != odd ? -0.5 : 0.5;
+    const float wr = (float)(0.5 * cr[0] + s * cr[1]), wi = (float)(0.5 * ci[0] - s * ci[1]);
+    _Float16 a, b, c, d;
+    split_h(wr * sf, a, b);
+    split_h(wi * sf, c, d);
+    _Float16* o = (_Float16*)Wf + (r * 4 * 64 + lane) * 8 + j;
+    o[0] = a; o[512] = b; o[1024] = c; o[1536] = d;        // planes 64 lanes x 8 halves apart
 }
 
-// Power-of-two scales of the lane's gV rows of one 32-row chunk, per spin and
-// 16-row half: rows 16 hf + 4 g4 .. + 3.  Read straight from the split-gV table;
-// the chunk's address goes through launder_v, so that the compiler issues these
-// loads where they stand instead of repeating them next to their uses, where
-// they would wait behind the global-to-LDS copies.
-struct GvScaleQ {
-    float4 q[2][2];       // [spin][hf]
-};
-__device__ __forceinline__ void bwdq_load_scales(GvScaleQ& g, const uint4* Gb, int c, int g4) {
-    gptr<uint4> Lg = launder_v(Gb + (int64_t)c * gvs_chunk<1>() + 512);
+// n groups of 64 slots (1 KB) into LDS by direct global-to-LDS loads of the eight
+// waves.  (wave is passed wave-uniform, so that the LDS destinations are scalar.)
+template <int N>
+__device__ __forceinline__ void bwdf_stage(uint4* Ls, const uint4* src, int tid, int wave) {
 #pragma unroll
-    for (int spin = 0; spin < 2; ++spin)
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
-            g.q[spin][hf] = __builtin_bit_cast(float4, ((gptr<u32x4>)Lg)[spin * 8 + 4 * hf + g4]);
+    for (int k = 0; k < (N + 7) / 8; ++k)
+        if (8 * k + 8 <= N || 8 * k + wave < N) dma16(src + k * 512, (uint32_t)tid * 16u, Ls + k * 512 + wave * 64);
+}
+// the split gV rows and scales of tile t (two chunks) the same way
+template <int NTB>
+__device__ __forceinline__ void bwdf_stage_g(uint4* Ls, const uint4* Gb, int t, int tid, int wave) {
+    const uint4* src = Gb + (int64_t)t * (2 * gvs_chunk<NTB>());
+    bwdf_stage<16 * NTB>(Ls, src, tid, wave);
+    if (tid < 32) dma16(src + 1024 * NTB, (uint32_t)tid * 16u, Ls + 1024 * NTB);
 }
 
-// One lowpass-adjoint product: gU of rows 16 hf + 4 g4 + r at the lane's column
-// from the split gV rows of the chunk staged in Lg (unscaled; the row scales are
-// applied by the modulus adjoint).
-__device__ __forceinline__ floatx4 bwdq_gu(const uint4* Lg, int g4, int j16, int spin, int hf, half8 fh, half8 fl) {
-    const int base = (((spin * 2 + (g4 >> 1)) * 2) * 2 + (g4 & 1)) * 32 + 16 * hf + j16;
-    const half8 ah = as_h8(Lg[base]), al = as_h8(Lg[base + 64]);
+// gU of rows 16 hf + 4 g4 + r of one chunk at the lane's column from its split gV rows
+// (Lg), times 2^-se of the row and c0
+template <int NTB>
+__device__ __forceinline__ floatx4 bwdf_gu(const uint4* Lg, int g4, int j16, int spin, int hf, const half8 (&fh)[NTB],
+                                           const half8 (&fl)[NTB], float c0) {
     floatx4 acc = z4();
-    acc = mfma16q(ah, fh, acc);
-    acc = mfma16q(ah, fl, acc);
-    acc = mfma16q(al, fh, acc);
+#pragma unroll
+    for (int n = 0; n < NTB; ++n) {
+        const int base = (((spin * 2 * NTB + 2 * n + (g4 >> 1)) * 2) * 2 + (g4 & 1)) * 32 + 16 * hf + j16;
+        const half8 ah = as_h8(Lg[base]), al = as_h8(Lg[base + 64]);
+        acc = mfma16q(ah, fh[n], acc);
+        acc = mfma16q(ah, fl[n], acc);
+        acc = mfma16q(al, fh[n], acc);
+    }
+    const float4 q = ((const float4*)(Lg + 512 * NTB))[spin * 8 + 4 * hf + g4];
+    acc[0] *= q.x * c0;
+    acc[1] *= q.y * c0;
+    acc[2] *= q.z * c0;
+    acc[3] *= q.w * c0;
     return acc;
 }
 
-// Modulus adjoint of the rows 16 hf + 4 g4 + 2 pr, + 1 (k-slots 4 hf + 2 pr, + 1):
-// P = gZ_up + gZ_down, Q' = i (gZ_down - gZ_up) with gZ = gU u from the stored unit
-// phase, split into FP16 hi / lo; word 2 hf + pr of the B planes (P re, P im, Q' re,
-// Q' im).
-__device__ __forceinline__ void bwdq_modadj(int hf, int pr, const floatx4 (&gu)[2][2], const GvScaleQ& g, float c0,
-                                            const uint4 (&pv)[2][2], half8 (&bh)[4], half8 (&bl)[4]) {
-    float vals[2][4];
+// the lane's stored phase of a tile: [chunk][spin], four rows of one column each
+__device__ __forceinline__ void bwdf_load_phase(uint4 (&pv)[2][2], const unsigned* pcol, int t, int64_t spin_stride,
+                                                int64_t c_stride) {
+    gptr<uint4> base = launder_v((const uint4*)(pcol + 2 * t * c_stride));
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int r = 2 * pr + e;
-        const unsigned wu = r == 0 ? pv[0][hf].x : r == 1 ? pv[0][hf].y : r == 2 ? pv[0][hf].z : pv[0][hf].w;
-        const unsigned wd = r == 0 ? pv[1][hf].x : r == 1 ? pv[1][hf].y : r == 2 ? pv[1][hf].z : pv[1][hf].w;
-        const float qu = r == 0 ? g.q[0][hf].x : r == 1 ? g.q[0][hf].y : r == 2 ? g.q[0][hf].z : g.q[0][hf].w;
-        const float qd = r == 0 ? g.q[1][hf].x : r == 1 ? g.q[1][hf].y : r == 2 ? g.q[1][hf].z : g.q[1][hf].w;
-        const float ux = (float)(int)(short)(wu & 0xffffu), uy = (float)((int)wu >> 16);
-        const float dx = (float)(int)(short)(wd & 0xffffu), dy = (float)((int)wd >> 16);
-        const float su = gu[0][hf][r] * (qu * c0), sd = gu[1][hf][r] * (qd * c0);
-        vals[e][0] = su * ux + sd * dx;
-        vals[e][1] = su * uy + sd * dy;
-        vals[e][2] = su * uy - sd * dy;
-        vals[e][3] = sd * dx - su * ux;
-    }
+    for (int cc = 0; cc < 2; ++cc)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        unsigned hp, lp;
-        split2(vals[0][q], vals[1][q], hp, lp);
-        const int w = 2 * hf + pr;
-        uint4 hv = __builtin_bit_cast(uint4, bh[q]), lv = __builtin_bit_cast(uint4, bl[q]);
-        if (w == 0) { hv.x = hp; lv.x = lp; }
-        else if (w == 1) { hv.y = hp; lv.y = lp; }
-        else if (w == 2) { hv.z = hp; lv.z = lp; }
-        else { hv.w = hp; lv.w = lp; }
-        bh[q] = __builtin_bit_cast(half8, hv);
-        bl[q] = __builtin_bit_cast(half8, lv);
-    }
-}
-
-// the lane's stored phase of a chunk: [spin][hf], four rows of one column each
-__device__ __forceinline__ void bwdq_load_phase(uint4 (&pv)[2][2], const unsigned* pbase, int c, int g4,
-                                                int64_t spin_stride, int64_t c_stride, int64_t g_stride) {
-    gptr<uint4> base = launder_v((const uint4*)(pbase + c * c_stride));
-#pragma unroll
-    for (int spin = 0; spin < 2; ++spin)
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            gptr<u32x4> p = (gptr<u32x4>)(base + (spin * spin_stride + ((g4 >> 1) + 2 * hf) * g_stride) / 4);
-            pv[spin][hf] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(p));   // read once
+        for (int spin = 0; spin < 2; ++spin) {
+            gptr<u32x4> p = (gptr<u32x4>)(base + (spin * spin_stride + cc * c_stride) / 4);
+            pv[cc][spin] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(p));   // read once
         }
 }
 
-// Half h (i-tiles NI h .. NI h + NI - 1, NI x 4 KB) of the W^T chunk c into LDS by
-// direct global-to-LDS loads: NI per thread of the 256.  A chunk's i-tiles are
-// contiguous in the table, each [plane][lane].
-// (wave is passed wave-uniform, so that the LDS destinations are scalar.)
-template <int NI>
-__device__ __forceinline__ void bwdq_stage_half(uint4* Ls, const uint4* WTq, int c, int h, int tid, int wave) {
-    const uint4* src = WTq + (int64_t)c * (NI * 512) + h * (NI * 256);
-    const uint32_t off = (uint32_t)tid * 16u;
+__device__ __forceinline__ unsigned word4(const uint4& v, int r) { return r == 0 ? v.x : r == 1 ? v.y : r == 2 ? v.z : v.w; }
+
+// Modulus adjoint of the lane's pairs 2 pr and 2 pr + 1: P = gZ_up + gZ_down and Q' = i
+// (gZ_down - gZ_up), gZ = gU u, of both rows; then P + P' and Q - Q' (own[q]) and P - P'
+// and Q + Q' (other[q]), split into FP16 hi and lo words (x, y: hi; z, w: lo).
+__device__ __forceinline__ void bwdf_modadj(int pr, const floatx4 (&gu)[2][2], const uint4 (&pv)[2][2],
+                                            uint4 (&own)[4], uint4 (&other)[4]) {
+    float v[2][2][4];                                  // [e][chunk][P re, P im, Q re, Q im]
 #pragma unroll
-    for (int k = 0; k < NI; ++k) dma16(src + k * 256, off, Ls + k * 256 + wave * 64);
-}
-// the split gV rows of chunk c (8 KB, without the scales) the same way
-__device__ __forceinline__ void bwdq_stage_g(uint4* Ls, const uint4* Gb, int c, int tid, int wave) {
-    const uint4* src = Gb + (int64_t)c * gvs_chunk<1>();
-    const uint32_t off = (uint32_t)tid * 16u;
+    for (int e = 0; e < 2; ++e)
 #pragma unroll
-    for (int k = 0; k < 2; ++k) dma16(src + k * 256, off, Ls + k * 256 + wave * 64);
+        for (int cc = 0; cc < 2; ++cc) {
+            const int r = 2 * pr + e;
+            const unsigned wu = word4(pv[cc][0], r), wd = word4(pv[cc][1], r);
+            const float ux = (float)(int)(short)(wu & 0xffffu), uy = (float)((int)wu >> 16);
+            const float dx = (float)(int)(short)(wd & 0xffffu), dy = (float)((int)wd >> 16);
+            const float su = gu[cc][0][r], sd = gu[cc][1][r];
+            v[e][cc][0] = su * ux + sd * dx;
+            v[e][cc][1] = su * uy + sd * dy;
+            v[e][cc][2] = su * uy - sd * dy;
+            v[e][cc][3] = sd * dx - su * ux;
+        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float p0 = v[0][0][q] + v[0][1][q], p1 = v[1][0][q] + v[1][1][q];
+        const float m0 = v[0][0][q] - v[0][1][q], m1 = v[1][0][q] - v[1][1][q];
+        unsigned h, l;
+        split2(q < 2 ? p0 : m0, q < 2 ? p1 : m1, h, l);
+        if (pr == 0) { own[q].x = h; own[q].z = l; } else { own[q].y = h; own[q].w = l; }
+        split2(q < 2 ? m0 : p0, q < 2 ? m1 : p1, h, l);
+        if (pr == 0) { other[q].x = h; other[q].z = l; } else { other[q].y = h; other[q].w = l; }
+    }
 }
 
-// The W^T products of i-tiles IT0 .. IT0 + NI - 1 (one half of the chunk, staged in
-// Lh), one scheduling region per i-tile; the work of chunk c + 1 placed in this
-// half (CHAINS: the four lowpass-adjoint chains from the gV rows in Lg; else the
-// four modulus-adjoint shares) is spread over the regions.
-template <int NI, int IT0, bool CHAINS>
-__device__ __forceinline__ void bwdq_half(const uint4* Lh, const uint4* Lg, int lane, int g4, int j16, half8 fh,
-                                          half8 fl, float c0, const half8 (&bh)[4], const half8 (&bl)[4],
-                                          half8 (&nh)[4], half8 (&nl)[4], const uint4 (&pnext)[2][2],
-                                          const GvScaleQ& snext, floatx4 (&gu)[2][2], floatx4 (&gyr)[2 * NI],
-                                          floatx4 (&gyi)[2 * NI]) {
-    const uint4* Lt = Lh + lane;
+// The products of one half's tiles (`nt` of the wave's tiles from T0 on, staged at Lt),
+// one scheduling region per tile; the next tile's work placed in this half (CHAINS:
+// the four lowpass-adjoint chains; else the two modulus-adjoint shares) is spread
+// over the regions.
+template <int NTB, int NS, int T0, int NT, bool CHAINS, bool SHORT>
+__device__ __forceinline__ void bwdf_half(const uint4* Lt, const uint4* Lg, int role, int g4, int j16,
+                                          const half8 (&fh)[NTB], const half8 (&fl)[NTB], float c0, float c1,
+                                          const half8 (&bh)[4], const half8 (&bl)[4], floatx4 (&gu)[2][2],
+                                          const uint4 (&pv)[2][2], uint4 (&own)[4], uint4 (&other)[4],
+                                          floatx4 (&gr)[NS], floatx4 (&gi)[NS]) {
+    constexpr int NE = CHAINS ? 4 : 2;
+    auto event = [&](int k) {
+        if constexpr (CHAINS)
+            gu[k >> 1][k & 1] = bwdf_gu<NTB>(Lg + (k >> 1) * gvs_chunk<NTB>(), g4, j16, k & 1, role, fh, fl,
+                                             k >> 1 ? c1 : c0);
+        else
+            bwdf_modadj(k, gu, pv, own, other);
+    };
+    if constexpr (NT == 0) {
+#pragma unroll
+        for (int k = 0; k < NE; ++k) event(k);
+        return;
+    }
     uint4 wc[4], wn[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) wc[p] = Lt[p * 64];
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-        const int it = IT0 + j;
-        if (j + 1 < NI) {
+    for (int j = 0; j < NT; ++j) {
+        const int k = T0 + j;
+        if (j + 1 < NT) {
 #pragma unroll
             for (int p = 0; p < 4; ++p) wn[p] = Lt[((j + 1) * 4 + p) * 64];
         }
         const half8 wrh = as_h8(wc[0]), wrl = as_h8(wc[1]), wih = as_h8(wc[2]), wil = as_h8(wc[3]);
-        gyr[it] = mfma16q(wrh, bh[0], gyr[it]); gyi[it] = mfma16q(wrh, bh[1], gyi[it]);
-        gyr[it] = mfma16q(wrh, bl[0], gyr[it]); gyi[it] = mfma16q(wrh, bl[1], gyi[it]);
-        gyr[it] = mfma16q(wrl, bh[0], gyr[it]); gyi[it] = mfma16q(wrl, bh[1], gyi[it]);
-        gyr[it] = mfma16q(wih, bh[2], gyr[it]); gyi[it] = mfma16q(wih, bh[3], gyi[it]);
-        gyr[it] = mfma16q(wih, bl[2], gyr[it]); gyi[it] = mfma16q(wih, bl[3], gyi[it]);
-        gyr[it] = mfma16q(wil, bh[2], gyr[it]); gyi[it] = mfma16q(wil, bh[3], gyi[it]);
-        // event k (chain (spin k & 1, half k >> 1), or share (half k >> 1, pair k & 1))
-        // in region (k NI) / 4 of the half
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if ((k * NI) / 4 != j) continue;
-            if constexpr (CHAINS) {
-                gu[k & 1][k >> 1] = bwdq_gu(Lg, g4, j16, k & 1, k >> 1, fh, fl);
-            } else {
-                bwdq_modadj(k >> 1, k & 1, gu, snext, c0, pnext, nh, nl);
-                interleave_mfma_valu<12, 4>();
-            }
+        // (the D tables may hold one tile less: that region's products then belong to S waves only)
+        if (!(SHORT && j + 1 == NT) || role == 0) {
+            gr[k] = mfma16q(wrh, bh[0], gr[k]); gi[k] = mfma16q(wrh, bh[1], gi[k]);
+            gr[k] = mfma16q(wrh, bl[0], gr[k]); gi[k] = mfma16q(wrh, bl[1], gi[k]);
+            gr[k] = mfma16q(wrl, bh[0], gr[k]); gi[k] = mfma16q(wrl, bh[1], gi[k]);
+            gr[k] = mfma16q(wih, bh[2], gr[k]); gi[k] = mfma16q(wih, bh[3], gi[k]);
+            gr[k] = mfma16q(wih, bl[2], gr[k]); gi[k] = mfma16q(wih, bl[3], gi[k]);
+            gr[k] = mfma16q(wil, bh[2], gr[k]); gi[k] = mfma16q(wil, bh[3], gi[k]);
         }
+#pragma unroll
+        for (int q = 0; q < NE; ++q)
+            if ((q * NT) / NE == j) event(q);
+        if constexpr (!CHAINS) interleave_mfma_valu<12, 4>();
 #pragma unroll
         for (int p = 0; p < 4; ++p) wc[p] = wn[p];
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// Backward contraction from the stored phase in 16 x 16 tiles: one signal, 64
-// columns t (four waves of 16, one per SIMD), all rows l in 32-row chunks, all NI
-// pairs of 16-row i-tiles accumulated in registers (16 NI of them per lane), so
-// that any K the split forward handles runs in one pass over the phase.
-// Per chunk:
-//   gU[l][t] = sum_tau gV[l][tau] Phi[t][tau]       (16 x 16 x 32, both spins, both row halves)
-//   P, Q' from gU and the stored unit phase         (the lane's eight rows of its column)
-//   gY[i][t] += sum_l Wr[l][i] P[l][t] + Wi[l][i] Q'[l][t]
-// pipelined so that the first two steps of chunk c + 1 run during the third of
-// chunk c.  The W^T chunk is staged in two halves by i-range, X (first NI
-// i-tiles) and Y (the rest), and the split gV rows in G, each a distinct LDS array
-// filled by direct global-to-LDS loads (8 NI + 8 KB in all):
-//   chunk start: Y <- W^T(c) second half; phase of chunk c + 2 requested
-//   first half:  products with X; lowpass-adjoint chains of chunk c + 1 from G
+// Backward contraction from the stored phase: one signal, 64 columns t, all rows l in
+// 64-row tiles of mirrored pairs.  Eight waves: waves w and w + 4 (one SIMD) own the
+// same 16 columns; w accumulates S, w + 4 accumulates D, NS tiles of 16 columns i
+// each (8 NS registers), so that any K of the split forward runs in one pass over
+// the phase.  Per tile:
+//   gU[l][t] = sum_tau gV[l][tau] Phi[t][tau]       (16 x 16 x 32; each wave one half of the rows)
+//   P, Q' from gU and the stored unit phase, P +- P', Q -+ Q' (each wave four of a
+//   lane's eight pairs; the other wave's share passes through LDS)
+//   S and D += coefficients x operands
+// pipelined so that the first two steps of the next tile run during the third of
+// this one.  The coefficients of a pass are staged in two halves, X (the first H1
+// tiles of both tables) and Y (the rest), and the split gV rows in G, each a
+// distinct LDS array filled by direct global-to-LDS loads:
+//   start:       Y <- this pass's second half; phase of the next tile requested
+//   first half:  products with X; lowpass-adjoint chains of the next tile from G
 //   full wait, barrier
-//   middle:      X <- W^T(c + 1) first half, G <- gV rows of chunk c + 2; their
-//                scales requested
-//   second half: products with Y; modulus adjoint of chunk c + 1
-//   full wait, barrier
-// Every copy thus has half a chunk of products to land, the arrays read in a half
-// are never the ones being filled (so the compiler adds no wait for the copies
-// before those reads), and nothing requested into registers is used before the
-// next barrier (a wait for a register load while a copy is in flight is a wait
-// for everything).  The last chunks request their own operands again.
-template <int NI>
-__global__ void __launch_bounds__(256) k_freq_bwd_q(const unsigned* __restrict__ phase, int64_t ph_bstride,
+//   middle:      X <- next pass's first half, G <- gV rows of the tile after
+//   second half: products with Y; modulus adjoint of the next tile, exchange written
+//   full wait, barrier, exchange read
+// Every copy thus has half a pass of products to land, the arrays read in a half are
+// never the ones being filled (so the compiler adds no wait for the copies before
+// those reads), and nothing requested into registers is used before the next
+// barrier.  Two waves per SIMD overlap one's vector work with the other's products;
+// the kernel before had one wave per SIMD and all the products, and its matrix
+// cores were busy half of the time.  32 x 2^18 (n1 = 285): 55 -> 39 ms per step;
+// 16 x 2^16 (n1 = 167) fwd+bwd 9.36 -> 9.00 ms.
+template <int NTB, int NS, bool SHORT>
+__global__ void __launch_bounds__(512) k_freq_bwd_f(const unsigned* __restrict__ phase, int64_t ph_bstride,
                                                     const FreqRate* __restrict__ rates,
                                                     const FreqUnit* __restrict__ tiles, int nT, int nU,
-                                                    const unsigned short* __restrict__ WTq, int Mp,
-                                                    int Kp, const unsigned short* __restrict__ PhTsp,
+                                                    const unsigned short* __restrict__ Wf, FoldPlan f, int Mp, int n1,
+                                                    const unsigned short* __restrict__ PhTsp,
                                                     const uint4* __restrict__ Gs, int64_t gs_bstride,
                                                     const float* __restrict__ gvmax, int n_beta,
-                                                    int n_alpha, float sw, float2* __restrict__ gY,
+                                                    int n_alpha, float sf, float2* __restrict__ gY,
                                                     int64_t gy_bstride) {
-    constexpr int NTp = 32, NQ = 2 * NI;
-    __shared__ uint4 Ls_X[NI * 256];
-    __shared__ uint4 Ls_Y[NI * 256];
-    __shared__ uint4 Ls_G[512];
+    constexpr int NTp = 32 * NTB, H1 = (NS + 1) / 2, H2 = NS - H1;
+    constexpr int NX = 2 * H1, NY = 2 * H2 - (SHORT ? 1 : 0);      // tiles of the halves
+    static_assert(!SHORT || H2 > 0, "a short D table needs a tile in the second half");
+    __shared__ uint4 Ls_X[NX * 256];
+    __shared__ uint4 Ls_Y[(H2 > 0 ? 2 * H2 : 1) * 256];            // (a short D table leaves a tile unused)
+    __shared__ uint4 Ls_G[2 * gvs_chunk<NTB>()];
+    __shared__ uint4 Ls_E[8 * 4 * 64];
     const int u = blockIdx.x;                         // half of a 128-column tile
     if (u >= nU) return;                              // whole block
     const int64_t b = (u >> 1) / nT;
     const FreqUnit un = tiles[(u >> 1) % nT];
     const FreqRate rate = rates[un.alpha];
-    const int alpha = un.alpha, t0 = un.t0 + 64 * (u & 1), Tp = rate.Tp;
-    const float sphi = rate.sphi;
+    const int alpha = un.alpha, Tp = rate.Tp;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), role = wave >> 2;
     const int j16 = lane & 15, g4 = lane >> 4;
-    const int t = t0 + wave * 16 + j16;               // this lane's column
-    const int nC = Mp / 32;
+    const int t = un.t0 + 64 * (u & 1) + (wave & 3) * 16 + j16;   // this lane's column
 
     float G = 0.f;
     for (int q = 0; q < 2 * n_beta; ++q) G = fmaxf(G, gvmax[(b * n_alpha + alpha) * 2 * n_beta + q]);
-    const float spq = pow2_scale(2.f * G * 16384.f / sphi);
-    const float c0 = spq / sphi * kSnormInv;
+    const float spq = pow2_scale(4.f * G * 16384.f / rate.sphi);   // |P|, |Q'| <= 2 G max|Phi|, twice that folded
+    const float c0 = spq / rate.sphi * kSnormInv;
 
-    floatx4 gyr[NQ], gyi[NQ];
+    floatx4 gr[NS], gi[NS];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) { gyr[q] = z4(); gyi[q] = z4(); }
+    for (int q = 0; q < NS; ++q) { gr[q] = z4(); gi[q] = z4(); }
 
-    // Phi of the lane's column, tau 8 g4 .. 8 g4 + 7: hi and lo planes
-    const uint4* phrow = (const uint4*)(PhTsp + rate.phioff * 2 + ((int64_t)t * (NTp / 8) + g4) * 16);
-    const half8 fh = as_h8(phrow[0]), fl = as_h8(phrow[1]);
-    const uint4* Gb = Gs + b * gs_bstride + (int64_t)alpha * (Mp / 32) * gvs_chunk<1>();
-    const uint4* Wt = (const uint4*)WTq;
-    // the lane's phase rows: 4 (g4 % 2) .. of row group g4 / 2 (rows 4 g4 ..) and of
-    // group 2 + g4 / 2 (rows 16 + 4 g4 ..)
-    const unsigned* pbase = phase + b * ph_bstride + rate.phase_off + (int64_t)t * 8 + 4 * (g4 & 1);
-    const int64_t spin_stride = (int64_t)Tp * Mp, c_stride = (int64_t)Tp * 32, g_stride = (int64_t)Tp * 8;
-    const int one = 1 < nC ? 1 : 0;
-
-    // chunk 0's B operands from its gV rows, scales and phase; then the gV rows of
-    // chunk 1 into G, and the first half of W^T(0) into X
-    half8 bh[4], bl[4];
-    uint4 pnext[2][2];
-    GvScaleQ snext;
+    // Phi of the lane's column, tau 8 g4 .. 8 g4 + 7 of each 32: hi and lo planes
+    half8 fh[NTB], fl[NTB];
     {
-        uint4 p0[2][2];
-        GvScaleQ s0;
-        bwdq_load_phase(p0, pbase, 0, g4, spin_stride, c_stride, g_stride);
-        bwdq_load_scales(s0, Gb, 0, g4);
-        bwdq_stage_g(Ls_G, Gb, 0, tid, wave);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        floatx4 gu[2][2];
+        const uint4* phrow = (const uint4*)(PhTsp + rate.phioff * 2 + ((int64_t)t * (NTp / 8) + g4) * 16);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) gu[k & 1][k >> 1] = bwdq_gu(Ls_G, g4, j16, k & 1, k >> 1, fh, fl);
-#pragma unroll
-        for (int uu = 0; uu < 4; ++uu) bwdq_modadj(uu >> 1, uu & 1, gu, s0, c0, p0, bh, bl);
+        for (int n = 0; n < NTB; ++n) { fh[n] = as_h8(phrow[8 * n]); fl[n] = as_h8(phrow[8 * n + 1]); }
     }
-    __syncthreads();                                  // every wave is done with chunk 0's gV rows
-    bwdq_load_phase(pnext, pbase, one, g4, spin_stride, c_stride, g_stride);
-    bwdq_load_scales(snext, Gb, one, g4);
-    bwdq_stage_g(Ls_G, Gb, one, tid, wave);
-    bwdq_stage_half<NI>(Ls_X, Wt, 0, 0, tid, wave);
+    const uint4* Gb = Gs + b * gs_bstride + (int64_t)alpha * (Mp / 32) * gvs_chunk<NTB>();
+    const uint4* Wt = (const uint4*)Wf;
+    const int64_t spin_stride = (int64_t)Tp * Mp, c_stride = (int64_t)Tp * 32;
+    // the lane's phase rows 16 role + 4 g4 ..: row group 2 role + g4 / 2 of 8, its half g4 % 2
+    const unsigned* pcol = phase + b * ph_bstride + rate.phase_off + (int64_t)(2 * role + (g4 >> 1)) * Tp * 8 +
+                           (int64_t)t * 8 + 4 * (g4 & 1);
+    auto tile_of = [&](int it) { return it < f.nD ? it : f.t0 + it - f.nD; };
+    // scale of the second row of a pair: negated for D waves (their operands are the S
+    // waves' with the second row's sign reversed) and in the odd passes
+    auto c1_of = [&](int it) { return (it < f.nD) != (role != 0) ? c0 : -c0; };
+
+    half8 bh[4], bl[4];
+    uint4 own[4], other[4], pv[2][2];
+    floatx4 gu[2][2];
+    auto send = [&]() {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Ls_E[(wave * 4 + q) * 64 + lane] = other[q];
+    };
+    auto receive = [&]() {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint4 r = Ls_E[((wave ^ 4) * 4 + q) * 64 + lane];
+            bh[q] = as_h8(make_uint4(own[q].x, own[q].y, r.x, r.y));
+            bl[q] = as_h8(make_uint4(own[q].z, own[q].w, r.z, r.w));
+        }
+    };
+    const int one = 1 < f.nI ? 1 : 0;
+    // operands of the first pass; then the gV rows of the second into G and the first
+    // half of the first pass's coefficients into X
+    bwdf_load_phase(pv, pcol, tile_of(0), spin_stride, c_stride);
+    bwdf_stage_g<NTB>(Ls_G, Gb, tile_of(0), tid, wave);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        gu[k >> 1][k & 1] = bwdf_gu<NTB>(Ls_G + (k >> 1) * gvs_chunk<NTB>(), g4, j16, k & 1, role, fh, fl,
+                                         k >> 1 ? c1_of(0) : c0);
+    bwdf_modadj(0, gu, pv, own, other);
+    bwdf_modadj(1, gu, pv, own, other);
+    send();
+    __syncthreads();                                  // every wave is done with G
+    bwdf_stage_g<NTB>(Ls_G, Gb, tile_of(one), tid, wave);
+    bwdf_stage<NX * 4>(Ls_X, Wt, tid, wave);
+    receive();
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    for (int c = 0; c < nC; ++c) {
-        const int c1 = c + 1 < nC ? c + 1 : nC - 1, c2 = c + 2 < nC ? c + 2 : nC - 1;
-        uint4 pfree[2][2];
-        GvScaleQ sfree;
-        half8 nh[4], nl[4];
-        floatx4 gu[2][2];
-        bwdq_stage_half<NI>(Ls_Y, Wt, c, 1, tid, wave);
-        bwdq_load_phase(pfree, pbase, c2, g4, spin_stride, c_stride, g_stride);
-        bwdq_half<NI, 0, true>(Ls_X, Ls_G, lane, g4, j16, fh, fl, c0, bh, bl, nh, nl, pnext, snext, gu, gyr, gyi);
+    for (int it = 0; it < f.nI; ++it) {
+        const int i1 = it + 1 < f.nI ? it + 1 : f.nI - 1, i2 = it + 2 < f.nI ? it + 2 : f.nI - 1;
+        const float c1 = c1_of(i1);
+        if constexpr (NY > 0) bwdf_stage<NY * 4>(Ls_Y, Wt + ((int64_t)it * (NX + NY) + NX) * 256, tid, wave);
+        bwdf_load_phase(pv, pcol, tile_of(i1), spin_stride, c_stride);
+        bwdf_half<NTB, NS, 0, H1, true, false>(Ls_X + role * (H1 * 256) + lane, Ls_G, role, g4, j16, fh, fl, c0, c1, bh,
+                                               bl, gu, pv, own, other, gr, gi);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        bwdq_stage_half<NI>(Ls_X, Wt, c1, 0, tid, wave);
-        bwdq_stage_g(Ls_G, Gb, c2, tid, wave);
-        bwdq_load_scales(sfree, Gb, c2, g4);
-        bwdq_half<NI, NI, false>(Ls_Y, Ls_G, lane, g4, j16, fh, fl, c0, bh, bl, nh, nl, pnext, snext, gu, gyr, gyi);
+        bwdf_stage<NX * 4>(Ls_X, Wt + (int64_t)i1 * (NX + NY) * 256, tid, wave);
+        bwdf_stage_g<NTB>(Ls_G, Gb, tile_of(i2), tid, wave);
+        bwdf_half<NTB, NS, H1, H2, false, SHORT>(Ls_Y + role * (H2 * 256) + lane, Ls_G, role, g4, j16, fh, fl, c0, c1,
+                                                 bh, bl, gu, pv, own, other, gr, gi);
+        send();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(nh[q]), "+v"(nl[q]));
+        for (int q = 0; q < 4; ++q)
+            asm volatile("" : "+v"(own[q].x), "+v"(own[q].y), "+v"(own[q].z), "+v"(own[q].w));
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { bh[q] = nh[q]; bl[q] = nl[q]; }
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) { pnext[s2][0] = pfree[s2][0]; pnext[s2][1] = pfree[s2][1]; }
-        snext = sfree;
+        receive();
     }
-    const float inv = 1.f / (sw * spq);
+    // D passes through LDS, four tiles at a time; the S waves form gY[i] = (S + D) / 2
+    // and gY[c2 - i] = (S - D) / 2
+    const float inv = 0.5f / (sf * spq);
     float2* o = gY + b * gy_bstride + rate.yoff;
+    __syncthreads();                                  // every wave has read the last exchange
 #pragma unroll
-    for (int it = 0; it < NQ; ++it)
+    for (int k0 = 0; k0 < NS; k0 += 4) {
+        if (role) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = 16 * it + 4 * g4 + r;
-            if (i < Kp) o[(int64_t)i * Tp + t] = make_float2(gyr[it][r] * inv, gyi[it][r] * inv);
+            for (int k = k0; k < k0 + 4 && k < NS; ++k) {
+                Ls_E[((wave & 3) * 8 + 2 * (k - k0)) * 64 + lane] = __builtin_bit_cast(uint4, gr[k]);
+                Ls_E[((wave & 3) * 8 + 2 * (k - k0) + 1) * 64 + lane] = __builtin_bit_cast(uint4, gi[k]);
+            }
         }
+        __syncthreads();
+        if (!role) {
+#pragma unroll
+            for (int k = k0; k < k0 + 4 && k < NS; ++k) {
+                const floatx4 dr = __builtin_bit_cast(floatx4, Ls_E[(wave * 8 + 2 * (k - k0)) * 64 + lane]);
+                const floatx4 di = __builtin_bit_cast(floatx4, Ls_E[(wave * 8 + 2 * (k - k0) + 1) * 64 + lane]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = 16 * k + 4 * g4 + r, im = f.c2 - i;
+                    if (2 * i > f.c2) continue;
+                    if (i < n1) o[(int64_t)i * Tp + t] = make_float2((gr[k][r] + dr[r]) * inv, (gi[k][r] + di[r]) * inv);
+                    if (im < n1 && im != i)
+                        o[(int64_t)im * Tp + t] = make_float2((gr[k][r] - dr[r]) * inv, (gi[k][r] - di[r]) * inv);
+                }
+            }
+        }
+        __syncthreads();
+    }
 }
 
 }  // namespace jtfs
@@ -1835,7 +1591,6 @@ using namespace jtfs;
 namespace jtfs {
 
 size_t split_fwd_lds(const Shapes& s, bool with_phase);
-int bwdp_max_ni(int NTp);
 
 bool split_supported(const Shapes& s) { return split_fwd_lds(s, false) <= (size_t)kMaxDynLds && s.NTp <= 64; }
 
@@ -1898,13 +1653,15 @@ int build_split_tables(jtfs_plan* P, std::vector<void*>& owned) {
         hipLaunchKernelGGL(k_phtsplit, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, P->Phi + s.phioff[a],
                            s.Tp[a], s.NTp, P->sphi[a], P->PhTsp + s.phioff[a] * 2);
     }
-    if (s.NTp == 32) {
-        // the W^T operand of the 16 x 16-tile stored-phase backward
-        P->WTq = (unsigned short*)alloc(sizeof(float2) * (size_t)P->KpT * s.Mp);
-        if (!P->WTq) { set_error("device allocation failed"); return JTFS_ENOMEM; }
-        const int64_t n = (int64_t)P->KpT * s.Mp;
-        hipLaunchKernelGGL(k_wtqsplit, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, P->Wl, s.Mp, s.Kp, P->KpT,
-                           P->sw, P->WTq);
+    P->split_bwdp_ok = split_fwd_lds(s, true) <= (size_t)kMaxDynLds;
+    if (P->split_bwdp_ok) {
+        // the folded coefficients of the stored-phase backward
+        const FoldPlan& f = s.fold;
+        const int64_t n = (int64_t)f.nI * (2 * f.NS - f.shortD) * 512;
+        P->Wf = (unsigned short*)alloc(sizeof(unsigned short) * 4 * n);
+        if (!P->Wf) { set_error("device allocation failed"); return JTFS_ENOMEM; }
+        hipLaunchKernelGGL(k_wfold, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, P->psi_fr, s.L, P->d_slot_beta,
+                           P->d_slot_l, P->d_kfr, f, 0.5f * P->sw, P->Wf);
     }
     if (s.NTp == 32) {
         // the W and lowpass operands of the 16 x 16-tile forward
@@ -1928,10 +1685,8 @@ int build_split_tables(jtfs_plan* P, std::vector<void*>& owned) {
         // recomputing backward: static LDS of a W chunk and two W^T chunks, 24 NI KB
         // (<= 160 KB), and one wave per SIMD without scratch
         P->split_bwd_ok = (s.NTp == 32 && NI <= 6) || (s.NTp == 64 && NI <= 5);
-        // stored-phase backward: two W^T chunks (16 NI KB) per launch, at most two
-        // launches over halves of the i-blocks; the forward must hold its phase
-        // transpose area beside the resident W tile
-        P->split_bwdp_ok = NI <= 2 * bwdp_max_ni(s.NTp) && split_fwd_lds(s, true) <= (size_t)kMaxDynLds;
+        // (the stored-phase backward holds whatever the forward holds with its phase
+        // transpose area beside the resident W tile: n1 <= 288, so NS <= kMaxFoldNS)
     }
     P->contraction = JTFS_CONTRACTION_SPLIT_F16;
     return JTFS_OK;
@@ -2100,36 +1855,6 @@ int launch_freq_bwd_split(const jtfs_plan* P, const unsigned short* Yh, const fl
     return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
 }
 
-// i-blocks one phase-backward workgroup holds in registers without scratch
-// (one wave per SIMD): 8 at 32 frames, 5 at 64
-int bwdp_max_ni(int NTp) { return NTp == 32 ? 8 : NTp == 64 ? 5 : 0; }
-
-template <int NTB>
-static void launch_bwdp_ni(int NI, int q_base, int nit, dim3 grid, hipStream_t st, const unsigned* phase, int64_t phb,
-                           int nT, const jtfs_plan* P, const uint4* Gs, int64_t gsb, const float* gvmax, float2* gY) {
-    const Shapes& s = P->s;
-    const int64_t yb = (int64_t)s.Kp * s.sumTp;
-#define JTFS_BWDP_CASE(ni)                                                                                       \
-    case ni:                                                                                                     \
-        hipLaunchKernelGGL((k_freq_bwd_p<NTB, ni>), grid, dim3(256), 0, st, phase, phb, P->d_rates, P->d_tiles, \
-                           nT, (int)grid.x, P->WTsp, q_base, nit, s.Mp, s.Kp, P->PhTsp, Gs, gsb, gvmax,          \
-                           s.n_beta, s.n_alpha, P->sw, gY, yb);                                                  \
-        break;
-    if constexpr (NTB == 1) {
-        switch (NI) {
-            JTFS_BWDP_CASE(1) JTFS_BWDP_CASE(2) JTFS_BWDP_CASE(3) JTFS_BWDP_CASE(4)
-            JTFS_BWDP_CASE(5) JTFS_BWDP_CASE(6) JTFS_BWDP_CASE(7) JTFS_BWDP_CASE(8)
-            default: break;
-        }
-    } else {
-        switch (NI) {
-            JTFS_BWDP_CASE(1) JTFS_BWDP_CASE(2) JTFS_BWDP_CASE(3) JTFS_BWDP_CASE(4) JTFS_BWDP_CASE(5)
-            default: break;
-        }
-    }
-#undef JTFS_BWDP_CASE
-}
-
 int launch_gv_split(const jtfs_plan* P, const float* gV, uint4* Gs, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int64_t nrows = B * s.n_alpha * 2 * (int64_t)s.Mp;
@@ -2142,51 +1867,41 @@ int launch_gv_split(const jtfs_plan* P, const float* gV, uint4* Gs, int64_t B, h
     return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
 }
 
-bool bwdq_supported(const jtfs_plan* P) {
-    const int NI = P->KpT / 32;
-    return P->WTq && P->s.NTp == 32 && NI >= 1 && NI <= 9;          // LDS: two W^T chunks of NI x 8 KB
-}
-
-template <int NI = 1>
-static void launch_bwdq_ni(int ni, unsigned nU, hipStream_t st, const unsigned* phase, int64_t phb, int nT,
-                           const jtfs_plan* P, const uint4* Gs, int64_t gsb, const float* gvmax, float2* gY) {
-    if constexpr (NI <= 9) {
-        if (ni != NI) {
-            launch_bwdq_ni<NI + 1>(ni, nU, st, phase, phb, nT, P, Gs, gsb, gvmax, gY);
+template <int NTB, int NS = 1>
+static void launch_bwdf_ns(dim3 grid, hipStream_t st, const unsigned* phase, int64_t phb, int nT, const jtfs_plan* P,
+                           const uint4* Gs, int64_t gsb, const float* gvmax, float2* gY) {
+    if constexpr (NS <= kMaxFoldNS) {
+        const Shapes& s = P->s;
+        if (s.fold.NS != NS) {
+            launch_bwdf_ns<NTB, NS + 1>(grid, st, phase, phb, nT, P, Gs, gsb, gvmax, gY);
             return;
         }
-        const Shapes& s = P->s;
-        hipLaunchKernelGGL((k_freq_bwd_q<NI>), dim3(nU), dim3(256), 0, st, phase, phb, P->d_rates, P->d_tiles, nT,
-                           (int)nU, P->WTq, s.Mp, s.Kp, P->PhTsp, Gs, gsb, gvmax, s.n_beta, s.n_alpha, P->sw, gY,
-                           (int64_t)s.Kp * s.sumTp);
+        const int64_t yb = (int64_t)s.Kp * s.sumTp;
+        if constexpr (NS > 1) {
+            if (s.fold.shortD) {
+                hipLaunchKernelGGL((k_freq_bwd_f<NTB, NS, true>), grid, dim3(512), 0, st, phase, phb, P->d_rates,
+                                   P->d_tiles, nT, (int)grid.x, P->Wf, s.fold, s.Mp, s.n1, P->PhTsp, Gs, gsb, gvmax,
+                                   s.n_beta, s.n_alpha, 0.5f * P->sw, gY, yb);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_freq_bwd_f<NTB, NS, false>), grid, dim3(512), 0, st, phase, phb, P->d_rates, P->d_tiles,
+                           nT, (int)grid.x, P->Wf, s.fold, s.Mp, s.n1, P->PhTsp, Gs, gsb, gvmax, s.n_beta, s.n_alpha,
+                           0.5f * P->sw, gY, yb);
     }
 }
 
 int launch_freq_bwd_phase(const jtfs_plan* P, const unsigned* phase, int64_t ph_bstride, const uint4* Gs,
                           int64_t gs_bstride, const float* gvmax, float2* gY2, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
-    const int NI = P->KpT / 32;
+    if (!P->split_bwdp_ok || s.fold.NS > kMaxFoldNS) {
+        set_error("stored-phase backward not available for these shapes"); return JTFS_ENOTSUP; }
     const int nT = (int)(s.sumTp / kTileTh);
-    if (P->tune.bwd16 && bwdq_supported(P)) {
-        JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st,
-                   launch_bwdq_ni(NI, (unsigned)(B * nT * 2), st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2));
-        return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
-    }
-    if (!P->split_bwdp_ok) { set_error("stored-phase backward not available for these shapes"); return JTFS_ENOTSUP; }
-    // one launch per range of i-blocks: a single one up to the register budget, else
-    // two balanced halves
-    const int nmax = bwdp_max_ni(s.NTp);
-    const int ng = NI <= nmax ? 1 : 2;
-    const int nia = (NI + ng - 1) / ng;
-    const dim3 grid((unsigned)(B * nT));
-    for (int g = 0, q0 = 0; g < ng; ++g) {
-        const int ni = g == 0 ? nia : NI - nia;
-        switch (s.NTp / 32) {
-            case 1: JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st, launch_bwdp_ni<1>(ni, q0, NI, grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2)); break;
-            case 2: JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st, launch_bwdp_ni<2>(ni, q0, NI, grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2)); break;
-            default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
-        }
-        q0 += ni;
+    const dim3 grid((unsigned)(B * nT * 2));
+    switch (s.NTp / 32) {
+        case 1: launch_bwdf_ns<1>(grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
+        case 2: launch_bwdf_ns<2>(grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
+        default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
     }
     return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
 }
