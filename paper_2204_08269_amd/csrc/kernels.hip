@@ -690,37 +690,67 @@ __global__ void __launch_bounds__(256) k_v_out(const float* __restrict__ Vp, int
 }
 
 // Time scattering (sec. 4): S2[b][alpha][lambda][tau] = sum_t |Y2[b][alpha][lambda][t]| Phi_alpha[t][tau]
-// (modulus of the second-order row, then the time lowpass on the N/T frames).
-// Threads are (tau, t-group) pairs; |Y2| of 256 samples at a time goes through LDS.
-__global__ void __launch_bounds__(256) k_ts_out(const float2* __restrict__ Y, int64_t y_bstride, int Tp, int Ta,
-                                                const float* __restrict__ Phi, int NTp, int NT, int alpha,
-                                                int n_alpha, float* __restrict__ S2, const float* __restrict__ mu2,
-                                                float eps) {
-    __shared__ float mag[256];
-    __shared__ float part[256];
-    const int lam = blockIdx.x, n1 = gridDim.x;
+// (modulus of the second-order row, then the time lowpass on the N/T frames) as a
+// product on the FP32 matrix cores: 32 rows lambda by 32 NTB frames a workgroup,
+// sixteen waves sharing the columns t, their partial sums added in wave order at
+// the end.  Every rate in one launch, grid (ceil(n1 / 32), B, n_alpha), the longest
+// rates first.  A workgroup reads Phi_alpha once for its 32 rows (a workgroup per
+// row had read it from L2 for each: 8 x 2^16 2.36 -> 0.25 ms, whose bytes take 0.11).
+template <int NTB>
+__global__ void __launch_bounds__(1024) k_ts_out(const float2* __restrict__ Y, int64_t y_bstride,
+                                                 const FreqRate* __restrict__ rates, const float* __restrict__ Phi,
+                                                 int n1, int NT, int n_alpha, float* __restrict__ S2,
+                                                 const float* __restrict__ mu2, float eps) {
+    constexpr int NTp = 32 * NTB;
+    __shared__ float red[16 * 1024];
+    const int alpha = blockIdx.z, r0 = 32 * (int)blockIdx.x;
     const int64_t b = blockIdx.y;
-    const float2* row = Y + b * y_bstride + (int64_t)lam * Tp;
-    const int tau = threadIdx.x % NTp, g = threadIdx.x / NTp, G = blockDim.x / NTp;
-    float acc = 0.f;
-    for (int t0 = 0; t0 < Ta; t0 += 256) {
-        __syncthreads();
-        const int t = t0 + threadIdx.x;
-        if (t < Ta) {
-            const float2 y = row[t];
-            mag[threadIdx.x] = sqrtf(y.x * y.x + y.y * y.y);
+    const FreqRate rate = rates[alpha];
+    const int Tp = rate.Tp;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, i32 = lane & 31;
+    const float4* row = (const float4*)(Y + b * y_bstride + rate.yoff + (int64_t)min(r0 + i32, n1 - 1) * Tp);
+    const float* ph = Phi + rate.phioff + i32;
+    floatx16 acc[NTB];
+#pragma unroll
+    for (int n = 0; n < NTB; ++n) acc[n] = zero16();
+    // per wave eight columns t of each 128; lane half h holds columns 2 h, 2 h + 1 of every four
+#pragma unroll 4
+    for (int t0 = 8 * wave; t0 < Tp; t0 += 128) {
+        float4 y[2];
+        float p[2][2][NTB];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int t = t0 + 4 * q + 2 * h;
+            y[q] = row[t >> 1];
+#pragma unroll
+            for (int n = 0; n < NTB; ++n) {
+                p[q][0][n] = ph[(int64_t)t * NTp + 32 * n];
+                p[q][1][n] = ph[(int64_t)(t + 1) * NTp + 32 * n];
+            }
         }
-        __syncthreads();
-        const int n = min(256, Ta - t0);
-        for (int j = g; j < n; j += G) acc += mag[j] * Phi[(int64_t)(t0 + j) * NTp + tau];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float u0 = sqrtf(y[q].x * y[q].x + y[q].y * y[q].y), u1 = sqrtf(y[q].z * y[q].z + y[q].w * y[q].w);
+#pragma unroll
+            for (int n = 0; n < NTB; ++n) {
+                acc[n] = mfma32(u0, p[q][0][n], acc[n]);
+                acc[n] = mfma32(u1, p[q][1][n], acc[n]);
+            }
+        }
     }
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    if (g == 0 && tau < NT) {
-        float s = 0.f;
-        for (int q = 0; q < G; ++q) s += part[q * NTp + tau];
-        S2[((b * n_alpha + alpha) * n1 + lam) * (int64_t)NT + tau] =
-            mulog_out(s, mu2, mulog_inv(mu2, alpha * n1 + lam, eps));
+#pragma unroll
+    for (int n = 0; n < NTB; ++n) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[wave * 1024 + r * 64 + lane] = acc[n][r];
+        __syncthreads();
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) sum += red[w * 1024 + tid];
+        const int lam = r0 + crow(tid >> 6, h), tau = 32 * n + i32;      // register tid / 64 of lane tid % 64
+        if (lam < n1 && tau < NT)
+            S2[((b * n_alpha + alpha) * n1 + lam) * (int64_t)NT + tau] =
+                mulog_out(sum, mu2, mulog_inv(mu2, alpha * n1 + lam, eps));
     }
 }
 
@@ -728,34 +758,49 @@ __global__ void __launch_bounds__(256) k_ts_out(const float2* __restrict__ Y, in
 // Backward.
 // ---------------------------------------------------------------------------
 
-// Time scattering adjoint: gY2[t] = (sum_tau gS2[tau] Phi_alpha[t][tau]) y_t / max(|y_t|, eps)
-// for t < Ta, zero for Ta <= t < Tp (rows lambda < n1).
-__global__ void __launch_bounds__(256) k_ts_bwd(const float2* __restrict__ Y, int64_t y_bstride, int Tp, int Ta,
-                                                const float* __restrict__ Phi, int NTp, int NT, int alpha,
-                                                int n_alpha, const float* __restrict__ gS2, float2* __restrict__ gY,
-                                                MuLogArg ml) {
-    __shared__ float gs[128];
-    const int lam = blockIdx.x, n1 = gridDim.x;
-    const int64_t b = blockIdx.y;
+// Time scattering adjoint: gY2[t] = (sum_tau gS2[tau] Phi_alpha[t][tau]) y_t / max(|y_t|, eps),
+// zero for Ta <= t < Tp where Phi and y are (rows lambda < n1).  The sum runs on the
+// FP32 matrix cores: 32 rows by 128 columns t a workgroup, a wave 32 columns, whose
+// Phi rows it reads once for the 32 rows.  Every rate in one launch, grid (tiles of
+// 128 columns, ceil(n1 / 32), B).  8 x 2^16: 1.67 -> 0.34 ms, whose bytes take 0.22.
+template <int NTB>
+__global__ void __launch_bounds__(256) k_ts_bwd(const float2* __restrict__ Y, int64_t y_bstride,
+                                                const FreqRate* __restrict__ rates, const FreqUnit* __restrict__ tiles,
+                                                const float* __restrict__ Phi, int n1, int NT, int n_alpha,
+                                                const float* __restrict__ gS2, float2* __restrict__ gY, MuLogArg ml) {
+    constexpr int NTp = 32 * NTB;
+    const FreqUnit un = tiles[blockIdx.x];
+    const FreqRate rate = rates[un.alpha];
+    const int alpha = un.alpha, r0 = 32 * (int)blockIdx.y;
+    const int64_t b = blockIdx.z;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, i32 = lane & 31;
+    const int t = un.t0 + 32 * wave + i32;
+    const int lam = r0 + i32;                        // this lane's row of the cotangent
     const int64_t so = ((b * n_alpha + alpha) * n1 + lam) * (int64_t)NT;
-    const float* src = gS2 ? gS2 + so : nullptr;
-    const float em = ml.mu2 ? ml.eps * ml.mu2[alpha * n1 + lam] : 0.f;
-    for (int i = threadIdx.x; i < NTp; i += blockDim.x)
-        gs[i] = (src && i < NT) ? mulog_cot(src[i], ml.mu2, em, ml.mu2 ? ml.o2[so + i] : 0.f) : 0.f;
-    __syncthreads();
-    const float2* row = Y + b * y_bstride + (int64_t)lam * Tp;
-    float2* out = gY + b * y_bstride + (int64_t)lam * Tp;
-    for (int t = threadIdx.x; t < Tp; t += blockDim.x) {
-        float2 r = make_float2(0.f, 0.f);
-        if (t < Ta) {
-            const float* ph = Phi + (int64_t)t * NTp;
-            float gu = 0.f;
-            for (int tau = 0; tau < NT; ++tau) gu += gs[tau] * ph[tau];
-            const float2 y = row[t];
-            const float sc = gu / fmaxf(sqrtf(y.x * y.x + y.y * y.y), kEpsMod);
-            r = make_float2(y.x * sc, y.y * sc);
+    const float em = ml.mu2 && lam < n1 ? ml.eps * ml.mu2[alpha * n1 + lam] : 0.f;
+    const float4* ph = (const float4*)(Phi + rate.phioff + (int64_t)t * NTp);
+    floatx16 gu = zero16();
+#pragma unroll
+    for (int q = 0; q < 4 * NTB; ++q) {              // lane half h holds frames 8 q + 4 h .. + 3
+        const float4 p4 = ph[2 * q + h];
+        const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int tau = 8 * q + 4 * h + j;
+            const bool in = gS2 && lam < n1 && tau < NT;
+            const float g = in ? mulog_cot(gS2[so + tau], ml.mu2, em, ml.mu2 ? ml.o2[so + tau] : 0.f) : 0.f;
+            gu = mfma32(g, p[j], gu);
         }
-        out[t] = r;
+    }
+    const float2* y_ = Y + b * y_bstride + rate.yoff + t;
+    float2* out = gY + b * y_bstride + rate.yoff + t;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = r0 + crow(r, h);
+        if (row >= n1) continue;
+        const float2 y = y_[(int64_t)row * rate.Tp];
+        const float sc = gu[r] / fmaxf(sqrtf(y.x * y.x + y.y * y.y), kEpsMod);
+        out[(int64_t)row * rate.Tp] = make_float2(y.x * sc, y.y * sc);
     }
 }
 
@@ -1437,10 +1482,11 @@ int forward_impl(const jtfs_plan* P, const float* x, int64_t B, float* s1, float
     float2* Y2 = (float2*)(base + w.Y2);
     float* Vp = (float*)(base + w.Vp);
     const int nlt = s.Mp / kTileL;
-    for (int a = 0; a < s.n_alpha && s.tscat; ++a) {
-        JTFS_TIMED(JTFS_STAGE_FREQ_FWD, st, hipLaunchKernelGGL(k_ts_out, dim3(s.n1, (unsigned)B), dim3(256), 0, st, Y2 + s.yoff[a],
-                           (int64_t)s.Kp * s.sumTp, s.Tp[a], s.Ta[a], P->Phi + s.phioff[a], s.NTp, s.NT, a,
-                           s.n_alpha, s2, ml.mu2, ml.eps));
+    if (s.tscat) {
+        // every temporal rate in one launch (N/T <= 128: one, two or four blocks of 32 frames)
+        auto k = s.NTp == 32 ? k_ts_out<1> : s.NTp == 64 ? k_ts_out<2> : k_ts_out<4>;
+        JTFS_TIMED(JTFS_STAGE_FREQ_FWD, st, hipLaunchKernelGGL(k, dim3((unsigned)((s.n1 + 31) / 32), (unsigned)B, (unsigned)s.n_alpha), dim3(1024), 0, st,
+                           Y2, (int64_t)s.Kp * s.sumTp, P->d_rates, P->Phi, s.n1, s.NT, s.n_alpha, s2, ml.mu2, ml.eps));
         LAUNCHCHK("time-scattering lowpass");
     }
     const bool split = P->contraction != JTFS_CONTRACTION_FP32 && !s.tscat;
@@ -1548,10 +1594,10 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
     const int64_t yb = (int64_t)s.Kp * s.sumTp;
     const int nlt = s.Mp / kTileL;
     // time scattering: the lowpass and modulus adjoints give gY2 directly
-    for (int a = 0; a < s.n_alpha && s.tscat; ++a) {
-        JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k_ts_bwd, dim3(s.n1, (unsigned)B), dim3(256), 0, st, Y2 + s.yoff[a],
-                           yb, s.Tp[a], s.Ta[a], P->Phi + s.phioff[a], s.NTp, s.NT, a, s.n_alpha, gs2,
-                           gY2 + s.yoff[a], ml));
+    if (s.tscat) {
+        auto k = s.NTp == 32 ? k_ts_bwd<1> : s.NTp == 64 ? k_ts_bwd<2> : k_ts_bwd<4>;
+        JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k, dim3((unsigned)(s.sumTp / kTileTh), (unsigned)((s.n1 + 31) / 32), (unsigned)B), dim3(256), 0, st,
+                           Y2, yb, P->d_rates, P->d_tiles, P->Phi, s.n1, s.NT, s.n_alpha, gs2, gY2, ml));
         LAUNCHCHK("time-scattering adjoint");
     }
     if (!s.tscat) {

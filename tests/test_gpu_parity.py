@@ -1051,3 +1051,27 @@ def test_folded_stored_phase_gradient(p):
     for b in range(3):
         check_paths(s1[b].detach().cpu().numpy(), s2[b].detach().cpu().numpy(), *O.jtfs(x[b].astype(np.float64), P))
         assert rel_l2(gx[b].cpu().numpy(), O.jtfs_vjp(x[b].astype(np.float64), gs1[b], gs2[b], P)) <= TOL_VJP
+
+
+@pytest.mark.parametrize("T", [4096, 256, 64, 32], ids=lambda T: f"{4096 // T}_frames")
+def test_time_scattering_frame_counts(T):
+    """1, 16, 64 and 128 frames (one, two and four blocks of 32; n1 = 56 leaves a ragged block of rows): the lowpass
+    is a sum of at most 2^11 positive FP32 products, its adjoint one of 2^7, so TOL and TOL_VJP hold with room; a null
+    second-order cotangent counts as zero."""
+    p = dict(N=4096, J=7, Q=(9, 1), J_fr=3, Q_fr=1, T=T, F=4)
+    P = oracle_plan(p)
+    x = synth.batch(5, B=2, N=4096)
+    op = gpu_op(p, time_scattering=True)
+    s1, s2 = run_forward(op, x)
+    g1, g2 = synth.cotangents(s1.shape, s2.shape, seed=5)
+    xt = torch.from_numpy(x).cuda()
+    gx = op.vjp(xt, torch.from_numpy(g1).cuda(), torch.from_numpy(g2).cuda()).cpu().numpy()
+    g0 = op.vjp(xt, torch.from_numpy(g1).cuda(), None).cpu().numpy()
+    for b in range(2):
+        xb = x[b].astype(np.float64)
+        r1, r2 = O.scattering1d(xb, P)
+        e1, _ = path_errors(s1[b], r1, 1)
+        e2, _ = path_errors(s2[b], r2, 1)
+        assert e1.max() <= TOL and e2.max() <= TOL
+        assert rel_l2(gx[b], O.scattering1d_vjp(xb, g1[b], g2[b], P)) <= TOL_VJP
+        assert rel_l2(g0[b], O.scattering1d_vjp(xb, g1[b], np.zeros_like(g2[b]), P)) <= TOL_VJP
