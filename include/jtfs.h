@@ -373,7 +373,7 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * zeros), one untimed and `reps` timed fwd+bwd steps per candidate: each
  * available contraction mode, once with all four stages register-resident and
  * 32 x 32 contraction tiles and once with all four in LDS and 16 x 16 tiles in
- * the forward and the stored-phase backward (where these choices exist).  It
+ * the forward (where these choices exist).  It
  * keeps the contraction whose own stages took least time (each contraction
  * kernel with its faster tile), per stage the faster transform, and the faster
  * tiles, then times the result (step_ms).  With the
@@ -403,10 +403,11 @@ void jtfs_texture_destroy(jtfs_texture* tex);
 #define JTFS_REG_ROW_FFT      4
 #define JTFS_REG_FIRST_ADJ    8
 /* In the same mask: the split forward contraction in 16 x 16 MFMA tiles (each
- * wave 64 rows l x 16 columns t; available where N/T <= 32), else 32 x 32 tiles. */
+ * wave 64 rows l x 16 columns t; available where N/T <= 32), else 32 x 32 tiles.
+ * Until launch choices are set or tuned, a plan takes the tile by a rule on its shapes. */
 #define JTFS_TUNE_FWD_TILE16  16
-/* ... and the stored-phase backward in 16 x 16 tiles (each wave 16 columns t and
- * all rows i, one pass for any K; N/T <= 32), else 32 x 32 tiles. */
+/* ... accepted and reported back, without effect: the stored-phase backward has one
+ * kernel (16 x 16 tiles, folded along log-frequency) for every shape. */
 #define JTFS_TUNE_BWD_TILE16  32
 /* ... the largest radix of the register-resident row transforms' passes, per
  * stage: radix 8 where the bit is set, else radix 16 (every pass of a 2^14-point

@@ -44,6 +44,7 @@ void set_rows(jtfs_plan* P, int mask) {
     P->tune.reg_second = (mask & JTFS_REG_SECOND_ORDER) != 0;
     P->tune.reg_rowfft = (mask & JTFS_REG_ROW_FFT) != 0;
     P->tune.reg_first_adj = (mask & JTFS_REG_FIRST_ADJ) != 0;
+    P->tune.fwd_auto = false;
     P->tune.fwd16 = (mask & JTFS_TUNE_FWD_TILE16) != 0;
     P->tune.bwd16 = (mask & JTFS_TUNE_BWD_TILE16) != 0;
     P->tune.r8_scalogram = (mask & JTFS_TUNE_RADIX8_SCALOGRAM) != 0;
@@ -64,7 +65,10 @@ constexpr int kRadix8Bits = JTFS_TUNE_RADIX8_SCALOGRAM | JTFS_TUNE_RADIX8_SECOND
 int get_rows(const jtfs_plan* P) {
     return (P->tune.reg_scalogram ? JTFS_REG_SCALOGRAM : 0) | (P->tune.reg_second ? JTFS_REG_SECOND_ORDER : 0) |
            (P->tune.reg_rowfft ? JTFS_REG_ROW_FFT : 0) | (P->tune.reg_first_adj ? JTFS_REG_FIRST_ADJ : 0) |
-           (P->tune.fwd16 ? JTFS_TUNE_FWD_TILE16 : 0) | (P->tune.bwd16 ? JTFS_TUNE_BWD_TILE16 : 0) |
+           ((P->tune.fwd_auto ? fwd_tile16(P, P->contraction == JTFS_CONTRACTION_SPLIT_F16_PHASE) : P->tune.fwd16)
+                ? JTFS_TUNE_FWD_TILE16
+                : 0) |
+           (P->tune.bwd16 ? JTFS_TUNE_BWD_TILE16 : 0) |
            (P->tune.r8_scalogram ? JTFS_TUNE_RADIX8_SCALOGRAM : 0) |
            (P->tune.r8_second ? JTFS_TUNE_RADIX8_SECOND_ORDER : 0) | (P->tune.r8_rowfft ? JTFS_TUNE_RADIX8_ROW_FFT : 0) |
            (P->tune.r8_first_adj ? JTFS_TUNE_RADIX8_FIRST_ADJ : 0) | (P->tune.batch8k ? JTFS_TUNE_LDS_BATCH8K : 0) |
@@ -190,6 +194,11 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     std::memset(out, 0, sizeof(*out));
     const Shapes& s = P->s;
     const int saved_mode = P->contraction, saved_rows = get_rows(P);
+    const bool saved_auto = P->tune.fwd_auto;
+    auto restore_rows = [&]() {
+        set_rows(P, saved_rows);
+        P->tune.fwd_auto = saved_auto;
+    };
     const std::string key = cache_key(P, B);
     {
         int cm = 0, cr = 0;
@@ -202,7 +211,7 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
             return JTFS_OK;
         }
         P->contraction = saved_mode;
-        set_rows(P, saved_rows);
+        restore_rows();
     }
     // candidates
     std::vector<int> modes;
@@ -240,7 +249,7 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
         jtfs_workspace_size(P, B, &b);
         wsb = std::max(wsb, b);
     }
-    set_rows(P, saved_rows);
+    restore_rows();
     DevBuf ws, s1, s2, gx, xz;
     if (!ws.alloc(wsb) || !s1.alloc(sizeof(float) * B * info.s1_per_signal) ||
         !s2.alloc(sizeof(float) * B * info.s2_per_signal) || !gx.alloc(sizeof(float) * B * s.N)) {
@@ -267,7 +276,7 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
                                      &total[mi][ri], stage[mi][ri]);
             if (rc != JTFS_OK) {
                 P->contraction = saved_mode;
-                set_rows(P, saved_rows);
+                restore_rows();
                 return rc;
             }
             const int slot = (modes[mi] == JTFS_CONTRACTION_FP32             ? 2
@@ -318,7 +327,7 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     set_rows(P, rows);
     auto fail = [&](int rc) {
         P->contraction = saved_mode;
-        set_rows(P, saved_rows);
+        restore_rows();
         return rc;
     };
     // radix of the register-resident passes and points per in-LDS workgroup: one

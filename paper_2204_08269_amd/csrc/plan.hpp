@@ -122,7 +122,8 @@ struct Tuning {
     bool reg_second = true;      // second-order rows of 2^14 points
     bool reg_rowfft = true;      // FFT of the gY2 rows of 2^14 points
     bool reg_first_adj = true;   // first-order adjoint rows of 2^14 points
-    bool fwd16 = false;          // forward contraction in 16 x 16 tiles (else 32 x 32)
+    bool fwd_auto = true;        // tile of the forward contraction by rule (fwd_tile16), until one is set
+    bool fwd16 = false;          // forward contraction in 16 x 16 tiles (else 32 x 32), as set
     bool bwd16 = false;          // (accepted and reported back: the stored-phase backward has one kernel)
     // register-resident rows: radix-8 passes instead of radix-16 ones, per stage
     bool r8_scalogram = false, r8_second = false, r8_rowfft = false, r8_first_adj = false;

@@ -1750,6 +1750,19 @@ bool fwdq_supported(const jtfs_plan* P, bool with_phase) {
            fwdq_lds(s.Kp, ntq, with_phase) <= (size_t)kMaxDynLds;
 }
 
+// The tile that was set, or else the faster one.  A wave of the 16 x 16 kernel loads
+// its Y fragments alone, where two waves of the 32 x 32 one load the same; the latter
+// reads half as much of W from LDS and takes fewer lowpass products.  Measured, 32 x 32
+// and 16 x 16: up to 16 frames 310 and 266 us (7 x 2^14, K = 160), 148 and 134 (3 x
+// 2^15, K = 128), 1641 and 1470 (2^18, K = 288), 1430 and 1426 (4 x 2^17, K = 144); 32
+// frames 193 and 205 (2^16), 1326 and 1396 (8 x 2^16), 11.4 and 13.4 (2^11, K = 48).
+// Below 128 rows or 8192 columns the launch is not what counts, and the tile stays
+// the wide one.  The same in both split modes, whose coefficients agree bit for bit.
+bool fwd_tile16(const jtfs_plan* P, bool with_phase) {
+    if (!fwdq_supported(P, with_phase)) return false;
+    return P->tune.fwd_auto ? P->s.NT <= 16 && P->s.Kp >= 128 && P->s.sumTp >= 8192 : P->tune.fwd16;
+}
+
 template <int NTB, int NK = 1, typename... Args>
 static void launch_fwd_nk(int nk, dim3 grid, size_t lds, hipStream_t st, Args... args) {
     if constexpr (NK <= kMaxFwdNK) {
@@ -1786,7 +1799,7 @@ int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const fl
     if (nk < 1 || nk > kMaxFwdNK) { set_error("K beyond the split contraction's LDS tile"); return JTFS_ENOTSUP; }
     const FreqRate* rt = P->d_rates;
     const FreqUnit* un = cs.d_units;
-    const bool tile16 = P->tune.fwd16 && fwdq_supported(P, phase != nullptr);
+    const bool tile16 = fwd_tile16(P, phase != nullptr);
     const int ntq = (s.NT + 15) / 16;
     const size_t ldsq = fwdq_lds(s.Kp, ntq, phase != nullptr);
     const unsigned short *Wq = P->Wq, *Pq = P->Phq, *Wsp = P->Wsp, *Ph = P->Phsp;

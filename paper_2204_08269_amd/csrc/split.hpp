@@ -27,4 +27,6 @@ int launch_freq_bwd_phase(const jtfs_plan* P, const unsigned* phase, int64_t ph_
 int launch_gv_split(const jtfs_plan* P, const float* gV, uint4* Gs, int64_t B, hipStream_t st);
 // whether the 16 x 16-tile forward contraction handles the plan's shapes
 bool fwdq_supported(const jtfs_plan* P, bool with_phase);
+// whether the forward contraction runs in 16 x 16 tiles
+bool fwd_tile16(const jtfs_plan* P, bool with_phase);
 }  // namespace jtfs

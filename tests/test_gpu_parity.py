@@ -1008,6 +1008,22 @@ def test_forward_chunk_lengths_agree(p):
         assert np.array_equal(c1[0], b1[1]) and np.array_equal(c2[0], b2[1])
 
 
+@pytest.mark.parametrize("p, tile", [(P1, 32), (dict(N=2 ** 15, J=11, Q=(16, 1), J_fr=4, Q_fr=2, T=2 ** 11, F=8), 16),
+                                     (dict(N=2 ** 15, J=11, Q=(16, 1), J_fr=4, Q_fr=2, T=2 ** 10, F=8), 32)],
+                         ids=["small", "frames16", "frames32"])
+def test_forward_tile_by_shapes(p, tile):
+    """The tile that a plan takes by itself, and the other one's coefficients: the same FP32 products, summed over
+    other waves (as across chunk lengths, 2e-6 in norm)."""
+    x = synth.batch(5, B=2, N=p["N"])
+    op = gpu_op(p, "split16")
+    assert op.tuning()[2] == tile
+    a1, a2 = run_forward(op, x)
+    op.set_tuning("split16", ALL_ROWS, fwd_tile=48 - tile)
+    assert op.tuning()[2] == 48 - tile
+    b1, b2 = run_forward(op, x)
+    assert np.array_equal(a1, b1) and rel_l2(b2, a2) <= 2e-6
+
+
 def test_more_short_rates_than_one_launch_holds():
     """71 temporal rates, all transformed in LDS: their second order and row FFTs take three launches (32 rates each)."""
     p = dict(N=2048, J=9, Q=(4, 10), J_fr=2, Q_fr=1, T=64, F=2)
