@@ -597,12 +597,14 @@ __device__ __forceinline__ float sum_slots(const float* __restrict__ v, int64_t 
 
 // Frequency lowpass (eq. (3)): S2[b][alpha][beta][theta][m][tau] =
 // sum_l PF_beta[m][l] V[theta][rowoff + l][tau], V summed over the partial slots
-// of the contraction's t-chunks.  grid (n_beta, 2 n_alpha, B), every temporal rate
-// in one launch.  The l axis runs in chunks of 64: the chunk's V (64 x TT columns
-// tau, its partial slots summed on the way in) and its rows of PF^T (64 x 32 rows
-// m, from the transposed table PFt) are staged in LDS, and each thread adds its
-// TT / 8 outputs (rows m of one tau) over the chunk, l in order.  Rows m beyond 32
-// and columns beyond TT take further passes.
+// of the contraction's t-chunks.  grid (n_beta ceil(NT / TT), 2 n_alpha, B), every
+// temporal rate in one launch.  The l axis runs in chunks of 64: the chunk's V (64 x
+// TT columns tau, its partial slots summed on the way in) and its rows of PF^T (64 x
+// 32 rows m, from the transposed table PFt) are staged in LDS, and each thread adds
+// its TT / 8 outputs (rows m of one tau) over the chunk, l in order.  Rows m beyond
+// 32 take further passes.  The launch takes 8 or 16 columns a workgroup where 32
+// would leave under 1024 workgroups, each summing many slots one after the other
+// (a whole call on one signal of 2^16 samples 428 -> 403 us); an output's terms keep their order.
 template <int TT>
 __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, int64_t vp_bstride,
                                                 const int64_t* __restrict__ vchoff, const int* __restrict__ nch,
@@ -610,12 +612,14 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
                                                 const int64_t* __restrict__ pfoff, const int* __restrict__ Lbv,
                                                 const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
                                                 int NL, int NLo, int n_alpha,
-                                                float* __restrict__ S2, const float* __restrict__ mu2, float eps) {
+                                                float* __restrict__ S2, const float* __restrict__ mu2, float eps,
+                                                int n_beta) {
     // NLo <= NL output rows (the unpadded lambda axis keeps the first NLo)
     constexpr int LC = 64, MB = 32, NG = 256 / TT, RR = MB / NG;
     __shared__ float Vs[LC][TT + 1];
     __shared__ float Ps[LC][MB];
-    const int beta = blockIdx.x, th = blockIdx.y & 1, alpha = blockIdx.y >> 1, n_beta = gridDim.x;
+    const int beta = blockIdx.x % n_beta, tb = (int)(blockIdx.x / n_beta) * TT;
+    const int th = blockIdx.y & 1, alpha = blockIdx.y >> 1;
     const int slot0 = (int)vchoff[alpha] * slot_mult, nslots = nch[alpha] * slot_mult;
     const int64_t b = blockIdx.z;
     const int Lb = Lbv[beta], ro = rowoffv[beta];
@@ -624,43 +628,42 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
     float* o = S2 + ((((b * n_alpha + alpha) * n_beta + beta) * 2 + th) * NLo) * (int64_t)NT;
     const int tau = threadIdx.x % TT, grp = threadIdx.x / TT;
     const float inv = mulog_inv(mu2, (alpha * n_beta + beta) * 2 + th, eps);
-    for (int mb = 0; mb < NLo; mb += MB)
-        for (int tb = 0; tb < NT; tb += TT) {
-            float acc[RR];
+    for (int mb = 0; mb < NLo; mb += MB) {
+        float acc[RR];
 #pragma unroll
-            for (int r = 0; r < RR; ++r) acc[r] = 0.f;
-            for (int l0 = 0; l0 < Lb; l0 += LC) {
-                const int lc = Lb - l0 < LC ? Lb - l0 : LC;
-                __syncthreads();                         // the previous chunk is read
-                for (int e = threadIdx.x; e < LC * TT; e += 256) {
-                    const int tt = e / LC, l = e - tt * LC;
-                    float v = 0.f;
-                    if (l < lc && tb + tt < NT) {
-                        const int row = rowpos[ro + l0 + l], lt = row / kTileL, lr = row % kTileL;
-                        const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL +
-                                          (int64_t)(tb + tt) * kTileL + lr;
-                        v = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
-                    }
-                    Vs[l][tt] = v;
+        for (int r = 0; r < RR; ++r) acc[r] = 0.f;
+        for (int l0 = 0; l0 < Lb; l0 += LC) {
+            const int lc = Lb - l0 < LC ? Lb - l0 : LC;
+            __syncthreads();                         // the previous chunk is read
+            for (int e = threadIdx.x; e < LC * TT; e += 256) {
+                const int tt = e / LC, l = e - tt * LC;
+                float v = 0.f;
+                if (l < lc && tb + tt < NT) {
+                    const int row = rowpos[ro + l0 + l], lt = row / kTileL, lr = row % kTileL;
+                    const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL +
+                                      (int64_t)(tb + tt) * kTileL + lr;
+                    v = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
                 }
-                for (int e = threadIdx.x; e < LC * MB; e += 256) {
-                    const int l = e / MB, mm = e - l * MB;
-                    Ps[l][mm] = l < lc && mb + mm < NLo ? PT[(int64_t)(l0 + l) * NL + mb + mm] : 0.f;
-                }
-                __syncthreads();
-                for (int l = 0; l < lc; ++l) {
-                    const float v = Vs[l][tau];
-#pragma unroll
-                    for (int r = 0; r < RR; ++r) acc[r] += Ps[l][grp * RR + r] * v;
-                }
+                Vs[l][tt] = v;
             }
-            if (tb + tau < NT)
+            for (int e = threadIdx.x; e < LC * MB; e += 256) {
+                const int l = e / MB, mm = e - l * MB;
+                Ps[l][mm] = l < lc && mb + mm < NLo ? PT[(int64_t)(l0 + l) * NL + mb + mm] : 0.f;
+            }
+            __syncthreads();
+            for (int l = 0; l < lc; ++l) {
+                const float v = Vs[l][tau];
 #pragma unroll
-                for (int r = 0; r < RR; ++r) {
-                    const int m = mb + grp * RR + r;
-                    if (m < NLo) o[(int64_t)m * NT + tb + tau] = mulog_out(acc[r], mu2, inv);
-                }
+                for (int r = 0; r < RR; ++r) acc[r] += Ps[l][grp * RR + r] * v;
+            }
         }
+        if (tb + tau < NT)
+#pragma unroll
+            for (int r = 0; r < RR; ++r) {
+                const int m = mb + grp * RR + r;
+                if (m < NLo) o[(int64_t)m * NT + tb + tau] = mulog_out(acc[r], mu2, inv);
+            }
+    }
 }
 
 // Eq. (4) (no frequential lowpass): V summed over its partial slots and stored per
@@ -1525,10 +1528,13 @@ int forward_impl(const jtfs_plan* P, const float* x, int64_t B, float* s1, float
         const ChunkSet& cs = split ? split_chunks(P) : fp32_chunks(P);
         const dim3 grid((unsigned)s.n_beta, (unsigned)(2 * s.n_alpha), (unsigned)B);
         if (s.avg_fr) {
-            auto k = s.NT <= 16 ? k_s2_out<16> : k_s2_out<32>;
-            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k, grid, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
+            int tt = s.NT <= 8 ? 8 : s.NT <= 16 ? 16 : 32;
+            while (tt > 8 && (int64_t)s.n_beta * ((s.NT + tt - 1) / tt) * 2 * s.n_alpha * B < 1024) tt /= 2;
+            auto k = tt == 8 ? k_s2_out<8> : tt == 16 ? k_s2_out<16> : k_s2_out<32>;
+            const dim3 g2((unsigned)(s.n_beta * ((s.NT + tt - 1) / tt)), (unsigned)(2 * s.n_alpha), (unsigned)B);
+            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k, g2, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
                                cs.d_nch, mult, nlt, s.NTp, s.NT, P->PFt, P->d_pfoff, P->d_Lb, P->d_rowoff, P->d_rowpos, s.NL, s.NLo, s.n_alpha, s2,
-                               ml.mu2, ml.eps));
+                               ml.mu2, ml.eps, s.n_beta));
         } else {
             JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k_v_out, grid, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
                                cs.d_nch, mult, nlt, s.NTp, s.NT, P->d_Lb, P->d_rowoff, P->d_rowpos, s.Mh, s.n_alpha, s2,

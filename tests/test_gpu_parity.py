@@ -1024,6 +1024,19 @@ def test_forward_tile_by_shapes(p, tile):
     assert np.array_equal(a1, b1) and rel_l2(b2, a2) <= 2e-6
 
 
+@pytest.mark.parametrize("T", [2048, 256, 128, 32], ids=lambda t: f"frames{2048 // t}")
+def test_frequency_lowpass_column_blocks(T):
+    """1, 8, 16 and 64 frames: one signal takes 8 columns a workgroup of the frequency lowpass, a batch of 48 more
+    where there are more; the sums keep their order, so each signal's bits."""
+    p = dict(P1, T=T)
+    x = synth.batch(5, B=48, N=p["N"])
+    op = gpu_op(p, "split16")
+    _, a = run_forward(op, x)
+    for b in (0, 47):
+        assert np.array_equal(run_forward(op, x[b:b + 1])[1][0], a[b])
+    assert rel_l2(a[47], O.jtfs(x[47].astype(np.float64), oracle_plan(p))[1]) <= TOL
+
+
 def test_more_short_rates_than_one_launch_holds():
     """71 temporal rates, all transformed in LDS: their second order and row FFTs take three launches (32 rates each)."""
     p = dict(N=2048, J=9, Q=(4, 10), J_fr=2, Q_fr=1, T=64, F=2)
