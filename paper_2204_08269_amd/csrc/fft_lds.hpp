@@ -157,13 +157,13 @@ __device__ __forceinline__ void fft_pass(C* s, int logn, int count, int stride, 
             const int j = g & ((1 << nb_log) - 1);
             const C* src = s + t * stride;
             const int k = j & (Ns - 1);
-            C w[R];
-            butterfly_twiddles<R>(w, tw, k << tws, inv);
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                C a = src[lpad(j + (r << nb_log))];
-                if (r) a = cmul(a, w[r]);
-                v[q][r] = a;
+            for (int r = 0; r < R; ++r) v[q][r] = src[lpad(j + (r << nb_log))];
+            if (lNs) {                           // (the first pass's twiddles are 1)
+                C w[R];
+                butterfly_twiddles<R>(w, tw, k << tws, inv);
+#pragma unroll
+                for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], w[r]);
             }
             dft_small<R>(v[q], inv);
         }

@@ -69,13 +69,18 @@ __device__ __forceinline__ void dft16(float2* a, bool inv) {
     }
 }
 
-// Twiddles w^r, r = 1..15, of one radix-16 butterfly: w, w^2, w^4, w^8 from the
-// table, the others products of those (at most three roundings deep).
-__device__ __forceinline__ void butterfly_twiddles16(float2 (&w)[16], const float2* __restrict__ tw, int k, bool inv) {
-    butterfly_twiddles<8>(*(float2(*)[8])w, tw, k, inv);
-    w[8] = twiddle(tw, 8 * k, inv);
+// Twiddles w^r, r = 1..R-1, of one radix-R butterfly from its powers of two (w, w^2,
+// w^4, w^8 from the table): the others are products of those, at most three
+// roundings deep.
+template <int LR>
+__device__ __forceinline__ void twiddle_products(float2 (&w)[1 << LR], const float2* p) {
+    w[1] = p[0];
 #pragma unroll
-    for (int r = 1; r < 8; ++r) w[8 + r] = cmul(w[r], w[8]);
+    for (int l = 1; l < LR; ++l) {
+        w[1 << l] = p[l];
+#pragma unroll
+        for (int r = 1; r < 1 << l; ++r) w[(1 << l) + r] = cmul(w[r], p[l]);
+    }
 }
 
 // The thread index as a value the compiler cannot relate to any other copy of it.
@@ -111,29 +116,45 @@ __device__ __forceinline__ int reg_out_pos(int e, int tid) {
 // only on the thread index; without this the loads of every pass are hoisted to
 // the start of the transform (an LDS-only barrier does not hold back global
 // loads) and their values occupy registers through all the passes before.
+// (Handed through as a pointer to global memory: as a generic one the loads became
+// flat ones, which every LDS wait then waits for.)
 template <typename T>
 __device__ __forceinline__ T* after(T* p, float2& v0) {
-    asm volatile("" : "+s"(p), "+v"(v0.x));
-    return p;
+    auto g = (__attribute__((address_space(1))) T*)p;
+    asm volatile("" : "+s"(g), "+v"(v0.x));
+    return (T*)g;
+}
+
+// The table's twiddles of a pass on the thread's E / R butterflies: the powers 1, 2,
+// 4.. R / 2 of each one's w.  None in the first pass, whose twiddles are 1.
+template <int LR, int LNS, int LOGN, int E>
+__device__ __forceinline__ void reg_load_twiddles(float2 (&p)[(E >> LR) * LR], const float2* __restrict__ tw0, int tw_log,
+                                                  bool inv, float2& after_v) {
+    constexpr int T = (1 << LOGN) / E;
+    const int tws = tw_log - LNS - LR;
+    const float2* tw = after(tw0, after_v);
+    const int tid = opaque_tid();
+#pragma unroll
+    for (int q = 0; q < E >> LR; ++q) {
+        const int k = (tid + q * T) & ((1 << LNS) - 1);
+#pragma unroll
+        for (int l = 0; l < LR; ++l) p[q * LR + l] = twiddle(tw, (k << tws) << l, inv);
+    }
 }
 
 // Butterflies of one pass on the thread's E values (E / R butterflies).
-template <int LR, int LNS, int LOGN, int E>
-__device__ __forceinline__ void reg_butterflies(float2 (&v)[E], const float2* __restrict__ tw0, int tw_log, bool inv) {
-    constexpr int R = 1 << LR, T = (1 << LOGN) / E;
-    const int tws = tw_log - LNS - LR;
-    const float2* tw = after(tw0, v[0]);
-    const int tid = opaque_tid();
+template <int LR, int LNS, int E>
+__device__ __forceinline__ void reg_butterflies(float2 (&v)[E], const float2 (&p)[(E >> LR) * LR], bool inv) {
+    constexpr int R = 1 << LR;
 #pragma unroll
     for (int q = 0; q < E / R; ++q) {
-        const int j = tid + q * T;
-        const int k = j & ((1 << LNS) - 1);
         float2* a = v + q * R;
-        float2 w[R];
-        if constexpr (R == 16) butterfly_twiddles16(w, tw, k << tws, inv);
-        else butterfly_twiddles<R>(w, tw, k << tws, inv);
+        if constexpr (LNS > 0) {
+            float2 w[R];
+            twiddle_products<LR>(w, p + q * LR);
 #pragma unroll
-        for (int r = 1; r < R; ++r) a[r] = cmul(a[r], w[r]);
+            for (int r = 1; r < R; ++r) a[r] = cmul(a[r], w[r]);
+        }
         if constexpr (R == 16) {
             dft16(a, inv);
         } else {
@@ -185,17 +206,24 @@ __device__ __forceinline__ void reg_exchange(float2 (&v)[E], float* x) {
     for (int e = 0; e < E; ++e) v[e] = rb[xpad<LR, LNS>(reg_in_pos<LR2, LOGN, E>(e, 0))];
 }
 
+// Passes I.. of a transform, p the table's twiddles of pass I.  Those of pass I + 1
+// are loaded before the exchange, so that they arrive while the values move through
+// LDS instead of holding up every pass (with the first pass's products by 1 left out, rows of
+// 2^14 points of 16 signals of 2^16 samples: second order 441 -> 397 us, scalogram 316
+// -> 250, first-order adjoint 380 -> 302).
 template <int E, int LOGN, int LRM, int I>
-__device__ __forceinline__ void reg_fft_from(float2 (&v)[E], float* x, const float2* __restrict__ tw, int tw_log,
-                                             bool inv) {
+__device__ __forceinline__ void reg_fft_from(float2 (&v)[E],
+                                             const float2 (&p)[(E >> reg_pass_lr(LOGN, I, LRM)) * reg_pass_lr(LOGN, I, LRM)],
+                                             float* x, const float2* __restrict__ tw, int tw_log, bool inv) {
     constexpr int NP = reg_num_passes(LOGN, LRM);
-    if constexpr (I < NP) {
-        constexpr int LR = reg_pass_lr(LOGN, I, LRM), LNS = reg_lns_before(LOGN, I, LRM);
-        reg_butterflies<LR, LNS, LOGN, E>(v, tw, tw_log, inv);
-        if constexpr (I + 1 < NP) {
-            reg_exchange<LR, reg_pass_lr(LOGN, I + 1, LRM), LNS, LOGN, E>(v, x);
-            reg_fft_from<E, LOGN, LRM, I + 1>(v, x, tw, tw_log, inv);
-        }
+    constexpr int LR = reg_pass_lr(LOGN, I, LRM), LNS = reg_lns_before(LOGN, I, LRM);
+    reg_butterflies<LR, LNS, E>(v, p, inv);
+    if constexpr (I + 1 < NP) {
+        constexpr int LR2 = reg_pass_lr(LOGN, I + 1, LRM);
+        float2 p2[(E >> LR2) * LR2];
+        reg_load_twiddles<LR2, LNS + LR, LOGN, E>(p2, tw, tw_log, inv, v[0]);
+        reg_exchange<LR, LR2, LNS, LOGN, E>(v, x);
+        reg_fft_from<E, LOGN, LRM, I + 1>(v, p2, x, tw, tw_log, inv);
     }
 }
 
@@ -207,7 +235,8 @@ template <int E, int LOGN, int LRM = reg_lr_max(E)>
 __device__ __forceinline__ void reg_fft(float2 (&v)[E], float* x, const float2* __restrict__ tw, int tw_log,
                                         bool inv) {
     static_assert(LOGN >= 6 && (1 << LOGN) % E == 0 && (1 << LRM) <= E, "transform shape");
-    reg_fft_from<E, LOGN, LRM, 0>(v, x, tw, tw_log, inv);
+    const float2 none[(E >> reg_pass_lr(LOGN, 0, LRM)) * reg_pass_lr(LOGN, 0, LRM)] = {};
+    reg_fft_from<E, LOGN, LRM, 0>(v, none, x, tw, tw_log, inv);
 }
 
 // input position of element e (that of the first pass)
