@@ -311,16 +311,18 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     // rows of 2^14 points: per stage, the faster of the two runs of the chosen mode
     int rows = all_rows;
     if (has14) {
-        const int kstage[4] = {JTFS_STAGE_SCALOGRAM, JTFS_STAGE_SECOND_ORDER, JTFS_STAGE_SECOND_ADJ_FFT,
-                               JTFS_STAGE_FIRST_ADJ};
-        const int kbit[4] = {JTFS_REG_SCALOGRAM, JTFS_REG_SECOND_ORDER, JTFS_REG_ROW_FFT, JTFS_REG_FIRST_ADJ};
+        const int kstage[2] = {JTFS_STAGE_SCALOGRAM, JTFS_STAGE_SECOND_ORDER};
+        const int kbit[2] = {JTFS_REG_SCALOGRAM, JTFS_REG_SECOND_ORDER};
         rows = 0;
-        for (int q = 0; q < 4; ++q) {
-            // the first-order adjoint's bit also chooses the kernel of the second-order adjoint
-            const double r0 = stage[best_m][0][kstage[q]] + (q == 3 ? stage[best_m][0][JTFS_STAGE_SECOND_ADJ] : 0.0);
-            const double r1 = stage[best_m][1][kstage[q]] + (q == 3 ? stage[best_m][1][JTFS_STAGE_SECOND_ADJ] : 0.0);
-            if (r0 <= r1) rows |= kbit[q];
-        }
+        for (int q = 0; q < 2; ++q)
+            if (stage[best_m][0][kstage[q]] <= stage[best_m][1][kstage[q]]) rows |= kbit[q];
+        // the first-order adjoint's bit also chooses the kernel of the second-order
+        // adjoint, which with both bits set takes the long rows' transforms in: one choice
+        auto adj = [&](int ri) {
+            const double* t = stage[best_m][ri];
+            return t[JTFS_STAGE_SECOND_ADJ_FFT] + t[JTFS_STAGE_SECOND_ADJ] + t[JTFS_STAGE_FIRST_ADJ];
+        };
+        if (adj(0) <= adj(1)) rows |= JTFS_REG_ROW_FFT | JTFS_REG_FIRST_ADJ;
     }
     if (use16) rows |= JTFS_TUNE_FWD_TILE16;
     P->contraction = modes[best_m];

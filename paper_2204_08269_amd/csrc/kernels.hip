@@ -1556,10 +1556,12 @@ namespace {
 
 // forward FFT of every gY2 row lambda < n1 (length T_alpha), in place; phi_T's rows go
 // back through the S1 adjoint untransformed
-int gy2_row_ffts(const jtfs_plan* P, float2* gY2, int64_t yb, int64_t B, hipStream_t st) {
+// the FFTs of the gY2 rows under 2^logmax points
+int gy2_row_ffts(const jtfs_plan* P, float2* gY2, int64_t yb, int logmax, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     for (int a = 0; a < s.n_alpha_psi; ++a) {
         const int logTa = s.logNX - s.k2[a];
+        if (logTa >= logmax) continue;
         if (!reg_row(logTa, P->tune.reg_rowfft)) continue;
         JTFS_TIMED(JTFS_STAGE_SECOND_ADJ_FFT, st,
                    launch_rowfft_r(P, gY2 + s.yoff[a], yb, (int64_t)s.Tp[a], s.n1, logTa, B, st));
@@ -1678,14 +1680,16 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
                            s.Tp[a], P->Wl, s.Mp, s.Kp, gY2 + s.yoff[a], yb));
         LAUNCHCHK("contraction adjoint (W^H)");
     }
-    rc = gy2_row_ffts(P, gY2, yb, B, st);
+    // with both in registers, the scalogram adjoint transforms the long gY2 rows itself
+    const bool rows_in_a = use_reg_rows(s.logNX, P->tune.reg_first_adj) && P->tune.reg_rowfft;
+    rc = gy2_row_ffts(P, gY2, yb, rows_in_a ? kRegMinLogRows - 1 : 31, B, st);
     if (rc != JTFS_OK) return rc;
     const int logNT = s.logN - s.logT;
     const size_t lds_a = sizeof(float2) * (lpad_len(s.NX / 2) + 1 + lpad_len(s.NT));   // g1 at lpad(H) + 1
     const float2* gYphi = s.complete ? gY2 + s.yoff[s.n_alpha_psi] : nullptr;
     const int Tphi = s.complete ? s.Tp[s.n_alpha_psi] : 0;
     if (use_reg_rows(s.logNX, P->tune.reg_first_adj)) {
-        JTFS_TIMED(JTFS_STAGE_SECOND_ADJ, st, launch_scal_bwd_a_r(P, gY2, yb, gs1, ml, gYphi, Tphi, gX, B, st));
+        JTFS_TIMED(JTFS_STAGE_SECOND_ADJ, st, launch_scal_bwd_a_r(P, gY2, yb, gs1, ml, gYphi, Tphi, gX, rows_in_a, B, st));
     } else {
         JTFS_TIMED(JTFS_STAGE_SECOND_ADJ, st, hipLaunchKernelGGL(k_scal_bwd_a, dim3(s.n1, (unsigned)B), dim3(1024), lds_a, st, gY2, yb, P->d_yoff, P->d_Tp, P->d_Ta, P->psi2,
                            P->band2, P->off2, s.n_alpha_psi, gs1, P->phiX, s.Mphi, logNT, s.logNX, gX, P->tw, P->tw_log, ml,

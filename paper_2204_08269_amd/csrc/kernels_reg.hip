@@ -456,13 +456,28 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_b_r(const float2* __restrict
 // sums): the Hermitian half-spectrum of gX,
 //   S[m] = 1/2 sum_alpha psi_hat_alpha[m] G_alpha[m mod Ta] (real part alone at m = 0, H)
 //        + phi_hat[m] G1[m mod NT],   m = 0..H,
-// G_alpha the FFT of the gY2 rows (taken beforehand), G1 the FFT of the S1
-// cotangent row (plus the real part of phi_T's second-order rows with the lowpass
-// pairs), is formed at the thread's input positions of the H-point transform and
+// G_alpha the FFT of the gY2 rows (taken beforehand, but for the long ones where
+// ROWS), G1 the FFT of the S1 cotangent row (plus the real part of phi_T's
+// second-order rows with the lowpass pairs), is formed at the thread's bins tid + 1024 i and
 // parked in LDS, so that each position k takes the packed spectrum
 // Z[k] = S[k] + conj(S[H-k]) + i w^k (S[k] - conj(S[H-k])) (w = e^{2 pi i / NX});
 // the inverse transform of Z gives gX[2n] + i gX[2n+1], scaled 1/NX.
-template <int E, int LOGH, int LRM>
+// Where ROWS, the kernel also transforms the long gY2 rows (Ta >= 2^13) itself, one
+// after the other in the exchange buffer, and G_alpha never leaves the registers:
+// every transform here ends with thread tid on the bins tid + 1024 i, so that the
+// thread that holds a bin of G_alpha holds the sums at all its images.  A row of
+// 2^15 points goes as its even and odd samples, E[k] + w^k O[k], of which only the
+// bins k <= H are formed.  In passes of their own the transforms wrote these rows and
+// this kernel read them back: 525 and 447 us for 16 signals of 2^16 samples, 683 now
+// (7.5 and 4.0 ms, 8.1 now, for 32 of 2^18).
+// grid (n1, B), 1024 threads; 147 KB of LDS, so one workgroup a CU.
+template <int LOGN, int E, int LRM>
+__device__ __forceinline__ constexpr int bin_elem(int i) {       // element of bin tid + 1024 i after reg_fft
+    constexpr int LR = reg_pass_lr(LOGN, reg_num_passes(LOGN, LRM) - 1, LRM), Q = E >> LR;
+    static_assert((1 << LOGN) == kRegT * E, "a full block");
+    return ((i & (Q - 1)) << LR) + (i / Q);
+}
+template <int LOGH, int LRM, bool ROWS>
 __global__ void __launch_bounds__(kRegT) k_scal_bwd_a_r(const float2* __restrict__ G, int64_t y_bstride,
                                                       const int64_t* __restrict__ yoff, const int* __restrict__ Tpv,
                                                       const int* __restrict__ Tav, const float* __restrict__ psi2,
@@ -472,12 +487,12 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_a_r(const float2* __restrict
                                                       float* __restrict__ gX, const float2* __restrict__ tw, int tw_log,
                                                       MuLogArg ml, const float2* __restrict__ gYphi, int Tphi) {
     extern __shared__ __align__(16) float xbuf[];
-    constexpr int H = 1 << LOGH;
+    constexpr int H = 1 << LOGH, E = H / kRegT, LRH = E >= 16 ? LRM : 3;
     const int lam = blockIdx.x, n1 = gridDim.x;
     const int64_t b = blockIdx.y;
     const int NT = 1 << logNT;
     float2* Sx = (float2*)xbuf;                                  // S[0..H] (H + 1 <= the exchange buffer)
-    float2* g1 = (float2*)(xbuf + reg_xbuf_floats(LOGH));        // G1, lpad_len(NT) slots
+    float2* g1 = (float2*)(xbuf + reg_xbuf_floats(ROWS ? kRegMinLog : LOGH));        // G1, lpad_len(NT) slots
     const float em = ml.mu1 ? ml.eps * ml.mu1[0] : 0.f;
     for (int t = threadIdx.x; t < NT; t += blockDim.x) {
         const int64_t i = (b * n1 + lam) * NT + t;
@@ -488,35 +503,128 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_a_r(const float2* __restrict
     __syncthreads();
     lds_fft<16>(g1, logNT, 1, NT, tw, tw_log, false);
     __syncthreads();
-    // the half-spectrum at the thread's positions k (and at H on thread 0): the
-    // temporal rates in the outer loop, so that a rate's loads for all positions
-    // issue together
+    // the half-spectrum at the bins tid + 1024 i (and at H on thread 0): the temporal
+    // rates in the outer loop, so that a rate's loads for all bins issue together
     const int extra = threadIdx.x == 0 ? 1 : 0;
     float2 c[E + 1];
 #pragma unroll
-    for (int e = 0; e <= E; ++e) c[e] = make_float2(0.f, 0.f);
+    for (int i = 0; i <= E; ++i) c[i] = make_float2(0.f, 0.f);
+    const float2* gr = G + b * y_bstride;
+    // All loads of a rate (of four rates where their bands end below bin 2048) issue
+    // before the first is used: one after the other they were most of this kernel's
+    // time (809 -> 683 us).  A bin outside a band takes part in no sum, whatever its value.
     for (int a = 0; a < n_alpha; ++a) {
-        const int lo = band2[2 * a], hi = band2[2 * a + 1];
+        const int lo = band2[2 * a], hi = band2[2 * a + 1], Ta = Tav[a];
         const float* pa = psi2 + off2[a] - lo;
-        const float2* ga = G + b * y_bstride + yoff[a] + (int64_t)lam * Tpv[a];
-        const int tmask = Tav[a] - 1;
+        const float2* ga = gr + yoff[a] + (int64_t)lam * Tpv[a];
+        auto in_band = [&](int i) {
+            const int m = (int)threadIdx.x + i * kRegT;
+            return m >= lo && m <= hi && (i < E || extra);
+        };
+        // the transform's output v: its bins' weights (and with TW the twiddles w^k of
+        // the odd samples' bins) load eight at a time
+        auto add = [&](auto& v, auto elem, bool odd) {
+            const float* pv = after(pa, v[0]);
+            const float2* twc = odd ? after(tw, v[0]) : tw;
+            const int tws = tw_log - kRegMinLog - 1;
 #pragma unroll
-        for (int e = 0; e <= E; ++e) {
-            if (e == E && !extra) continue;
-            const int m = e < E ? reg_input_pos<LOGH, E, LRM>(e) : H;
-            if (m >= lo && m <= hi) {
-                const float g = pa[m];
-                const float2 v = ga[m & tmask];
-                c[e].x += g * v.x;
-                c[e].y += g * v.y;
+            for (int i0 = 0; i0 <= E; i0 += 8) {
+                float g[8];
+                float2 w[8];
+#pragma unroll
+                for (int q = 0; q < 8 && i0 + q <= E; ++q) {
+                    const int m = (int)threadIdx.x + (i0 + q) * kRegT;
+                    g[q] = 0.f;
+                    if (in_band(i0 + q)) g[q] = pv[m];
+                    if (LOGH == kRegMinLog && odd) w[q] = i0 + q < E ? twc[m << tws] : make_float2(-1.f, 0.f);
+                }
+#pragma unroll
+                for (int q = 0; q < 8 && i0 + q <= E; ++q) {
+                    float2 z = v[elem(i0 + q)];
+                    if (LOGH == kRegMinLog && odd) z = cmul(z, w[q]);
+                    if (in_band(i0 + q)) {
+                        c[i0 + q].x += g[q] * z.x;
+                        c[i0 + q].y += g[q] * z.y;
+                    }
+                }
+            }
+        };
+        if (ROWS && Ta >= 1 << kRegMinLog) {
+            const int parts = LOGH == kRegMinLog ? Ta >> kRegMinLog : 1;
+            for (int p = 0; p < parts; ++p) {
+                float2 v[kRegE];
+#pragma unroll
+                for (int e = 0; e < kRegE; ++e) v[e] = ga[reg_input_pos<kRegMinLog, kRegE, LRM>(e) * parts + p];
+                reg_fft<kRegE, kRegMinLog, LRM>(v, xbuf, tw, tw_log, false);
+                add(v, [](int i) { return bin_elem<kRegMinLog, kRegE, LRM>(i & (kRegE - 1)); }, p == 1);
+            }
+        } else if (ROWS && Ta == 1 << (kRegMinLog - 1)) {
+            constexpr int E8 = kRegE / 2;
+            float2 v[E8];
+#pragma unroll
+            for (int e = 0; e < E8; ++e) v[e] = ga[reg_input_pos<kRegMinLog - 1, E8, 3>(e)];
+            reg_fft<E8, kRegMinLog - 1, 3>(v, xbuf, tw, tw_log, false);
+            add(v, [](int i) { return bin_elem<kRegMinLog - 1, E8, 3>(i & (E8 - 1)); }, false);
+        } else if (hi < 2 * kRegT) {
+            // up to four rates of so low a band at once
+            float g[4][2];
+            float2 z[4][2];
+            int n = 0;
+            while (n < 4 && a + n < n_alpha && band2[2 * (a + n) + 1] < 2 * kRegT &&
+                   (!ROWS || Tav[a + n] < 1 << (kRegMinLog - 1))) ++n;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int au = a + (u < n ? u : 0), lu = band2[2 * au], hu = band2[2 * au + 1];
+                const float* pu = psi2 + off2[au] - lu;
+                const float2* gu = gr + yoff[au] + (int64_t)lam * Tpv[au];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int m = (int)threadIdx.x + i * kRegT;
+                    g[u][i] = 0.f;
+                    z[u][i] = make_float2(0.f, 0.f);
+                    if (u < n && m >= lu && m <= hu) {
+                        g[u][i] = pu[m];
+                        z[u][i] = gu[m & (Tav[au] - 1)];
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    c[i].x += g[u][i] * z[u][i].x;
+                    c[i].y += g[u][i] * z[u][i].y;
+                }
+            a += n - 1;
+        } else {
+#pragma unroll
+            for (int i0 = 0; i0 <= E; i0 += 9) {
+                float g[9];
+                float2 z[9];
+#pragma unroll
+                for (int q = 0; q < 9 && i0 + q <= E; ++q) {
+                    g[q] = 0.f;
+                    z[q] = make_float2(0.f, 0.f);
+                    if (in_band(i0 + q)) {
+                        const int m = (int)threadIdx.x + (i0 + q) * kRegT;
+                        g[q] = pa[m];
+                        z[q] = ga[m & (Ta - 1)];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 9 && i0 + q <= E; ++q) {
+                    c[i0 + q].x += g[q] * z[q].x;
+                    c[i0 + q].y += g[q] * z[q].y;
+                }
             }
         }
     }
+    if (ROWS) __syncthreads();                                   // the last transform's exchange is read
 #pragma unroll
-    for (int e = 0; e <= E; ++e) {
-        if (e == E && !extra) continue;
-        const int m = e < E ? reg_input_pos<LOGH, E, LRM>(e) : H;
-        float2 hm = (m == 0 || m == H) ? make_float2(c[e].x, 0.f) : cscale(c[e], 0.5f);
+    for (int i = 0; i <= E; ++i) {
+        if (i == E && !extra) continue;
+        const int m = (int)threadIdx.x + i * kRegT;
+        float2 hm = (m == 0 || m == H) ? make_float2(c[i].x, 0.f) : cscale(c[i], 0.5f);
         if (m <= Mphi) {
             const float2 v = g1[lpad(m & (NT - 1))];
             hm.x += phiX[m] * v.x;
@@ -529,7 +637,7 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_a_r(const float2* __restrict
     float2 v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int k = reg_input_pos<LOGH, E, LRM>(e);
+        const int k = reg_input_pos<LOGH, E, LRH>(e);
         const float2 p = Sx[k], q = Sx[H - k];
         const float2 Sm = make_float2(p.x + q.x, p.y - q.y);
         const float2 D = make_float2(p.x - q.x, p.y + q.y);
@@ -537,11 +645,11 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_a_r(const float2* __restrict
         v[e] = make_float2(Sm.x - wD.y, Sm.y + wD.x);
     }
     __syncthreads();                                             // S is read; the transform reuses the buffer
-    reg_fft<E, LOGH, LRM>(v, xbuf, tw, tw_log, true);
+    reg_fft<E, LOGH, LRH>(v, xbuf, tw, tw_log, true);
     float2* o = (float2*)(gX + (b * n1 + lam) * (int64_t)(2 * H));
     const float sc = 1.f / (float)(2 * H);
 #pragma unroll
-    for (int e = 0; e < E; ++e) o[reg_output_pos<LOGH, E, LRM>(e)] = cscale(v[e], sc);
+    for (int e = 0; e < E; ++e) o[reg_output_pos<LOGH, E, LRH>(e)] = cscale(v[e], sc);
 }
 
 // Each long-row kernel in both row lengths and both largest radices of its
@@ -552,9 +660,12 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_a_r(const float2* __restrict
 int reg_attributes() {
     const void* ks[] = {JTFS_REG_VARIANTS(k_scalogram_r), JTFS_REG_VARIANTS(k_second_order_r),
                         JTFS_REG_VARIANTS(k_rowfft_r), JTFS_REG_VARIANTS(k_scal_bwd_b_r),
-                        (const void*)k_scal_bwd_a_r<kRegE, kRegMinLog, 4>,
-                        (const void*)k_scal_bwd_a_r<kRegE, kRegMinLog, 3>,
-                        (const void*)k_scal_bwd_a_r<kRegE / 2, kRegMinLog - 1, 3>, (const void*)k_rowfft_rs<13>,
+                        (const void*)k_scal_bwd_a_r<kRegMinLog, 4, true>, (const void*)k_scal_bwd_a_r<kRegMinLog, 3, true>,
+                        (const void*)k_scal_bwd_a_r<kRegMinLog - 1, 4, true>,
+                        (const void*)k_scal_bwd_a_r<kRegMinLog - 1, 3, true>,
+                        (const void*)k_scal_bwd_a_r<kRegMinLog, 4, false>,
+                        (const void*)k_scal_bwd_a_r<kRegMinLog, 3, false>,
+                        (const void*)k_scal_bwd_a_r<kRegMinLog - 1, 3, false>, (const void*)k_rowfft_rs<13>,
                         (const void*)k_rowfft_rs<12>, (const void*)k_rowfft_rs<11>,
                         (const void*)k_second_order_rs<13>, (const void*)k_second_order_rs<12>,
                         (const void*)k_second_order_rs<11>};
@@ -624,15 +735,18 @@ void launch_rowfft_r(const jtfs_plan* P, float2* base, int64_t bs, int64_t rs, i
 }
 
 void launch_scal_bwd_a_r(const jtfs_plan* P, const float2* G, int64_t y_bstride, const float* gS1, const MuLogArg& ml,
-                         const float2* gYphi, int Tphi, float* gX, int64_t B, hipStream_t st) {
+                         const float2* gYphi, int Tphi, float* gX, bool rows, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int logNT = s.logN - s.logT;
     // rows of 2^15 points: a 2^14-point transform of 16 values per thread; 2^14: 2^13 of 8
-    auto k = s.logNX == kRegMinLog + 1
-                 ? (P->tune.r8_first_adj ? k_scal_bwd_a_r<kRegE, kRegMinLog, 3> : k_scal_bwd_a_r<kRegE, kRegMinLog, 4>)
-                 : k_scal_bwd_a_r<kRegE / 2, kRegMinLog - 1, 3>;
-    const int logH = s.logNX - 1;
-    const size_t lds = sizeof(float) * ((size_t)reg_xbuf_floats(logH) + 2 * (size_t)lpad_len(s.NT));
+    const bool r8 = P->tune.r8_first_adj, l = s.logNX == kRegMinLog + 1;
+    auto k = !rows ? (!l   ? k_scal_bwd_a_r<kRegMinLog - 1, 3, false>
+                      : r8 ? k_scal_bwd_a_r<kRegMinLog, 3, false>
+                           : k_scal_bwd_a_r<kRegMinLog, 4, false>)
+             : l   ? (r8 ? k_scal_bwd_a_r<kRegMinLog, 3, true> : k_scal_bwd_a_r<kRegMinLog, 4, true>)
+                   : (r8 ? k_scal_bwd_a_r<kRegMinLog - 1, 3, true> : k_scal_bwd_a_r<kRegMinLog - 1, 4, true>);
+    const int logx = rows ? kRegMinLog : s.logNX - 1;
+    const size_t lds = sizeof(float) * ((size_t)reg_xbuf_floats(logx) + 2 * (size_t)lpad_len(s.NT));
     hipLaunchKernelGGL(k, dim3(s.n1, (unsigned)B), dim3(reg_threads()), lds, st, G, y_bstride, P->d_yoff, P->d_Tp,
                        P->d_Ta, P->psi2, P->band2, P->off2, s.n_alpha_psi, gS1, P->phiX, s.Mphi, logNT, gX, P->tw,
                        P->tw_log, ml, gYphi, Tphi);

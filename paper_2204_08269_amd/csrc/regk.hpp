@@ -36,9 +36,10 @@ void launch_second_order_r(const jtfs_plan* P, int a, const float2* Xh, int64_t 
                            int64_t B, hipStream_t st);
 void launch_rowfft_r(const jtfs_plan* P, float2* base, int64_t bs, int64_t rs, int rows, int logn, int64_t B,
                      hipStream_t st);
-// adjoint of the second order and of S1 for rows of N_X = 2^14 or 2^15 points
+// adjoint of the second order and of S1 for rows of N_X = 2^14 or 2^15 points (rows:
+// with the FFTs of the gY2 rows of 2^13 points and more)
 void launch_scal_bwd_a_r(const jtfs_plan* P, const float2* G, int64_t y_bstride, const float* gS1, const MuLogArg& ml,
-                         const float2* gYphi, int Tphi, float* gX, int64_t B, hipStream_t st);
+                         const float2* gYphi, int Tphi, float* gX, bool rows, int64_t B, hipStream_t st);
 void launch_scal_bwd_b_r(const jtfs_plan* P, const float2* xh, int64_t xh_pitch, const float* gX, float2* g1,
                          int64_t B, hipStream_t st);
 }  // namespace jtfs

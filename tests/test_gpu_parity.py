@@ -1037,6 +1037,28 @@ def test_frequency_lowpass_column_blocks(T):
     assert rel_l2(a[47], O.jtfs(x[47].astype(np.float64), oracle_plan(p))[1]) <= TOL
 
 
+LONG_ROWS = [dict(N=2 ** 16, J=12, Q=(16, 1), J_fr=4, Q_fr=1, T=2 ** 11, F=8),      # rows of 2^14: rates 2^14, 2^13, shorter
+             dict(N=2 ** 17, J=13, Q=(12, 2), J_fr=4, Q_fr=1, T=2 ** 13, F=8),      # 2^15: even and odd samples; two rates each
+             dict(N=2 ** 16, J=12, Q=(16, 1), J_fr=4, Q_fr=1, T=2 ** 10, F=8)]      # 64 frames
+
+
+@pytest.mark.parametrize("radix8", [(), ALL_ROWS], ids=["radix16", "radix8"])
+@pytest.mark.parametrize("p", LONG_ROWS, ids=lambda p: f"N{p['N']}_T{p['T']}_Q{p['Q'][1]}")
+def test_long_rows_transformed_in_the_adjoint(p, radix8):
+    """The scalogram adjoint with the long rows' transforms inside against the transforms in passes of their own: two
+    FP32 transforms of each row (15 stages of 2 roundings each) and sums over at most 26 rates, so 56 roundings of
+    2^-24 on each side's way: 3.3e-6 if all of one side went the same way."""
+    P = oracle_plan(p)
+    x = torch.from_numpy(synth.batch(5, B=2, N=p["N"])).cuda()
+    gs1, gs2 = synth.cotangents((2,) + P.s1_shape(), (2,) + P.s2_shape())
+    op = gpu_op(p, "split16")
+    g = []
+    for rows in (ALL_ROWS, tuple(r for r in ALL_ROWS if r != "row_fft")):
+        op.set_tuning("split16", rows, radix8=radix8)
+        g.append(op.vjp(x, torch.from_numpy(gs1).cuda(), torch.from_numpy(gs2).cuda()).cpu().numpy())
+    assert rel_l2(g[0], g[1]) <= 3.3e-6
+
+
 def test_more_short_rates_than_one_launch_holds():
     """71 temporal rates, all transformed in LDS: their second order and row FFTs take three launches (32 rates each)."""
     p = dict(N=2048, J=9, Q=(4, 10), J_fr=2, Q_fr=1, T=64, F=2)
