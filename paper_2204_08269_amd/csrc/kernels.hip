@@ -33,12 +33,23 @@ __device__ __forceinline__ floatx16 zero16() {
 // row (within a 32x32 tile) held by register r of a lane in half h
 __device__ __forceinline__ int crow(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
+// Inverse of the real-spectrum post-pass: Z'[k] = (X[k] + conj X[H-k]) + i w_n^{-k} (X[k] - conj X[H-k]),
+// whose unnormalised inverse FFT is n times the interleaved real signal.
+__device__ __forceinline__ float2 irfft_bin(float2 p, float2 q, float2 w) {
+    const float2 S = make_float2(p.x + q.x, p.y - q.y);          // p + conj q
+    const float2 D = make_float2(p.x - q.x, p.y + q.y);          // p - conj q
+    const float2 wD = cmulc(D, w);                               // w^{-k} D
+    return make_float2(S.x - wD.y, S.y + wD.x);                  // S + i wD
+}
+
 // ---------------------------------------------------------------------------
 // Generic batched FFT over LDS: transform c of batch b has element e at
 // in[b*ib + c*ics + e*ies]; the output X_c[k] (times w_n^{c k} when twl > 0, the
 // four-step twist, and times scale) goes to out[b*ob + c*ocs + k*oes].
 // Column mode (ics == 1): C = 2^logC adjacent transforms per workgroup, loaded
 // with adjacent columns on adjacent threads.  Row mode: transforms contiguous.
+// PACK: the input rows are half spectra, packed on the way in (element i of the row's
+// 2^twl from its bins i and 2^twl - i) instead of by a pass of its own.
 // ---------------------------------------------------------------------------
 template <typename CI, typename C>
 __device__ __forceinline__ C to_cplx(CI v) {
@@ -46,7 +57,7 @@ __device__ __forceinline__ C to_cplx(CI v) {
     return cplx<C>::make((R)v.x, (R)v.y);
 }
 
-template <typename CI, typename C>
+template <typename CI, typename C, bool PACK = false>
 __global__ void __launch_bounds__(1024) k_fft_cols_t(const CI* in, C* out, int loglen, int ncols, int logC,
                                                     int64_t ib, int64_t ics, int64_t ies, int64_t ob, int64_t ocs,
                                                     int64_t oes, int twl, const C* __restrict__ tw, int tw_log, int inv,
@@ -71,7 +82,9 @@ __global__ void __launch_bounds__(1024) k_fft_cols_t(const CI* in, C* out, int l
         const int e = threadIdx.x + q * blockDim.x;
         if (e < tot) {
             const int c = ics == 1 ? (e & (Cn - 1)) : (e >> loglen), k = ics == 1 ? (e >> logC) : (e & (len - 1));
-            v[q] = to_cplx<CI, C>(in[(int64_t)(c0 + c) * ics + (int64_t)k * ies]);
+            const int64_t i = (int64_t)(c0 + c) * ics + (int64_t)k * ies;
+            if constexpr (PACK) v[q] = irfft_bin(in[i], in[((int64_t)1 << twl) - i], tw[i << (tw_log - twl - 1)]);
+            else v[q] = to_cplx<CI, C>(in[i]);
         }
     }
 #pragma unroll
@@ -106,9 +119,60 @@ __global__ void __launch_bounds__(1024) k_fft_cols_t(const CI* in, C* out, int l
 #define k_fft_cols k_fft_cols_t<float2, float2>
 
 // Real-input spectrum in FP64 from the half-length complex FFT of
-// z[k] = x[2k] + i x[2k+1] (z rows of pitch zp): X[m] = E[m] + w_n^m O[m], E/O the
-// spectra of the even/odd samples; bins 0..H rounded once to FP32 into rows of
-// pitch H+1 (H = n/2).
+// z[k] = x[2k] + i x[2k+1]: X[m] = E[m] + w_n^m O[m], E/O the spectra of the
+// even/odd samples; bins m and H - m (H = n/2) from z's bins a and b at them, rounded
+// once to FP32.  w: the twiddle of bin m; m = 0 gives bins 0 and H.
+__device__ __forceinline__ float2 rfft_bin64(double2 p, double2 q, double2 w) {
+    const double2 E = make_double2(0.5 * (p.x + q.x), 0.5 * (p.y - q.y));
+    const double2 D = make_double2(p.x - q.x, p.y + q.y);          // p - conj(q)
+    const double2 O = make_double2(0.5 * D.y, -0.5 * D.x);      // D / (2i)
+    const double2 X = cadd(E, cmul(O, w));
+    return make_float2((float)X.x, (float)X.y);
+}
+
+// The input transform of rows of up to 2^14 samples in one launch: the FP64 FFT of
+// the sample pairs in LDS and the spectrum's bins 0..H straight from there (two
+// launches and a round trip of the FP64 row: with the output transform below one signal
+// of 2^11 samples took 49.4 us in all, 46.5 now).  2^logH pairs a row, C = 2^logC rows a workgroup.
+__global__ void __launch_bounds__(1024) k_rfft64_rows(const float2* __restrict__ x, int rows, int logH, int logC,
+                                                     float2* __restrict__ xh, int64_t pitch,
+                                                     const double2* __restrict__ tw, int tw_log) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    double2* s = (double2*)lds_raw;
+    const int H = 1 << logH, st = lpad_len(H) + 1;
+    const int c0 = blockIdx.x << logC, nc = min(1 << logC, rows - c0);
+    const int tot = nc << logH;
+    constexpr int kMaxPerThread = 8;                 // tot <= 2^13
+    float2 v[kMaxPerThread];
+#pragma unroll
+    for (int q = 0; q < kMaxPerThread; ++q) {
+        const int e = threadIdx.x + q * blockDim.x;
+        if (e < tot) v[q] = x[((int64_t)c0 << logH) + e];
+    }
+#pragma unroll
+    for (int q = 0; q < kMaxPerThread; ++q) {
+        const int e = threadIdx.x + q * blockDim.x;
+        if (e < tot) s[(e >> logH) * st + lpad(e & (H - 1))] = make_double2((double)v[q].x, (double)v[q].y);
+    }
+    __syncthreads();
+    lds_fft<16>(s, logH, nc, st, tw, tw_log, false);
+    const int tws = tw_log - logH - 1, nm = H / 2 + 1;
+    for (int e = threadIdx.x; e < nc * nm; e += blockDim.x) {
+        const int c = e / nm, m = e - c * nm;
+        float2* row = xh + (c0 + c) * pitch;
+        const double2 a = s[c * st + lpad(m)];
+        if (m == 0) {
+            row[0] = make_float2((float)(a.x + a.y), 0.f);
+            row[H] = make_float2((float)(a.x - a.y), 0.f);
+            continue;
+        }
+        const double2 b = s[c * st + lpad(H - m)];
+        row[m] = rfft_bin64(a, b, tw[m << tws]);
+        row[H - m] = rfft_bin64(b, a, tw[(H - m) << tws]);
+    }
+}
+
+// The same bins from the FP64 transform in memory (z rows of pitch zp), for longer rows.
 __global__ void k_rfft_post64(const double2* __restrict__ z, int64_t zp, float2* __restrict__ xh, int64_t pitch,
                               int logn, const double2* __restrict__ tw, int tw_log) {
     const int H = 1 << (logn - 1);
@@ -124,36 +188,31 @@ __global__ void k_rfft_post64(const double2* __restrict__ z, int64_t zp, float2*
         return;
     }
     const double2 a = zr[m], b = zr[H - m];
-    auto spec = [&](double2 p, double2 q, int k) {
-        const double2 E = make_double2(0.5 * (p.x + q.x), 0.5 * (p.y - q.y));
-        const double2 D = make_double2(p.x - q.x, p.y + q.y);          // p - conj(q)
-        const double2 O = make_double2(0.5 * D.y, -0.5 * D.x);      // D / (2i)
-        const double2 X = cadd(E, cmul(O, tw[k << tws]));
-        return make_float2((float)X.x, (float)X.y);
-    };
-    row[m] = spec(a, b, m);
-    row[H - m] = spec(b, a, H - m);
+    row[m] = rfft_bin64(a, b, tw[m << tws]);
+    row[H - m] = rfft_bin64(b, a, tw[(H - m) << tws]);
 }
 
-// Inverse of the real-spectrum post-pass: Z'[k] = (X[k] + conj X[H-k]) + i w_n^{-k} (X[k] - conj X[H-k]),
-// whose unnormalised inverse FFT is n times the interleaved real signal.
-__global__ void k_irfft_pack(const float2* __restrict__ xh, int64_t pitch, float2* __restrict__ z, int64_t zpitch,
-                             int logn, const float2* __restrict__ tw, int tw_log) {
-    const int H = 1 << (logn - 1);
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k > H / 2) return;
-    const float2* row = xh + (int64_t)blockIdx.y * pitch;
-    float2* zr = z + (int64_t)blockIdx.y * zpitch;
-    const int tws = tw_log - logn;
-    auto pk = [&](float2 p, float2 q, int kk) {
-        const float2 S = make_float2(p.x + q.x, p.y - q.y);          // p + conj q
-        const float2 D = make_float2(p.x - q.x, p.y + q.y);          // p - conj q
-        const float2 wD = cmulc(D, tw[kk << tws]);                   // w^{-k} D
-        return make_float2(S.x - wD.y, S.y + wD.x);                  // S + i wD
-    };
-    const float2 a = row[k], b = row[H - k];
-    zr[k] = pk(a, b, k);
-    if (k > 0 && H - k != k) zr[H - k] = pk(b, a, H - k);
+// The output transform of rows of up to 2^15 samples in one launch: packing into LDS,
+// inverse FFT, scaled samples out (2^11 samples with gradient 147 -> 141 us, the input
+// transform included).  2^logH pairs a row, 2^logC rows a workgroup.
+__global__ void __launch_bounds__(1024) k_irfft_rows(const float2* __restrict__ xh, int64_t pitch, int rows, int logH,
+                                                    int logC, float2* __restrict__ out, float scale,
+                                                    const float2* __restrict__ tw, int tw_log) {
+    extern __shared__ float2 s[];
+    const int H = 1 << logH, st = lpad_len(H) + 1;
+    const int c0 = blockIdx.x << logC, nc = min(1 << logC, rows - c0);
+    const int tws = tw_log - logH - 1, nm = H / 2 + 1;
+    for (int e = threadIdx.x; e < nc * nm; e += blockDim.x) {
+        const int c = e / nm, k = e - c * nm;
+        const float2* row = xh + (c0 + c) * pitch;
+        const float2 a = row[k], b = row[H - k];
+        s[c * st + lpad(k)] = irfft_bin(a, b, tw[k << tws]);
+        if (k > 0 && H - k != k) s[c * st + lpad(H - k)] = irfft_bin(b, a, tw[(H - k) << tws]);
+    }
+    __syncthreads();
+    lds_fft<16>(s, logH, nc, st, tw, tw_log, true);
+    for (int e = threadIdx.x; e < nc << logH; e += blockDim.x)
+        out[((int64_t)c0 << logH) + e] = cscale(s[(e >> logH) * st + lpad(e & (H - 1))], scale);
 }
 
 // ---------------------------------------------------------------------------
@@ -1275,8 +1334,8 @@ static bool g_attr_done = false;
 int setup_kernel_attributes() {
     if (g_attr_done) return JTFS_OK;
     const int lds = kMaxDynLds;
-    const void* ks[] = {(const void*)k_fft_cols_t<float2, float2>, (const void*)k_fft_cols_t<float2, double2>,
-                        (const void*)k_fft_cols_t<double2, double2>, (const void*)k_scalogram,
+    const void* ks[] = {(const void*)k_fft_cols_t<float2, float2>, (const void*)k_fft_cols_t<float2, float2, true>, (const void*)k_fft_cols_t<float2, double2>,
+                        (const void*)k_fft_cols_t<double2, double2>, (const void*)k_scalogram, (const void*)k_rfft64_rows, (const void*)k_irfft_rows,
                         (const void*)k_s2_bwd, (const void*)k_s2_bwd_avg<16>, (const void*)k_s2_bwd_avg<32>,
                         (const void*)k_second_order, (const void*)k_rowfft_short, (const void*)k_scal_bwd_a, (const void*)k_scal_bwd_b};
     for (const void* k : ks) {
@@ -1294,32 +1353,23 @@ int setup_kernel_attributes() {
     return JTFS_OK;
 }
 
-// FFT of B rows of length n = 2^logn: in (row pitch ip) -> out (row pitch op),
-// through scratch (pitch n) when n exceeds one LDS transform (four-step).
-static void fft_rows(const float2* in, int64_t ip, float2* out, int64_t op, float2* scratch, int logn, int64_t B,
-                     bool inv, float scale, const jtfs_plan* P, hipStream_t st) {
-    if (logn <= kLdsFftMax) {
-        const int logC = logn >= 12 ? 0 : 12 - logn;       // rows per workgroup
-        const size_t lds = (size_t)(1 << logC) * (lpad_len(1 << logn) + 1) * sizeof(float2);
-        hipLaunchKernelGGL((k_fft_cols), dim3((unsigned)((B + (1 << logC) - 1) >> logC)), dim3(1024), lds, st, in, out,
-                           logn, (int)B, logC, (int64_t)0, ip, (int64_t)1, (int64_t)0, op, (int64_t)1, 0, P->tw,
-                           P->tw_log, (int)inv, scale);
-        return;
-    }
+// Real rows of 2 H = 2^(logn+1) samples, H beyond one LDS transform, from their half
+// spectra (pitch ip): the packed spectrum's inverse FFT, four-step through scratch
+// (pitch H).
+static void irfft_four_step(const float2* in, int64_t ip, float2* out, float2* scratch, int logn, int64_t B, float scale,
+                            const jtfs_plan* P, hipStream_t st) {
     // n = P Q: input index a + P*bq (a < P columns, bq < Q), output k_b + Q*k_a
     const int lq = (logn + 1) / 2, lp = logn - lq;
-    const int64_t Pn = (int64_t)1 << lp, Qn = (int64_t)1 << lq;
-    int logC = std::max(0, 12 - lq);
-    logC = std::min(logC, lp);
+    const int64_t Pn = (int64_t)1 << lp, Qn = (int64_t)1 << lq, n = (int64_t)1 << logn;
+    int logC = std::min(std::max(0, 12 - lq), lp);
     size_t lds = (size_t)(1 << logC) * (lpad_len(Qn) + 1) * sizeof(float2);
-    hipLaunchKernelGGL((k_fft_cols), dim3((unsigned)(Pn >> logC), (unsigned)B), dim3(1024), lds, st, in, scratch, lq,
-                       (int)Pn, logC, ip, (int64_t)1, Pn, (int64_t)1 << logn, Qn, (int64_t)1, logn, P->tw, P->tw_log,
-                       (int)inv, 1.0f);
+    hipLaunchKernelGGL((k_fft_cols_t<float2, float2, true>), dim3((unsigned)(Pn >> logC), (unsigned)B), dim3(1024), lds,
+                       st, in, scratch, lq, (int)Pn, logC, ip, (int64_t)1, Pn, n, Qn, (int64_t)1, logn, P->tw,
+                       P->tw_log, 1, 1.0f);
     logC = std::min(std::max(0, 12 - lp), lq);
     lds = (size_t)(1 << logC) * (lpad_len(Pn) + 1) * sizeof(float2);
     hipLaunchKernelGGL((k_fft_cols), dim3((unsigned)(Qn >> logC), (unsigned)B), dim3(1024), lds, st, scratch, out, lp,
-                       (int)Qn, logC, (int64_t)1 << logn, (int64_t)1, Qn, op, (int64_t)1, Qn, 0, P->tw, P->tw_log,
-                       (int)inv, scale);
+                       (int)Qn, logC, n, (int64_t)1, Qn, n, (int64_t)1, Qn, 0, P->tw, P->tw_log, 1, scale);
 }
 
 // Real FFT of the B input rows (N samples) in FP64: the complex FFT of the N/2
@@ -1336,10 +1386,11 @@ static void input_fft64(const float* x, int64_t B, float2* xh, int64_t xh_pitch,
     if (logn <= 13) {
         const int logC = logn >= 12 ? 0 : 12 - logn;
         const size_t lds = (size_t)(1 << logC) * (lpad_len(H) + 1) * sizeof(double2);
-        hipLaunchKernelGGL((k_fft_cols_t<float2, double2>), dim3((unsigned)((B + (1 << logC) - 1) >> logC)), dim3(1024),
-                           lds, st, in, z, logn, (int)B, logC, (int64_t)0, H, (int64_t)1, (int64_t)0, H, (int64_t)1, 0,
-                           P->tw64, P->tw_log, 0, 1.0);
-    } else {
+        hipLaunchKernelGGL(k_rfft64_rows, dim3((unsigned)((B + (1 << logC) - 1) >> logC)), dim3(1024), lds, st, in, (int)B,
+                           logn, logC, xh, xh_pitch, P->tw64, P->tw_log);
+        return;
+    }
+    {
         const int lq = (logn + 1) / 2, lp = logn - lq;
         const int64_t Pn = (int64_t)1 << lp, Qn = (int64_t)1 << lq;
         int logC = std::min(std::max(0, 12 - lq), lp);
@@ -1735,10 +1786,15 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
     JTFS_TIMED(JTFS_STAGE_BAND_ACCUM, st, hipLaunchKernelGGL(k_band_accum, dim3((unsigned)((Hn + 1 + 255) / 256), (unsigned)B), dim3(256), 0, st, g1, s.n1,
                        s.logNX, P->psi1, P->band1, P->off1, P->lam_range, Hn, gxh, w.xh_pitch));
     LAUNCHCHK("band accumulation");
-    JTFS_TIMED(JTFS_STAGE_OUTPUT_FFT, st, hipLaunchKernelGGL(k_irfft_pack, dim3((unsigned)((Hn / 2 + 1 + 255) / 256), (unsigned)B), dim3(256), 0, st, gxh,
-                       w.xh_pitch, tmp, (int64_t)Hn, s.logN, P->tw, P->tw_log));
-    LAUNCHCHK("inverse real-FFT packing");
-    JTFS_TIMED(JTFS_STAGE_OUTPUT_FFT, st, fft_rows(tmp, Hn, (float2*)gx, Hn, gxh, s.logN - 1, B, true, 1.0f / (float)s.N, P, st));
+    const int logH = s.logN - 1;
+    if (logH <= kLdsFftMax) {
+        const int logC = logH >= 12 ? 0 : 12 - logH;
+        const size_t lds = (size_t)(1 << logC) * (lpad_len(Hn) + 1) * sizeof(float2);
+        JTFS_TIMED(JTFS_STAGE_OUTPUT_FFT, st, hipLaunchKernelGGL(k_irfft_rows, dim3((unsigned)((B + (1 << logC) - 1) >> logC)), dim3(1024), lds, st,
+                           gxh, w.xh_pitch, (int)B, logH, logC, (float2*)gx, 1.0f / (float)s.N, P->tw, P->tw_log));
+    } else {
+        JTFS_TIMED(JTFS_STAGE_OUTPUT_FFT, st, irfft_four_step(gxh, w.xh_pitch, (float2*)gx, tmp, logH, B, 1.0f / (float)s.N, P, st));
+    }
     LAUNCHCHK("output inverse FFT");
     return JTFS_OK;
 }
