@@ -4,7 +4,7 @@
 // stored by the forward, or FP32 matrix cores); the tile of the split forward
 // contraction (32 x 32 or 16 x 16 MFMA tiles); and, for rows of 2^14 points, the
 // register-resident or the in-LDS transform in each of the four stages that have
-// both (scalogram, second order, gY2 row FFTs, first-order adjoint).  Every
+// both (scalogram, second order, gY2 row FFTs and first-order adjoint together).  Every
 // candidate runs whole fwd+bwd steps; the per-stage HIP-event timers attribute
 // the time, so these binary choices are settled from two runs per contraction
 // mode (all register-resident with 32 x 32 tiles, all in LDS with 16 x 16 tiles)

@@ -674,11 +674,15 @@ __device__ __forceinline__ float sum_slots(const float* __restrict__ v, int64_t 
 // of the contraction's t-chunks.  grid (n_beta ceil(NT / TT), 2 n_alpha, B), every
 // temporal rate in one launch.  The l axis runs in chunks of 64: the chunk's V (64 x
 // TT columns tau, its partial slots summed on the way in) and its rows of PF^T (64 x
-// 32 rows m, from the transposed table PFt) are staged in LDS, and each thread adds
-// its TT / 8 outputs (rows m of one tau) over the chunk, l in order.  Rows m beyond
-// 32 take further passes.  The launch takes 8 or 16 columns a workgroup where 32
-// would leave under 1024 workgroups, each summing many slots one after the other
-// (a whole call on one signal of 2^16 samples 428 -> 403 us); an output's terms keep their order.
+// 32 rows m, from the transposed table PFt) are staged in LDS and multiplied by FP32
+// matrix operations, 16 rows l to each of the four waves, whose sums are added at
+// the end; rows m beyond 32 take further passes.  What bounded it was the chain of
+// loads (row, slots, then the next element) and after that the LDS reads of vector
+// multiply-adds: 84 -> 48 us for 8 signals of 2^16 samples, 141 -> 86 for 16, 453 ->
+// 194 for 32 of 2^18, 5.6 -> 3.8 for one of 2^11.  The launch takes 8 or 16 columns
+// a workgroup where 32 would leave under 1024 workgroups, each summing many slots one
+// after the other (a whole call on one signal of 2^16 samples 428 -> 403 us); an
+// output's terms keep their order.
 template <int TT>
 __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, int64_t vp_bstride,
                                                 const int64_t* __restrict__ vchoff, const int* __restrict__ nch,
@@ -689,54 +693,66 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
                                                 float* __restrict__ S2, const float* __restrict__ mu2, float eps,
                                                 int n_beta) {
     // NLo <= NL output rows (the unpadded lambda axis keeps the first NLo)
-    constexpr int LC = 64, MB = 32, NG = 256 / TT, RR = MB / NG;
-    __shared__ float Vs[LC][TT + 1];
-    __shared__ float Ps[LC][MB];
+    constexpr int LC = 64, MB = 32, VS = TT + 1, kUn = 64 / TT;    // kUn: 16 loads of V in flight
+    __shared__ float buf[LC * VS + LC * MB > 4096 ? LC * VS + LC * MB : 4096];
+    float *Vs = buf, *Ps = buf + LC * VS, *red = buf;    // red: the four waves' sums
     const int beta = blockIdx.x % n_beta, tb = (int)(blockIdx.x / n_beta) * TT;
     const int th = blockIdx.y & 1, alpha = blockIdx.y >> 1;
     const int slot0 = (int)vchoff[alpha] * slot_mult, nslots = nch[alpha] * slot_mult;
     const int64_t b = blockIdx.z;
     const int Lb = Lbv[beta], ro = rowoffv[beta];
-    const float* PT = PFt + pfoff[beta];             // [Lb][NL]
+    const float* PT = PFt + pfoff[beta];                 // Lb x NL
     const float* Vb = Vp + b * vp_bstride;
     float* o = S2 + ((((b * n_alpha + alpha) * n_beta + beta) * 2 + th) * NLo) * (int64_t)NT;
-    const int tau = threadIdx.x % TT, grp = threadIdx.x / TT;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i32 = lane & 31, h = lane >> 5;
     const float inv = mulog_inv(mu2, (alpha * n_beta + beta) * 2 + th, eps);
     for (int mb = 0; mb < NLo; mb += MB) {
-        float acc[RR];
-#pragma unroll
-        for (int r = 0; r < RR; ++r) acc[r] = 0.f;
+        floatx16 acc = zero16();
         for (int l0 = 0; l0 < Lb; l0 += LC) {
             const int lc = Lb - l0 < LC ? Lb - l0 : LC;
-            __syncthreads();                         // the previous chunk is read
-            for (int e = threadIdx.x; e < LC * TT; e += 256) {
-                const int tt = e / LC, l = e - tt * LC;
-                float v = 0.f;
-                if (l < lc && tb + tt < NT) {
-                    const int row = rowpos[ro + l0 + l], lt = row / kTileL, lr = row % kTileL;
-                    const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL +
-                                      (int64_t)(tb + tt) * kTileL + lr;
-                    v = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
-                }
-                Vs[l][tt] = v;
-            }
-            for (int e = threadIdx.x; e < LC * MB; e += 256) {
-                const int l = e / MB, mm = e - l * MB;
-                Ps[l][mm] = l < lc && mb + mm < NLo ? PT[(int64_t)(l0 + l) * NL + mb + mm] : 0.f;
-            }
-            __syncthreads();
-            for (int l = 0; l < lc; ++l) {
-                const float v = Vs[l][tau];
+            // a thread's row l is the same for all its columns; every load of a slot
+            // (and of PF) issues before the first is used
+            const int l = threadIdx.x & 63, t4 = threadIdx.x >> 6;
+            float v[TT / 4], p[LC * MB / 256];
 #pragma unroll
-                for (int r = 0; r < RR; ++r) acc[r] += Ps[l][grp * RR + r] * v;
+            for (int q = 0; q < LC * MB / 256; ++q) {
+                const int e = threadIdx.x + 256 * q, ll = min(e / MB, lc - 1), mm = min(mb + e % MB, NLo - 1);
+                p[q] = PT[(int64_t)(l0 + ll) * NL + mm];
+            }
+            const int row = rowpos[ro + l0 + min(l, lc - 1)], lt = row / kTileL, lr = row % kTileL;
+            const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL + (int64_t)(tb + t4) * kTileL + lr;
+#pragma unroll
+            for (int q = 0; q < TT / 4; ++q) v[q] = 0.f;
+#pragma unroll kUn
+            for (int sl = 0; sl < nslots; ++sl, vs += (int64_t)nlt * 2 * NTp * kTileL)
+#pragma unroll
+                for (int q = 0; q < TT / 4; ++q) v[q] += vs[4 * q * kTileL];
+            __syncthreads();                         // the previous chunk (or pass) is read
+#pragma unroll
+            for (int q = 0; q < LC * MB / 256; ++q) {
+                const int e = threadIdx.x + 256 * q;
+                Ps[e] = e / MB < lc && mb + e % MB < NLo ? p[q] : 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q < TT / 4; ++q) Vs[l * VS + t4 + 4 * q] = l < lc && tb + t4 + 4 * q < NT ? v[q] : 0.f;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < LC / 8; ++k) {
+                const int l = wave * (LC / 4) + 2 * k + h;
+                acc = mfma32(Ps[l * MB + i32], i32 < TT ? Vs[l * VS + i32] : 0.f, acc);
             }
         }
-        if (tb + tau < NT)
+        __syncthreads();
 #pragma unroll
-            for (int r = 0; r < RR; ++r) {
-                const int m = mb + grp * RR + r;
-                if (m < NLo) o[(int64_t)m * NT + tb + tau] = mulog_out(acc[r], mu2, inv);
-            }
+        for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = acc[r];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = wave * 4 + q, m = mb + crow(r, h);
+            const float* p = red + r * 64 + lane;
+            const float a = (p[0] + p[1024]) + (p[2048] + p[3072]);
+            if (m < NLo && i32 < TT && tb + i32 < NT) o[(int64_t)m * NT + tb + i32] = mulog_out(a, mu2, inv);
+        }
     }
 }
 
