@@ -653,22 +653,6 @@ __global__ void __launch_bounds__(256) k_freq_fwd(const float2* __restrict__ Y, 
     }
 }
 
-// Sum of n partial-V slots, `stride` floats apart, in slot order; eight loads are
-// in flight at a time (one at a time, each slot cost the latency of a load).
-__device__ __forceinline__ float sum_slots(const float* __restrict__ v, int64_t stride, int n) {
-    float acc = 0.f;
-    int s = 0;
-    for (; s + 8 <= n; s += 8) {
-        float q[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) q[j] = v[(s + j) * stride];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc += q[j];
-    }
-    for (; s < n; ++s) acc += v[s * stride];
-    return acc;
-}
-
 // Frequency lowpass (eq. (3)): S2[b][alpha][beta][theta][m][tau] =
 // sum_l PF_beta[m][l] V[theta][rowoff + l][tau], V summed over the partial slots
 // of the contraction's t-chunks.  grid (n_beta ceil(NT / TT), 2 n_alpha, B), every
@@ -758,27 +742,47 @@ __global__ void __launch_bounds__(256) k_s2_out(const float* __restrict__ Vp, in
 
 // Eq. (4) (no frequential lowpass): V summed over its partial slots and stored per
 // (beta, theta) at rows 2 rowoff(beta) + theta Lb + l of S2[b][alpha][2 Mh][NT].
-// lambda runs fastest so that the partial-slot reads are contiguous.
+// grid (n_beta nlc ceil(NT / TT), 2 n_alpha, B), every temporal rate in one launch: 64 rows l
+// (chunk of nlc) and TT frames a workgroup, the sums through LDS so that the stores
+// run along the frames.  (A workgroup per scale, a load after the other and stores NT
+// floats apart: one call on 3 signals of 2^15 samples with gradient 851 us, 837 now.)
+template <int TT>
 __global__ void __launch_bounds__(256) k_v_out(const float* __restrict__ Vp, int64_t vp_bstride,
                                                const int64_t* __restrict__ vchoff, const int* __restrict__ nch,
                                                int slot_mult, int nlt, int NTp, int NT, const int* __restrict__ Lbv,
                                                const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
                                                int Mh, int n_alpha,
-                                               float* __restrict__ S2, const float* __restrict__ mu2, float eps) {
-    // grid (n_beta, 2 n_alpha, B): every temporal rate in one launch
-    const int beta = blockIdx.x, th = blockIdx.y & 1, alpha = blockIdx.y >> 1;
+                                               float* __restrict__ S2, const float* __restrict__ mu2, float eps,
+                                               int n_beta, int nlc) {
+    constexpr int LC = 64, VS = TT + 1, kUn = 64 / TT;             // kUn: 16 loads of V in flight
+    __shared__ float Vs[LC * VS];
+    const int beta = blockIdx.x % n_beta, bx = (int)(blockIdx.x / n_beta);
+    const int l0 = bx % nlc * LC, tb = bx / nlc * TT;
+    const int th = blockIdx.y & 1, alpha = blockIdx.y >> 1;
     const int slot0 = (int)vchoff[alpha] * slot_mult, nslots = nch[alpha] * slot_mult;
     const int64_t b = blockIdx.z;
-    const int Lb = Lbv[beta], ro = rowoffv[beta];
-    const float* Vb = Vp + b * vp_bstride;
-    float* o = S2 + ((b * n_alpha + alpha) * 2 * (int64_t)Mh + 2 * ro + th * Lb) * NT;
-    const float inv = mulog_inv(mu2, (alpha * (int)gridDim.x + beta) * 2 + th, eps);
-    for (int e = threadIdx.x; e < Lb * NT; e += blockDim.x) {
-        const int tau = e / Lb, l = e - tau * Lb;
-        const int row = rowpos[ro + l], lt = row / kTileL, lr = row % kTileL;
-        const float* vs = Vb + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL + (int64_t)tau * kTileL + lr;
-        const float acc = sum_slots(vs, (int64_t)nlt * 2 * NTp * kTileL, nslots);
-        o[(int64_t)l * NT + tau] = mulog_out(acc, mu2, inv);
+    const int Lb = Lbv[beta], ro = rowoffv[beta], lc = min(LC, Lb - l0);
+    if (lc <= 0) return;
+    const int l = threadIdx.x & 63, t4 = threadIdx.x >> 6;
+    const int row = rowpos[ro + l0 + min(l, lc - 1)], lt = row / kTileL, lr = row % kTileL;
+    const float* vs = Vp + b * vp_bstride + (((int64_t)slot0 * nlt + lt) * 2 + th) * NTp * kTileL +
+                      (int64_t)(tb + t4) * kTileL + lr;
+    float v[TT / 4];
+#pragma unroll
+    for (int q = 0; q < TT / 4; ++q) v[q] = 0.f;
+#pragma unroll kUn
+    for (int sl = 0; sl < nslots; ++sl, vs += (int64_t)nlt * 2 * NTp * kTileL)
+#pragma unroll
+        for (int q = 0; q < TT / 4; ++q) v[q] += vs[4 * q * kTileL];
+#pragma unroll
+    for (int q = 0; q < TT / 4; ++q) Vs[l * VS + t4 + 4 * q] = v[q];
+    __syncthreads();
+    float* o = S2 + ((b * n_alpha + alpha) * 2 * (int64_t)Mh + 2 * ro + th * Lb + l0) * NT + tb;
+    const float inv = mulog_inv(mu2, (alpha * n_beta + beta) * 2 + th, eps);
+    const int nt = min(TT, NT - tb);
+    for (int e = threadIdx.x; e < lc * nt; e += 256) {
+        const int ll = e / nt, tau = e - ll * nt;
+        o[(int64_t)ll * NT + tau] = mulog_out(Vs[ll * VS + tau], mu2, inv);
     }
 }
 
@@ -1621,7 +1625,6 @@ int forward_impl(const jtfs_plan* P, const float* x, int64_t B, float* s1, float
         // slots per t-chunk (both halves of its row tile), the split one one
         const int mult = split ? 1 : 2;
         const ChunkSet& cs = split ? split_chunks(P) : fp32_chunks(P);
-        const dim3 grid((unsigned)s.n_beta, (unsigned)(2 * s.n_alpha), (unsigned)B);
         if (s.avg_fr) {
             int tt = s.NT <= 8 ? 8 : s.NT <= 16 ? 16 : 32;
             while (tt > 8 && (int64_t)s.n_beta * ((s.NT + tt - 1) / tt) * 2 * s.n_alpha * B < 1024) tt /= 2;
@@ -1631,9 +1634,12 @@ int forward_impl(const jtfs_plan* P, const float* x, int64_t B, float* s1, float
                                cs.d_nch, mult, nlt, s.NTp, s.NT, P->PFt, P->d_pfoff, P->d_Lb, P->d_rowoff, P->d_rowpos, s.NL, s.NLo, s.n_alpha, s2,
                                ml.mu2, ml.eps, s.n_beta));
         } else {
-            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k_v_out, grid, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
+            const int tt = s.NT <= 8 ? 8 : s.NT <= 16 ? 16 : 32, nlc = (s.L + 63) / 64;
+            auto k = tt == 8 ? k_v_out<8> : tt == 16 ? k_v_out<16> : k_v_out<32>;
+            const dim3 g4((unsigned)(s.n_beta * nlc * ((s.NT + tt - 1) / tt)), (unsigned)(2 * s.n_alpha), (unsigned)B);
+            JTFS_TIMED(JTFS_STAGE_FREQ_LOWPASS, st, hipLaunchKernelGGL(k, g4, dim3(256), 0, st, Vp, w.vp_bstride, cs.d_vchoff,
                                cs.d_nch, mult, nlt, s.NTp, s.NT, P->d_Lb, P->d_rowoff, P->d_rowpos, s.Mh, s.n_alpha, s2,
-                               ml.mu2, ml.eps));
+                               ml.mu2, ml.eps, s.n_beta, nlc));
         }
         LAUNCHCHK("frequency lowpass");
     }
