@@ -130,10 +130,11 @@ __device__ __forceinline__ float2 rfft_bin64(double2 p, double2 q, double2 w) {
     return make_float2((float)X.x, (float)X.y);
 }
 
-// The input transform of rows of up to 2^14 samples in one launch: the FP64 FFT of
+// The input transform of rows of up to 2^12 samples in one launch: the FP64 FFT of
 // the sample pairs in LDS and the spectrum's bins 0..H straight from there (two
 // launches and a round trip of the FP64 row: with the output transform below one signal
-// of 2^11 samples took 49.4 us in all, 46.5 now).  2^logH pairs a row, C = 2^logC rows a workgroup.
+// of 2^11 samples took 49.4 us in all, 46.5 now).  2^logH pairs a row, 2^logC rows a
+// workgroup.
 __global__ void __launch_bounds__(1024) k_rfft64_rows(const float2* __restrict__ x, int rows, int logH, int logC,
                                                      float2* __restrict__ xh, int64_t pitch,
                                                      const double2* __restrict__ tw, int tw_log) {
@@ -142,7 +143,7 @@ __global__ void __launch_bounds__(1024) k_rfft64_rows(const float2* __restrict__
     const int H = 1 << logH, st = lpad_len(H) + 1;
     const int c0 = blockIdx.x << logC, nc = min(1 << logC, rows - c0);
     const int tot = nc << logH;
-    constexpr int kMaxPerThread = 8;                 // tot <= 2^13
+    constexpr int kMaxPerThread = 4;                 // tot <= 2^12
     float2 v[kMaxPerThread];
 #pragma unroll
     for (int q = 0; q < kMaxPerThread; ++q) {
@@ -192,7 +193,7 @@ __global__ void k_rfft_post64(const double2* __restrict__ z, int64_t zp, float2*
     row[H - m] = rfft_bin64(b, a, tw[(H - m) << tws]);
 }
 
-// The output transform of rows of up to 2^15 samples in one launch: packing into LDS,
+// The output transform of rows of up to 2^12 samples in one launch: packing into LDS,
 // inverse FFT, scaled samples out (2^11 samples with gradient 147 -> 141 us, the input
 // transform included).  2^logH pairs a row, 2^logC rows a workgroup.
 __global__ void __launch_bounds__(1024) k_irfft_rows(const float2* __restrict__ xh, int64_t pitch, int rows, int logH,
@@ -1373,6 +1374,21 @@ int setup_kernel_attributes() {
     return JTFS_OK;
 }
 
+// Rows of more than 2^kOneRowLog complex points are transformed in four steps: in one
+// launch, a workgroup per row, the output of 3 signals of 2^15 samples kept 3 of the 256
+// CUs busy for 26 us (844 us in all, 824 now).
+constexpr int kOneRowLog = 11;
+
+// Columns (log2) a workgroup of the four-step takes of 2^logcols transforms of 2^loglen
+// points, B times: 4096 points, but down to four columns (64-byte runs) while the launch
+// holds under 256 workgroups (one signal of 2^16 samples had 8: 364 us in all, 355 now).
+static int step_cols(int loglen, int logcols, int64_t B) {
+    int logC = std::min(std::max(0, 12 - loglen), logcols);
+    while (logC > 2 && ((int64_t)1 << (logcols - logC)) * B < 256) --logC;
+    return logC;
+}
+static dim3 step_threads(int logpoints) { return dim3((unsigned)std::min(1024, std::max(256, 1 << logpoints >> 2))); }
+
 // Real rows of 2 H = 2^(logn+1) samples, H beyond one LDS transform, from their half
 // spectra (pitch ip): the packed spectrum's inverse FFT, four-step through scratch
 // (pitch H).
@@ -1381,21 +1397,20 @@ static void irfft_four_step(const float2* in, int64_t ip, float2* out, float2* s
     // n = P Q: input index a + P*bq (a < P columns, bq < Q), output k_b + Q*k_a
     const int lq = (logn + 1) / 2, lp = logn - lq;
     const int64_t Pn = (int64_t)1 << lp, Qn = (int64_t)1 << lq, n = (int64_t)1 << logn;
-    int logC = std::min(std::max(0, 12 - lq), lp);
+    int logC = step_cols(lq, lp, B);
     size_t lds = (size_t)(1 << logC) * (lpad_len(Qn) + 1) * sizeof(float2);
-    hipLaunchKernelGGL((k_fft_cols_t<float2, float2, true>), dim3((unsigned)(Pn >> logC), (unsigned)B), dim3(1024), lds,
-                       st, in, scratch, lq, (int)Pn, logC, ip, (int64_t)1, Pn, n, Qn, (int64_t)1, logn, P->tw,
-                       P->tw_log, 1, 1.0f);
-    logC = std::min(std::max(0, 12 - lp), lq);
+    hipLaunchKernelGGL((k_fft_cols_t<float2, float2, true>), dim3((unsigned)(Pn >> logC), (unsigned)B),
+                       step_threads(lq + logC), lds, st, in, scratch, lq, (int)Pn, logC, ip, (int64_t)1, Pn, n, Qn,
+                       (int64_t)1, logn, P->tw, P->tw_log, 1, 1.0f);
+    logC = step_cols(lp, lq, B);
     lds = (size_t)(1 << logC) * (lpad_len(Pn) + 1) * sizeof(float2);
-    hipLaunchKernelGGL((k_fft_cols), dim3((unsigned)(Qn >> logC), (unsigned)B), dim3(1024), lds, st, scratch, out, lp,
-                       (int)Qn, logC, n, (int64_t)1, Qn, n, (int64_t)1, Qn, 0, P->tw, P->tw_log, 1, scale);
+    hipLaunchKernelGGL((k_fft_cols), dim3((unsigned)(Qn >> logC), (unsigned)B), step_threads(lp + logC), lds, st, scratch,
+                       out, lp, (int)Qn, logC, n, (int64_t)1, Qn, n, (int64_t)1, Qn, 0, P->tw, P->tw_log, 1, scale);
 }
 
 // Real FFT of the B input rows (N samples) in FP64: the complex FFT of the N/2
-// interleaved pairs (one LDS transform up to 2^13 points, four-step above, the
-// double-precision rows being twice as large), then the real-spectrum
-// post-pass, which rounds each bin once to FP32.  Every later stage works on
+// interleaved pairs (one LDS transform up to 2^kOneRowLog points, four-step above),
+// then the real-spectrum post-pass, which rounds each bin once to FP32.  Every later stage works on
 // bands of x_hat, so the only transform that mixes all bands keeps its error
 // below FP32 rounding of each bin (not of the whole spectrum).
 static void input_fft64(const float* x, int64_t B, float2* xh, int64_t xh_pitch, double2* scratch, double2* z,
@@ -1403,27 +1418,25 @@ static void input_fft64(const float* x, int64_t B, float2* xh, int64_t xh_pitch,
     const int logn = P->s.logN - 1;
     const int64_t H = (int64_t)1 << logn;
     const float2* in = (const float2*)x;
-    if (logn <= 13) {
-        const int logC = logn >= 12 ? 0 : 12 - logn;
+    if (logn <= kOneRowLog) {
+        const int logC = 12 - logn;
         const size_t lds = (size_t)(1 << logC) * (lpad_len(H) + 1) * sizeof(double2);
         hipLaunchKernelGGL(k_rfft64_rows, dim3((unsigned)((B + (1 << logC) - 1) >> logC)), dim3(1024), lds, st, in, (int)B,
                            logn, logC, xh, xh_pitch, P->tw64, P->tw_log);
         return;
     }
-    {
-        const int lq = (logn + 1) / 2, lp = logn - lq;
-        const int64_t Pn = (int64_t)1 << lp, Qn = (int64_t)1 << lq;
-        int logC = std::min(std::max(0, 12 - lq), lp);
-        size_t lds = (size_t)(1 << logC) * (lpad_len(Qn) + 1) * sizeof(double2);
-        hipLaunchKernelGGL((k_fft_cols_t<float2, double2>), dim3((unsigned)(Pn >> logC), (unsigned)B), dim3(1024), lds,
-                           st, in, scratch, lq, (int)Pn, logC, H, (int64_t)1, Pn, H, Qn, (int64_t)1, logn, P->tw64,
-                           P->tw_log, 0, 1.0);
-        logC = std::min(std::max(0, 12 - lp), lq);
-        lds = (size_t)(1 << logC) * (lpad_len(Pn) + 1) * sizeof(double2);
-        hipLaunchKernelGGL((k_fft_cols_t<double2, double2>), dim3((unsigned)(Qn >> logC), (unsigned)B), dim3(1024), lds,
-                           st, scratch, z, lp, (int)Qn, logC, H, (int64_t)1, Qn, H, (int64_t)1, Qn, 0, P->tw64,
-                           P->tw_log, 0, 1.0);
-    }
+    const int lq = (logn + 1) / 2, lp = logn - lq;
+    const int64_t Pn = (int64_t)1 << lp, Qn = (int64_t)1 << lq;
+    int logC = step_cols(lq, lp, B);
+    size_t lds = (size_t)(1 << logC) * (lpad_len(Qn) + 1) * sizeof(double2);
+    hipLaunchKernelGGL((k_fft_cols_t<float2, double2>), dim3((unsigned)(Pn >> logC), (unsigned)B), step_threads(lq + logC),
+                       lds, st, in, scratch, lq, (int)Pn, logC, H, (int64_t)1, Pn, H, Qn, (int64_t)1, logn, P->tw64,
+                       P->tw_log, 0, 1.0);
+    logC = step_cols(lp, lq, B);
+    lds = (size_t)(1 << logC) * (lpad_len(Pn) + 1) * sizeof(double2);
+    hipLaunchKernelGGL((k_fft_cols_t<double2, double2>), dim3((unsigned)(Qn >> logC), (unsigned)B), step_threads(lp + logC),
+                       lds, st, scratch, z, lp, (int)Qn, logC, H, (int64_t)1, Qn, H, (int64_t)1, Qn, 0, P->tw64,
+                       P->tw_log, 0, 1.0);
     hipLaunchKernelGGL(k_rfft_post64, dim3((unsigned)((H / 2 + 1 + 255) / 256), (unsigned)B), dim3(256), 0, st, z, H,
                        xh, xh_pitch, P->s.logN, P->tw64, P->tw_log);
 }
@@ -1809,8 +1822,8 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
                        s.logNX, P->psi1, P->band1, P->off1, P->lam_range, Hn, gxh, w.xh_pitch));
     LAUNCHCHK("band accumulation");
     const int logH = s.logN - 1;
-    if (logH <= kLdsFftMax) {
-        const int logC = logH >= 12 ? 0 : 12 - logH;
+    if (logH <= kOneRowLog) {
+        const int logC = 12 - logH;
         const size_t lds = (size_t)(1 << logC) * (lpad_len(Hn) + 1) * sizeof(float2);
         JTFS_TIMED(JTFS_STAGE_OUTPUT_FFT, st, hipLaunchKernelGGL(k_irfft_rows, dim3((unsigned)((B + (1 << logC) - 1) >> logC)), dim3(1024), lds, st,
                            gxh, w.xh_pitch, (int)B, logH, logC, (float2*)gx, 1.0f / (float)s.N, P->tw, P->tw_log));

@@ -26,7 +26,6 @@ constexpr int kTileT = 64;         // frequential GEMM: columns (t) per tile
 constexpr int kTileTh = 128;       // split-FP16 contraction: columns (t) per tile (t padding unit)
 constexpr int kKStep = 16;         // frequential GEMM: K (lambda_1) per LDS stage
 constexpr int kChunkT = 4096;      // frequential GEMM: t-range reduced by one workgroup
-constexpr int kLdsFftMax = 14;     // log2 of the largest complex FFT held in LDS
 constexpr int kMaxLogNX = 15;      // longest scalogram row
 constexpr int kRegMinLogRows = 14; // shortest row length (log2) with a register-resident kernel
 constexpr int kMaxDynLds = 159 * 1024;  // dynamic LDS limit set on kernels (1 KB left for static LDS)

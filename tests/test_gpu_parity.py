@@ -1037,6 +1037,22 @@ def test_frequency_lowpass_column_blocks(T):
     assert rel_l2(a[47], O.jtfs(x[47].astype(np.float64), oracle_plan(p))[1]) <= TOL
 
 
+@pytest.mark.parametrize("logN", [12, 13, 14])
+def test_input_and_output_transform_splits(logN):
+    """The longest row transformed in one launch, the shortest in four steps, and the next: one signal takes four
+    columns a workgroup of the steps, a batch of 70 more; each signal's bits, and the oracle's values."""
+    p = dict(N=2 ** logN, J=7, Q=(4, 1), J_fr=2, Q_fr=1, T=256, F=2)
+    P = oracle_plan(p)
+    x = synth.batch(5, B=70, N=p["N"])
+    gs1, gs2 = synth.cotangents((70,) + P.s1_shape(), (70,) + P.s2_shape())
+    op = gpu_op(p, "split16")
+    run = lambda i: op.vjp(*(torch.from_numpy(a[i]).cuda() for a in (x, gs1, gs2))).cpu().numpy()
+    g = run(slice(0, 70))
+    for b in (0, 69):
+        assert np.array_equal(run(slice(b, b + 1))[0], g[b])
+    assert rel_l2(g[69], O.jtfs_vjp(x[69].astype(np.float64), gs1[69], gs2[69], P)) <= TOL_VJP
+
+
 LONG_ROWS = [dict(N=2 ** 16, J=12, Q=(16, 1), J_fr=4, Q_fr=1, T=2 ** 11, F=8),      # rows of 2^14: rates 2^14, 2^13, shorter
              dict(N=2 ** 17, J=13, Q=(12, 2), J_fr=4, Q_fr=1, T=2 ** 13, F=8),      # 2^15: even and odd samples; two rates each
              dict(N=2 ** 16, J=12, Q=(16, 1), J_fr=4, Q_fr=1, T=2 ** 10, F=8)]      # 64 frames
