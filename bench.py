@@ -147,12 +147,13 @@ def algorithmic_bytes(info, N, shapes, B):
     gX = 4 * n1 * NX
     g1 = 8 * n1 * NX
     # (S1 and the band accumulation read only band-limited bins of their inputs;
-    # their mandatory bytes depend on the filter supports and they are not listed)
+    # their mandatory bytes depend on the filter supports and they are not listed;
+    # nor are the row FFTs of gY2, of which the second-order adjoint takes the long
+    # rows in)
     per = {
         "input_fft": 4 * N + xh,
         "scalogram": xh + Xh,
         "second_order": Xh + Y2,
-        "second_adj_fft": 2 * Y2,
         "second_adj": Y2 + S1 + gX,
         "first_adj": xh + gX + g1,
         "output_fft": xh + 4 * N,
@@ -166,10 +167,10 @@ def algorithmic_bytes(info, N, shapes, B):
 # Keyed by (stage, contraction mode, tile of that stage's kernel).
 TRAFFIC_KERNELS = {("freq_fwd", "split16", 32): "k_freq_fwd_h", ("freq_adj_pq", "split16", 32): "k_freq_bwd_h",
                    ("freq_fwd", "split16_phase", 32): "k_freq_fwd_h_phase",
-                   ("freq_adj_pq", "split16_phase", 32): "k_freq_bwd_p",
+                   ("freq_adj_pq", "split16_phase", 32): "k_freq_bwd_f",
                    ("freq_fwd", "split16", 16): "k_freq_fwd_q",
                    ("freq_fwd", "split16_phase", 16): "k_freq_fwd_q_phase",
-                   ("freq_adj_pq", "split16_phase", 16): "k_freq_bwd_q"}
+                   ("freq_adj_pq", "split16_phase", 16): "k_freq_bwd_f"}
 TRAFFIC_SOURCE = "paper_2204_08269_amd/csrc/split.hip"
 
 

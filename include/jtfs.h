@@ -375,8 +375,9 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * 32 x 32 contraction tiles and once with all four in LDS and 16 x 16 tiles in
  * the forward (where these choices exist).  It
  * keeps the contraction whose own stages took least time (each contraction
- * kernel with its faster tile), per stage the faster transform, and the faster
- * tiles, then times the result (step_ms).  With the
+ * kernel with its faster tile), per stage the faster transform (one choice for the
+ * gY2 row FFTs and the first-order adjoint, which share kernels), and the faster
+ * tile, then times the result (step_ms).  With the
  * environment variable JTFS_TUNE_CACHE naming a file, a result is appended to it
  * under a key of the device's architecture and name, the plan parameters and B,
  * and a later call with the same key applies the stored choice without timing
@@ -391,9 +392,9 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * sets the mode with jtfs_plan_set_tuning instead).  candidates_ms: fwd+bwd per step of
  * (split, first run), (split, second run), (FP32, first), (FP32, second), (split with
  * stored phase, first), (split with stored phase, second); 0 for candidates not run.
- * fwd_ms, bwd_ms: the chosen mode's forward contraction and backward contraction
- * per step with 32 x 32 and 16 x 16 tiles (0 where not run).  Then, for the chosen
- * mode and tiles, one run with every register-resident stage in radix-8 passes
+ * fwd_ms: the chosen mode's forward contraction per step with 32 x 32 and 16 x 16
+ * tiles (0 where not run); bwd_ms[0]: its backward contraction (one kernel; bwd_ms[1]
+ * is 0).  Then, for the chosen mode and tile, one run with every register-resident stage in radix-8 passes
  * (where rows of 2^14 points or more exist), one with 8192-point in-LDS
  * workgroups (where rows of 2^12 points or fewer exist) and one with 1024-column
  * t-chunks in the forward contraction (where a rate has more than 1024 columns)
@@ -448,7 +449,7 @@ int jtfs_plan_get_tuning(const jtfs_plan* plan, int* contraction, int* reg_rows)
  * stage.  Process-wide; thread-safe.  Disabled by default (no events recorded). */
 #define JTFS_STAGE_INPUT_FFT      0  /* real FFT of x                                    */
 #define JTFS_STAGE_SCALOGRAM      1  /* first order: fold, iFFT, modulus, real FFT of X   */
-#define JTFS_STAGE_S1             2  /* (no launch of its own: S1 is part of SECOND_ORDER)   */
+#define JTFS_STAGE_S1             2  /* (no launches: part of SECOND_ORDER)               */
 #define JTFS_STAGE_SECOND_ORDER   3  /* second-order temporal wavelets -> Y2              */
 #define JTFS_STAGE_OPERAND_SPLIT  4  /* Y2 -> scaled FP16 halves (split contraction only) */
 #define JTFS_STAGE_FREQ_FWD       5  /* frequential contraction + modulus + time lowpass  */
@@ -457,7 +458,8 @@ int jtfs_plan_get_tuning(const jtfs_plan* plan, int* contraction, int* reg_rows)
 #define JTFS_STAGE_FREQ_ADJ_PQ    8  /* contraction recompute, lowpass and modulus adj.
                                         (split mode: also the W^H product)                */
 #define JTFS_STAGE_FREQ_ADJ_WH    9  /* adjoint of the contraction (W^H), FP32 mode       */
-#define JTFS_STAGE_SECOND_ADJ_FFT 10 /* forward FFT of the gY2 rows                       */
+#define JTFS_STAGE_SECOND_ADJ_FFT 10 /* forward FFT of the gY2 rows (long ones: part of
+                                        SECOND_ADJ where both are register-resident)      */
 #define JTFS_STAGE_SECOND_ADJ     11 /* second-order and S1 adjoints -> gX                */
 #define JTFS_STAGE_FIRST_ADJ      12 /* modulus adjoint and FFT of each first-order row   */
 #define JTFS_STAGE_BAND_ACCUM     13 /* band-limited accumulation over lambda1 -> gx_hat  */
