@@ -1763,11 +1763,12 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
         if (rc != JTFS_OK) { if (rc == JTFS_EHIP) set_error("gV split launch failed"); return rc; }
     }
     if (split) {
-        // every temporal rate in one launch (from the phase, one or two, each timed on its own)
+        // every temporal rate in one launch
         if (from_phase) {
-            rc = launch_freq_bwd_phase(P, (const unsigned*)(base + w.phase), w.ph_bstride,
-                                       (const uint4*)(base + w.gvs), w.gvs_bstride, (const float*)(base + w.gvmax),
-                                       gY2, B, st);
+            JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st,
+                       rc = launch_freq_bwd_phase(P, (const unsigned*)(base + w.phase), w.ph_bstride,
+                                                  (const uint4*)(base + w.gvs), w.gvs_bstride,
+                                                  (const float*)(base + w.gvmax), gY2, B, st));
         } else {
             JTFS_TIMED(JTFS_STAGE_FREQ_ADJ_PQ, st,
                        rc = launch_freq_bwd_split(P, Yh, ysc, gV, (const float*)(base + w.gvmax), gY2, B, st));

@@ -1053,6 +1053,26 @@ def test_input_and_output_transform_splits(logN):
     assert rel_l2(g[69], O.jtfs_vjp(x[69].astype(np.float64), gs1[69], gs2[69], P)) <= TOL_VJP
 
 
+@pytest.mark.parametrize("mode", ["split16", "split16_phase", "fp32"])
+def test_every_contraction_launch_is_timed(mode):
+    """The stage timers, from which the tuner chooses the mode, hold a forward and a backward contraction."""
+    from paper_2204_08269_amd import _lib
+    op = gpu_op(P1, mode)
+    x = torch.from_numpy(synth.batch(1, B=2)).cuda()
+    ws = op.new_workspace(2)
+    s1, s2 = op.forward(x, ws)
+    _lib.timing_enable(True)
+    try:
+        op.forward(x, ws)
+        op.vjp(x, s1, s2, ws=ws, reuse_forward=True)
+        torch.cuda.synchronize()
+        t = _lib.timing_read()
+    finally:
+        _lib.timing_enable(False)
+    for stage in ("freq_fwd", "freq_adj_pq"):
+        assert t[stage][1] >= 1 and t[stage][0] > 0, (stage, t)
+
+
 LONG_ROWS = [dict(N=2 ** 16, J=12, Q=(16, 1), J_fr=4, Q_fr=1, T=2 ** 11, F=8),      # rows of 2^14: rates 2^14, 2^13, shorter
              dict(N=2 ** 17, J=13, Q=(12, 2), J_fr=4, Q_fr=1, T=2 ** 13, F=8),      # 2^15: even and odd samples; two rates each
              dict(N=2 ** 16, J=12, Q=(16, 1), J_fr=4, Q_fr=1, T=2 ** 10, F=8)]      # 64 frames
