@@ -239,6 +239,7 @@ __device__ __forceinline__ unsigned pack_snorm16(float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_i16(a, b));
 }
 constexpr float kSnormInv = 1.f / 32767.f;
+constexpr float kMinNormal = 1.17549435e-38f;   // the least FP32 number the hardware's reciprocal root takes
 
 // ------------------------------------------------------- forward contraction
 
@@ -302,7 +303,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
     float eps2s = 0.f;
     if (phase) {
         const double wy = (double)sw * (double)yscale[b * n_alpha + alpha];
-        eps2s = (float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), 1.1754943508222875e-38);
+        eps2s = (float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), (double)kMinNormal);
     }
     floatx16 vu[NTB], vd[NTB];
 #pragma unroll
@@ -620,10 +621,10 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     }
     const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
     if (phase) phase += rate.phase_off;
-    float eps2s;                             // the floor of |z|^2 in the scaled units of Z
-    {
+    float inv_eps = 0.f;                     // 1 / (floor of |z| in the phase), in the scaled units of Z
+    if (phase) {
         const double wy = (double)sw * (double)yscale[b * n_alpha + alpha];
-        eps2s = (float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), 1.1754943508222875e-38);
+        inv_eps = __builtin_amdgcn_rsqf((float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), (double)kMinNormal));
     }
     floatx4 vacc[NTQ][4][2];
 #pragma unroll
@@ -714,16 +715,18 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
             for (int lb = 0; lb < 4; ++lb) {
                 float uv[4];
                 float m = 0.f;
-                // |z| = |z|^2 rsq(|z|^2), with the reciprocal square root that the phase
-                // uses (below the floor eps^2, |z|^2 / eps < eps: nothing the lowpass sees)
+                // |z| = |z|^2 rsq(|z|^2), floored at the smallest normal number alone; the
+                // phase takes the same reciprocal root, at most 1 / eps.  (The gradient's
+                // guard eps in the modulus itself made S2 quadratic below |z| = 1e-18.)
                 float qn[4], zrs[4], zis[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float zr = spin ? rr[lb][r] + ii[lb][r] : rr[lb][r] - ii[lb][r];
                     const float zi = spin ? ir[lb][r] - ri[lb][r] : ir[lb][r] + ri[lb][r];
                     const float m2 = zr * zr + zi * zi;
-                    qn[r] = __builtin_amdgcn_rsqf(fmaxf(m2, eps2s));
-                    uv[r] = m2 * qn[r];
+                    const float q = __builtin_amdgcn_rsqf(fmaxf(m2, kMinNormal));
+                    uv[r] = m2 * q;
+                    qn[r] = fminf(q, inv_eps);
                     zrs[r] = zr;
                     zis[r] = zi;
                     m = fmaxf(m, uv[r]);
@@ -1088,7 +1091,7 @@ __global__ void __launch_bounds__(256) k_freq_bwd_h(const unsigned short* __rest
     const float spq = pow2_scale(2.f * G * 16384.f / sphi);
     const float sy = yscale[b * n_alpha + alpha];
     const double wy = (double)sw * (double)sy;
-    const float eps2s = (float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), 1.1754943508222875e-38);
+    const float eps2s = (float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), (double)kMinNormal);
     const float ips = spq / sphi;
 
     floatx16 gyr[NI], gyi[NI];

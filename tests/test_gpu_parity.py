@@ -1162,3 +1162,25 @@ def test_time_scattering_frame_counts(T):
         assert e1.max() <= TOL and e2.max() <= TOL
         assert rel_l2(gx[b], O.scattering1d_vjp(xb, g1[b], g2[b], P)) <= TOL_VJP
         assert rel_l2(g0[b], O.scattering1d_vjp(xb, g1[b], np.zeros_like(g2[b]), P)) <= TOL_VJP
+
+
+@pytest.mark.parametrize("mode", ["split16", "split16_phase"])
+@pytest.mark.parametrize("T", [2 ** 11, 2 ** 10], ids=["frames16", "frames32"])
+def test_small_amplitudes_scale(T, mode):
+    """Signals whose second-order coefficients lie far below the gradient's guard (|z| = 1e-18), by the plan's own
+    forward tile (16 columns at 16 frames, 32 at 32) and by each that is set. S(a x) = a S(x) at a = 2^-54: every
+    operation scales exactly by a power of two but for squares that underflow, and those of the first-order moduli (N
+    times the modulus is squared) stay 20 orders above 2^-126, so 1e-6 in norm is far more than is lost. At 2^-66 those
+    squares do underflow in part, before the contraction: there the two tiles have to agree, as they do at any other
+    amplitude (the same products, summed over other waves: 2e-6)."""
+    p = dict(N=2 ** 15, J=11, Q=(16, 1), J_fr=4, Q_fr=2, T=T, F=8)
+    x = synth.batch(5, B=2, N=p["N"])
+    op = gpu_op(p, mode)
+    tiny = []
+    for tile in (None, 32, 16):
+        if tile:
+            op.set_tuning(mode, ALL_ROWS, fwd_tile=tile)
+        for r, s in zip(run_forward(op, x), run_forward(op, x * np.float32(2.0 ** -54))):
+            assert rel_l2(s.astype(np.float64) * 2.0 ** 54, r) <= 1e-6
+        tiny.append(run_forward(op, x * np.float32(2.0 ** -66))[1].astype(np.float64) * 2.0 ** 66)
+    assert rel_l2(tiny[2], tiny[1]) <= 2e-6 and rel_l2(tiny[0], tiny[1]) <= 2e-6
