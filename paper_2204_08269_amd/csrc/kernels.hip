@@ -921,24 +921,19 @@ __device__ __forceinline__ float group_sum(float a, int width) {
     return a;
 }
 
-// gV[b][alpha][theta][rowoff+l][tau] = sum_m PF_beta[m][l] gS2[b][alpha][beta][theta][m][tau]
-// (adjoint of the frequency lowpass), or with avg = 0 (eq. (4)) the gS2 row
-// itself; block n_beta zeroes the padding rows.
-// Also writes, per (signal, alpha, spin, beta), the largest row sum over tau of
-// |gV| (a bound used to scale the split backward contraction).
-// Adjoint of the frequency lowpass: gV[l][tau] = sum_m PF[m][l] gS2[m][tau] (or
-// gS2 itself without frequential averaging), with the per-row sums of |gV| whose
-// maximum sets the split scale of the backward contraction.  The gS2 tile and,
-// with stage_pf, PF are held in LDS; row sums are reduced across the lanes of a
-// row before one LDS atomic per row segment.
-__global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, const float* __restrict__ PFall,
-                                                const int64_t* __restrict__ pfoff, const int* __restrict__ Lbv,
+// Eq. (4), whose gV is the gS2 row itself: gV[b][alpha][theta][slot of row l][tau] =
+// gS2[b][alpha][2 rowoff + theta Lb + l][tau] (after the mu-log adjoint when set), zero
+// for tau >= N/T; block n_beta of the grid (n_beta + 1, 2 n_alpha, B) zeroes the padding
+// rows.  Also writes, per (signal, alpha, spin, beta), the largest row sum over tau of
+// |gV| (a bound used to scale the split backward contraction): the sums of a row's
+// lanes are reduced by a cross-lane sum before one LDS atomic per row segment.  LDS
+// holds the Lb row sums alone.
+__global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, const int* __restrict__ Lbv,
                                                 const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
-                                                const int* __restrict__ pad, int n_beta, int NL, int NLo, int NT, int NTp,
-                                                int Mh, int Mp, int n_alpha, int avg, int stage_pf,
+                                                const int* __restrict__ pad, int n_beta, int NT, int NTp,
+                                                int Mh, int Mp, int n_alpha,
                                                 float* __restrict__ gV, float* __restrict__ gvmax, MuLogArg ml) {
-    extern __shared__ float sm[];      // rowsum [Lb] | gS2 tile [NL][NT] | (stage_pf) PF [NL][Lb]
-    // grid (n_beta + 1, 2 n_alpha, B): every temporal rate in one launch
+    extern __shared__ float rowsum[];
     const int beta = blockIdx.x, th = blockIdx.y & 1, alpha = blockIdx.y >> 1;
     const int64_t b = blockIdx.z;
     float* g = gV + (((b * n_alpha + alpha) * 2 + th) * (int64_t)Mp) * NTp;
@@ -947,22 +942,11 @@ __global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, c
         return;
     }
     const int Lb = Lbv[beta], ro = rowoffv[beta];
-    float* rowsum = sm;
-    float* st = sm + Lb;
-    float* pf = st + NL * NT;
-    const float* PF = PFall + pfoff[beta];
-    const int64_t so = avg ? ((((b * n_alpha + alpha) * n_beta + beta) * 2 + th) * NLo) * (int64_t)NT
-                           : ((b * n_alpha + alpha) * 2 * (int64_t)Mh + 2 * ro + th * Lb) * NT;
+    const int64_t so = ((b * n_alpha + alpha) * 2 * (int64_t)Mh + 2 * ro + th * Lb) * NT;
     const float* src = gS2 ? gS2 + so : nullptr;
     const float* osrc = ml.mu2 ? ml.o2 + so : nullptr;
     const float em = ml.mu2 ? ml.eps * ml.mu2[(alpha * n_beta + beta) * 2 + th] : 0.f;
     for (int l = threadIdx.x; l < Lb; l += blockDim.x) rowsum[l] = 0.f;
-    if (src && avg) {
-        for (int e = threadIdx.x; e < NLo * NT; e += blockDim.x)
-            st[e] = mulog_cot(src[e], ml.mu2, em, osrc ? osrc[e] : 0.f);
-        if (stage_pf)
-            for (int e = threadIdx.x; e < NL * Lb; e += blockDim.x) pf[e] = PF[e];
-    }
     __syncthreads();
     const int width = NTp < 64 ? NTp : 64;           // lanes of one row segment within a wave
     for (int e0 = 0; e0 < Lb * NTp; e0 += blockDim.x) {
@@ -970,14 +954,8 @@ __global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, c
         const bool valid = e < Lb * NTp;
         const int l = e / NTp, tau = e - l * NTp;
         float acc = 0.f;
-        if (valid && src && tau < NT) {
-            if (avg) {
-                const float* pc = stage_pf ? pf + l : PF + l;
-                for (int m = 0; m < NLo; ++m) acc += pc[m * Lb] * st[m * NT + tau];
-            } else {
-                acc = mulog_cot(src[(int64_t)l * NT + tau], ml.mu2, em, osrc ? osrc[(int64_t)l * NT + tau] : 0.f);
-            }
-        }
+        if (valid && src && tau < NT)
+            acc = mulog_cot(src[(int64_t)l * NT + tau], ml.mu2, em, osrc ? osrc[(int64_t)l * NT + tau] : 0.f);
         if (valid) g[(int64_t)rowpos[ro + l] * NTp + tau] = acc;
         float a = fabsf(acc);
         a = group_sum(a, width);
@@ -1341,15 +1319,6 @@ __global__ void __launch_bounds__(256) k_band_accum(const float2* __restrict__ g
 // ---------------------------------------------------------------------------
 // Launch helpers
 // ---------------------------------------------------------------------------
-// LDS of the frequency lowpass and its adjoint: V tile (or row sums and the gS2
-// tile), and the PF matrix when all of it fits kS2LdsCap (then held in LDS)
-constexpr size_t kS2LdsCap = 96 * 1024;
-static size_t s2_bwd_floats(const Shapes& s, bool stage) {
-    return (size_t)s.L + (size_t)s.NL * s.NT + (stage ? (size_t)s.NL * s.L : 0);
-}
-static int s2_bwd_stage(const Shapes& s) { return sizeof(float) * s2_bwd_floats(s, true) <= kS2LdsCap ? 1 : 0; }
-static size_t s2_bwd_lds(const Shapes& s) { return sizeof(float) * s2_bwd_floats(s, s2_bwd_stage(s)); }
-
 static bool g_attr_done = false;
 
 int setup_kernel_attributes() {
@@ -1357,7 +1326,7 @@ int setup_kernel_attributes() {
     const int lds = kMaxDynLds;
     const void* ks[] = {(const void*)k_fft_cols_t<float2, float2>, (const void*)k_fft_cols_t<float2, float2, true>, (const void*)k_fft_cols_t<float2, double2>,
                         (const void*)k_fft_cols_t<double2, double2>, (const void*)k_scalogram, (const void*)k_rfft64_rows, (const void*)k_irfft_rows,
-                        (const void*)k_s2_bwd, (const void*)k_s2_bwd_avg<16>, (const void*)k_s2_bwd_avg<32>,
+                        (const void*)k_s2_bwd_avg<16>, (const void*)k_s2_bwd_avg<32>,
                         (const void*)k_second_order, (const void*)k_rowfft_short, (const void*)k_scal_bwd_a, (const void*)k_scal_bwd_b};
     for (const void* k : ks) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1731,9 +1700,9 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
                                P->PF, P->d_pfoff, P->d_Lb, P->d_rowoff, P->d_rowpos, P->d_pad, s.n_beta, s.NLo, s.NT, s.NTp, s.Mh, s.Mp,
                                s.n_alpha, gV, (float*)(base + w.gvmax), ml));
         } else {
-            JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k_s2_bwd, grid, dim3(256), s2_bwd_lds(s), st, gs2, P->PF, P->d_pfoff, P->d_Lb,
-                               P->d_rowoff, P->d_rowpos, P->d_pad, s.n_beta, s.NL, s.NLo, s.NT, s.NTp, s.Mh, s.Mp, s.n_alpha, (int)s.avg_fr,
-                               s2_bwd_stage(s), gV, (float*)(base + w.gvmax), ml));
+            JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k_s2_bwd, grid, dim3(256), sizeof(float) * s.L, st, gs2, P->d_Lb,
+                               P->d_rowoff, P->d_rowpos, P->d_pad, s.n_beta, s.NT, s.NTp, s.Mh, s.Mp, s.n_alpha,
+                               gV, (float*)(base + w.gvmax), ml));
         }
         LAUNCHCHK("frequency lowpass adjoint");
     }

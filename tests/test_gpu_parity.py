@@ -1184,3 +1184,20 @@ def test_small_amplitudes_scale(T, mode):
             assert rel_l2(s.astype(np.float64) * 2.0 ** 54, r) <= 1e-6
         tiny.append(run_forward(op, x * np.float32(2.0 ** -66))[1].astype(np.float64) * 2.0 ** 66)
     assert rel_l2(tiny[2], tiny[1]) <= 2e-6 and rel_l2(tiny[0], tiny[1]) <= 2e-6
+
+
+def test_many_frames_and_rows_unaveraged():
+    """Eq. (4) at 128 frames and L = 512 rows without decimation (F = 1): the gradient against the oracle's VJP, and a
+    null second-order cotangent. Every gV row is a copy of its cotangent, so TOL_VJP is the FP32 contraction's."""
+    p = dict(N=2 ** 12, J=9, Q=(44, 1), J_fr=3, Q_fr=1, T=2 ** 5, F=1)
+    P = oracle_plan(p)
+    assert P.L == 512 and P.out_t == 128
+    x = synth.batch(5, B=2, N=p["N"])
+    op = gpu_op(p, average_fr=False)
+    gs1, gs2 = synth.cotangents((2,) + P.s1_shape(), (2,) + P.s2_shape(False), seed=12)
+    xt, g1, g2 = (torch.from_numpy(v).cuda() for v in (x, gs1, gs2))
+    gx, g0 = op.vjp(xt, g1, g2).cpu().numpy(), op.vjp(xt, g1, None).cpu().numpy()
+    for b in range(2):
+        xb = x[b].astype(np.float64)
+        assert rel_l2(gx[b], O.jtfs_vjp(xb, gs1[b], gs2[b], P, average_fr=False)) <= TOL_VJP
+        assert rel_l2(g0[b], O.jtfs_vjp(xb, gs1[b], np.zeros_like(gs2[b]), P, average_fr=False)) <= TOL_VJP
