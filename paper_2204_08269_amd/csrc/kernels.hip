@@ -976,16 +976,18 @@ __global__ void __launch_bounds__(256) k_s2_bwd(const float* __restrict__ gS2, c
 // set) sits in LDS and every lane reads the same element of it at a time (a
 // broadcast), PF[m][l] comes from global memory with consecutive lanes on
 // consecutive l, and each lane keeps TT outputs of its row in registers, stores
-// them as 16-byte writes and sums their moduli itself.  grid (n_beta + 1,
-// 2 n_alpha, B); block n_beta zeroes the padding rows Mh..Mp.
+// them as 16-byte writes and sums their moduli itself.  The tile holds all N/T frames
+// where they fit the LDS limit, else TT of them at a time (cols), with the rows' sums
+// so far in LDS behind it.  grid (n_beta + 1, 2 n_alpha, B); block n_beta zeroes the
+// padding rows.
 template <int TT>
 __global__ void __launch_bounds__(256) k_s2_bwd_avg(const float* __restrict__ gS2, const float* __restrict__ PFall,
                                                     const int64_t* __restrict__ pfoff, const int* __restrict__ Lbv,
                                                     const int* __restrict__ rowoffv, const int* __restrict__ rowpos,
                                                     const int* __restrict__ pad, int n_beta, int NLo, int NT,
-                                                    int NTp, int Mh, int Mp, int n_alpha, float* __restrict__ gV,
-                                                    float* __restrict__ gvmax, MuLogArg ml) {
-    extern __shared__ __align__(16) float st[];      // gS2 tile [NLo][NT]
+                                                    int NTp, int cols, int Mh, int Mp, int n_alpha,
+                                                    float* __restrict__ gV, float* __restrict__ gvmax, MuLogArg ml) {
+    extern __shared__ __align__(16) float st[];      // gS2 tile [NLo][cols] | (cols < NT) sums [Lb]
     __shared__ float red[256];
     const int beta = blockIdx.x, th = blockIdx.y & 1, alpha = blockIdx.y >> 1;
     const int64_t b = blockIdx.z;
@@ -1000,48 +1002,56 @@ __global__ void __launch_bounds__(256) k_s2_bwd_avg(const float* __restrict__ gS
     const float* src = gS2 ? gS2 + so : nullptr;
     const float* osrc = ml.mu2 ? ml.o2 + so : nullptr;
     const float em = ml.mu2 ? ml.eps * ml.mu2[(alpha * n_beta + beta) * 2 + th] : 0.f;
-    for (int e = threadIdx.x; e < NLo * NT; e += blockDim.x)
-        st[e] = src ? mulog_cot(src[e], ml.mu2, em, osrc ? osrc[e] : 0.f) : 0.f;
-    __syncthreads();
+    float* sums = st + NLo * cols;
     float mx = 0.f;
-    for (int l = threadIdx.x; l < Lb; l += blockDim.x) {
-        float* grow = g + (int64_t)rowpos[ro + l] * NTp;
-        float rs = 0.f;
-        for (int t0 = 0; t0 < NTp; t0 += TT) {
-            float acc[TT];
+    for (int c0 = 0; c0 < NT; c0 += cols) {
+        const bool last = c0 + cols >= NT;
+        if (c0) __syncthreads();                     // the tile before is read
+        for (int e = threadIdx.x; e < NLo * cols; e += blockDim.x) {
+            const int i = cols == NT ? e : e / cols * NT + c0 + e % cols;
+            st[e] = src ? mulog_cot(src[i], ml.mu2, em, osrc ? osrc[i] : 0.f) : 0.f;
+        }
+        __syncthreads();
+        for (int l = threadIdx.x; l < Lb; l += blockDim.x) {
+            float* grow = g + (int64_t)rowpos[ro + l] * NTp;
+            float rs = c0 ? sums[l] : 0.f;
+            for (int t0 = c0; t0 < (last ? NTp : c0 + cols); t0 += TT) {
+                float acc[TT];
 #pragma unroll
-            for (int j = 0; j < TT; ++j) acc[j] = 0.f;
-            if (t0 < NT) {
-                if (NT - t0 >= TT) {
-                    for (int m = 0; m < NLo; ++m) {
-                        const float p = PF[(int64_t)m * Lb + l];
-                        const float4* s4 = (const float4*)(st + m * NT + t0);
+                for (int j = 0; j < TT; ++j) acc[j] = 0.f;
+                if (t0 < NT) {
+                    if (NT - t0 >= TT) {
+                        for (int m = 0; m < NLo; ++m) {
+                            const float p = PF[(int64_t)m * Lb + l];
+                            const float4* s4 = (const float4*)(st + m * cols + t0 - c0);
 #pragma unroll
-                        for (int q = 0; q < TT / 4; ++q) {
-                            const float4 v = s4[q];
-                            acc[4 * q] += p * v.x;
-                            acc[4 * q + 1] += p * v.y;
-                            acc[4 * q + 2] += p * v.z;
-                            acc[4 * q + 3] += p * v.w;
+                            for (int q = 0; q < TT / 4; ++q) {
+                                const float4 v = s4[q];
+                                acc[4 * q] += p * v.x;
+                                acc[4 * q + 1] += p * v.y;
+                                acc[4 * q + 2] += p * v.z;
+                                acc[4 * q + 3] += p * v.w;
+                            }
+                        }
+                    } else {
+                        for (int m = 0; m < NLo; ++m) {
+                            const float p = PF[(int64_t)m * Lb + l];
+#pragma unroll
+                            for (int j = 0; j < TT; ++j)
+                                if (t0 + j < NT) acc[j] += p * st[m * cols + t0 - c0 + j];
                         }
                     }
-                } else {
-                    for (int m = 0; m < NLo; ++m) {
-                        const float p = PF[(int64_t)m * Lb + l];
+                }
+                float4* o4 = (float4*)(grow + t0);
 #pragma unroll
-                        for (int j = 0; j < TT; ++j)
-                            if (t0 + j < NT) acc[j] += p * st[m * NT + t0 + j];
-                    }
+                for (int q = 0; q < TT / 4; ++q) {
+                    o4[q] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+                    rs += fabsf(acc[4 * q]) + fabsf(acc[4 * q + 1]) + fabsf(acc[4 * q + 2]) + fabsf(acc[4 * q + 3]);
                 }
             }
-            float4* o4 = (float4*)(grow + t0);
-#pragma unroll
-            for (int q = 0; q < TT / 4; ++q) {
-                o4[q] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-                rs += fabsf(acc[4 * q]) + fabsf(acc[4 * q + 1]) + fabsf(acc[4 * q + 2]) + fabsf(acc[4 * q + 3]);
-            }
+            if (last) mx = fmaxf(mx, rs);
+            else sums[l] = rs;                       // (this thread's row in every pass)
         }
-        mx = fmaxf(mx, rs);
     }
     red[threadIdx.x] = mx;
     __syncthreads();
@@ -1696,8 +1706,11 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
         const dim3 grid(s.n_beta + 1, 2 * s.n_alpha, (unsigned)B);
         if (s.avg_fr) {
             auto k = s.NTp % 32 == 0 && s.NT >= 32 ? k_s2_bwd_avg<32> : k_s2_bwd_avg<16>;
-            JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k, grid, dim3(256), sizeof(float) * s.NLo * s.NT, st, gs2,
-                               P->PF, P->d_pfoff, P->d_Lb, P->d_rowoff, P->d_rowpos, P->d_pad, s.n_beta, s.NLo, s.NT, s.NTp, s.Mh, s.Mp,
+            const size_t whole = sizeof(float) * s.NLo * s.NT;
+            const int cols = whole <= (size_t)kMaxDynLds ? s.NT : 32;
+            const size_t lds = cols == s.NT ? whole : sizeof(float) * (s.NLo * 32 + s.L);
+            JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k, grid, dim3(256), lds, st, gs2,
+                               P->PF, P->d_pfoff, P->d_Lb, P->d_rowoff, P->d_rowpos, P->d_pad, s.n_beta, s.NLo, s.NT, s.NTp, cols, s.Mh, s.Mp,
                                s.n_alpha, gV, (float*)(base + w.gvmax), ml));
         } else {
             JTFS_TIMED(JTFS_STAGE_LOWPASS_ADJ, st, hipLaunchKernelGGL(k_s2_bwd, grid, dim3(256), sizeof(float) * s.L, st, gs2, P->d_Lb,

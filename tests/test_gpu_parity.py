@@ -1201,3 +1201,21 @@ def test_many_frames_and_rows_unaveraged():
         xb = x[b].astype(np.float64)
         assert rel_l2(gx[b], O.jtfs_vjp(xb, gs1[b], gs2[b], P, average_fr=False)) <= TOL_VJP
         assert rel_l2(g0[b], O.jtfs_vjp(xb, gs1[b], np.zeros_like(gs2[b]), P, average_fr=False)) <= TOL_VJP
+
+
+@pytest.mark.parametrize("Q", [44, 30], ids=["rows512", "rows256"])
+def test_many_frames_and_rows_averaged(Q):
+    """Eq. (3) at 128 frames and F = 1: 512 rows, whose cotangent tile passes the LDS limit and goes 32 frames at a
+    time, and 256, whose tile fits whole. The lowpass adjoint is a sum of at most 2^9 FP32 products: TOL_VJP."""
+    p = dict(N=2 ** 12, J=9, Q=(Q, 1), J_fr=3, Q_fr=1, T=2 ** 5, F=1)
+    P = oracle_plan(p)
+    assert P.L == (512 if Q == 44 else 256) and P.out_t == 128
+    x = synth.batch(5, B=2, N=p["N"])
+    gs1, gs2 = synth.cotangents((2,) + P.s1_shape(), (2,) + P.s2_shape(), seed=13)
+    op = gpu_op(p)
+    xt, g1, g2 = (torch.from_numpy(v).cuda() for v in (x, gs1, gs2))
+    gx, g0 = op.vjp(xt, g1, g2).cpu().numpy(), op.vjp(xt, g1, None).cpu().numpy()
+    for b in range(2):
+        xb = x[b].astype(np.float64)
+        assert rel_l2(gx[b], O.jtfs_vjp(xb, gs1[b], gs2[b], P)) <= TOL_VJP
+        assert rel_l2(g0[b], O.jtfs_vjp(xb, gs1[b], np.zeros_like(gs2[b]), P)) <= TOL_VJP
