@@ -167,7 +167,7 @@ def algorithmic_bytes(info, N, shapes, B):
 # Keyed by (stage, contraction mode, tile of that stage's kernel).
 TRAFFIC_KERNELS = {("freq_fwd", "split16", 32): "k_freq_fwd_h", ("freq_adj_pq", "split16", 32): "k_freq_bwd_h",
                    ("freq_fwd", "split16_phase", 32): "k_freq_fwd_h_phase",
-                   ("freq_adj_pq", "split16_phase", 32): "k_freq_bwd_f",
+                   ("freq_adj_pq", "split16_phase", 32): "k_freq_bwd_p",
                    ("freq_fwd", "split16", 16): "k_freq_fwd_q",
                    ("freq_fwd", "split16_phase", 16): "k_freq_fwd_q_phase",
                    ("freq_adj_pq", "split16_phase", 16): "k_freq_bwd_f"}
@@ -455,7 +455,8 @@ def rooflines(res, steps):
             out[k] = {"bound": "mfma", "achieved": round(a, 2), "peak": peak, "unit": "TFLOP/s",
                       "frac": round(a / peak, 4),
                       "dtype": "f16 operands (hi/lo split, 3 products), f32 accumulate" if on_split else "f32"}
-            if on_split and not (k == "freq_adj_pq" and mode == "split16_phase"):   # (folded: about half of its products run)
+            # (folded, in 16 x 16 tiles: about half of the products run)
+            if on_split and not (k == "freq_adj_pq" and mode == "split16_phase" and res["tiles"][1] == 16):
                 out[k]["executed_frac"] = round(3 * a / peak, 4)
         elif k in nbytes:
             a = nbytes[k] * steps / (ms * 1e-3) / 1e9

@@ -372,12 +372,12 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * contraction).  jtfs_plan_autotune runs, for B signals x (device, [B][N]; NULL:
  * zeros), one untimed and `reps` timed fwd+bwd steps per candidate: each
  * available contraction mode, once with all four stages register-resident and
- * 32 x 32 contraction tiles and once with all four in LDS and 16 x 16 tiles in
- * the forward (where these choices exist).  It
+ * 32 x 32 contraction tiles and once with all four in LDS, 16 x 16 tiles in
+ * the forward and the folded stored-phase backward (where these choices exist).  It
  * keeps the contraction whose own stages took least time (each contraction
  * kernel with its faster tile), per stage the faster transform (one choice for the
  * gY2 row FFTs and the first-order adjoint, which share kernels), and the faster
- * tile, then times the result (step_ms).  With the
+ * tiles, then times the result (step_ms).  With the
  * environment variable JTFS_TUNE_CACHE naming a file, a result is appended to it
  * under a key of the device's architecture and name, the plan parameters and B,
  * and a later call with the same key applies the stored choice without timing
@@ -392,9 +392,8 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * sets the mode with jtfs_plan_set_tuning instead).  candidates_ms: fwd+bwd per step of
  * (split, first run), (split, second run), (FP32, first), (FP32, second), (split with
  * stored phase, first), (split with stored phase, second); 0 for candidates not run.
- * fwd_ms: the chosen mode's forward contraction per step with 32 x 32 and 16 x 16
- * tiles (0 where not run); bwd_ms[0]: its backward contraction (one kernel; bwd_ms[1]
- * is 0).  Then, for the chosen mode and tile, one run with every register-resident stage in radix-8 passes
+ * fwd_ms, bwd_ms: the chosen mode's forward and backward contraction per step with
+ * 32 x 32 and 16 x 16 tiles (0 where not run).  Then, for the chosen mode and tiles, one run with every register-resident stage in radix-8 passes
  * (where rows of 2^14 points or more exist), one with 8192-point in-LDS
  * workgroups (where rows of 2^12 points or fewer exist) and one with 1024-column
  * t-chunks in the forward contraction (where a rate has more than 1024 columns)
@@ -407,8 +406,11 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * wave 64 rows l x 16 columns t; available where N/T <= 32), else 32 x 32 tiles.
  * Until launch choices are set or tuned, a plan takes the tile by a rule on its shapes. */
 #define JTFS_TUNE_FWD_TILE16  16
-/* ... accepted and reported back, without effect: the stored-phase backward has one
- * kernel (16 x 16 tiles, folded along log-frequency) for every shape. */
+/* ... and the stored-phase backward folded along log-frequency, in 16 x 16 tiles, else
+ * every product in 32 x 32 tiles.  Folding halves the products, and costs accuracy
+ * where the gradient is weak: a column of gY2 is then half the sum or the difference
+ * of two, so that it carries the rounding of its mirror image (lambda -> c - lambda)
+ * as well.  Until launch choices are set or tuned, a plan folds by a rule on its shapes. */
 #define JTFS_TUNE_BWD_TILE16  32
 /* ... the largest radix of the register-resident row transforms' passes, per
  * stage: radix 8 where the bit is set, else radix 16 (every pass of a 2^14-point

@@ -2,7 +2,8 @@
 //
 // Candidates: the contraction arithmetic (split FP16, split FP16 with the phase
 // stored by the forward, or FP32 matrix cores); the tile of the split forward
-// contraction (32 x 32 or 16 x 16 MFMA tiles); and, for rows of 2^14 points, the
+// contraction (32 x 32 or 16 x 16 MFMA tiles); the kernel of the stored-phase backward
+// (every product in 32 x 32 tiles, or folded in 16 x 16 ones); and, for rows of 2^14 points, the
 // register-resident or the in-LDS transform in each of the four stages that have
 // both (scalogram, second order, gY2 row FFTs and first-order adjoint together).  Every
 // candidate runs whole fwd+bwd steps; the per-stage HIP-event timers attribute
@@ -46,6 +47,7 @@ void set_rows(jtfs_plan* P, int mask) {
     P->tune.reg_first_adj = (mask & JTFS_REG_FIRST_ADJ) != 0;
     P->tune.fwd_auto = false;
     P->tune.fwd16 = (mask & JTFS_TUNE_FWD_TILE16) != 0;
+    P->tune.bwd_auto = false;
     P->tune.bwd16 = (mask & JTFS_TUNE_BWD_TILE16) != 0;
     P->tune.r8_scalogram = (mask & JTFS_TUNE_RADIX8_SCALOGRAM) != 0;
     P->tune.r8_second = (mask & JTFS_TUNE_RADIX8_SECOND_ORDER) != 0;
@@ -68,7 +70,9 @@ int get_rows(const jtfs_plan* P) {
            ((P->tune.fwd_auto ? fwd_tile16(P, P->contraction == JTFS_CONTRACTION_SPLIT_F16_PHASE) : P->tune.fwd16)
                 ? JTFS_TUNE_FWD_TILE16
                 : 0) |
-           (P->tune.bwd16 ? JTFS_TUNE_BWD_TILE16 : 0) |
+           ((P->tune.bwd_auto ? P->contraction == JTFS_CONTRACTION_SPLIT_F16_PHASE && bwd_folded(P) : P->tune.bwd16)
+                ? JTFS_TUNE_BWD_TILE16
+                : 0) |
            (P->tune.r8_scalogram ? JTFS_TUNE_RADIX8_SCALOGRAM : 0) |
            (P->tune.r8_second ? JTFS_TUNE_RADIX8_SECOND_ORDER : 0) | (P->tune.r8_rowfft ? JTFS_TUNE_RADIX8_ROW_FFT : 0) |
            (P->tune.r8_first_adj ? JTFS_TUNE_RADIX8_FIRST_ADJ : 0) | (P->tune.batch8k ? JTFS_TUNE_LDS_BATCH8K : 0) |
@@ -194,10 +198,11 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     std::memset(out, 0, sizeof(*out));
     const Shapes& s = P->s;
     const int saved_mode = P->contraction, saved_rows = get_rows(P);
-    const bool saved_auto = P->tune.fwd_auto;
+    const bool saved_fwd_auto = P->tune.fwd_auto, saved_bwd_auto = P->tune.bwd_auto;
     auto restore_rows = [&]() {
         set_rows(P, saved_rows);
-        P->tune.fwd_auto = saved_auto;
+        P->tune.fwd_auto = saved_fwd_auto;
+        P->tune.bwd_auto = saved_bwd_auto;
     };
     const std::string key = cache_key(P, B);
     {
@@ -235,10 +240,14 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     for (int a = 0; a < s.n_alpha_psi; ++a)
         has14 = has14 || (s.logNX - s.k2[a] <= kRegMinLogRows && s.logNX - s.k2[a] >= kRegMinLogRows - 3);
     const int all_rows = JTFS_REG_SCALOGRAM | JTFS_REG_SECOND_ORDER | JTFS_REG_ROW_FFT | JTFS_REG_FIRST_ADJ;
-    // second run: rows in LDS and the 16 x 16 contraction tiles, where any of these choices exists
+    // second run: rows in LDS, the 16 x 16 tiles of the forward contraction and the folded
+    // stored-phase backward, where any of these choices exists
     const bool tile16 = P->split_ok && !s.tscat && fwdq_supported(P, false);
+    const bool btile16 = P->split_ok && P->split_bwdp_ok && !s.tscat;
     std::vector<int> row_opts{all_rows};
-    if (has14 || tile16) row_opts.push_back((has14 ? 0 : all_rows) | (tile16 ? JTFS_TUNE_FWD_TILE16 : 0));
+    if (has14 || tile16 || btile16)
+        row_opts.push_back((has14 ? 0 : all_rows) | (tile16 ? JTFS_TUNE_FWD_TILE16 : 0) |
+                           (btile16 ? JTFS_TUNE_BWD_TILE16 : 0));
     // buffers: the largest workspace over the modes (at the shortest t-chunk, whose
     // partial V is largest); the coefficients double as cotangents
     size_t wsb = 0;
@@ -295,11 +304,14 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
         return tile16 && row_opts.size() == 2 && modes[mi] != JTFS_CONTRACTION_FP32 &&
                fwdq_supported(P, modes[mi] == JTFS_CONTRACTION_SPLIT_F16_PHASE);
     };
+    auto btile_ok = [&](size_t mi) { return btile16 && modes[mi] == JTFS_CONTRACTION_SPLIT_F16_PHASE; };
     size_t best_m = 0;
     double best_c = 1e300;
+    bool buse16 = false;                   // (a choice of the stored-phase mode, whichever mode is kept)
     for (size_t mi = 0; mi < modes.size(); ++mi) {
         double c = tile_ok(mi) ? std::min(fwd_ms(mi, 0), fwd_ms(mi, 1)) : fwd_ms(mi, 0);
-        c += bwd_ms(mi, 0);
+        c += btile_ok(mi) ? std::min(bwd_ms(mi, 0), bwd_ms(mi, 1)) : bwd_ms(mi, 0);
+        if (btile_ok(mi)) buse16 = bwd_ms(mi, 1) < bwd_ms(mi, 0);
         for (int k : cstages) c += stage[mi][0][k];
         if (c < best_c) { best_c = c; best_m = mi; }
     }
@@ -307,7 +319,7 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     out->fwd_ms[0] = fwd_ms(best_m, 0);
     out->fwd_ms[1] = tile_ok(best_m) ? fwd_ms(best_m, 1) : 0.0;
     out->bwd_ms[0] = bwd_ms(best_m, 0);
-    out->bwd_ms[1] = 0.0;                  // one kernel per mode
+    out->bwd_ms[1] = btile_ok(best_m) ? bwd_ms(best_m, 1) : 0.0;
     // rows of 2^14 points: per stage, the faster of the two runs of the chosen mode
     int rows = all_rows;
     if (has14) {
@@ -325,6 +337,7 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
         if (adj(0) <= adj(1)) rows |= JTFS_REG_ROW_FFT | JTFS_REG_FIRST_ADJ;
     }
     if (use16) rows |= JTFS_TUNE_FWD_TILE16;
+    if (buse16) rows |= JTFS_TUNE_BWD_TILE16;
     P->contraction = modes[best_m];
     set_rows(P, rows);
     auto fail = [&](int rc) {

@@ -123,7 +123,8 @@ struct Tuning {
     bool reg_first_adj = true;   // first-order adjoint rows of 2^14 points
     bool fwd_auto = true;        // tile of the forward contraction by rule (fwd_tile16), until one is set
     bool fwd16 = false;          // forward contraction in 16 x 16 tiles (else 32 x 32), as set
-    bool bwd16 = false;          // (accepted and reported back: the stored-phase backward has one kernel)
+    bool bwd_auto = true;        // kernel of the stored-phase backward by rule (bwd_folded), until one is set
+    bool bwd16 = false;          // the folded one in 16 x 16 tiles (else every product, in 32 x 32 tiles), as set
     // register-resident rows: radix-8 passes instead of radix-16 ones, per stage
     bool r8_scalogram = false, r8_second = false, r8_rowfft = false, r8_first_adj = false;
     bool batch8k = false;        // in-LDS row transforms: 8192 points per workgroup (else 4096)

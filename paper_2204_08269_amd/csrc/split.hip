@@ -1207,7 +1207,7 @@ __device__ __forceinline__ void split2(float v0, float v1, unsigned& hp, unsigne
 
 // Scheduling hint for a half: NM groups of one MFMA followed by NV VALU
 // instructions, so that the vector work of the next rows issues while the matrix
-// cores work (one wave per SIMD: nothing else would fill those cycles).
+// cores work.
 template <int NM, int NV>
 __device__ __forceinline__ void interleave_mfma_valu() {
 #pragma unroll
@@ -1215,6 +1215,310 @@ __device__ __forceinline__ void interleave_mfma_valu() {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x002, NV, 0);
     }
+}
+
+// Chunk c of the split gV into LDS (all 256 threads; lane order = source order).
+template <int NTB>
+__device__ __forceinline__ void stage_g(uint4* Ls, const uint4* Gb, int c, int tid) {
+    const uint4* src = Gb + (int64_t)c * gvs_chunk<NTB>();
+    uint4* dst = Ls + 64 * (tid >> 6);
+#pragma unroll
+    for (int k = 0; k < 2 * NTB; ++k) dma16(src + 256 * k, (uint32_t)tid * 16u, dst + 256 * k);
+    if (tid < 16) dma16(src + 512 * NTB, (uint32_t)tid * 16u, Ls + 512 * NTB);
+}
+
+// Stored unit phase of rows crow(r, h), r = 8 s .. 8 s + 7 (g = 2 s, 2 s + 1), of one
+// 32-row block, this lane's column t, both spins: one 16-byte load (four rows) per
+// (spin, g); a wave's load is one contiguous 1 KB run.  pcol points at element 4 h
+// of the lane's column in row group 0 of the block of spin 0; row groups are
+// g_stride elements apart.
+__device__ __forceinline__ void load_phase_half(uint4 (&pv)[2][4], int s, gptr<uint4> pcol, int64_t spin_stride,
+                                                int64_t g_stride) {
+#pragma unroll
+    for (int spin = 0; spin < 2; ++spin)
+#pragma unroll
+        for (int gg = 0; gg < 2; ++gg) {
+            const int g = 2 * s + gg;
+            gptr<u32x4> p = (gptr<u32x4>)(pcol + (spin * spin_stride + g * g_stride) / 4);   // element offsets, % 4 = 0
+            pv[spin][g] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(p));   // read once
+        }
+}
+
+// the two snorm16 of row crow(r, h) as integers in [-32767, 32767] (real, imaginary)
+__device__ __forceinline__ float2 phase_at(const uint4 (&pv)[2][4], int spin, int r) {
+    const uint4 q = pv[spin][r >> 2];
+    const unsigned w = (r & 3) == 0 ? q.x : (r & 3) == 1 ? q.y : (r & 3) == 2 ? q.z : q.w;
+    return make_float2((float)(int)(short)(w & 0xffffu), (float)((int)w >> 16));
+}
+
+// gU = gV Phi^T of one chunk for both spins (A operand from the split gV in LDS, Phi
+// pre-split in registers); each row then scaled by its 2^-se times c0 (the scale of
+// P and Q' over the snorm16 unit of the phase).
+template <int NTB>
+__device__ __forceinline__ void gu_chunk(const uint4* Lg, const uint4 (&phv)[NTB * 2][2], int h, int i32, float c0,
+                                         floatx16 (&gu)[2]) {
+    const float4* rs = (const float4*)(Lg + 512 * NTB);
+#pragma unroll
+    for (int spin = 0; spin < 2; ++spin) {
+        floatx16 acc = z16();
+#pragma unroll
+        for (int kb = 0; kb < NTB * 2; ++kb) {
+            const half8 ah = as_h8(Lg[(((spin * 2 * NTB + kb) * 2 + 0) * 2 + h) * 32 + i32]);
+            const half8 al = as_h8(Lg[(((spin * 2 * NTB + kb) * 2 + 1) * 2 + h) * 32 + i32]);
+            const half8 bh = as_h8(phv[kb][0]), bl = as_h8(phv[kb][1]);
+            acc = mfma16(ah, bh, acc);
+            acc = mfma16(ah, bl, acc);
+            acc = mfma16(al, bh, acc);
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 q = rs[spin * 8 + 2 * g + h];        // rows 8 g + 4 h .. + 3
+            acc[4 * g + 0] *= q.x * c0;
+            acc[4 * g + 1] *= q.y * c0;
+            acc[4 * g + 2] *= q.z * c0;
+            acc[4 * g + 3] *= q.w * c0;
+        }
+        gu[spin] = acc;
+    }
+}
+
+// Modulus adjoint of row pairs 8 s + 2 p0 .. 8 s + 2 p1 - 1 from the scaled gU and
+// the stored phase: P and Q', split into FP16 hi / lo (lanes r - 8 s of ph[s],
+// pl[s]).
+__device__ __forceinline__ void modadj_pairs(int s, int p0, int p1, const floatx16 (&gu)[2], const uint4 (&pv)[2][4],
+                                             half8 (&ph)[2][4], half8 (&pl)[2][4]) {
+#pragma unroll
+    for (int pr = 0; pr < 4; ++pr) {
+        if (pr < p0 || pr >= p1) continue;
+        float vals[2][4];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int r = 8 * s + 2 * pr + e;
+            const float2 u = phase_at(pv, 0, r), d = phase_at(pv, 1, r);
+            const float su = gu[0][r], sd = gu[1][r];
+            vals[e][0] = su * u.x + sd * d.x;
+            vals[e][1] = su * u.y + sd * d.y;
+            vals[e][2] = su * u.y - sd * d.y;
+            vals[e][3] = sd * d.x - su * u.x;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            unsigned hp, lp;
+            split2(vals[0][q], vals[1][q], hp, lp);
+            uint4 hv = __builtin_bit_cast(uint4, ph[s][q]), lv = __builtin_bit_cast(uint4, pl[s][q]);
+            if (pr == 0) { hv.x = hp; lv.x = lp; }
+            else if (pr == 1) { hv.y = hp; lv.y = lp; }
+            else if (pr == 2) { hv.z = hp; lv.z = lp; }
+            else { hv.w = hp; lv.w = lp; }
+            ph[s][q] = __builtin_bit_cast(half8, hv);
+            pl[s][q] = __builtin_bit_cast(half8, lv);
+        }
+    }
+}
+__device__ __forceinline__ void modadj_half(int s, const floatx16 (&gu)[2], const uint4 (&pv)[2][4],
+                                            half8 (&ph)[2][4], half8 (&pl)[2][4]) {
+    modadj_pairs(s, 0, 4, gu, pv, ph, pl);
+}
+
+// W^T fragments (hi, lo of Wr and Wi) of i-blocks q0 and q0 + 1 (clamped to q0 past
+// NI) for the rows of half sp of the staged chunk.
+struct WtFrag {
+    half8 wr[2][2], wi[2][2];             // [block][hi, lo]
+};
+template <int NI>
+__device__ __forceinline__ void load_wt(WtFrag& f, const uint4* Tcur, int sp, int q0, int h, int i32) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const int q = q0 + d < NI ? q0 + d : q0;
+        const uint4* lt = Tcur + (q * 16 + (sp * 2 + h) * 4) * 32 + i32;
+        f.wr[d][0] = as_h8(lt[0]); f.wr[d][1] = as_h8(lt[32]);
+        f.wi[d][0] = as_h8(lt[64]); f.wi[d][1] = as_h8(lt[96]);
+    }
+}
+
+// gY[q0], gY[q0 + 1] += Wr^T P + Wi^T Q' over the rows of half sp: the two i-blocks
+// alternate, so that four accumulations are in flight.
+template <int NI>
+__device__ __forceinline__ void mma_group(const WtFrag& f, int sp, int q0, const half8 (&ph)[2][4],
+                                          const half8 (&pl)[2][4], floatx16 (&gyr)[NI], floatx16 (&gyi)[NI]) {
+#pragma unroll
+    for (int term = 0; term < 6; ++term) {
+        const int wsel = term < 3 ? 0 : 1, whl = (term % 3) == 2 ? 1 : 0, phl = (term % 3) == 1 ? 1 : 0;
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            if (q0 + d >= NI) continue;
+            const half8 a = wsel ? f.wi[d][whl] : f.wr[d][whl];
+            const half8 br = phl ? pl[sp][wsel * 2] : ph[sp][wsel * 2];
+            const half8 bi = phl ? pl[sp][wsel * 2 + 1] : ph[sp][wsel * 2 + 1];
+            gyr[q0 + d] = mfma16(a, br, gyr[q0 + d]);
+            gyi[q0 + d] = mfma16(a, bi, gyi[q0 + d]);
+        }
+    }
+}
+
+// Values a half produces for the next half are pinned before its barrier (an empty
+// asm that reads and writes them), so that the compiler cannot sink their
+// arithmetic past the barrier into the next half, where it would not overlap with
+// matrix work.
+__device__ __forceinline__ void pin_pq(half8 (&ph)[2][4], half8 (&pl)[2][4], int s) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(ph[s][q]), "+v"(pl[s][q]));
+}
+__device__ __forceinline__ void pin_gu(floatx16 (&gu)[2]) {
+    asm volatile("" : "+v"(gu[0]), "+v"(gu[1]));
+}
+
+// One 32-row chunk c in two halves.  On entry: P/Q' of rows 0-15 in ph/pl[0], gU of
+// the chunk (scaled) in gu, the phase of rows 16-31 in pv[.][2..3], W^T of the chunk
+// in Tcur.  First half: the W^T product over rows 0-15 while the modulus adjoint of
+// rows 16-31 runs; the next chunk's W^T, split gV and phase of rows 0-15 are
+// requested at its start.  Second half: the product over rows 16-31 while gU of the
+// next chunk and the modulus adjoint of its rows 0-15 run; the phase of its rows
+// 16-31 is requested at its start.  Each half ends with a full wait and a barrier,
+// so every request has a half chunk of matrix work to land.  Within a half, each
+// pair of i-blocks is one scheduling region: the W^T fragments of the next pair are
+// read from LDS at its top (they land while its products run) and a share of the
+// rows' modulus adjoint is interleaved with its products.
+template <int NTB, int NI>
+__device__ __forceinline__ void bwd_phase_chunk(int c, int nC, int wave, int lane, int tid, int h, int i32,
+                                                const uint4 (&phv)[NTB * 2][2], const uint4* Tsrc, const uint4* Gb,
+                                                uint4* Ls_G, const unsigned* pbase, int64_t spin_stride,
+                                                int64_t c_stride, float c0, int64_t cstride, const uint4* Tcur,
+                                                uint4* Tnext,
+                                                floatx16 (&gyr)[NI], floatx16 (&gyi)[NI], floatx16 (&gu)[2],
+                                                uint4 (&pv)[2][4], half8 (&ph)[2][4], half8 (&pl)[2][4]) {
+    constexpr int NG = (NI + 1) / 2;             // pairs of i-blocks
+    const int cn = c + 1 < nC ? c + 1 : c;       // the last chunk reloads itself
+    WtFrag f[2];
+    // ---- first half
+    stage_t<NI>(Tnext, Tsrc, cn, cstride, wave, lane);
+    stage_g<NTB>(Ls_G, Gb, cn, tid);
+    load_phase_half(pv, 0, launder_v((const uint4*)(pbase + cn * c_stride)), spin_stride, c_stride / 4);
+    load_wt<NI>(f[0], Tcur, 0, 0, h, i32);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        if (g + 1 < NG) load_wt<NI>(f[(g + 1) & 1], Tcur, 0, 2 * (g + 1), h, i32);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_group<NI>(f[g & 1], 0, 2 * g, ph, pl, gyr, gyi);
+        modadj_pairs(1, g * 4 / NG, (g + 1) * 4 / NG, gu, pv, ph, pl);
+        interleave_mfma_valu<24, 4>();
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    pin_pq(ph, pl, 1);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    // ---- second half
+    load_phase_half(pv, 1, launder_v((const uint4*)(pbase + cn * c_stride)), spin_stride, c_stride / 4);
+    load_wt<NI>(f[0], Tcur, 1, 0, h, i32);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        if (g + 1 < NG) load_wt<NI>(f[(g + 1) & 1], Tcur, 1, 2 * (g + 1), h, i32);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_group<NI>(f[g & 1], 1, 2 * g, ph, pl, gyr, gyi);
+        if (g == 0) {
+            gu_chunk<NTB>(Ls_G, phv, h, i32, c0, gu);
+            if (NG == 1) modadj_pairs(0, 0, 4, gu, pv, ph, pl);
+            interleave_mfma_valu<24 + 6 * NTB, 2>();
+        } else {
+            modadj_pairs(0, (g - 1) * 4 / (NG - 1), g * 4 / (NG - 1), gu, pv, ph, pl);
+            interleave_mfma_valu<24, 5>();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    pin_pq(ph, pl, 0);
+    pin_gu(gu);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+}
+
+// Backward contraction from the stored phase: one signal, 128 columns t (four
+// waves of 32), all rows l in 32-row chunks; gY accumulated in registers for the
+// NI i-blocks q_base .. q_base + NI - 1 of the nit blocks of W^T (the register
+// budget holds at most 8 at 32 frames; larger K runs as several launches over
+// disjoint i-ranges, each repeating the modulus adjoint).  Every product of the
+// contraction runs, so that a column gY[i] carries the rounding of its own terms alone.
+template <int NTB, int NI>
+__global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__ phase, int64_t ph_bstride,
+                                                    const FreqRate* __restrict__ rates,
+                                                    const FreqUnit* __restrict__ tiles, int nT, int nU,
+                                                    const unsigned short* __restrict__ WTsp, int q_base, int nit,
+                                                    int Mp, int Kp, const unsigned short* __restrict__ PhTsp,
+                                                    const uint4* __restrict__ Gs, int64_t gs_bstride,
+                                                    const float* __restrict__ gvmax, int n_beta,
+                                                    int n_alpha, float sw, float2* __restrict__ gY,
+                                                    int64_t gy_bstride) {
+    constexpr int NTp = 32 * NTB;
+    __shared__ uint4 Ls_T0[NI * 512];
+    __shared__ uint4 Ls_T1[NI * 512];
+    __shared__ uint4 Ls_G[gvs_chunk<NTB>()];
+    const int u = blockIdx.x;
+    if (u >= nU) return;                            // whole block
+    const int64_t b = u / nT;
+    const FreqUnit un = tiles[u % nT];
+    const FreqRate rate = rates[un.alpha];
+    const int alpha = un.alpha, t0 = un.t0, Tp = rate.Tp;
+    const float sphi = rate.sphi;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int h = lane >> 5, i32 = lane & 31;
+    const int tw0 = t0 + wave * 32;                 // this wave's columns
+    const int nC = Mp / 32;
+
+    float G = 0.f;
+    for (int q = 0; q < 2 * n_beta; ++q) G = fmaxf(G, gvmax[(b * n_alpha + alpha) * 2 * n_beta + q]);
+    const float spq = pow2_scale(2.f * G * 16384.f / sphi);
+    const float c0 = spq / sphi * kSnormInv;
+
+    floatx16 gyr[NI], gyi[NI];
+#pragma unroll
+    for (int q = 0; q < NI; ++q) { gyr[q] = z16(); gyi[q] = z16(); }
+
+    const uint4* phrow = (const uint4*)(PhTsp + rate.phioff * 2 + ((int64_t)(tw0 + i32) * (NTp / 8) + h) * 16);
+    const uint4* Tsrc = (const uint4*)WTsp + (int64_t)q_base * 512;
+    const int64_t cstride = (int64_t)nit * 512;
+    const uint4* Gb = Gs + b * gs_bstride + (int64_t)alpha * (Mp / 32) * gvs_chunk<NTB>();
+    // this lane's column of the stored phase, rows 4h.. of each 8-row group
+    // (blocks [spin][Mp / 32], each four row groups of Tp x 8 elements)
+    const unsigned* pbase = phase + b * ph_bstride + rate.phase_off + (int64_t)(tw0 + i32) * 8 + 4 * h;
+    const int64_t spin_stride = (int64_t)Tp * Mp, c_stride = (int64_t)Tp * 32;
+
+    uint4 phv[NTB * 2][2];
+#pragma unroll
+    for (int kb = 0; kb < NTB * 2; ++kb) {
+        phv[kb][0] = phrow[4 * kb];
+        phv[kb][1] = phrow[4 * kb + 1];
+    }
+    uint4 pv[2][4];
+    floatx16 gu[2];
+    half8 ph[2][4], pl[2][4];
+    // chunk 0: operands, gU and the P/Q' of its rows 0-15
+    stage_t<NI>(Ls_T0, Tsrc, 0, cstride, wave, lane);
+    stage_g<NTB>(Ls_G, Gb, 0, tid);
+    load_phase_half(pv, 0, (gptr<uint4>)pbase, spin_stride, c_stride / 4);
+    load_phase_half(pv, 1, (gptr<uint4>)pbase, spin_stride, c_stride / 4);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    gu_chunk<NTB>(Ls_G, phv, h, i32, c0, gu);
+    modadj_half(0, gu, pv, ph, pl);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    // nC is even (Mp is a multiple of 64): the W^T buffers alternate at compile time
+    for (int c = 0; c < nC; c += 2) {
+        bwd_phase_chunk<NTB, NI>(c, nC, wave, lane, tid, h, i32, phv, Tsrc, Gb, Ls_G, pbase, spin_stride, c_stride,
+                                 c0, cstride, Ls_T0, Ls_T1, gyr, gyi, gu, pv, ph, pl);
+        bwd_phase_chunk<NTB, NI>(c + 1, nC, wave, lane, tid, h, i32, phv, Tsrc, Gb, Ls_G, pbase, spin_stride,
+                                 c_stride, c0, cstride, Ls_T1, Ls_T0, gyr, gyi, gu, pv, ph, pl);
+    }
+    const float inv = 1.f / (sw * spq);
+    float2* o = gY + b * gy_bstride + rate.yoff;
+#pragma unroll
+    for (int q = 0; q < NI; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int i = (q_base + q) * 32 + crow(r, h);
+            if (i < Kp) o[(int64_t)i * Tp + tw0 + i32] = make_float2(gyr[q][r] * inv, gyi[q][r] * inv);
+        }
 }
 
 // ------------------- backward from the stored phase, folded along lambda
@@ -1437,10 +1741,10 @@ __device__ __forceinline__ void bwdf_half(const uint4* Lt, const uint4* Lg, int 
 // Every copy thus has half a pass of products to land, the arrays read in a half are
 // never the ones being filled (so the compiler adds no wait for the copies before
 // those reads), and nothing requested into registers is used before the next
-// barrier.  Two waves per SIMD overlap one's vector work with the other's products;
-// the kernel before had one wave per SIMD and all the products, and its matrix
-// cores were busy half of the time.  32 x 2^18 (n1 = 285): 55 -> 39 ms per step;
-// 16 x 2^16 (n1 = 167) fwd+bwd 9.36 -> 9.00 ms.
+// barrier.  Two waves per SIMD overlap one's vector work with the other's products
+// (with all the products, on one wave per SIMD, the matrix cores are busy half of the
+// time).  Against k_freq_bwd_p: 55 -> 36 ms for 32 x 2^18 (n1 = 285), 2.89 -> 2.57 for
+// 16 x 2^16 (n1 = 167, 16 frames); bwd_folded has the others.
 template <int NTB, int NS, bool SHORT>
 __global__ void __launch_bounds__(512) k_freq_bwd_f(const unsigned* __restrict__ phase, int64_t ph_bstride,
                                                     const FreqRate* __restrict__ rates,
@@ -1688,8 +1992,9 @@ int build_split_tables(jtfs_plan* P, std::vector<void*>& owned) {
         // recomputing backward: static LDS of a W chunk and two W^T chunks, 24 NI KB
         // (<= 160 KB), and one wave per SIMD without scratch
         P->split_bwd_ok = (s.NTp == 32 && NI <= 6) || (s.NTp == 64 && NI <= 5);
-        // (the stored-phase backward holds whatever the forward holds with its phase
-        // transpose area beside the resident W tile: n1 <= 288, so NS <= kMaxFoldNS)
+        // (both stored-phase backwards hold whatever the forward holds with its phase
+        // transpose area beside the resident W tile: n1 <= 288, so NS <= kMaxFoldNS and
+        // at most two ranges of i-blocks)
     }
     P->contraction = JTFS_CONTRACTION_SPLIT_F16;
     return JTFS_OK;
@@ -1871,6 +2176,36 @@ int launch_freq_bwd_split(const jtfs_plan* P, const unsigned short* Yh, const fl
     return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
 }
 
+// i-blocks one phase-backward workgroup holds in registers (one wave per SIMD): 8 at
+// 32 frames (12 bytes of scratch, without below), 5 at 64
+static int bwdp_max_ni(int NTp) { return NTp == 32 ? 8 : NTp == 64 ? 5 : 0; }
+
+template <int NTB>
+static void launch_bwdp_ni(int NI, int q_base, int nit, dim3 grid, hipStream_t st, const unsigned* phase, int64_t phb,
+                           int nT, const jtfs_plan* P, const uint4* Gs, int64_t gsb, const float* gvmax, float2* gY) {
+    const Shapes& s = P->s;
+    const int64_t yb = (int64_t)s.Kp * s.sumTp;
+#define JTFS_BWDP_CASE(ni)                                                                                       \
+    case ni:                                                                                                     \
+        hipLaunchKernelGGL((k_freq_bwd_p<NTB, ni>), grid, dim3(256), 0, st, phase, phb, P->d_rates, P->d_tiles, \
+                           nT, (int)grid.x, P->WTsp, q_base, nit, s.Mp, s.Kp, P->PhTsp, Gs, gsb, gvmax,          \
+                           s.n_beta, s.n_alpha, P->sw, gY, yb);                                                  \
+        break;
+    if constexpr (NTB == 1) {
+        switch (NI) {
+            JTFS_BWDP_CASE(1) JTFS_BWDP_CASE(2) JTFS_BWDP_CASE(3) JTFS_BWDP_CASE(4)
+            JTFS_BWDP_CASE(5) JTFS_BWDP_CASE(6) JTFS_BWDP_CASE(7) JTFS_BWDP_CASE(8)
+            default: break;
+        }
+    } else {
+        switch (NI) {
+            JTFS_BWDP_CASE(1) JTFS_BWDP_CASE(2) JTFS_BWDP_CASE(3) JTFS_BWDP_CASE(4) JTFS_BWDP_CASE(5)
+            default: break;
+        }
+    }
+#undef JTFS_BWDP_CASE
+}
+
 int launch_gv_split(const jtfs_plan* P, const float* gV, uint4* Gs, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int64_t nrows = B * s.n_alpha * 2 * (int64_t)s.Mp;
@@ -1907,19 +2242,50 @@ static void launch_bwdf_ns(dim3 grid, hipStream_t st, const unsigned* phase, int
     }
 }
 
+// The kernel that was set, or else the faster one: folding halves the products, but a
+// pass of it costs a lane the modulus adjoint of both rows of a pair, two full waits
+// and an exchange whatever K is, and the fixed points take passes of their own.
+// Contraction alone, all products and folded, us: K = 48 468 and 739, 80 486 and 579,
+// 112 570 and 648 (64 x 2^13, 32 frames); 128 575 and 655, 144 1262 and 1172, 176 714
+// and 608 (16 x 2^15, 32 frames), at 64 frames 614 and 712, 1328 and 1233, 1058 and
+// 662; 128 1192 and 1359, 144 2534 and 2391, 208 1683 and 1349 (16 x 2^16, 16 frames);
+// 288 55 and 36 ms (32 x 2^18).
+bool bwd_folded(const jtfs_plan* P) {
+    if (P->s.fold.NS > kMaxFoldNS) return false;
+    return P->tune.bwd_auto ? P->s.Kp >= 144 : P->tune.bwd16;
+}
+
 int launch_freq_bwd_phase(const jtfs_plan* P, const unsigned* phase, int64_t ph_bstride, const uint4* Gs,
                           int64_t gs_bstride, const float* gvmax, float2* gY2, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
-    if (!P->split_bwdp_ok || s.fold.NS > kMaxFoldNS) {
-        set_error("stored-phase backward not available for these shapes"); return JTFS_ENOTSUP; }
+    if (!P->split_bwdp_ok) { set_error("stored-phase backward not available for these shapes"); return JTFS_ENOTSUP; }
     const int nT = (int)(s.sumTp / kTileTh);
-    const dim3 grid((unsigned)(B * nT * 2));
-    switch (s.NTp / 32) {
-        case 1: launch_bwdf_ns<1>(grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
-        case 2: launch_bwdf_ns<2>(grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
-        default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
+    if (bwd_folded(P)) {
+        const dim3 grid((unsigned)(B * nT * 2));
+        switch (s.NTp / 32) {
+            case 1: launch_bwdf_ns<1>(grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
+            case 2: launch_bwdf_ns<2>(grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
+            default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
+        }
+        return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
     }
-    return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
+    // one launch per range of i-blocks: a single one up to the register budget, else
+    // two balanced halves
+    const int NI = P->KpT / 32;
+    const int ng = NI <= bwdp_max_ni(s.NTp) ? 1 : 2;
+    const int nia = (NI + ng - 1) / ng;
+    const dim3 grid((unsigned)(B * nT));
+    for (int g = 0, q0 = 0; g < ng; ++g) {
+        const int ni = g == 0 ? nia : NI - nia;
+        switch (s.NTp / 32) {
+            case 1: launch_bwdp_ni<1>(ni, q0, NI, grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
+            case 2: launch_bwdp_ni<2>(ni, q0, NI, grid, st, phase, ph_bstride, nT, P, Gs, gs_bstride, gvmax, gY2); break;
+            default: set_error("unsupported N/T"); return JTFS_ENOTSUP;
+        }
+        if (hipGetLastError() != hipSuccess) return JTFS_EHIP;
+        q0 += ni;
+    }
+    return JTFS_OK;
 }
 
 }  // namespace jtfs

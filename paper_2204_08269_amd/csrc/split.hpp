@@ -29,4 +29,6 @@ int launch_gv_split(const jtfs_plan* P, const float* gV, uint4* Gs, int64_t B, h
 bool fwdq_supported(const jtfs_plan* P, bool with_phase);
 // whether the forward contraction runs in 16 x 16 tiles
 bool fwd_tile16(const jtfs_plan* P, bool with_phase);
+// whether the stored-phase backward runs folded (in 16 x 16 tiles; else all products, in 32 x 32 ones)
+bool bwd_folded(const jtfs_plan* P);
 }  // namespace jtfs

@@ -1219,3 +1219,28 @@ def test_many_frames_and_rows_averaged(Q):
         xb = x[b].astype(np.float64)
         assert rel_l2(gx[b], O.jtfs_vjp(xb, gs1[b], gs2[b], P)) <= TOL_VJP
         assert rel_l2(g0[b], O.jtfs_vjp(xb, gs1[b], np.zeros_like(gs2[b]), P)) <= TOL_VJP
+
+
+@pytest.mark.parametrize("p", FOLD_SHAPES + [dict(N=4096, J=7, Q=(32, 1), J_fr=4, Q_fr=2, T=256, F=8)],
+                         ids=lambda p: f"N{p['N']}_Q{p['Q'][0]}_F{p['F']}")
+def test_stored_phase_kernels_by_shape(p):
+    """The kernel of the stored-phase backward that a plan takes by itself (folded, tile 16, for more than 128
+    rows), and the gradient of each kernel that is set: the bounds of the test of the folded one, and the same bits for
+    any batch."""
+    P = oracle_plan(p)
+    x = synth.batch(5, B=3, N=p["N"])
+    gs1, gs2 = synth.cotangents((3,) + P.s1_shape(), (3,) + P.s2_shape(), seed=21)
+    op = gpu_op(p, "split16_phase")
+    assert op.tuning()[3] == (16 if P.n1 > 128 else 32)
+    xt, g1, g2 = (torch.from_numpy(v).cuda() for v in (x, gs1, gs2))
+    for tile in (32, 16):
+        op.set_tuning("split16_phase", ALL_ROWS, bwd_tile=tile)
+        assert op.tuning()[3] == tile
+        ws = op.new_workspace(3)
+        op.forward(xt, ws)
+        g = op.vjp(xt, g1, g2, ws=ws, reuse_forward=True).cpu().numpy()
+        op.forward(xt[1:2].contiguous(), ws)
+        one = op.vjp(xt[1:2].contiguous(), g1[1:2], g2[1:2], ws=ws, reuse_forward=True).cpu().numpy()
+        assert np.array_equal(one[0], g[1])
+        for b in range(3):
+            assert rel_l2(g[b], O.jtfs_vjp(x[b].astype(np.float64), gs1[b], gs2[b], P)) <= TOL_VJP
