@@ -38,7 +38,11 @@ class JTFS:
     contraction: "split16" (FP16 matrix cores with split operands, the default
     where available), "split16_phase" (split16, and the forward stores the unit
     phase of the contraction so that a vjp that reuses the forward's workspace
-    need not recompute it; a larger workspace) or "fp32" (FP32 matrix cores).  Calling the object is
+    need not recompute it; a larger workspace, and a phase rounded to 16 bits per
+    component; with more than 128 first-order bands the gradient of an octave far
+    weaker than the one opposite it on the log-frequency axis also carries the
+    stronger one's rounding, unless set_tuning asks for bwd_tile=32) or "fp32"
+    (FP32 matrix cores).  Calling the object is
     differentiable through torch.autograd; forward() and vjp() call the library
     directly."""
 

@@ -1244,3 +1244,37 @@ def test_stored_phase_kernels_by_shape(p):
         assert np.array_equal(one[0], g[1])
         for b in range(3):
             assert rel_l2(g[b], O.jtfs_vjp(x[b].astype(np.float64), gs1[b], gs2[b], P)) <= TOL_VJP
+
+
+@pytest.mark.parametrize("side", ["high", "low"])
+def test_stored_phase_gradient_per_octave(side):
+    """A cotangent on the 32 highest or lowest first-order frequencies alone, n1 = 165: the gradient per octave. With
+    every product (tile 32) an octave's error is that of the recomputing mode plus the phase's rounding, 0.5 / 32767 per
+    component, so 2.2e-5 of each term. Folded (tile 16, the plan's own choice here), a weak octave is the difference of
+    two sums of the size of its mirror image, each formed to 22 bits: 2^-22 of the whole gradient beside that."""
+    p = dict(N=2 ** 13, J=9, Q=(24, 2), J_fr=5, Q_fr=2, T=2 ** 9, F=16)
+    P = oracle_plan(p)
+    x = synth.batch(5, B=1, N=p["N"])
+    g1, g2 = synth.cotangents((1,) + P.s1_shape(), (1,) + P.s2_shape(), seed=3)
+    g1[:] = 0
+    rows = np.arange(P.out_l) < 2 if side == "high" else np.arange(P.out_l) >= (P.n1 - 1) // p["F"] - 1
+    g2[:, :, :, :, ~rows] = 0
+    ref = np.fft.rfft(O.jtfs_vjp(x[0].astype(np.float64), g1[0], g2[0], P))
+    xt, g1, g2 = (torch.from_numpy(v).cuda() for v in (x, g1, g2))
+
+    def octaves(mode, tile):
+        op = gpu_op(p, mode)
+        assert mode == "split16" or op.tuning()[3] == 16
+        op.set_tuning(mode, ALL_ROWS, bwd_tile=tile)
+        ws = op.new_workspace(1)
+        op.forward(xt, ws)
+        e = np.fft.rfft(op.vjp(xt, g1, g2, ws=ws, reuse_forward=True).cpu().numpy()[0].astype(np.float64)) - ref
+        cut = [p["N"] >> k for k in range(1, 10)]
+        band = lambda v: np.array([np.linalg.norm(v[b:a]) for a, b in zip(cut, cut[1:])])
+        return band(e) / band(ref), band(ref) / np.linalg.norm(ref)
+
+    base, _ = octaves("split16", 32)
+    every, share = octaves("split16_phase", 32)
+    fold, _ = octaves("split16_phase", 16)
+    assert (every <= base + 2.2e-5).all()
+    assert (fold <= base + 2.2e-5 + 2.0 ** -22 / share).all()
