@@ -248,6 +248,13 @@ constexpr float kMinNormal = 1.17549435e-38f;   // the least FP32 number the har
 template <int NK>
 constexpr int kPhaseTrp = 64 * (16 * NK * 8 + 16) + 8 * 32 * 36 * 4 <= kMaxDynLds ? 32 : 8;
 
+// LDS of k_freq_fwd_h's sum over the waves (8 waves x 2 spins x 64 lanes x 16 floats),
+// and whether it lies beside the resident W rows (up to 32 frames, K <= 176; else over them)
+constexpr size_t kFwdhSum = (size_t)8 * 2 * 64 * 16 * sizeof(float);
+constexpr bool fwdh_keeps_w(int Kp, int NTp) {
+    return NTp == 32 && (size_t)64 * (Kp * 8 + 16) + kFwdhSum <= (size_t)kMaxDynLds;
+}
+
 // One workgroup: 64 rows l (W resident in LDS) x one t-chunk, in tiles of 128 t.
 // Eight waves: wave (wl, wt) owns rows 32 wl.. and t 32 wt.. of each 128-t tile and
 // streams its Y fragments from global memory (no barrier inside the K loop).
@@ -259,10 +266,17 @@ constexpr int kPhaseTrp = 64 * (16 * NK * 8 + 16) + 8 * 32 * 36 * 4 <= kMaxDynLd
 // One launch covers the t-chunks of every temporal rate and signal (nU units,
 // longest chunks first): the short rates' few workgroups, which alone leave most
 // of the GPU idle for a launch each, run beside and behind the long ones.
+// Where the launch is large, a workgroup takes per_wg units one after the other (up to
+// 32 frames; at 64 there are no registers for the loop): there is one workgroup a CU
+// (256 registers), so that staging W and the sum over the waves are not hidden by
+// another's products, and a chunk short enough for one signal to fill the GPU holds
+// only two to four tiles of products between them.  256 x 2^14 (K = 80): 2.91 ms with
+// chunks of 4096 columns, 3.32 with 256 and one a workgroup, 3.04 with 16.
 template <int NTB, int NK>
 __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __restrict__ Yh, int64_t yh_bstride,
                                                     const FreqRate* __restrict__ rates,
-                                                    const FreqUnit* __restrict__ units, int nB, int u0, int nU, int nlt,
+                                                    const FreqUnit* __restrict__ units, int nB, int g0, int nU,
+                                                    int per_wg, int nlt,
                                                     const unsigned short* __restrict__ Wsp,
                                                     const unsigned short* __restrict__ Phall,
                                                     const float* __restrict__ yscale, int n_alpha,
@@ -271,34 +285,41 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
     constexpr int NTp = 32 * NTB;
     constexpr int Kp = 16 * NK;            // K = NK k-steps of 16 (compile time: the K loop is unrolled)
     extern __shared__ __align__(16) unsigned char lds[];
-    const int WS = Kp * 8 + 16;            // bytes per resident W row
+    constexpr int WS = Kp * 8 + 16;        // bytes per resident W row
+    constexpr bool KEEP = fwdh_keeps_w(Kp, NTp);    // W stays in LDS beside the sum's buffer
     unsigned char* lw_ = lds;
 
     const int g = blockIdx.x;
-    const int u = u0 + ((g >> 3) / nlt) * 8 + (g & 7);
+    const int first = (g0 + ((g >> 3) / nlt) * 8 + (g & 7)) * per_wg;
     const int lt = (g >> 3) % nlt;
-    if (u >= nU) return;
+    if (first >= nU) return;
+    const int end = NTB == 1 ? min(first + per_wg, nU) : first + 1;
+    constexpr int nkb = Kp / 8;
+    for (int u = first; u < end; ++u) {
+    // (a copy of the thread index of its own for each unit: what depends on it is not
+    // kept in registers across the units, of which none are left)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = tid >> 6;
+    const int h = lane >> 5, i32 = lane & 31;
+    const int wl = wave & 1, wt = wave >> 1;
+    const unsigned char* wbase = lw_ + (wl * 32 + i32) * WS + h * 64;
     const int64_t b = u % nB;
     const FreqUnit un = units[u / nB];
     const FreqRate rate = rates[un.alpha];
     const int alpha = un.alpha, Tp = rate.Tp;
     const unsigned short* __restrict__ Phsp = Phall + rate.phioff * 2;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = lane >> 5, i32 = lane & 31;
-    const int wl = wave & 1, wt = wave >> 1;
-    const int nkb = Kp / 8;
-
-    // resident W rows l0 .. l0+63
-    {
+    // resident W rows l0 .. l0+63 (again where the sum before wrote over them)
+    if (u == first || !KEEP) {
         const uint4* src = (const uint4*)(Wsp + (int64_t)lt * 64 * Kp * 4);
-        const int per_row = Kp / 2;        // uint4 per row
+        constexpr int per_row = Kp / 2;    // uint4 per row
         for (int e = tid; e < 64 * per_row; e += 512) {
             const int r = e / per_row, c = e - r * per_row;
             *(uint4*)(lw_ + r * WS + c * 16) = src[e];
         }
     }
     const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
-    if (phase) phase += rate.phase_off;
+    unsigned* ph_u = phase ? phase + rate.phase_off : nullptr;
     // floor of |z|^2 in the scaled units of z (kEpsMod2 (sw sy)^2, kept a normal number)
     float eps2s = 0.f;
     if (phase) {
@@ -309,8 +330,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
 #pragma unroll
     for (int n = 0; n < NTB; ++n) { vu[n] = z16(); vd[n] = z16(); }
 
-    __syncthreads();                     // resident W complete
-    const unsigned char* wbase = lw_ + (wl * 32 + i32) * WS + h * 64;
+    if (u == first || !KEEP) __syncthreads();        // resident W complete
     // Each lane streams its own Y fragments (column t, k-group 2 kq + h; one
     // k-step is 4 uint4) from global memory through a ring of NR k-steps,
     // refilled as it drains; the next tile's first NR k-steps are requested
@@ -418,7 +438,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
                         const float q = __builtin_amdgcn_rsqf(fmaxf(zr * zr + zi * zi, eps2s));
                         tb[(crow(r, h) & (TRP - 1)) * 36 + i32] = pack_snorm16(zr * q, zi * q);
                     }
-                    unsigned* pb = phase + b * ph_bstride + ((int64_t)(spin * nlt + lt) * 2 + wl) * 4 * Tp * 8 +
+                    unsigned* pb = ph_u + b * ph_bstride + ((int64_t)(spin * nlt + lt) * 2 + wl) * 4 * Tp * 8 +
                                    (int64_t)(t0 + wt * 32 + pass * TRP) * 8;
 #pragma unroll
                     for (int k = 0; k < TRP / 8; ++k) {
@@ -473,33 +493,33 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
         }
         if constexpr (!early) next_tile();
     }
-    // sum the four t-quarter waves of each row half through LDS, unscale, store
+    // sum the four t-quarter waves of each row half through LDS, unscale, store; each
+    // of the four takes a quarter of the sums
     const float unscale = rate.unscale_wphi / yscale[b * n_alpha + alpha];
-    float* red = (float*)lds;                        // [wave][spin][64 lanes][16]
+    float* red = (float*)(KEEP ? lds + 64 * WS : lds);   // [wave][spin][4][64 lanes][4]
 #pragma unroll
     for (int n = 0; n < NTB; ++n) {
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            red[((wave * 2 + 0) * 64 + lane) * 16 + r] = vu[n][r];
-            red[((wave * 2 + 1) * 64 + lane) * 16 + r] = vd[n][r];
+            red[(((wave * 2 + 0) * 4 + (r >> 2)) * 64 + lane) * 4 + (r & 3)] = vu[n][r];
+            red[(((wave * 2 + 1) * 4 + (r >> 2)) * 64 + lane) * 4 + (r & 3)] = vd[n][r];
         }
         __syncthreads();
-        if (wt == 0) {
-            float* o = Vp + b * vp_bstride;
+        float* o = Vp + b * vp_bstride;
 #pragma unroll
-            for (int spin = 0; spin < 2; ++spin) {
+        for (int spin = 0; spin < 2; ++spin)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float acc = 0.f;
+            for (int j = 0; j < 4; ++j) {
+                const int r = 4 * wt + j;
+                float acc = 0.f;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) acc += red[(((wl + 2 * q) * 2 + spin) * 64 + lane) * 16 + r];
-                    const int tau = n * 32 + crow(r, h);
-                    o[((((int64_t)un.slot * nlt + lt) * 2 + spin) * NTp + tau) * kTileL + wl * 32 + i32] =
-                        acc * unscale;
-                }
+                for (int q = 0; q < 4; ++q) acc += red[((((wl + 2 * q) * 2 + spin) * 4 + wt) * 64 + lane) * 4 + j];
+                const int tau = n * 32 + crow(r, h);
+                o[((((int64_t)un.slot * nlt + lt) * 2 + spin) * NTp + tau) * kTileL + wl * 32 + i32] = acc * unscale;
             }
-        }
+    }
+    if (u + 1 < end) __syncthreads();                // the sum is read
     }
 }
 
@@ -564,12 +584,16 @@ __global__ void k_wqsplit(const float2* __restrict__ Wl, int Mp, int Kp, int NS,
 }
 
 // LDS of k_freq_fwd_q: the resident W tile (16 KB per k-step of 32) and a
-// 16 x 20-word phase transpose area per wave, then the cross-wave reduction of V
-// (8 waves x NTQ x 4 row blocks x 2 spins x 64 lanes x 4 floats).
+// 16 x 20-word phase transpose area per wave, then the sum of V over the waves
+// (8 waves x NTQ x 4 row blocks x 2 spins x 64 lanes x 4 floats), beside the W tile
+// where it fits (K <= 160 at 16 frames, 32 at 32; else over it).
+constexpr size_t fwdq_sum(int NTQ) { return (size_t)8 * NTQ * 4 * 2 * 64 * 4 * sizeof(float); }
+constexpr size_t fwdq_w(int Kp) { return (size_t)((Kp / 16 + 1) / 2) * 16384; }
+constexpr bool fwdq_keeps_w(int Kp, int NTQ) { return fwdq_w(Kp) + fwdq_sum(NTQ) <= (size_t)kMaxDynLds; }
 constexpr size_t fwdq_lds(int Kp, int NTQ, bool with_phase) {
-    const size_t main_loop = (size_t)((Kp / 16 + 1) / 2) * 16384 + (with_phase ? (size_t)8 * 16 * 20 * 4 : 0);
-    const size_t reduction = (size_t)8 * NTQ * 4 * 2 * 64 * 4 * sizeof(float);
-    return main_loop > reduction ? main_loop : reduction;
+    const size_t main_loop = fwdq_w(Kp) + (with_phase ? (size_t)8 * 16 * 20 * 4 : 0);
+    const size_t sum = (fwdq_keeps_w(Kp, NTQ) ? fwdq_w(Kp) : 0) + fwdq_sum(NTQ);
+    return main_loop > sum ? main_loop : sum;
 }
 
 // One workgroup: 64 rows l (W resident in LDS) x one t-chunk, in tiles of 128 t.
@@ -586,8 +610,8 @@ constexpr size_t fwdq_lds(int Kp, int NTQ, bool with_phase) {
 template <int NK, int NTQ>
 __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __restrict__ Yh, int64_t yh_bstride,
                                                     const FreqRate* __restrict__ rates,
-                                                    const FreqUnit* __restrict__ units, int nB, int u0, int nU, int nlt,
-                                                    const unsigned short* __restrict__ Wq,
+                                                    const FreqUnit* __restrict__ units, int nB, int g0, int nU,
+                                                    int per_wg, int nlt, const unsigned short* __restrict__ Wq,
                                                     const unsigned short* __restrict__ Phall,
                                                     const float* __restrict__ yscale, int n_alpha,
                                                     float* __restrict__ Vp, int64_t vp_bstride,
@@ -599,28 +623,34 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     constexpr int NR = NS < 2 ? NS : 2;      // Y ring depth (k-steps)
     extern __shared__ __align__(16) unsigned char lds[];
 
+    constexpr bool KEEP = fwdq_keeps_w(Kp, NTQ);
     const int g = blockIdx.x;
-    const int u = u0 + ((g >> 3) / nlt) * 8 + (g & 7);
+    const int first = (g0 + ((g >> 3) / nlt) * 8 + (g & 7)) * per_wg;
     const int lt = (g >> 3) % nlt;
-    if (u >= nU) return;
+    if (first >= nU) return;
+    const int end = min(first + per_wg, nU);
+    constexpr int nkb = Kp / 8;
+    for (int u = first; u < end; ++u) {
+    int tid = (int)threadIdx.x;              // (a copy of its own for each unit, as above)
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = tid >> 6;
+    const int j16 = lane & 15, g4 = lane >> 4;
     const int64_t b = u % nB;
     const FreqUnit un = units[u / nB];
     const FreqRate rate = rates[un.alpha];
     const int alpha = un.alpha, Tp = rate.Tp;
     const unsigned short* __restrict__ Phq = Phall + rate.phioff * 2;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j16 = lane & 15, g4 = lane >> 4;
-    constexpr int nkb = Kp / 8;
 
-    // resident W tile of rows l0 .. l0+63, in read order (NS x 1024 slots)
-    {
+    // resident W tile of rows l0 .. l0+63, in read order (NS x 1024 slots; again where
+    // the sum before wrote over it)
+    if (u == first || !KEEP) {
         const uint4* src = (const uint4*)Wq + (int64_t)lt * NS * 1024;
         uint4* dst = (uint4*)lds;
 #pragma unroll
         for (int e = 0; e < 2 * NS; ++e) dst[e * 512 + tid] = src[e * 512 + tid];
     }
     const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
-    if (phase) phase += rate.phase_off;
+    unsigned* ph_u = phase ? phase + rate.phase_off : nullptr;
     float inv_eps = 0.f;                     // 1 / (floor of |z| in the phase), in the scaled units of Z
     if (phase) {
         const double wy = (double)sw * (double)yscale[b * n_alpha + alpha];
@@ -631,7 +661,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     for (int n = 0; n < NTQ; ++n)
 #pragma unroll
         for (int lb = 0; lb < 4; ++lb) { vacc[n][lb][0] = z4(); vacc[n][lb][1] = z4(); }
-    __syncthreads();                         // resident W complete
+    if (u == first || !KEEP) __syncthreads();    // resident W complete
 
     // this lane's W fragments: row 16 lb + j16, k-group 4 ks + g4, plane p
     const uint4* wfr = (const uint4*)lds + lane;
@@ -740,7 +770,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
                     const int tt = lane >> 2, jq = lane & 3;
                     const int ll = lb * 16 + 4 * jq;                 // first row of the quad in the 64-row tile
                     const int wl = ll >> 5, g8 = (ll & 31) >> 3;
-                    unsigned* pb = phase + b * ph_bstride +
+                    unsigned* pb = ph_u + b * ph_bstride +
                                    ((((int64_t)(spin * nlt + lt) * 2 + wl) * 4 + g8) * Tp + t0 + wave * 16 + tt) * 8 +
                                    (ll & 7);
                     const u32x4 v = __builtin_bit_cast(u32x4, *(const uint4*)(tb + tt * 20 + 4 * jq));
@@ -785,7 +815,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     }
     // sum the eight waves' partial V through LDS, unscale, store
     const float unscale = rate.unscale_wphi / yscale[b * n_alpha + alpha];
-    float* red = (float*)lds;                // [wave][n][lb][spin][64 lanes][4]
+    float* red = (float*)(KEEP ? lds + NS * 16384 : lds);   // [wave][n][lb][spin][64 lanes][4]
     __syncthreads();
 #pragma unroll
     for (int n = 0; n < NTQ; ++n)
@@ -807,6 +837,8 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
         for (int w = 0; w < 8; ++w) acc += red[(((w * NTQ * 4 * 2) * 64) * 4) + e];
         const int tau = 16 * n + 4 * (ln >> 4) + r, l = 16 * lb + (ln & 15);
         o[((int64_t)spin * NTp + tau) * kTileL + l] = acc * unscale;
+    }
+    if (u + 1 < end) __syncthreads();        // the sum is read
     }
 }
 
@@ -1902,14 +1934,13 @@ size_t split_fwd_lds(const Shapes& s, bool with_phase);
 bool split_supported(const Shapes& s) { return split_fwd_lds(s, false) <= (size_t)kMaxDynLds && s.NTp <= 64; }
 
 // LDS of k_freq_fwd_h: resident W rows during the main loop (with the stored phase
-// also a transpose area of 32 or 8 rows of 36 elements per wave), then the
-// cross-wave reduction buffer (8 waves x 2 spins x 64 lanes x 16 floats).
+// also a transpose area of 32 or 8 rows of 36 elements per wave), then the sum over
+// the waves.
 size_t split_fwd_lds(const Shapes& s, bool with_phase) {
     const size_t wres = (size_t)64 * (s.Kp * 8 + 16);
     const size_t trans = wres + (size_t)8 * 32 * 36 * 4 <= (size_t)kMaxDynLds ? 32 : 8;   // kPhaseTrp
     const size_t main_loop = wres + (with_phase ? (size_t)8 * trans * 36 * 4 : 0);
-    const size_t reduction = (size_t)8 * 2 * 64 * 16 * sizeof(float);
-    return std::max(main_loop, reduction);
+    return std::max(main_loop, fwdh_keeps_w(s.Kp, s.NTp) ? wres + kFwdhSum : kFwdhSum);
 }
 
 int build_split_tables(jtfs_plan* P, std::vector<void*>& owned) {
@@ -2092,12 +2123,23 @@ int launch_ysplit(const jtfs_plan* P, const float2* Y2, const float* rowmax, uns
     return hipGetLastError() == hipSuccess ? JTFS_OK : JTFS_EHIP;
 }
 
+// Units that a workgroup takes one after the other: as many as leave about 4096
+// workgroups (16 rounds of one a CU) in the launch, up to 4096 columns.  A sum's terms
+// do not depend on it.
+static int fwd_units_per_wg(const jtfs_plan* P, int64_t groups) {
+    if (P->s.NTp > 32) return 1;
+    const int chunk = P->tune.chunk == kChunkT ? 1 << (kChunkLogs[0] + P->auto_chunk) : P->tune.chunk;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kChunkT / chunk, groups / 4096));
+}
+
 int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const float* yscale, float* Vp,
                           int64_t vp_bstride, unsigned* phase, int64_t ph_bstride, int64_t B, hipStream_t st) {
     const Shapes& s = P->s;
     const int nlt = s.Mp / kTileL;
     const ChunkSet& cs = split_chunks(P);
     const int nU = (int)(B * cs.sumch), nB = (int)B;
+    const int per_wg = fwd_units_per_wg(P, (int64_t)nU * nlt);
+    const int nG = (nU + per_wg - 1) / per_wg;
     // one launch, unless its workgroups pass the limit of a grid (2^32 threads)
     const int per = kMaxFwdGroups / nlt / 8 * 8;
     const int64_t yhb = (int64_t)s.Kp * s.sumTp * 4;
@@ -2112,17 +2154,17 @@ int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const fl
     const size_t ldsq = fwdq_lds(s.Kp, ntq, phase != nullptr);
     const unsigned short *Wq = P->Wq, *Pq = P->Phq, *Wsp = P->Wsp, *Ph = P->Phsp;
     if (!tile16 && s.NTp > 64) { set_error("unsupported N/T"); return JTFS_ENOTSUP; }
-    for (int u0 = 0; u0 < nU; u0 += per) {
-        const int n = std::min(per, nU - u0), end = u0 + n;
+    for (int g0 = 0; g0 < nG; g0 += per) {
+        const int n = std::min(per, nG - g0), end = std::min(nU, (g0 + n) * per_wg);
         const dim3 grid((unsigned)((n + 7) / 8 * 8 * nlt));
         if (tile16 && ntq == 1)
-            launch_fwdq_nk<1>(nk, grid, ldsq, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wq, Pq, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
+            launch_fwdq_nk<1>(nk, grid, ldsq, st, Yh, yhb, rt, un, nB, g0, end, per_wg, nlt, Wq, Pq, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
         else if (tile16)
-            launch_fwdq_nk<2>(nk, grid, ldsq, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wq, Pq, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
+            launch_fwdq_nk<2>(nk, grid, ldsq, st, Yh, yhb, rt, un, nB, g0, end, per_wg, nlt, Wq, Pq, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
         else if (s.NTp == 32)
-            launch_fwd_nk<1>(nk, grid, lds, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wsp, Ph, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
+            launch_fwd_nk<1>(nk, grid, lds, st, Yh, yhb, rt, un, nB, g0, end, per_wg, nlt, Wsp, Ph, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
         else
-            launch_fwd_nk<2>(nk, grid, lds, st, Yh, yhb, rt, un, nB, u0, end, nlt, Wsp, Ph, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
+            launch_fwd_nk<2>(nk, grid, lds, st, Yh, yhb, rt, un, nB, g0, end, per_wg, nlt, Wsp, Ph, yscale, s.n_alpha, Vp, vp_bstride, phase, ph_bstride, P->sw);
         if (hipGetLastError() != hipSuccess) return JTFS_EHIP;
     }
     return JTFS_OK;

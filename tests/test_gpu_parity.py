@@ -1278,3 +1278,27 @@ def test_stored_phase_gradient_per_octave(side):
     fold, _ = octaves("split16_phase", 16)
     assert (every <= base + 2.2e-5).all()
     assert (fold <= base + 2.2e-5 + 2.0 ** -22 / share).all()
+
+
+@pytest.mark.parametrize("p, B", [(dict(N=2 ** 11, J=6, Q=(8, 1), J_fr=3, Q_fr=1, T=2 ** 6, F=4), 1031),
+                                  (dict(N=2 ** 12, J=9, Q=(44, 1), J_fr=3, Q_fr=1, T=2 ** 8, F=1), 301),
+                                  (dict(N=2 ** 11, J=6, Q=(8, 1), J_fr=3, Q_fr=1, T=2 ** 5, F=4), 1031)],
+                         ids=["K48_frames32", "K272_frames16", "K48_frames64"])
+@pytest.mark.parametrize("mode", ["split16", "split16_phase"])
+def test_large_batches_keep_each_signals_bits(p, B, mode):
+    """Launches so large that a workgroup of the forward contraction takes several chunks one after the other (batches
+    that they do not divide, W kept in LDS and staged again, both tiles): each signal's coefficients and gradient have
+    the bits of a call of its own, where a workgroup takes one."""
+    x = np.resize(synth.batch(5, B=8, N=p["N"]), (B, p["N"])) * np.linspace(0.5, 1.5, B, dtype=np.float32)[:, None]
+    xt = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    op = gpu_op(p, mode)
+    for tile in (32, 16) if p["N"] // p["T"] <= 32 else (32,):
+        op.set_tuning(mode, ALL_ROWS, fwd_tile=tile)
+        ws = op.new_workspace(B)
+        s1, s2 = op.forward(xt, ws)
+        g = op.vjp(xt, s1, s2, ws=ws, reuse_forward=True)
+        for b in (0, 1, B // 2, B - 2, B - 1):
+            one = xt[b:b + 1].contiguous()
+            a1, a2 = op.forward(one, ws)
+            ga = op.vjp(one, a1, a2, ws=ws, reuse_forward=True)
+            assert torch.equal(a1[0], s1[b]) and torch.equal(a2[0], s2[b]) and torch.equal(ga[0], g[b]), (tile, b)
