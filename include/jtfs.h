@@ -395,8 +395,8 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * fwd_ms, bwd_ms: the chosen mode's forward and backward contraction per step with
  * 32 x 32 and 16 x 16 tiles (0 where not run).  Then, for the chosen mode and tiles, one run with every register-resident stage in radix-8 passes
  * (where rows of 2^14 points or more exist), one with 8192-point in-LDS
- * workgroups (where rows of 2^12 points or fewer exist) and one with 1024-column
- * t-chunks in the forward contraction (where a rate has more than 1024 columns)
+ * workgroups (where rows of 2^12 points or fewer exist) and one each with 1024- and
+ * 4096-column t-chunks in the forward contraction (where a rate has more than 1024 columns)
  * settle those bits per stage (a stage must gain 1 % to take the other setting). */
 #define JTFS_REG_SCALOGRAM    1
 #define JTFS_REG_SECOND_ORDER 2
@@ -424,13 +424,19 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * workgroups of twice the LDS), else 4096. */
 #define JTFS_TUNE_LDS_BATCH8K 1024
 /* ... and the t-columns per workgroup of the forward contraction (its t-chunk):
- * 1024 or 2048 where one of these bits is set (1024 if both), else 4096 in FP32
- * mode and, in the split modes, a length of 256 to 4096 columns that the plan
+ * 1024, 2048 or 4096 where one of these bits is set (the least of them), else 4096 in
+ * FP32 mode and, in the split modes, a length of 256 to 4096 columns that the plan
  * takes from its shapes (so that one signal fills the GPU).  Shorter chunks give
  * more workgroups to small batches and more partial V slots to sum; the
  * workspace size follows the bits (query it again after setting them). */
 #define JTFS_TUNE_TCHUNK_1K   2048
 #define JTFS_TUNE_TCHUNK_2K   4096
+#define JTFS_TUNE_TCHUNK_4K   8192
+/* ... the forward tile, and the stored-phase backward, by the plan's rules on its shapes
+ * (whatever their tile bits say), as before any choice is set; jtfs_plan_get_tuning
+ * reports the tile bits that the rules give beside these. */
+#define JTFS_TUNE_FWD_BY_SHAPE 16384
+#define JTFS_TUNE_BWD_BY_SHAPE 32768
 typedef struct {
     int32_t contraction;
     int32_t reg_rows;                 /* including JTFS_TUNE_FWD_TILE16 */

@@ -45,19 +45,22 @@ void set_rows(jtfs_plan* P, int mask) {
     P->tune.reg_second = (mask & JTFS_REG_SECOND_ORDER) != 0;
     P->tune.reg_rowfft = (mask & JTFS_REG_ROW_FFT) != 0;
     P->tune.reg_first_adj = (mask & JTFS_REG_FIRST_ADJ) != 0;
-    P->tune.fwd_auto = false;
+    P->tune.fwd_auto = (mask & JTFS_TUNE_FWD_BY_SHAPE) != 0;
     P->tune.fwd16 = (mask & JTFS_TUNE_FWD_TILE16) != 0;
-    P->tune.bwd_auto = false;
+    P->tune.bwd_auto = (mask & JTFS_TUNE_BWD_BY_SHAPE) != 0;
     P->tune.bwd16 = (mask & JTFS_TUNE_BWD_TILE16) != 0;
     P->tune.r8_scalogram = (mask & JTFS_TUNE_RADIX8_SCALOGRAM) != 0;
     P->tune.r8_second = (mask & JTFS_TUNE_RADIX8_SECOND_ORDER) != 0;
     P->tune.r8_rowfft = (mask & JTFS_TUNE_RADIX8_ROW_FFT) != 0;
     P->tune.r8_first_adj = (mask & JTFS_TUNE_RADIX8_FIRST_ADJ) != 0;
     P->tune.batch8k = (mask & JTFS_TUNE_LDS_BATCH8K) != 0;
-    const int chunk = (mask & JTFS_TUNE_TCHUNK_1K) ? 1024 : (mask & JTFS_TUNE_TCHUNK_2K) ? 2048 : kChunkT;
+    const int chunk = (mask & JTFS_TUNE_TCHUNK_1K)   ? 1024
+                      : (mask & JTFS_TUNE_TCHUNK_2K) ? 2048
+                      : (mask & JTFS_TUNE_TCHUNK_4K) ? 4096
+                                                     : 0;
     if (chunk != P->tune.chunk) {
         P->tune.chunk = chunk;           // the plan holds the device tables of every length
-        set_chunks(&P->s, chunk);
+        set_chunks(&P->s, chunk ? chunk : kChunkT);
     }
 }
 
@@ -76,7 +79,11 @@ int get_rows(const jtfs_plan* P) {
            (P->tune.r8_scalogram ? JTFS_TUNE_RADIX8_SCALOGRAM : 0) |
            (P->tune.r8_second ? JTFS_TUNE_RADIX8_SECOND_ORDER : 0) | (P->tune.r8_rowfft ? JTFS_TUNE_RADIX8_ROW_FFT : 0) |
            (P->tune.r8_first_adj ? JTFS_TUNE_RADIX8_FIRST_ADJ : 0) | (P->tune.batch8k ? JTFS_TUNE_LDS_BATCH8K : 0) |
-           (P->tune.chunk == 1024 ? JTFS_TUNE_TCHUNK_1K : P->tune.chunk == 2048 ? JTFS_TUNE_TCHUNK_2K : 0);
+           (P->tune.fwd_auto ? JTFS_TUNE_FWD_BY_SHAPE : 0) | (P->tune.bwd_auto ? JTFS_TUNE_BWD_BY_SHAPE : 0) |
+           (P->tune.chunk == 1024   ? JTFS_TUNE_TCHUNK_1K
+            : P->tune.chunk == 2048 ? JTFS_TUNE_TCHUNK_2K
+            : P->tune.chunk         ? JTFS_TUNE_TCHUNK_4K
+                                    : 0);
 }
 
 // Cache key: the device's architecture and name, the plan parameters and B.
@@ -174,7 +181,8 @@ extern "C" int jtfs_plan_set_tuning(jtfs_plan* P, int contraction, int reg_rows)
     if (!P) { set_error("null plan"); return JTFS_EINVAL; }
     if (reg_rows & ~(JTFS_REG_SCALOGRAM | JTFS_REG_SECOND_ORDER | JTFS_REG_ROW_FFT | JTFS_REG_FIRST_ADJ |
                      JTFS_TUNE_FWD_TILE16 | JTFS_TUNE_BWD_TILE16 | kRadix8Bits | JTFS_TUNE_LDS_BATCH8K |
-                     JTFS_TUNE_TCHUNK_1K | JTFS_TUNE_TCHUNK_2K)) {
+                     JTFS_TUNE_TCHUNK_1K | JTFS_TUNE_TCHUNK_2K | JTFS_TUNE_TCHUNK_4K | JTFS_TUNE_FWD_BY_SHAPE |
+                     JTFS_TUNE_BWD_BY_SHAPE)) {
         set_error("unknown row-kernel bits"); return JTFS_EINVAL; }
     const int rc = jtfs_plan_set_contraction(P, contraction);
     if (rc != JTFS_OK) return rc;
@@ -198,19 +206,14 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     std::memset(out, 0, sizeof(*out));
     const Shapes& s = P->s;
     const int saved_mode = P->contraction, saved_rows = get_rows(P);
-    const bool saved_fwd_auto = P->tune.fwd_auto, saved_bwd_auto = P->tune.bwd_auto;
-    auto restore_rows = [&]() {
-        set_rows(P, saved_rows);
-        P->tune.fwd_auto = saved_fwd_auto;
-        P->tune.bwd_auto = saved_bwd_auto;
-    };
+    auto restore_rows = [&]() { set_rows(P, saved_rows); };
     const std::string key = cache_key(P, B);
     {
         int cm = 0, cr = 0;
         double cms = 0.0;
         if (cache_lookup(key, &cm, &cr, &cms) && jtfs_plan_set_tuning(P, cm, cr) == JTFS_OK) {
             out->contraction = cm;
-            out->reg_rows = cr;
+            out->reg_rows = get_rows(P);
             out->step_ms = cms;
             out->from_cache = 1;
             return JTFS_OK;
@@ -307,11 +310,11 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
     auto btile_ok = [&](size_t mi) { return btile16 && modes[mi] == JTFS_CONTRACTION_SPLIT_F16_PHASE; };
     size_t best_m = 0;
     double best_c = 1e300;
-    bool buse16 = false;                   // (a choice of the stored-phase mode, whichever mode is kept)
+    bool buse16 = false, btimed = false;   // (a choice of the stored-phase mode, whichever mode is kept)
     for (size_t mi = 0; mi < modes.size(); ++mi) {
         double c = tile_ok(mi) ? std::min(fwd_ms(mi, 0), fwd_ms(mi, 1)) : fwd_ms(mi, 0);
         c += btile_ok(mi) ? std::min(bwd_ms(mi, 0), bwd_ms(mi, 1)) : bwd_ms(mi, 0);
-        if (btile_ok(mi)) buse16 = bwd_ms(mi, 1) < bwd_ms(mi, 0);
+        if (btile_ok(mi)) buse16 = bwd_ms(mi, 1) < bwd_ms(mi, 0), btimed = true;
         for (int k : cstages) c += stage[mi][0][k];
         if (c < best_c) { best_c = c; best_m = mi; }
     }
@@ -337,7 +340,8 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
         if (adj(0) <= adj(1)) rows |= JTFS_REG_ROW_FFT | JTFS_REG_FIRST_ADJ;
     }
     if (use16) rows |= JTFS_TUNE_FWD_TILE16;
-    if (buse16) rows |= JTFS_TUNE_BWD_TILE16;
+    if (btimed && buse16) rows |= JTFS_TUNE_BWD_TILE16;
+    if (btile16 && !btimed) rows |= JTFS_TUNE_BWD_BY_SHAPE;      // (its workspace did not fit: a smaller batch may)
     P->contraction = modes[best_m];
     set_rows(P, rows);
     auto fail = [&](int rc) {
@@ -383,15 +387,22 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
             if (a1 < 0.99 * a0) next |= JTFS_TUNE_LDS_BATCH8K;
         }
         if (has_chunks) {
-            // 1024 t-columns per forward workgroup instead of 4096: the forward contraction
-            // and the frequency lowpass that sums its partial slots
-            double ms = 0.0, stc[JTFS_NUM_STAGES];
-            set_rows(P, rows | JTFS_TUNE_TCHUNK_1K);
-            rc = run_steps(P, x, B, (float*)s1.p, (float*)s2.p, (float*)gx.p, ws.p, wsb, reps, st, &ms, stc);
-            if (rc != JTFS_OK) return fail(rc);
-            const double a0 = base_st[JTFS_STAGE_FREQ_FWD] + base_st[JTFS_STAGE_FREQ_LOWPASS];
-            const double a1 = stc[JTFS_STAGE_FREQ_FWD] + stc[JTFS_STAGE_FREQ_LOWPASS];
-            if (a1 < 0.99 * a0) next |= JTFS_TUNE_TCHUNK_1K;
+            // 1024 t-columns per chunk of the forward contraction, and 4096 where the plan's
+            // own length is another: the contraction and the frequency lowpass that sums its
+            // partial slots
+            const bool split = P->contraction != JTFS_CONTRACTION_FP32;
+            double least = 0.99 * (base_st[JTFS_STAGE_FREQ_FWD] + base_st[JTFS_STAGE_FREQ_LOWPASS]);
+            int keep = 0;
+            for (int bit : {JTFS_TUNE_TCHUNK_1K, JTFS_TUNE_TCHUNK_4K}) {
+                if (bit == JTFS_TUNE_TCHUNK_4K && !(split && 1 << (kChunkLogs[0] + P->auto_chunk) < kChunkT)) continue;
+                double ms = 0.0, stc[JTFS_NUM_STAGES];
+                set_rows(P, rows | bit);
+                rc = run_steps(P, x, B, (float*)s1.p, (float*)s2.p, (float*)gx.p, ws.p, wsb, reps, st, &ms, stc);
+                if (rc != JTFS_OK) return fail(rc);
+                const double t = stc[JTFS_STAGE_FREQ_FWD] + stc[JTFS_STAGE_FREQ_LOWPASS];
+                if (t < least) { least = t; keep = bit; }
+            }
+            next |= keep;
         }
         rows = next;
         set_rows(P, rows);
@@ -401,7 +412,7 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
                              stage_final);
     if (rc != JTFS_OK) return fail(rc);
     out->contraction = P->contraction;
-    out->reg_rows = rows;
+    out->reg_rows = get_rows(P);
     cache_store(key, out->contraction, rows, out->step_ms);
     return JTFS_OK;
 }

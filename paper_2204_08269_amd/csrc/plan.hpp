@@ -128,9 +128,9 @@ struct Tuning {
     // register-resident rows: radix-8 passes instead of radix-16 ones, per stage
     bool r8_scalogram = false, r8_second = false, r8_rowfft = false, r8_first_adj = false;
     bool batch8k = false;        // in-LDS row transforms: 8192 points per workgroup (else 4096)
-    // t-columns per workgroup of the forward contraction: 1024 or 2048 as set, or
-    // kChunkT: 4096 in FP32, auto_chunk of the plan in the split modes
-    int chunk = kChunkT;
+    // t-columns per workgroup of the forward contraction: 1024, 2048 or 4096 as set, or
+    // 0: kChunkT in FP32, auto_chunk of the plan in the split modes
+    int chunk = 0;
 };
 // A temporal rate as the split contraction's kernels read it (device table, one per alpha).
 struct FreqRate {
@@ -215,10 +215,8 @@ struct jtfs_plan {
 namespace jtfs {
 // the chunk set of the plan's tuning: as set, else 4096 columns (FP32 contraction)
 // or the plan's own choice (split contraction)
-inline const ChunkSet& fp32_chunks(const jtfs_plan* P) {
-    return P->cset[P->tune.chunk == 1024 ? 2 : P->tune.chunk == 2048 ? 3 : 4];
-}
-inline const ChunkSet& split_chunks(const jtfs_plan* P) {
-    return P->tune.chunk == kChunkT ? P->cset[P->auto_chunk] : fp32_chunks(P);
-}
+inline int fp32_chunk_index(const jtfs_plan* P) { return P->tune.chunk == 1024 ? 2 : P->tune.chunk == 2048 ? 3 : 4; }
+inline int split_chunk_index(const jtfs_plan* P) { return P->tune.chunk ? fp32_chunk_index(P) : P->auto_chunk; }
+inline const ChunkSet& fp32_chunks(const jtfs_plan* P) { return P->cset[fp32_chunk_index(P)]; }
+inline const ChunkSet& split_chunks(const jtfs_plan* P) { return P->cset[split_chunk_index(P)]; }
 }  // namespace jtfs

@@ -2128,7 +2128,7 @@ int launch_ysplit(const jtfs_plan* P, const float2* Y2, const float* rowmax, uns
 // do not depend on it.
 static int fwd_units_per_wg(const jtfs_plan* P, int64_t groups) {
     if (P->s.NTp > 32) return 1;
-    const int chunk = P->tune.chunk == kChunkT ? 1 << (kChunkLogs[0] + P->auto_chunk) : P->tune.chunk;
+    const int chunk = 1 << (kChunkLogs[0] + split_chunk_index(P));
     return (int)std::max<int64_t>(1, std::min<int64_t>(kChunkT / chunk, groups / 4096));
 }
 

@@ -162,7 +162,8 @@ class JTFS:
     BWD_TILE16 = 32
     RADIX8_BITS = {"scalogram": 64, "second_order": 128, "row_fft": 256, "first_adj": 512}
     LDS_BATCH8K = 1024
-    TCHUNK_BITS = {1024: 2048, 2048: 4096, 4096: 0}
+    TCHUNK_BITS = {1024: 2048, 2048: 4096, 4096: 8192, None: 0}
+    FWD_BY_SHAPE, BWD_BY_SHAPE = 16384, 32768
 
     def autotune(self, B, x=None, reps=3):
         """Times the candidate launch choices for B signals (x: [B, N] on the
@@ -188,30 +189,34 @@ class JTFS:
                                   "split16_phase_lds": t.candidates_ms[5]}}
 
     def _chunk_of(self, mask):
-        return 1024 if mask & self.TCHUNK_BITS[1024] else 2048 if mask & self.TCHUNK_BITS[2048] else 4096
+        return next((k for k, v in self.TCHUNK_BITS.items() if mask & v), None)
 
     def set_tuning(self, contraction, register_rows, fwd_tile=32, bwd_tile=32, radix8=(), lds_batch=4096,
-                   t_chunk=4096):
+                   t_chunk=None):
         """Launch choices: contraction mode; stages whose 2^14-point rows are
-        register-resident; contraction tiles; stages whose register-resident
+        register-resident; tile of the forward contraction (32 or 16) and kernel of
+        the stored-phase backward (32: every product, 16: folded; None for either:
+        the plan's rule on its shapes); stages whose register-resident
         transforms use radix-8 passes (else radix 16); points per workgroup of
         the in-LDS row transforms (4096 or 8192); t-columns per workgroup of the
-        forward contraction (1024, 2048, or 4096 for the plan's own choice of up to
-        4096; the workspace size follows)."""
+        forward contraction (1024, 2048 or 4096; None: the plan's own choice, 4096 in
+        fp32 mode and up to 4096 in the others; the workspace size follows)."""
         mode = _lib.CONTRACTIONS[contraction]
         if lds_batch not in (4096, 8192):
             raise ValueError("lds_batch must be 4096 or 8192")
         if t_chunk not in self.TCHUNK_BITS:
-            raise ValueError("t_chunk must be 1024, 2048 or 4096")
+            raise ValueError("t_chunk must be 1024, 2048, 4096 or None")
         mask = (sum(self.REG_BITS[k] for k in register_rows) | (self.FWD_TILE16 if fwd_tile == 16 else 0) |
                 (self.BWD_TILE16 if bwd_tile == 16 else 0) | sum(self.RADIX8_BITS[k] for k in radix8) |
-                (self.LDS_BATCH8K if lds_batch == 8192 else 0) | self.TCHUNK_BITS[t_chunk])
+                (self.LDS_BATCH8K if lds_batch == 8192 else 0) | self.TCHUNK_BITS[t_chunk] |
+                (self.FWD_BY_SHAPE if fwd_tile is None else 0) | (self.BWD_BY_SHAPE if bwd_tile is None else 0))
         _lib.check(self.lib.jtfs_plan_set_tuning(self.plan, mode, mask))
         self.contraction = contraction
         self._ws = {}
 
     def tuning_radix(self):
-        """(stages in radix-8 passes, points per in-LDS workgroup, forward t-chunk) now set on the plan."""
+        """(stages in radix-8 passes, points per in-LDS workgroup, forward t-chunk or None for the plan's own)
+        now set on the plan."""
         m, r = ctypes.c_int(0), ctypes.c_int(0)
         _lib.check(self.lib.jtfs_plan_get_tuning(self.plan, ctypes.byref(m), ctypes.byref(r)))
         return ([k for k, v in self.RADIX8_BITS.items() if r.value & v],

@@ -1302,3 +1302,23 @@ def test_large_batches_keep_each_signals_bits(p, B, mode):
             a1, a2 = op.forward(one, ws)
             ga = op.vjp(one, a1, a2, ws=ws, reuse_forward=True)
             assert torch.equal(a1[0], s1[b]) and torch.equal(a2[0], s2[b]) and torch.equal(ga[0], g[b]), (tile, b)
+
+
+def test_launch_choices_are_what_is_reported():
+    """t_chunk=4096 sets 4096 columns in the split modes too (a plan whose own length is 256 sums fewer slots, so other
+    bits within the bound of the chunk lengths' test), None and fwd_tile=None, bwd_tile=None the plan's own choices: the
+    bits of a plan that nobody tuned; and each is reported as it was set."""
+    p = dict(N=2 ** 15, J=11, Q=(16, 1), J_fr=4, Q_fr=2, T=2 ** 11, F=8)
+    x = synth.batch(5, B=1, N=p["N"])
+    op = gpu_op(p, "split16_phase")
+    own = run_forward(op, x)[1]
+    assert op.tuning_radix()[2] is None and op.tuning()[2:] == (16, 16)
+    op.set_tuning("split16_phase", ALL_ROWS, fwd_tile=None, t_chunk=4096)
+    whole = run_forward(op, x)[1]
+    assert op.tuning_radix()[2] == 4096 and op.tuning()[2:] == (16, 32)
+    assert not np.array_equal(whole, own) and rel_l2(whole, own) <= 2e-6
+    op.set_tuning("split16_phase", ALL_ROWS, fwd_tile=None, bwd_tile=None)
+    assert op.tuning_radix()[2] is None and op.tuning()[2:] == (16, 16)
+    assert np.array_equal(run_forward(op, x)[1], own)
+    with pytest.raises(ValueError):
+        op.set_tuning("split16_phase", ALL_ROWS, t_chunk=512)
