@@ -371,7 +371,11 @@ extern "C" int jtfs_plan_autotune(jtfs_plan* P, const float* x, int64_t B, int r
                                    JTFS_STAGE_FIRST_ADJ};
             const int kbit[4] = {JTFS_TUNE_RADIX8_SCALOGRAM, JTFS_TUNE_RADIX8_SECOND_ORDER, JTFS_TUNE_RADIX8_ROW_FFT,
                                  JTFS_TUNE_RADIX8_FIRST_ADJ};
+            // (where the first-order adjoint's kernels take the long gY2 rows in, no transform
+            // with a choice of radix is left to the row FFTs)
+            const bool fused = rows_in_adjoint(P);
             for (int q = 0; q < 4; ++q) {
+                if (q == 2 && fused) continue;
                 const double r16 = base_st[kstage[q]] + (q == 3 ? base_st[JTFS_STAGE_SECOND_ADJ] : 0.0);
                 const double r8 = st8[kstage[q]] + (q == 3 ? st8[JTFS_STAGE_SECOND_ADJ] : 0.0);
                 if (r8 < 0.99 * r16) next |= kbit[q];

@@ -1778,7 +1778,7 @@ int backward_impl(const jtfs_plan* P, const float* x, const float* gs1, const fl
         LAUNCHCHK("contraction adjoint (W^H)");
     }
     // with both in registers, the scalogram adjoint transforms the long gY2 rows itself
-    const bool rows_in_a = use_reg_rows(s.logNX, P->tune.reg_first_adj) && P->tune.reg_rowfft;
+    const bool rows_in_a = rows_in_adjoint(P);
     rc = gy2_row_ffts(P, gY2, yb, rows_in_a ? kRegMinLogRows - 1 : 31, B, st);
     if (rc != JTFS_OK) return rc;
     const int logNT = s.logN - s.logT;

@@ -213,6 +213,10 @@ struct jtfs_plan {
 };
 
 namespace jtfs {
+// whether the scalogram adjoint transforms the gY2 rows of 2^13 points and more itself
+inline bool rows_in_adjoint(const jtfs_plan* P) {
+    return use_reg_rows(P->s.logNX, P->tune.reg_first_adj) && P->tune.reg_rowfft;
+}
 // the chunk set of the plan's tuning: as set, else 4096 columns (FP32 contraction)
 // or the plan's own choice (split contraction)
 inline int fp32_chunk_index(const jtfs_plan* P) { return P->tune.chunk == 1024 ? 2 : P->tune.chunk == 2048 ? 3 : 4; }

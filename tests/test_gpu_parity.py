@@ -1322,3 +1322,12 @@ def test_launch_choices_are_what_is_reported():
     assert np.array_equal(run_forward(op, x)[1], own)
     with pytest.raises(ValueError):
         op.set_tuning("split16_phase", ALL_ROWS, t_chunk=512)
+
+
+def test_autotune_leaves_the_radix_that_no_kernel_reads():
+    """Where the long gY2 rows are transformed inside the scalogram adjoint, the row FFTs hold no transform with a choice
+    of radix: the tuner compares two runs of the same kernels, and records none. (Three tunings: noise chose before.)"""
+    op = gpu_op(LONG_ROWS[0])
+    for _ in range(3):
+        choice = op.autotune(1, reps=1)
+        assert not {"row_fft", "first_adj"} <= set(choice["register_rows"]) or "row_fft" not in choice["radix8"]
