@@ -379,8 +379,8 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * gY2 row FFTs and the first-order adjoint, which share kernels), and the faster
  * tiles, then times the result (step_ms).  With the
  * environment variable JTFS_TUNE_CACHE naming a file, a result is appended to it
- * under a key of the device's architecture and name, the plan parameters and B,
- * and a later call with the same key applies the stored choice without timing
+ * under a key of the version of these choices, the device's architecture and name,
+ * the plan parameters and B, and a later call with the same key applies the stored choice without timing
  * (from_cache = 1; candidates and fwd_ms then 0).  It
  * allocates its buffers itself (the largest workspace over the modes plus
  * coefficients and gradient for B signals), synchronises the stream, uses the

@@ -86,7 +86,12 @@ int get_rows(const jtfs_plan* P) {
                                     : 0);
 }
 
-// Cache key: the device's architecture and name, the plan parameters and B.
+// Raised whenever a mask bit changes its meaning or a kernel that a choice was timed on
+// is replaced: choices that another version stored are then timed anew.
+constexpr int kChoiceVersion = 2;
+
+// Cache key: the version of the choices, the device's architecture and name, the plan
+// parameters and B.
 std::string cache_key(const jtfs_plan* P, int64_t B) {
     hipDeviceProp_t prop;
     std::string dev = "unknown";
@@ -97,7 +102,7 @@ std::string cache_key(const jtfs_plan* P, int64_t B) {
     char buf[256];
     std::snprintf(buf, sizeof buf, "N=%lld,J=%d,Q=%d/%d,Jfr=%d,Qfr=%d,T=%lld,F=%lld,flags=%u,B=%lld", (long long)p.N,
                   p.J, p.Q1, p.Q2, p.J_fr, p.Q_fr, (long long)p.T, (long long)p.F, p.flags, (long long)B);
-    return dev + "|" + buf;
+    return "choices" + std::to_string(kChoiceVersion) + "|" + dev + "|" + buf;
 }
 
 const char* cache_path() {

@@ -1331,3 +1331,17 @@ def test_autotune_leaves_the_radix_that_no_kernel_reads():
     for _ in range(3):
         choice = op.autotune(1, reps=1)
         assert not {"row_fft", "first_adj"} <= set(choice["register_rows"]) or "row_fft" not in choice["radix8"]
+
+
+def test_autotune_cache_of_another_version_is_not_applied(tmp_path, monkeypatch):
+    """An entry without the version of the choices, as earlier builds wrote it, and one of another version: timed anew."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("JTFS_TUNE_CACHE", str(cache))
+    assert not gpu_op(P1).autotune(2, reps=1)["from_cache"]
+    entry = cache.read_text()
+    version, rest = entry.split("|", 1)
+    assert version.startswith("choices") and gpu_op(P1).autotune(2, reps=1)["from_cache"]
+    for other in (rest, "choices1|" + rest):
+        cache.write_text(other)
+        assert not gpu_op(P1).autotune(2, reps=1)["from_cache"]
+        assert gpu_op(P1).autotune(2, reps=1)["from_cache"]
