@@ -248,6 +248,22 @@ constexpr float kMinNormal = 1.17549435e-38f;   // the least FP32 number the har
 template <int NK>
 constexpr int kPhaseTrp = 64 * (16 * NK * 8 + 16) + 8 * 32 * 36 * 4 <= kMaxDynLds ? 32 : 8;
 
+// The thread index, formed anew from the wave's (a scalar) and the lane's, and a scalar:
+// values that the compiler cannot relate to any other copy, so that nothing that
+// depends on them is kept in registers from one unit of a workgroup to the next (there
+// are none left).
+__device__ __forceinline__ int opaque_tid(int wave) {
+    unsigned base = 64u * (unsigned)wave;
+    asm volatile("" : "+s"(base));
+    int tid = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, base));
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+__device__ __forceinline__ float opaque_scalar(float v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 // LDS of k_freq_fwd_h's sum over the waves (8 waves x 2 spins x 64 lanes x 16 floats),
 // and whether it lies beside the resident W rows (up to 32 frames, K <= 176; else over them)
 constexpr size_t kFwdhSum = (size_t)8 * 2 * 64 * 16 * sizeof(float);
@@ -266,12 +282,12 @@ constexpr bool fwdh_keeps_w(int Kp, int NTp) {
 // One launch covers the t-chunks of every temporal rate and signal (nU units,
 // longest chunks first): the short rates' few workgroups, which alone leave most
 // of the GPU idle for a launch each, run beside and behind the long ones.
-// Where the launch is large, a workgroup takes per_wg units one after the other (up to
-// 32 frames; at 64 there are no registers for the loop): there is one workgroup a CU
-// (256 registers), so that staging W and the sum over the waves are not hidden by
-// another's products, and a chunk short enough for one signal to fill the GPU holds
-// only two to four tiles of products between them.  256 x 2^14 (K = 80): 2.91 ms with
-// chunks of 4096 columns, 3.32 with 256 and one a workgroup, 3.04 with 16.
+// Where the launch is large, a workgroup takes per_wg units one after the other (where W
+// stays in LDS beside the sum; at 64 frames there are no registers for the loop): there
+// is one workgroup a CU (256 registers), so that staging W and the sum over the waves
+// are not hidden by another's products, and a chunk short enough for one signal to fill
+// the GPU holds only two to four tiles of products between them.  256 x 2^14 (K = 80):
+// 2.91 ms with chunks of 4096 columns, 3.32 with 256 and one a workgroup, 3.04 with 16.
 template <int NTB, int NK>
 __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __restrict__ Yh, int64_t yh_bstride,
                                                     const FreqRate* __restrict__ rates,
@@ -293,13 +309,20 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
     const int first = (g0 + ((g >> 3) / nlt) * 8 + (g & 7)) * per_wg;
     const int lt = (g >> 3) % nlt;
     if (first >= nU) return;
-    const int end = NTB == 1 ? min(first + per_wg, nU) : first + 1;
+    const int end = KEEP ? min(first + per_wg, nU) : first + 1;
     constexpr int nkb = Kp / 8;
+    const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // resident W rows l0 .. l0+63
+    {
+        const uint4* src = (const uint4*)(Wsp + (int64_t)lt * 64 * Kp * 4);
+        constexpr int per_row = Kp / 2;    // uint4 per row
+        for (int e = threadIdx.x; e < 64 * per_row; e += 512) {
+            const int r = e / per_row, c = e - r * per_row;
+            *(uint4*)(lw_ + r * WS + c * 16) = src[e];
+        }
+    }
     for (int u = first; u < end; ++u) {
-    // (a copy of the thread index of its own for each unit: what depends on it is not
-    // kept in registers across the units, of which none are left)
-    int tid = (int)threadIdx.x;
-    asm volatile("" : "+v"(tid));
+    const int tid = opaque_tid(wave0);
     const int lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, i32 = lane & 31;
     const int wl = wave & 1, wt = wave >> 1;
@@ -309,28 +332,19 @@ __global__ void __launch_bounds__(512) k_freq_fwd_h(const unsigned short* __rest
     const FreqRate rate = rates[un.alpha];
     const int alpha = un.alpha, Tp = rate.Tp;
     const unsigned short* __restrict__ Phsp = Phall + rate.phioff * 2;
-    // resident W rows l0 .. l0+63 (again where the sum before wrote over them)
-    if (u == first || !KEEP) {
-        const uint4* src = (const uint4*)(Wsp + (int64_t)lt * 64 * Kp * 4);
-        constexpr int per_row = Kp / 2;    // uint4 per row
-        for (int e = tid; e < 64 * per_row; e += 512) {
-            const int r = e / per_row, c = e - r * per_row;
-            *(uint4*)(lw_ + r * WS + c * 16) = src[e];
-        }
-    }
     const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
     unsigned* ph_u = phase ? phase + rate.phase_off : nullptr;
     // floor of |z|^2 in the scaled units of z (kEpsMod2 (sw sy)^2, kept a normal number)
     float eps2s = 0.f;
     if (phase) {
-        const double wy = (double)sw * (double)yscale[b * n_alpha + alpha];
+        const double wy = (double)opaque_scalar(sw) * (double)yscale[b * n_alpha + alpha];
         eps2s = (float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), (double)kMinNormal);
     }
     floatx16 vu[NTB], vd[NTB];
 #pragma unroll
     for (int n = 0; n < NTB; ++n) { vu[n] = z16(); vd[n] = z16(); }
 
-    if (u == first || !KEEP) __syncthreads();        // resident W complete
+    if (u == first) __syncthreads();     // resident W complete
     // Each lane streams its own Y fragments (column t, k-group 2 kq + h; one
     // k-step is 4 uint4) from global memory through a ring of NR k-steps,
     // refilled as it drains; the next tile's first NR k-steps are requested
@@ -628,11 +642,18 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     const int first = (g0 + ((g >> 3) / nlt) * 8 + (g & 7)) * per_wg;
     const int lt = (g >> 3) % nlt;
     if (first >= nU) return;
-    const int end = min(first + per_wg, nU);
+    const int end = KEEP ? min(first + per_wg, nU) : first + 1;
     constexpr int nkb = Kp / 8;
+    const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // resident W tile of rows l0 .. l0+63, in read order (NS x 1024 slots)
+    {
+        const uint4* src = (const uint4*)Wq + (int64_t)lt * NS * 1024;
+        uint4* dst = (uint4*)lds;
+#pragma unroll
+        for (int e = 0; e < 2 * NS; ++e) dst[e * 512 + threadIdx.x] = src[e * 512 + threadIdx.x];
+    }
     for (int u = first; u < end; ++u) {
-    int tid = (int)threadIdx.x;              // (a copy of its own for each unit, as above)
-    asm volatile("" : "+v"(tid));
+    const int tid = opaque_tid(wave0);
     const int lane = tid & 63, wave = tid >> 6;
     const int j16 = lane & 15, g4 = lane >> 4;
     const int64_t b = u % nB;
@@ -640,20 +661,11 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     const FreqRate rate = rates[un.alpha];
     const int alpha = un.alpha, Tp = rate.Tp;
     const unsigned short* __restrict__ Phq = Phall + rate.phioff * 2;
-
-    // resident W tile of rows l0 .. l0+63, in read order (NS x 1024 slots; again where
-    // the sum before wrote over it)
-    if (u == first || !KEEP) {
-        const uint4* src = (const uint4*)Wq + (int64_t)lt * NS * 1024;
-        uint4* dst = (uint4*)lds;
-#pragma unroll
-        for (int e = 0; e < 2 * NS; ++e) dst[e * 512 + tid] = src[e * 512 + tid];
-    }
     const unsigned short* Yb = Yh + b * yh_bstride + rate.yoff * 4;
     unsigned* ph_u = phase ? phase + rate.phase_off : nullptr;
     float inv_eps = 0.f;                     // 1 / (floor of |z| in the phase), in the scaled units of Z
     if (phase) {
-        const double wy = (double)sw * (double)yscale[b * n_alpha + alpha];
+        const double wy = (double)opaque_scalar(sw) * (double)yscale[b * n_alpha + alpha];
         inv_eps = __builtin_amdgcn_rsqf((float)fmax(fmin((double)kEpsMod2 * wy * wy, 1e30), (double)kMinNormal));
     }
     floatx4 vacc[NTQ][4][2];
@@ -661,7 +673,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
     for (int n = 0; n < NTQ; ++n)
 #pragma unroll
         for (int lb = 0; lb < 4; ++lb) { vacc[n][lb][0] = z4(); vacc[n][lb][1] = z4(); }
-    if (u == first || !KEEP) __syncthreads();    // resident W complete
+    if (u == first) __syncthreads();         // resident W complete
 
     // this lane's W fragments: row 16 lb + j16, k-group 4 ks + g4, plane p
     const uint4* wfr = (const uint4*)lds + lane;
@@ -675,8 +687,7 @@ __global__ void __launch_bounds__(512) k_freq_fwd_q(const unsigned short* __rest
         // the column offset formed from the thread index here, not kept live across
         // the tile loop (at 256 registers the compiler spilled it, and its reload
         // waited for every memory operation in flight)
-        int tq = (int)threadIdx.x;
-        asm volatile("" : "+v"(tq));
+        const int tq = opaque_tid(wave0);
         const int t = t0 + (tq >> 6) * 16 + (tq & 15);
         return launder_v((const uint4*)Yb + (((int64_t)(t >> 5) * nkb + ((tq >> 4) & 3)) * 128 + (t & 31)));
     };
@@ -2126,8 +2137,9 @@ int launch_ysplit(const jtfs_plan* P, const float2* Y2, const float* rowmax, uns
 // Units that a workgroup takes one after the other: as many as leave about 4096
 // workgroups (16 rounds of one a CU) in the launch, up to 4096 columns.  A sum's terms
 // do not depend on it.
-static int fwd_units_per_wg(const jtfs_plan* P, int64_t groups) {
-    if (P->s.NTp > 32) return 1;
+static int fwd_units_per_wg(const jtfs_plan* P, bool with_phase, int64_t groups) {
+    const Shapes& s = P->s;
+    if (!(fwd_tile16(P, with_phase) ? fwdq_keeps_w(s.Kp, (s.NT + 15) / 16) : fwdh_keeps_w(s.Kp, s.NTp))) return 1;
     const int chunk = 1 << (kChunkLogs[0] + split_chunk_index(P));
     return (int)std::max<int64_t>(1, std::min<int64_t>(kChunkT / chunk, groups / 4096));
 }
@@ -2138,7 +2150,7 @@ int launch_freq_fwd_split(const jtfs_plan* P, const unsigned short* Yh, const fl
     const int nlt = s.Mp / kTileL;
     const ChunkSet& cs = split_chunks(P);
     const int nU = (int)(B * cs.sumch), nB = (int)B;
-    const int per_wg = fwd_units_per_wg(P, (int64_t)nU * nlt);
+    const int per_wg = fwd_units_per_wg(P, phase != nullptr, (int64_t)nU * nlt);
     const int nG = (nU + per_wg - 1) / per_wg;
     // one launch, unless its workgroups pass the limit of a grid (2^32 threads)
     const int per = kMaxFwdGroups / nlt / 8 * 8;

@@ -1282,13 +1282,14 @@ def test_stored_phase_gradient_per_octave(side):
 
 @pytest.mark.parametrize("p, B", [(dict(N=2 ** 11, J=6, Q=(8, 1), J_fr=3, Q_fr=1, T=2 ** 6, F=4), 1031),
                                   (dict(N=2 ** 12, J=9, Q=(44, 1), J_fr=3, Q_fr=1, T=2 ** 8, F=1), 301),
+                                  (dict(N=2 ** 11, J=6, Q=(8, 1), J_fr=3, Q_fr=1, T=2 ** 7, F=4), 1031),
                                   (dict(N=2 ** 11, J=6, Q=(8, 1), J_fr=3, Q_fr=1, T=2 ** 5, F=4), 1031)],
-                         ids=["K48_frames32", "K272_frames16", "K48_frames64"])
+                         ids=["K48_frames32", "K272_frames16", "K48_frames16", "K48_frames64"])
 @pytest.mark.parametrize("mode", ["split16", "split16_phase"])
 def test_large_batches_keep_each_signals_bits(p, B, mode):
-    """Launches so large that a workgroup of the forward contraction takes several chunks one after the other (batches
-    that they do not divide, W kept in LDS and staged again, both tiles): each signal's coefficients and gradient have
-    the bits of a call of its own, where a workgroup takes one."""
+    """Launches so large that a workgroup of the forward contraction takes several chunks one after the other, in batches
+    that they do not divide (K = 48; at 32 frames by the wide tile alone), and those where it never does (K = 272, 64
+    frames): each signal's coefficients and gradient have the bits of a call of its own, where a workgroup takes one."""
     x = np.resize(synth.batch(5, B=8, N=p["N"]), (B, p["N"])) * np.linspace(0.5, 1.5, B, dtype=np.float32)[:, None]
     xt = torch.from_numpy(np.ascontiguousarray(x)).cuda()
     op = gpu_op(p, mode)
