@@ -43,11 +43,10 @@ __device__ __forceinline__ float2 irfft_bin(float2 p, float2 q, float2 w) {
 }
 
 // ---------------------------------------------------------------------------
-// Generic batched FFT over LDS: transform c of batch b has element e at
-// in[b*ib + c*ics + e*ies]; the output X_c[k] (times w_n^{c k} when twl > 0, the
-// four-step twist, and times scale) goes to out[b*ob + c*ocs + k*oes].
-// Column mode (ics == 1): C = 2^logC adjacent transforms per workgroup, loaded
-// with adjacent columns on adjacent threads.  Row mode: transforms contiguous.
+// One step of a four-step transform over LDS: transform c of batch b has element e at
+// in[b*ib + c + e*ies]; the output X_c[k] (times w_n^{c k} when twl > 0, the four-step
+// twist, and times scale) goes to out[b*ob + c*ocs + k*oes].  2^logC adjacent
+// transforms per workgroup, loaded with adjacent columns on adjacent threads.
 // PACK: the input rows are half spectra, packed on the way in (element i of the row's
 // 2^twl from its bins i and 2^twl - i) instead of by a pass of its own.
 // ---------------------------------------------------------------------------
@@ -59,7 +58,7 @@ __device__ __forceinline__ C to_cplx(CI v) {
 
 template <typename CI, typename C, bool PACK = false>
 __global__ void __launch_bounds__(1024) k_fft_cols_t(const CI* in, C* out, int loglen, int ncols, int logC,
-                                                    int64_t ib, int64_t ics, int64_t ies, int64_t ob, int64_t ocs,
+                                                    int64_t ib, int64_t ies, int64_t ob, int64_t ocs,
                                                     int64_t oes, int twl, const C* __restrict__ tw, int tw_log, int inv,
                                                     typename cplx<C>::real scale) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -81,8 +80,7 @@ __global__ void __launch_bounds__(1024) k_fft_cols_t(const CI* in, C* out, int l
     for (int q = 0; q < kMaxPerThread; ++q) {
         const int e = threadIdx.x + q * blockDim.x;
         if (e < tot) {
-            const int c = ics == 1 ? (e & (Cn - 1)) : (e >> loglen), k = ics == 1 ? (e >> logC) : (e & (len - 1));
-            const int64_t i = (int64_t)(c0 + c) * ics + (int64_t)k * ies;
+            const int64_t i = c0 + (e & (Cn - 1)) + (int64_t)(e >> logC) * ies;
             if constexpr (PACK) v[q] = irfft_bin(in[i], in[((int64_t)1 << twl) - i], tw[i << (tw_log - twl - 1)]);
             else v[q] = to_cplx<CI, C>(in[i]);
         }
@@ -91,7 +89,7 @@ __global__ void __launch_bounds__(1024) k_fft_cols_t(const CI* in, C* out, int l
     for (int q = 0; q < kMaxPerThread; ++q) {
         const int e = threadIdx.x + q * blockDim.x;
         if (e < tot) {
-            const int c = ics == 1 ? (e & (Cn - 1)) : (e >> loglen), k = ics == 1 ? (e >> logC) : (e & (len - 1));
+            const int c = e & (Cn - 1), k = e >> logC;
             s[c * st + lpad(k)] = v[q];
         }
     }
@@ -114,9 +112,6 @@ __global__ void __launch_bounds__(1024) k_fft_cols_t(const CI* in, C* out, int l
         }
     }
 }
-
-// The FP32 transform used by the intermediate stages.
-#define k_fft_cols k_fft_cols_t<float2, float2>
 
 // Real-input spectrum in FP64 from the half-length complex FFT of
 // z[k] = x[2k] + i x[2k+1]: X[m] = E[m] + w_n^m O[m], E/O the spectra of the
@@ -1355,12 +1350,17 @@ int setup_kernel_attributes() {
 
 // Rows of more than 2^kOneRowLog complex points are transformed in four steps: in one
 // launch, a workgroup per row, the output of 3 signals of 2^15 samples kept 3 of the 256
-// CUs busy for 26 us (844 us in all, 824 now).
+// CUs busy for 26 us (844 us in all, 824 now).  By the length alone, so that a signal's
+// bits do not depend on its batch: up to 64 rows the steps are the faster ones (input and
+// output transform of 2^14 samples, one launch and four steps, us: 1 signal 47 and 31, 16
+// 51 and 38, 64 53 and 53), and a batch with a row for every CU loses by them what is
+// little beside the rest (256: 70 and 110, of 15.7 ms forward and gradient).
 constexpr int kOneRowLog = 11;
 
 // Columns (log2) a workgroup of the four-step takes of 2^logcols transforms of 2^loglen
-// points, B times: 4096 points, but down to four columns (64-byte runs) while the launch
-// holds under 256 workgroups (one signal of 2^16 samples had 8: 364 us in all, 355 now).
+// points, B times: 4096 points, but down to four columns (runs of 32 bytes, 64 in FP64)
+// while the launch holds under 256 workgroups (one signal of 2^16 samples had 8: 364 us
+// in all, 355 now).
 static int step_cols(int loglen, int logcols, int64_t B) {
     int logC = std::min(std::max(0, 12 - loglen), logcols);
     while (logC > 2 && ((int64_t)1 << (logcols - logC)) * B < 256) --logC;
@@ -1379,12 +1379,12 @@ static void irfft_four_step(const float2* in, int64_t ip, float2* out, float2* s
     int logC = step_cols(lq, lp, B);
     size_t lds = (size_t)(1 << logC) * (lpad_len(Qn) + 1) * sizeof(float2);
     hipLaunchKernelGGL((k_fft_cols_t<float2, float2, true>), dim3((unsigned)(Pn >> logC), (unsigned)B),
-                       step_threads(lq + logC), lds, st, in, scratch, lq, (int)Pn, logC, ip, (int64_t)1, Pn, n, Qn,
+                       step_threads(lq + logC), lds, st, in, scratch, lq, (int)Pn, logC, ip, Pn, n, Qn,
                        (int64_t)1, logn, P->tw, P->tw_log, 1, 1.0f);
     logC = step_cols(lp, lq, B);
     lds = (size_t)(1 << logC) * (lpad_len(Pn) + 1) * sizeof(float2);
-    hipLaunchKernelGGL((k_fft_cols), dim3((unsigned)(Qn >> logC), (unsigned)B), step_threads(lp + logC), lds, st, scratch,
-                       out, lp, (int)Qn, logC, n, (int64_t)1, Qn, n, (int64_t)1, Qn, 0, P->tw, P->tw_log, 1, scale);
+    hipLaunchKernelGGL((k_fft_cols_t<float2, float2>), dim3((unsigned)(Qn >> logC), (unsigned)B), step_threads(lp + logC), lds, st, scratch,
+                       out, lp, (int)Qn, logC, n, Qn, n, (int64_t)1, Qn, 0, P->tw, P->tw_log, 1, scale);
 }
 
 // Real FFT of the B input rows (N samples) in FP64: the complex FFT of the N/2
@@ -1409,12 +1409,12 @@ static void input_fft64(const float* x, int64_t B, float2* xh, int64_t xh_pitch,
     int logC = step_cols(lq, lp, B);
     size_t lds = (size_t)(1 << logC) * (lpad_len(Qn) + 1) * sizeof(double2);
     hipLaunchKernelGGL((k_fft_cols_t<float2, double2>), dim3((unsigned)(Pn >> logC), (unsigned)B), step_threads(lq + logC),
-                       lds, st, in, scratch, lq, (int)Pn, logC, H, (int64_t)1, Pn, H, Qn, (int64_t)1, logn, P->tw64,
+                       lds, st, in, scratch, lq, (int)Pn, logC, H, Pn, H, Qn, (int64_t)1, logn, P->tw64,
                        P->tw_log, 0, 1.0);
     logC = step_cols(lp, lq, B);
     lds = (size_t)(1 << logC) * (lpad_len(Pn) + 1) * sizeof(double2);
     hipLaunchKernelGGL((k_fft_cols_t<double2, double2>), dim3((unsigned)(Qn >> logC), (unsigned)B), step_threads(lp + logC),
-                       lds, st, scratch, z, lp, (int)Qn, logC, H, (int64_t)1, Qn, H, (int64_t)1, Qn, 0, P->tw64,
+                       lds, st, scratch, z, lp, (int)Qn, logC, H, Qn, H, (int64_t)1, Qn, 0, P->tw64,
                        P->tw_log, 0, 1.0);
     hipLaunchKernelGGL(k_rfft_post64, dim3((unsigned)((H / 2 + 1 + 255) / 256), (unsigned)B), dim3(256), 0, st, z, H,
                        xh, xh_pitch, P->s.logN, P->tw64, P->tw_log);
@@ -1481,7 +1481,10 @@ bool reg_row(int logn, bool knob) {
 // The next launch over `nrows` rows of each rate from *a on that is transformed in
 // LDS (false where none is left).  Rows per workgroup: what fills its LDS (4096 or
 // 8192 points), at most max_rows, and fewer where the launch would hold under about
-// 1024 workgroups.
+// 1024 workgroups.  A launch's workgroups all ask for the LDS of its longest rate (147 KB
+// for rows of 2^14 points); with launches of their own for such rates, 8 x 2^16 with all
+// rows in LDS took 465 us for the second order instead of 483, but 555 for the row FFTs
+// instead of 490.
 bool short_rates(const jtfs_plan* P, bool knob, int* a, int nrows, int max_rows, int64_t B, ShortRates* sr,
                  unsigned* blocks, size_t* lds) {
     const Shapes& s = P->s;

@@ -1,7 +1,7 @@
-// First- and second-order kernels for long rows (2^14 and 2^15 points) built on
-// the register-resident FFT: 32 values per thread, LDS used only as a float
-// exchange buffer of one row (64 KB at 2^14 -> two workgroups per CU; 128 KB at
-// 2^15, which an in-LDS complex transform could not hold).
+// First- and second-order kernels for long rows (2^14 and 2^15 points, and 2^11 to
+// 2^13 by the same choice) built on the register-resident FFT: 16 values per thread
+// (8 for the shorter rows), LDS used only as the exchange buffer of a transform of up
+// to 2^14 points (147 KB, one workgroup per CU); a row of 2^15 points takes two.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -470,7 +470,10 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_b_r(const float2* __restrict
 // bins k <= H are formed.  In passes of their own the transforms wrote these rows and
 // this kernel read them back: 525 and 447 us for 16 signals of 2^16 samples, 683 now
 // (7.5 and 4.0 ms, 8.1 now, for 32 of 2^18).
-// grid (n1, B), 1024 threads; 147 KB of LDS, so one workgroup a CU.
+// grid (n1, B), 1024 threads; 147 KB of LDS where ROWS or H = 2^14, so one workgroup a
+// CU, else 74.  With ROWS and H = 2^14 the 17 sums, 16 values of a row and eight weights
+// with their twiddles pass the 128 registers: 38 of them, 140 bytes a lane, are in scratch
+// (none at H = 2^13: 93 registers).
 template <int LOGN, int E, int LRM>
 __device__ __forceinline__ constexpr int bin_elem(int i) {       // element of bin tid + 1024 i after reg_fft
     constexpr int LR = reg_pass_lr(LOGN, reg_num_passes(LOGN, LRM) - 1, LRM), Q = E >> LR;
@@ -521,8 +524,8 @@ __global__ void __launch_bounds__(kRegT) k_scal_bwd_a_r(const float2* __restrict
             const int m = (int)threadIdx.x + i * kRegT;
             return m >= lo && m <= hi && (i < E || extra);
         };
-        // the transform's output v: its bins' weights (and with TW the twiddles w^k of
-        // the odd samples' bins) load eight at a time
+        // the transform's output v: its bins' weights (and, where odd, the twiddles w^k
+        // of the odd samples' bins) load eight at a time
         auto add = [&](auto& v, auto elem, bool odd) {
             const float* pv = after(pa, v[0]);
             const float2* twc = odd ? after(tw, v[0]) : tw;

@@ -2032,7 +2032,8 @@ int build_split_tables(jtfs_plan* P, std::vector<void*>& owned) {
     {
         const int NI = P->KpT / 32;
         // recomputing backward: static LDS of a W chunk and two W^T chunks, 24 NI KB
-        // (<= 160 KB), and one wave per SIMD without scratch
+        // (<= 160 KB), and one wave per SIMD (NI = 6, and 5 at 64 frames: 12 to 20 bytes of
+        // scratch a lane)
         P->split_bwd_ok = (s.NTp == 32 && NI <= 6) || (s.NTp == 64 && NI <= 5);
         // (both stored-phase backwards hold whatever the forward holds with its phase
         // transpose area beside the resident W tile: n1 <= 288, so NS <= kMaxFoldNS and
@@ -2102,12 +2103,16 @@ bool fwdq_supported(const jtfs_plan* P, bool with_phase) {
 
 // The tile that was set, or else the faster one.  A wave of the 16 x 16 kernel loads
 // its Y fragments alone, where two waves of the 32 x 32 one load the same; the latter
-// reads half as much of W from LDS and takes fewer lowpass products.  Measured, 32 x 32
-// and 16 x 16: up to 16 frames 310 and 266 us (7 x 2^14, K = 160), 148 and 134 (3 x
-// 2^15, K = 128), 1641 and 1470 (2^18, K = 288), 1430 and 1426 (4 x 2^17, K = 144); 32
-// frames 193 and 205 (2^16), 1326 and 1396 (8 x 2^16), 11.4 and 13.4 (2^11, K = 48).
-// Below 128 rows or 8192 columns the launch is not what counts, and the tile stays
-// the wide one.  The same in both split modes, whose coefficients agree bit for bit.
+// reads half as much of W from LDS and takes fewer lowpass products.  Contraction, 32 x
+// 32 and 16 x 16, us.  16 frames: 43 x 2^14 with K = 48 379 and 445, 64 433 and 454, 80
+// 488 and 517, 96 549 and 524, 112 609 and 603, 128 664 and 600, 144 1377 and 1342; 8 x
+// 2^16 with K = 80 658 and 698, 112 446 and 435, 144 972 and 939, 160 1073 and 944, 176
+// 1163 and 1187, 240 795 and 746; one signal of 2^18 with K = 288 1641 and 1470.  32 frames:
+// 8 x 2^16 with K = 96 402 and 415, 144 979 and 1006, 160 1073 and 1006, 176 1154 and
+// 1233.  So from 128 rows on, up to 16 frames (96 and 112 rows differ by 5 and 1 %).
+// Plans of fewer than 8192 columns keep the wide tile, though the narrow one gains a
+// tenth from 192 rows on (43 x 2^14, 6400 columns: 983 and 910).  The same in both split
+// modes, whose coefficients agree bit for bit.
 bool fwd_tile16(const jtfs_plan* P, bool with_phase) {
     if (!fwdq_supported(P, with_phase)) return false;
     return P->tune.fwd_auto ? P->s.NT <= 16 && P->s.Kp >= 128 && P->s.sumTp >= 8192 : P->tune.fwd16;
@@ -2199,7 +2204,7 @@ static void launch_bwd_ni(int NI, int NK, dim3 grid, hipStream_t st, const unsig
                                P->d_rates, P->d_tiles, nT, (int)grid.x, P->Wsp, P->WTsp, s.Mp, P->PhTsp, gV,      \
                                gvmax, s.n_beta, yscale, s.n_alpha, P->sw, gY, yb);                                \
         break;
-    // LDS 24 NI KB and one wave per SIMD without scratch: NI <= 6 at N/T <= 32, NI <= 5 at N/T = 64
+    // LDS 24 NI KB and one wave per SIMD: NI <= 6 at N/T <= 32, NI <= 5 at N/T = 64
     if constexpr (NTB == 1) {
         switch (NI) {
             JTFS_BWD_CASE(1) JTFS_BWD_CASE(2) JTFS_BWD_CASE(3) JTFS_BWD_CASE(4)
