@@ -1478,15 +1478,16 @@ __device__ __forceinline__ void bwd_phase_chunk(int c, int nC, int wave, int lan
 
 // Backward contraction from the stored phase: one signal, 128 columns t (four
 // waves of 32), all rows l in 32-row chunks; gY accumulated in registers for the
-// NI i-blocks q_base .. q_base + NI - 1 of the nit blocks of W^T (the register
+// NI i-blocks from q_base + NI blockIdx.y on of the nit blocks of W^T (the register
 // budget holds at most 8 at 32 frames; larger K runs as several launches over
-// disjoint i-ranges, each repeating the modulus adjoint).  Every product of the
-// contraction runs, so that a column gY[i] carries the rounding of its own terms alone.
+// disjoint i-ranges, each repeating the modulus adjoint, and a launch that would leave
+// CUs idle as several ranges in grid y).  Every product of the contraction runs, so that
+// a column gY[i] carries the rounding of its own terms alone, whatever the ranges.
 template <int NTB, int NI>
 __global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__ phase, int64_t ph_bstride,
                                                     const FreqRate* __restrict__ rates,
                                                     const FreqUnit* __restrict__ tiles, int nT, int nU,
-                                                    const unsigned short* __restrict__ WTsp, int q_base, int nit,
+                                                    const unsigned short* __restrict__ WTsp, int q_base0, int nit,
                                                     int Mp, int Kp, const unsigned short* __restrict__ PhTsp,
                                                     const uint4* __restrict__ Gs, int64_t gs_bstride,
                                                     const float* __restrict__ gvmax, int n_beta,
@@ -1496,7 +1497,7 @@ __global__ void __launch_bounds__(256) k_freq_bwd_p(const unsigned* __restrict__
     __shared__ uint4 Ls_T0[NI * 512];
     __shared__ uint4 Ls_T1[NI * 512];
     __shared__ uint4 Ls_G[gvs_chunk<NTB>()];
-    const int u = blockIdx.x;
+    const int u = blockIdx.x, q_base = q_base0 + NI * (int)blockIdx.y;
     if (u >= nU) return;                            // whole block
     const int64_t b = u / nT;
     const FreqUnit un = tiles[u % nT];
@@ -2308,7 +2309,9 @@ static void launch_bwdf_ns(dim3 grid, hipStream_t st, const unsigned* phase, int
 // 112 570 and 648 (64 x 2^13, 32 frames); 128 575 and 655, 144 1262 and 1172, 176 714
 // and 608 (16 x 2^15, 32 frames), at 64 frames 614 and 712, 1328 and 1233, 1058 and
 // 662; 128 1192 and 1359, 144 2534 and 2391, 208 1683 and 1349 (16 x 2^16, 16 frames);
-// 288 55 and 36 ms (32 x 2^18).
+// 288 55 and 36 ms (32 x 2^18).  By the shapes alone, so that a signal's bits do not
+// depend on its batch: launches that leave CUs idle are a little faster folded, with 64
+// columns a workgroup for 128 (2 x 2^11, 103 rows: 33 and 31 us).
 bool bwd_folded(const jtfs_plan* P) {
     if (P->s.fold.NS > kMaxFoldNS) return false;
     return P->tune.bwd_auto ? P->s.Kp >= 144 : P->tune.bwd16;
@@ -2332,8 +2335,13 @@ int launch_freq_bwd_phase(const jtfs_plan* P, const unsigned* phase, int64_t ph_
     // two balanced halves
     const int NI = P->KpT / 32;
     const int ng = NI <= bwdp_max_ni(s.NTp) ? 1 : 2;
-    const int nia = (NI + ng - 1) / ng;
-    const dim3 grid((unsigned)(B * nT));
+    // equal ranges of i-blocks in grid y while there is a CU for each (2 x 2^11, 103 rows:
+    // 44 -> 33 us)
+    int ny = 1;
+    for (int q = 2; q <= NI && ng == 1; ++q)
+        if (NI % q == 0 && B * nT * q <= 256) ny = q;
+    const int nia = (NI / ny + ng - 1) / ng;
+    const dim3 grid((unsigned)(B * nT), (unsigned)ny);
     for (int g = 0, q0 = 0; g < ng; ++g) {
         const int ni = g == 0 ? nia : NI - nia;
         switch (s.NTp / 32) {
