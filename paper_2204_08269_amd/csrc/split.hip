@@ -1787,7 +1787,7 @@ __device__ __forceinline__ void bwdf_half(const uint4* Lt, const uint4* Lg, int 
 // those reads), and nothing requested into registers is used before the next
 // barrier.  Two waves per SIMD overlap one's vector work with the other's products
 // (with all the products, on one wave per SIMD, the matrix cores are busy half of the
-// time).  Against k_freq_bwd_p: 55 -> 36 ms for 32 x 2^18 (n1 = 285), 2.89 -> 2.57 for
+// time).  Against k_freq_bwd_p: 66 -> 38 ms for 32 x 2^18 (n1 = 285), 2.89 -> 2.57 for
 // 16 x 2^16 (n1 = 167, 16 frames); bwd_folded has the others.
 template <int NTB, int NS, bool SHORT>
 __global__ void __launch_bounds__(512) k_freq_bwd_f(const unsigned* __restrict__ phase, int64_t ph_bstride,
@@ -2309,7 +2309,7 @@ static void launch_bwdf_ns(dim3 grid, hipStream_t st, const unsigned* phase, int
 // 112 570 and 648 (64 x 2^13, 32 frames); 128 575 and 655, 144 1262 and 1172, 176 714
 // and 608 (16 x 2^15, 32 frames), at 64 frames 614 and 712, 1328 and 1233, 1058 and
 // 662; 128 1192 and 1359, 144 2534 and 2391, 208 1683 and 1349 (16 x 2^16, 16 frames);
-// 288 55 and 36 ms (32 x 2^18).  By the shapes alone, so that a signal's bits do not
+// 288 66 and 38 ms (32 x 2^18).  By the shapes alone, so that a signal's bits do not
 // depend on its batch: launches that leave CUs idle are a little faster folded, with 64
 // columns a workgroup for 128 (2 x 2^11, 103 rows: 33 and 31 us).
 bool bwd_folded(const jtfs_plan* P) {
