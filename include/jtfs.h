@@ -423,7 +423,8 @@ void jtfs_texture_destroy(jtfs_texture* tex);
  * transforms (rows shorter than 2^13: more rows per workgroup, fewer
  * workgroups of twice the LDS), else 4096. */
 #define JTFS_TUNE_LDS_BATCH8K 1024
-/* ... and the t-columns per workgroup of the forward contraction (its t-chunk):
+/* ... and the t-columns per chunk of the forward contraction (a workgroup of a large
+ * launch takes several chunks one after the other, each with its own partial sums):
  * 1024, 2048 or 4096 where one of these bits is set (the least of them), else 4096 in
  * FP32 mode and, in the split modes, a length of 256 to 4096 columns that the plan
  * takes from its shapes (so that one signal fills the GPU).  Shorter chunks give
